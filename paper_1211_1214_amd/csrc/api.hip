@@ -135,6 +135,7 @@ struct ddwc_ctx {
     cx<float>* Uh32 = nullptr;
     double2* Kh64 = nullptr;
     cx<f16>* Uh16 = nullptr;  // FP16 half-order links (storage of the FP16 inner solver)
+    void* Uh32w = nullptr;       // packed FP32 half-order links (the LDS-resident block solver, where it applies)
     cx<float>* Uh32s = nullptr;  // own-site link records [2][V/2][8][9] (FP32, FP16) read by the
     cx<f16>* Uh16s = nullptr;    // RHS-innermost kernels of the global solver
     float4* Kh32 = nullptr;
@@ -321,6 +322,13 @@ extern "C" int ddwc_create(ddwc_ctx** out, const int lat[4], const int blk[4], i
         }
         launch_eo_setup(ex, g, C->U64, C->K64, C->nbr, C->Uh64, C->Uh32, C->Kh64, C->Kh32, C->nbr_eo);
         launch_eo_links_own(ex, (unsigned)n2, C->Uh32, C->nbr_eo, C->Uh32s);
+        if (blk_lds_fits(g, C->lds_max)) {
+            if (hipMalloc(&C->Uh32w, (size_t)8 * PACKED_LINK_BYTES * n2) != hipSuccess) {
+                ddwc_destroy(C);
+                return fail(DDWC_EHIP, "device allocation of the even-odd fields failed");
+            }
+            launch_eo_links_packed(ex, (unsigned)n2, C->Uh32, C->Uh32w);
+        }
         launch_links_to_half(ex, (size_t)2 * 36 * n2, C->Uh32, C->Uh16);
         launch_links_to_half(ex, (size_t)2 * 72 * n2, C->Uh32s, C->Uh16s);
     }
@@ -363,7 +371,7 @@ extern "C" int ddwc_destroy(ddwc_ctx* C) {
     if (C->K32) (void)hipFree(C->K32);
     if (C->nbr) (void)hipFree(C->nbr);
     for (void* q : {(void*)C->Uh64, (void*)C->Uh32, (void*)C->Kh64, (void*)C->Kh32, (void*)C->nbr_eo, (void*)C->Uh16,
-                    (void*)C->Uh32s, (void*)C->Uh16s})
+                    (void*)C->Uh32s, (void*)C->Uh16s, C->Uh32w})
         if (q) (void)hipFree(q);
     for (auto& a : C->ainv) {
         (void)hipFree(a.a64);
@@ -533,6 +541,7 @@ EoFields<float> eo_fields<float>(const ddwc_ctx* C, bool site_major) {
         F.U[p] = site_major ? C->Uh32s + (size_t)p * 72 * F.n2 : C->Uh32 + (size_t)p * 36 * F.n2;
         F.K[p] = C->Kh32 + (size_t)p * 18 * F.n2;
         F.nbr[p] = C->nbr_eo + (size_t)p * 8 * F.n2;
+        if (C->Uh32w) F.W[p] = (const char*)C->Uh32w + (size_t)p * 4 * PACKED_LINK_BYTES * F.n2;
     }
     return F;
 }

@@ -14,6 +14,7 @@
 
 #include "ddwc_internal.h"
 #include "eo.h"
+#include "uniform_mem.h"
 #include "../../include/ddwc.h"
 
 namespace ddwc {
@@ -411,102 +412,177 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
 // The same BiCGStab on M_k as k_blk_inner, one workgroup per (block, RHS), for block parities of
 // at most BL_MAX sites: one thread per local half index l < hvb owns the even site and the odd
 // site of that index.  The operand of M_k (p, then s; even sites) and the odd intermediate
-// A_oo^-1 H^k_oe (operand) are staged in LDS (2 x hvb x 96 bytes, 124 KB for a 6^4 block), so
-// the in-block neighbour gathers of both passes, and each site's own operand, are LDS reads.
-// r, p, v, rh and the correction e of a thread's own site are global slabs (slots 0, 2, 3, 1,
-// 5), each read or written once or twice per iteration, so that no iterate stays live in
-// registers across the stencil passes (s and t are formed in registers from the LDS operand and
-// the even pass).  Links and clover are read from global
-// memory: the RHS of one block run on one XCD and share them in its L2.  Arithmetic FP32, dot
-// products accumulated in FP64 as in k_blk_inner.
+// A_oo^-1 H^k_oe (operand) are staged in LDS (2 x (hvb + 1) x 96 bytes, 124 KB for a 6^4 block), so
+// the in-block neighbour gathers of both passes, and each site's own operand, are LDS reads.  r
+// stays in registers until s is formed from it and v then takes its place until p is updated, so
+// that p, rh and the correction e are the only global slabs (slots 2, 1, 5), each touched once or
+// twice per iteration.  Links (packed, five loads each) and clover are read from global memory: the
+// RHS of one block run on one XCD and share them in its L2.  Arithmetic FP32, dot products accumulated
+// in FP64 as in k_blk_inner.
+//
+// What bounds it: one 11-wave workgroup per CU (6^4) issues vector loads and ALU work in barrier-
+// separated phases.  Times per launch at 48x24^3, 6^4, 12 RHS, one colour (9.5 iterations): 5677 us with
+// entry-major links (nine 8-byte loads each), r and v as slabs, conditional hops and shuffle
+// reductions; 4883 us with r and v in registers and branch-free hops; 4296 us with the packed links;
+// 4002 us with the exchanging reduction.  With no loads but the LDS reads it takes about 3000 us, which
+// is the ALU work (6500 instructions a site and iteration in 3 waves per SIMD): the load path, 64 bytes a
+// cycle and CU for 3.4 KB a site and iteration, is what remains.  Loading the next pass's first link
+// and the clover words earlier spilled and was slower (5033 to 5544 us).
 constexpr int BL_MAX = 768;  // 12 waves: 3 per SIMD at up to 168 VGPRs
 
-__device__ __forceinline__ void lds_load(const float4* __restrict__ L, unsigned HV, unsigned li, cx<float> q[12]) {
+// Exchanges halves between a and b and adds, on the two dwords of each double: with W = 32 the lower 32
+// lanes get a(lane) + a(lane + 32) and the upper ones b(lane - 32) + b(lane); with W = 16 the same
+// within each pair of 16-lane rows.
+template <int W>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    u2 p, q;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (W == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
+            p[i] = r[0], q[i] = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane16_swap(x[i], y[i], false, false);
+            p[i] = r[0], q[i] = r[1];
+        }
+    }
+    return __builtin_bit_cast(double, p) + __builtin_bit_cast(double, q);
+}
+// v(lane) + v(lane rotated by N inside its 16-lane row)
+template <int N>
+__device__ __forceinline__ double ror_add(double v) {
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    const i2 x = __builtin_bit_cast(i2, v);
+    i2 y;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y[i] = __builtin_amdgcn_update_dpp(0, x[i], 0x120 + N, 0xf, 0xf, false);
+    return v + __builtin_bit_cast(double, y);
+}
+__device__ __forceinline__ double row_sum(double v) { return ror_add<1>(ror_add<2>(ror_add<4>(ror_add<8>(v)))); }
+
+// Sums of NV <= 8 values over the workgroup (full waves, at most 16), in a fixed order, with one
+// barrier.  Inside a wave the values are exchanged against each other, so that each step halves the
+// values a lane carries (about 40 instructions for eight values, against 144 and the LDS permutes
+// of one shuffle tree per value), and the waves' sums are added the same way, one value per
+// 16-lane row.  lds holds 8 x 16 doubles, zero in the slots of waves that do not exist, and must not be the
+// slot of the previous call (alternate two slots).
+template <int NV>
+__device__ __forceinline__ void wg_sums(double v[NV], double* lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int NP = NV > 4 ? 4 : NV > 2 ? 2 : 1;  // values per half wave
+    double h[4], w[2];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) h[k] = swap_add<32>(v[k], k + NP < NV ? v[k + NP] : v[k]);
+    constexpr int NQ = NP > 2 ? 2 : 1;  // values per row
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) w[k] = row_sum(swap_add<16>(h[k], NP > NQ ? h[k + NQ] : h[k]));
+    // row r = lane / 16 holds value NP (r / 2) + NQ (r % 2) + k (NP > NQ), the same in both rows of a half otherwise
+    const int r = lane >> 4, k0 = NP * (r >> 1) + (NP > NQ ? NQ * (r & 1) : 0);
+    if ((lane & 15) == 0) {
+#pragma unroll
+        for (int k = 0; k < NQ; ++k)
+            if (k0 + k < NV) lds[(k0 + k) * 16 + wave] = w[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < NV; b += 4) {
+        const double s = row_sum(lds[b * 16 + lane]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (b + k < NV) {
+                typedef int i2 __attribute__((ext_vector_type(2)));
+                const i2 x = __builtin_bit_cast(i2, s);
+                i2 y;
+                y[0] = __builtin_amdgcn_readlane(x[0], 16 * k);
+                y[1] = __builtin_amdgcn_readlane(x[1], 16 * k);
+                v[b + k] = __builtin_bit_cast(double, y);
+            }
+    }
+}
+
+// Block field in LDS, one 96-byte record per site: a record has one address register and the rest
+// in the offsets of its six 16-byte words (consecutive lanes' words of a record pitch of 24 banks
+// fall on distinct banks for the eight lanes that are served together).
+__device__ __forceinline__ void lds_load(const float4* __restrict__ L, unsigned li, cx<float> q[12]) {
+    const float4* p = L + li * 6;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-        const float4 w = L[k * HV + li];
+        const float4 w = p[k];
         q[2 * k] = mk(w.x, w.y);
         q[2 * k + 1] = mk(w.z, w.w);
     }
 }
-__device__ __forceinline__ void lds_store(float4* __restrict__ L, unsigned HV, unsigned li, const cx<float> q[12]) {
+__device__ __forceinline__ void lds_store(float4* __restrict__ L, unsigned li, const cx<float> q[12]) {
+    float4* p = L + li * 6;
 #pragma unroll
-    for (int k = 0; k < 6; ++k)
-        L[k * HV + li] = make_float4(q[2 * k].re, q[2 * k].im, q[2 * k + 1].re, q[2 * k + 1].im);
+    for (int k = 0; k < 6; ++k) p[k] = make_float4(q[2 * k].re, q[2 * k].im, q[2 * k + 1].re, q[2 * k + 1].im);
 }
 
-// acc = sum over the hops of half site s that stay inside its block (neighbour t with
-// t - h0 < HV) of (1 -+ g_mu) W q(t), q read from LDS at t - h0; forward links Uf at s, backward
-// links Ub at t (entry-major [4][9][n2]); nbr is the half-field table [8][n2] of s's parity.
-// Software-pipelined: while hop d is applied, the link of hop d + 1 and the table entry of hop
-// d + 2 are in flight (about one global latency per pass instead of one or two per hop).  The
-// direction loop is unrolled: with a run-time direction the spin algebra sat behind a switch
-// whose merge copied the accumulator and the prefetched link (42 moves per hop against 108
-// arithmetic instructions); unrolled, the block kernel is 6.7% faster with identical results.
-__device__ __forceinline__ void lds_hops(unsigned n2, unsigned s, unsigned h0, unsigned HV,
-                                         const float4* __restrict__ L, const cx<float>* __restrict__ Uf,
-                                         const cx<float>* __restrict__ Ub, const int* __restrict__ nbr,
+// Local half indices of the in-block neighbours of one site, packed two per register; a hop that
+// leaves the block has index HV, the record of zeros after the block's sites in LDS.
+struct BlkNbr {
+    unsigned w[4];
+    __device__ __forceinline__ unsigned operator[](int d) const { return (d & 1) ? w[d >> 1] >> 16 : w[d >> 1] & 0xffffu; }
+};
+__device__ __forceinline__ BlkNbr blk_nbr(const int* __restrict__ nbr, unsigned n2, unsigned s, unsigned h0, unsigned HV,
+                                          bool act) {
+    BlkNbr b;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        unsigned li[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int e = at(nbr + (size_t)(2 * k + q) * n2, s);
+            const unsigned t = (e < 0 ? (unsigned)~e : (unsigned)e) - h0;
+            li[q] = act && t < HV ? t : HV;
+        }
+        b.w[k] = li[0] | (li[1] << 16);
+    }
+    return b;
+}
+
+// acc = sum over the in-block hops of the site with link byte offset own and neighbours nb, of
+// (1 -+ g_mu) W q(neighbour), q read from LDS; forward links Uf at own, backward links Ub at the
+// neighbour (packed links; own and the operand's h0 + neighbour index the whole half field).  A hop that leaves the block
+// reads the record of zeros (and some link of the block), so every hop runs without a branch: the
+// waves of a block take nearly every hop for some lane anyway, and as straight-line code the link of hop
+// d + 1 is loaded while d is computed.  (In-block hops never cross the time boundary,
+// whose sign the table carries: there are at least two blocks per direction.)
+__device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own, BlkNbr nb, unsigned HV,
+                                         const float4* __restrict__ L, const char* Uf, const char* Ub,
                                          cx<float> acc[12]) {
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = mk(0.f, 0.f);
-    int e = at(nbr, s), en = at(nbr + (size_t)n2, s);
+    PackedLinks pf(fresh(Uf), n2), pb(fresh(Ub), n2);
     cx<float> u[9];
-    {
-        const unsigned t = e < 0 ? (unsigned)~e : (unsigned)e;
-        if (t - h0 < HV) hop_link<LK_ENTRY>(Uf, Ub, n2, 0, s, t, u);
-    }
+    pf.next(reissue(own), u);
+    // (opaque here, so that the sixteen addresses formed from nb are not kept across the iteration loop)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(nb.w[k]));
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
-        const unsigned t = e < 0 ? (unsigned)~e : (unsigned)e;
-        int enn = 0;
-        if (d + 2 < 8) enn = at(nbr + (size_t)(d + 2) * n2, s);
-        cx<float> un[9];
+        cx<float> un[9], q[12];
+        lds_load(L, nb[d], q);
         if (d + 1 < 8) {
-            const unsigned tn = en < 0 ? (unsigned)~en : (unsigned)en;
-            if (tn - h0 < HV) hop_link<LK_ENTRY>(Uf, Ub, n2, d + 1, s, tn, un);
+            const unsigned t = reissue(nb[d + 1]);
+            if ((d + 1) & 1)
+                pb.next(byte_offset(h0 + (t < HV ? t : 0u), 16), un);
+            else
+                pf.next(reissue(own), un);
         }
-        const unsigned li = t - h0;
-        if (li < HV) {
-            cx<float> q[12];
-            lds_load(L, HV, li, q);
-            if (e < 0) {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) q[c] = -q[c];
-            }
-            hop_dispatch<float>(d, u, q, acc);
-        }
+        __builtin_amdgcn_sched_barrier(0);
+        hop_dispatch<float>(d, u, q, acc);
+        pin(acc);
 #pragma unroll
         for (int k = 0; k < 9; ++k) u[k] = un[k];
-        e = en;
-        en = enn;
     }
-}
-
-// w = A_oo^-1 H^k_oe q at odd half site j (q: even operand in LDS L).
-__device__ __forceinline__ void odd_lds(const EoFields<float>& F, const float4* __restrict__ Ainv, unsigned j,
-                                        unsigned h0, unsigned HV, const float4* __restrict__ L, cx<float> w[12]) {
-    cx<float> acc[12];
-    lds_hops(F.n2, j, h0, HV, L, F.U[1], F.U[0], F.nbr[1], acc);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) w[c] = mk(0.f, 0.f);
-    apply_diag<float>(Ainv, F.n2, j, 0.f, acc, w, 0.f);
-}
-
-// y = (4 + m + C) q_e - 1/4 H^k_eo q_o at even half site i: q_e the even operand in LDS Le (own
-// site, local index l), q_o the odd intermediate in LDS Lo.
-__device__ __forceinline__ void even_lds(const EoFields<float>& F, float m4, unsigned i, unsigned l, unsigned h0,
-                                         unsigned HV, const float4* __restrict__ Le, const float4* __restrict__ Lo,
-                                         cx<float> y[12]) {
-    lds_hops(F.n2, i, h0, HV, Lo, F.U[0], F.U[1], F.nbr[0], y);
-    cx<float> c[12];
-    lds_load(Le, HV, l, c);
-    apply_diag<float>(F.K[0], F.n2, i, m4, c, y, -0.25f);
 }
 
 __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, const float4* __restrict__ Ainv,
-                                                    const double2* __restrict__ re, double2* __restrict__ xe,
-                                                    float4* __restrict__ rg, float4* __restrict__ rhg, float4* __restrict__ pg,
-                                                    float4* __restrict__ vg, float4* __restrict__ eg,
+                                                    const double2* re, double2* xe, float4* rhg, float4* pg,
+                                                    float4* eg,
                                                     const double* __restrict__ bb, const double* __restrict__ rr,
                                                     double mass4, double tol, double inner_floor, int maxit,
                                                     int* iters, int colour, int nrhs) {
@@ -517,96 +593,115 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     if (!(b2 > 0) || !(r2 > tol * tol * b2) || !isfinite(r2)) return;  // uniform over the workgroup
     const unsigned n2 = F.n2, HV = (unsigned)g.hvb, h0 = k.h0;
     float4* op = bl_lds;          // operand of M_k on the even sites of the block
-    float4* tp = bl_lds + 6 * HV;  // A_oo^-1 H^k_oe (operand) on the odd sites
-    const unsigned l = threadIdx.x;
-    const bool act = l < HV;
-    unsigned i = h0 + (act ? l : 0u);  // half index of this thread's even and odd site
-    const size_t oh = (size_t)k.rhs * 12 * n2, oR = (size_t)k.rhs * 6 * n2;
-    rg += oR;
+    float4* tp = bl_lds + 6 * (HV + 1);  // A_oo^-1 H^k_oe (operand) on the odd sites
+    // l: local half index of this thread's even and odd site.  The last wave's threads past the block
+    // run the same code on the record of zeros (their stores are masked), so that the passes have no
+    // divergent branches.
+    const bool act = threadIdx.x < HV;
+    const unsigned l = act ? threadIdx.x : HV, lg = act ? threadIdx.x : 0u;
+    const unsigned lo = byte_offset(lg, 16), own = byte_offset(h0 + lg, 16);  // its byte offsets in the planes
+    const size_t oh = (size_t)k.rhs * 12 * n2 + h0, oR = (size_t)k.rhs * 6 * n2 + h0;
+    // everything below is addressed from the block's first site
     rhg += oR;
     pg += oR;
-    vg += oR;
     eg += oR;
+    re += oh;
+    xe += oh;
+    const char *Ue = (const char*)F.W[0], *Uo = (const char*)F.W[1];
+    const float4 *Ke = F.K[0] + h0, *Ko = Ainv + h0;
+    const BlkNbr ne = blk_nbr(F.nbr[0], n2, h0 + lg, h0, HV, act), no = blk_nbr(F.nbr[1], n2, h0 + lg, h0, HV, act);
+    for (unsigned k = threadIdx.x; k < 2 * 8 * 16; k += blockDim.x) red_lds[0][k] = 0;
+    if (threadIdx.x < 12) (threadIdx.x < 6 ? op : tp)[HV * 6 + threadIdx.x % 6] = make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
     const float m4 = (float)mass4;
+    // tp = A_oo^-1 H^k_oe q on the odd sites (q: operand in op)
+    auto odd = [&]() {
+        cx<float> acc[12], w[12];
+        UDiag<float> K(fresh(Ko), n2, lo);
+        lds_hops(n2, h0, own, no, HV, op, Uo, Ue, acc);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) w[c] = mk(0.f, 0.f);
+        K.off = reissue(lo), K.first();
+        K.apply(0.f, acc, w, 0.f);
+        if (act) lds_store(tp, l, w);
+    };
+    // y = (4 + m + C) q_e - 1/4 H^k_eo q_o on the even sites (q_e in op, q_o in tp); h = rh
+    auto even = [&](cx<float> y[12], cx<float> h[12]) {
+        UDiag<float> K(fresh(Ke), n2, lo);
+        lds_hops(n2, h0, own, ne, HV, tp, Ue, Uo, y);
+        cx<float> c[12];
+        lds_load(op, l, c);
+        K.off = reissue(lo), K.first();
+        K.apply(m4, c, y, -0.25f);
+        uload_spinor(fresh(rhg), n2, lo, h);
+    };
     const double rn = sqrt(r2), sc = 1.0 / rn;
     double eps = 0.5 * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     int phase = 0;  // reduction slot
     double red[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (act) {
+    cx<float> r[12];  // r until s is formed, then v until p is updated
+    {
         cx<double> a[12];
-        load_spinor(re + oh, n2, i, a);
-        cx<float> r[12], z[12];
+        uload_spinor(re, n2, lo, a);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            r[c] = mk((float)(sc * a[c].re), (float)(sc * a[c].im));
-            z[c] = mk(0.f, 0.f);
-        }
-        store_spinor(rg, n2, i, r);
-        store_spinor(rhg, n2, i, r);
-        store_spinor(pg, n2, i, r);
-        store_spinor(eg, n2, i, z);
-        lds_store(op, HV, l, r);
-        red[0] = acc_nrm(r);
+        for (int c = 0; c < 12; ++c) r[c] = act ? mk((float)(sc * a[c].re), (float)(sc * a[c].im)) : mk(0.f, 0.f);
     }
-    block_sum1<1>(red, red_lds[phase ^= 1]);  // (its barrier also publishes the operand)
+    if (act) {
+        const cx<float> z[12] = {};
+        ustore_spinor(fresh(rhg), n2, lo, r);
+        ustore_spinor(fresh(pg), n2, lo, r);
+        ustore_spinor(fresh(eg), n2, lo, z);
+        lds_store(op, l, r);
+    }
+    red[0] = acc_nrm(r);
+    wg_sums<1>(red, red_lds[phase ^= 1]);  // (its barrier also publishes the operand)
     cx<double> rho = mk(red[0], 0.0);
     const double thr2 = eps * eps * red[0];
     int it = 0;
     while (it < maxit) {
-        // an opaque redefinition of the site index: keeps the compiler from hoisting every per-lane
-        // 64-bit address out of the loop (they would not fit the 168 registers and would spill)
-        asm volatile("" : "+v"(i));
         // v = M_k p, (rh, v)
-        if (act) {
-            cx<float> w[12];
-            odd_lds(F, Ainv, i, h0, HV, op, w);
-            lds_store(tp, HV, l, w);
-        }
+        odd();
         __syncthreads();
         red[0] = red[1] = 0;
-        if (act) {
-            cx<float> v[12], h[12];
-            even_lds(F, m4, i, l, h0, HV, op, tp, v);
-            store_spinor(vg, n2, i, v);
-            load_spinor(rhg, n2, i, h);
+        cx<float> v[12];
+        {
+            cx<float> h[12];
+            even(v, h);
             acc_dot(h, v, red[0], red[1]);
         }
-        block_sum1<2>(red, red_lds[phase ^= 1]);
+        wg_sums<2>(red, red_lds[phase ^= 1]);
         if (!(red[0] * red[0] + red[1] * red[1] > 0)) break;
         const cx<float> alpha = cdiv_r<float>(rho, mk(red[0], red[1]));
-        // s = r - alpha v (kept in r), staged as the operand
-        if (act) {
-            cx<float> v[12], r[12];
-            load_spinor(vg, n2, i, v);
-            load_spinor(rg, n2, i, r);
+        // s = r - alpha v, staged as the operand
 #pragma unroll
-            for (int c = 0; c < 12; ++c) r[c] = r[c] - alpha * v[c];
-            lds_store(op, HV, l, r);
+        for (int c = 0; c < 12; ++c) {
+            const cx<float> sv = r[c] - alpha * v[c];
+            r[c] = v[c];
+            v[c] = sv;
         }
+        if (act) lds_store(op, l, v);
         __syncthreads();
         // t = M_k s, (t, s), (t, t), (rh, s), (rh, t), (s, s)
-        if (act) {
-            cx<float> w[12];
-            odd_lds(F, Ainv, i, h0, HV, op, w);
-            lds_store(tp, HV, l, w);
-        }
+        odd();
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < 8; ++c) red[c] = 0;
-        cx<float> t[12];
-        if (act) {
-            even_lds(F, m4, i, l, h0, HV, op, tp, t);
+        cx<float> t[12], e[12], pp[12];
+        {
             cx<float> sv[12], h[12];
-            lds_load(op, HV, l, sv);
+            even(t, h);
+            lds_load(op, l, sv);
             acc_dot(t, sv, red[0], red[1]);
             red[2] = acc_nrm(t);
-            load_spinor(rhg, n2, i, h);
             acc_dot(h, sv, red[3], red[4]);
             acc_dot(h, t, red[5], red[6]);
             red[7] = acc_nrm(sv);
+            // (needed after the reduction)
+            uload_spinor(fresh(eg), n2, lo, e);
+            uload_spinor(fresh(pg), n2, lo, pp);
         }
-        block_sum1<8>(red, red_lds[phase ^= 1]);
+        wg_sums<8>(red, red_lds[phase ^= 1]);
         ++it;
         cx<float> omega = mk(0.f, 0.f);
         if (red[2] > 0) omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
@@ -628,46 +723,41 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
         }
         rho = rn_;
         // e += alpha p + omega s ; r = s - omega t ; p = r + beta (p - omega v), staged as the next operand
-        if (act) {
-            cx<float> e[12], pp[12], r[12];
-            lds_load(op, HV, l, r);
-            load_spinor(eg, n2, i, e);
-            load_spinor(pg, n2, i, pp);
+        lds_load(op, l, v);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                e[c] = e[c] + (alpha * pp[c] + omega * r[c]);
-                r[c] = r[c] - omega * t[c];
-            }
-            store_spinor(eg, n2, i, e);
-            if (!stop) {
-                cx<float> v[12];
-                store_spinor(rg, n2, i, r);
-                load_spinor(vg, n2, i, v);
-#pragma unroll
-                for (int c = 0; c < 12; ++c) pp[c] = r[c] + beta * (pp[c] - omega * v[c]);
-                store_spinor(pg, n2, i, pp);
-                // (only this thread reads its own operand slot after the last barrier)
-                lds_store(op, HV, l, pp);
-            }
+        for (int c = 0; c < 12; ++c) {
+            e[c] = e[c] + (alpha * pp[c] + omega * v[c]);
+            v[c] = v[c] - omega * t[c];
         }
+        if (act) ustore_spinor(fresh(eg), n2, lo, e);
         if (stop) break;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            pp[c] = v[c] + beta * (pp[c] - omega * r[c]);
+            r[c] = v[c];
+        }
+        if (act) {
+            ustore_spinor(fresh(pg), n2, lo, pp);
+            // (only this thread reads its own operand slot after the last barrier)
+            lds_store(op, l, pp);
+        }
         __syncthreads();
     }
     // x_e += ||r_e|| e in FP64
     if (act) {
         cx<float> e[12];
         cx<double> x[12];
-        load_spinor(eg, n2, i, e);
-        load_spinor(xe + oh, n2, i, x);
+        uload_spinor(fresh(eg), n2, lo, e);
+        uload_spinor(xe, n2, lo, x);
 #pragma unroll
         for (int c = 0; c < 12; ++c) x[c] = x[c] + mk(rn * (double)e[c].re, rn * (double)e[c].im);
-        store_spinor(xe + oh, n2, i, x);
+        ustore_spinor(xe, n2, lo, x);
     }
     if (threadIdx.x == 0) iters[k.key] += it;
 }
 
 bool blk_lds_fits(const Geom& g, int lds_max_bytes) {
-    return g.eo && g.hvb <= BL_MAX && (long long)2 * 6 * 16 * g.hvb + 3 * 16 * 8 <= lds_max_bytes;
+    return g.eo && g.hvb <= BL_MAX && (long long)2 * 6 * 16 * (g.hvb + 1) + 2 * 8 * 16 * 8 <= lds_max_bytes;
 }
 
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
@@ -675,10 +765,10 @@ void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const floa
                     int maxit, int* iters, int colour, int nrhs) {
     Timed t(e, 2, 0);
     const int threads = ((g.hvb + 63) / 64) * 64;
-    const size_t lds = (size_t)2 * 6 * g.hvb * sizeof(float4);
+    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
     // the inner solve stops at this relative residual at the least (FP32's reach)
-    k_blk_lds<<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (float4*)w[0], (float4*)w[1], (float4*)w[2],
-                                                        (float4*)w[3], (float4*)w[5], bb, rr, mass4, tol, 2e-6,
+    k_blk_lds<<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (float4*)w[1], (float4*)w[2], (float4*)w[5],
+                                                        bb, rr, mass4, tol, 2e-6,
                                                         maxit, iters, colour, nrhs);
 }
 

@@ -423,8 +423,30 @@ DDWC_HD void load_clover_block(const float4* __restrict__ K, unsigned V, unsigne
     }
 }
 
+// w = (mass4 + d, o) v + hsc w for one packed Hermitian 6x6 block (w holds the accumulated hop
+// terms on entry, hsc = -1/2; hsc = 0 ignores them).
+template <class R>
+DDWC_HD void diag_block(const R d[6], const R o[30], R mass4, const cx<R> v[6], cx<R> w[6], R hsc) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const R di = mass4 + d[i];
+        w[i] = mk(fmad(di, v[i].re, hsc * w[i].re), fmad(di, v[i].im, hsc * w[i].im));
+    }
+    int k = 0;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+#pragma unroll
+        for (int j = i + 1; j < 6; ++j) {
+            const cx<R> aij = mk(o[2 * k], o[2 * k + 1]);
+            cmadd(w[i], aij, v[j]);
+            cjmadd(w[j], aij, v[i]);
+            ++k;
+        }
+    }
+}
+
 // y = (4 + m) psi + C psi + hsc * y with the two packed Hermitian 6x6 blocks, one block at
-// a time (y holds the accumulated hop terms on entry, hsc = -1/2; hsc = 0 ignores them).
+// a time.
 template <class R>
 DDWC_HD void apply_diag(const typename Traits<R>::word* __restrict__ K, unsigned V, unsigned s, R mass4,
                         const cx<R> p[12], cx<R> y[12], R hsc) {
@@ -432,24 +454,7 @@ DDWC_HD void apply_diag(const typename Traits<R>::word* __restrict__ K, unsigned
     for (int blk = 0; blk < 2; ++blk) {
         R d[6], o[30];
         load_clover_block(K, V, s, blk, d, o);
-        const cx<R>* v = p + 6 * blk;
-        cx<R>* w = y + 6 * blk;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            const R di = mass4 + d[i];
-            w[i] = mk(fmad(di, v[i].re, hsc * w[i].re), fmad(di, v[i].im, hsc * w[i].im));
-        }
-        int k = 0;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-#pragma unroll
-            for (int j = i + 1; j < 6; ++j) {
-                const cx<R> aij = mk(o[2 * k], o[2 * k + 1]);
-                cmadd(w[i], aij, v[j]);
-                cjmadd(w[j], aij, v[i]);
-                ++k;
-            }
-        }
+        diag_block<R>(d, o, mass4, p + 6 * blk, y + 6 * blk, hsc);
     }
 }
 
@@ -667,25 +672,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
-}
-
-// Workgroup sum with one barrier: `lds` (NV x 16 doubles) must not be the slot of the previous
-// block_sum1 of the workgroup (alternate two slots), which all threads have finished reading
-// before any of them reaches this barrier.
-template <int NV>
-__device__ __forceinline__ void block_sum1(double v[NV], double* lds) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
-    if (lane == 0)
-        for (int k = 0; k < NV; ++k) lds[k * 16 + wave] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        double t = 0;
-        for (int w = 0; w < nw; ++w) t += lds[k * 16 + w];
-        v[k] = t;
-    }
 }
 
 template <int NV>

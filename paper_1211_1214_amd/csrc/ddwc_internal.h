@@ -71,6 +71,7 @@ struct Timed {
 // ------------------------------------------------------------------ launchers (kernels.hip)
 constexpr int WG = 256;  // sites per workgroup of the site-parallel kernels
 constexpr int NPART = 8; // doubles per partial-sum slot
+constexpr unsigned PACKED_LINK_BYTES = 72;  // one packed FP32 link (nine complex entries)
 
 inline int tiles_of(int n) { return (n + WG - 1) / WG; }
 
@@ -209,6 +210,7 @@ struct EoFields {
     const cx<typename Traits<R>::link>* U[2];           // [4][9][n2] links of the sites of parity p
     const typename Traits<R>::kword* K[2];              // clover of the sites of parity p
     const int* nbr[2];                                  // [8][n2] neighbour half indices (other parity)
+    const void* W[2] = {nullptr, nullptr};              // packed FP32 links (uniform_mem.h) of parity p (FP32 only)
     int op_threads = WG;                                // workgroup size of the RHS-innermost operator kernels
     const int* order = nullptr;                         // their tile dispatch order (null: index order)
 };
@@ -235,6 +237,8 @@ void launch_eo_setup(Exec& e, const Geom& g, const cx<double>* U64, const double
 // Own-site link records [2][V/2][8][9] (LK_OWN) read by the RHS-innermost kernels of the global
 // solver, from Uh32 and the half-field neighbour tables.
 void launch_eo_links_own(Exec& e, unsigned n2, const cx<float>* Uh32, const int* nbr_eo, cx<float>* Lown);
+// Packed FP32 links [2][4]{[4][V/2] float4, [V/2] float2} read by the LDS-resident block solver, from Uh32.
+void launch_eo_links_packed(Exec& e, unsigned n2, const cx<float>* Uh32, void* W);
 void launch_eo_inverse(Exec& e, unsigned V2, const double2* Kp, double mass4, double2* A64, float4* A32);
 void launch_eo_split(Exec& e, const Geom& g, const double2* full, double2* he, double2* ho, int nrhs);
 void launch_eo_merge(Exec& e, const Geom& g, const double2* he, const double2* ho, double2* full, int nrhs,

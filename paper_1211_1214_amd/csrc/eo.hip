@@ -1,6 +1,7 @@
 // Even-odd preconditioned operator kernels on half fields (see eo.h for the algebra).
 #include "ddwc_internal.h"
 #include "eo.h"
+#include "uniform_mem.h"
 #include "vec_items.h"
 
 namespace ddwc {
@@ -58,6 +59,27 @@ __global__ void k_links_to_half(size_t n, const cx<float>* __restrict__ src, cx<
 void launch_links_to_half(Exec& e, size_t n, const cx<float>* src, cx<f16>* dst) {
     Timed t(e, 4, 0);
     k_links_to_half<<<(unsigned)((n + 255) / 256), 256, 0, e.stream>>>(n, src, dst);
+}
+
+// Packed copy of the entry-major half links (setup): link (p, mu) of the n2 sites is four planes of
+// float4 (entries 2 k, 2 k + 1) and one of float2 (entry 8).
+__global__ void k_links_packed(unsigned n2, const cx<float>* __restrict__ Uh, char* __restrict__ W) {
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n2) return;
+    const cx<float>* u = Uh + (size_t)blockIdx.y * 9 * n2 + i;  // blockIdx.y = 4 p + mu
+    char* w = W + (size_t)blockIdx.y * PACKED_LINK_BYTES * n2;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const cx<float> a = u[(size_t)(2 * k) * n2], b = u[(size_t)(2 * k + 1) * n2];
+        ((float4*)w)[(size_t)k * n2 + i] = make_float4(a.re, a.im, b.re, b.im);
+    }
+    const cx<float> a = u[(size_t)8 * n2];
+    ((float2*)(w + (size_t)64 * n2))[i] = make_float2(a.re, a.im);
+}
+
+void launch_eo_links_packed(Exec& e, unsigned n2, const cx<float>* Uh32, void* W) {
+    Timed t(e, 4, 0);
+    k_links_packed<<<dim3((n2 + 255) / 256, 8), 256, 0, e.stream>>>(n2, Uh32, (char*)W);
 }
 
 // A_pp^-1 for the sites of parity p of half clover Kp (once per mass).

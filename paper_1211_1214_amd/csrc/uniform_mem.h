@@ -1,0 +1,178 @@
+// Global accesses at (wave-uniform plane pointer, 32-bit byte offset per lane).
+//
+// The planes of a field (spinor words, link entries, clover words) share one per-lane offset and
+// differ in their base, which is uniform.  Left alone, the compiler folds the per-lane offset into
+// one 64-bit pointer and then adds each plane's distance to it in vector registers: one 64-bit
+// vector add and two registers per load, and in a loop it hoists all of these sums out of it.  A
+// Planes walks the planes of a field instead: its pointer is a scalar register pair that passes
+// through an empty asm statement, so that every access is that pair plus the shared offset, and the
+// step to the next plane is two scalar additions.
+//
+// The pointer MUST be uniform over the wave (kernel arguments, blockIdx); byte offsets stay below
+// 4 GiB and come from byte_offset().
+#pragma once
+#include "ddwc_device.h"
+
+namespace ddwc {
+
+// i * size as a byte offset, opaque to the compiler (which would otherwise fold the shift into the
+// 64-bit address, in vector registers).
+__device__ __forceinline__ unsigned byte_offset(unsigned i, unsigned size) {
+    unsigned o = i * size;
+    asm("" : "+v"(o));
+    return o;
+}
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef double d2v __attribute__((ext_vector_type(2)));
+template <class R>
+struct VecOf;
+template <>
+struct VecOf<float> {
+    typedef f4v word;  // spinor and clover word
+    typedef f2v link;  // link entry
+};
+template <>
+struct VecOf<double> {
+    typedef d2v word;
+    typedef d2v link;
+};
+
+struct Planes {
+    typedef __attribute__((address_space(1))) char* gptr;
+    gptr p;
+    unsigned long long step;  // bytes from plane to plane
+    // n elements of size bytes per plane, from plane k of base
+    template <class T>
+    __device__ __forceinline__ Planes(const T* base, unsigned n, unsigned k = 0)
+        : p((gptr)(unsigned long long)base + (unsigned long long)n * sizeof(T) * k),
+          step((unsigned long long)n * sizeof(T)) {}
+    // the element at byte offset off of the next plane
+    template <class V>
+    __device__ __forceinline__ V load(unsigned off) {
+        asm("" : "+s"(p));
+        const V v = *(const __attribute__((address_space(1))) V*)(p + off);
+        p += step;
+        return v;
+    }
+    template <class V>
+    __device__ __forceinline__ void store(unsigned off, V v) {
+        asm("" : "+s"(p));
+        *(__attribute__((address_space(1))) V*)(p + off) = v;
+        p += step;
+    }
+};
+
+// An opaque copy of a uniform pointer: what is computed from it is neither merged with what was
+// computed from another copy nor moved out of a loop (either would keep the pointers of all planes
+// alive).
+template <class T>
+__device__ __forceinline__ T* fresh(T* p) {
+    unsigned long long q = (unsigned long long)p;
+    asm volatile("" : "+s"(q));
+    return (T*)q;
+}
+
+// Orders the computation of a spinor before every later fresh(), pin() and reissue(): instruction
+// selection otherwise gathers the loads of a long straight-line body at its start and spills them.
+template <class R>
+__device__ __forceinline__ void pin(cx<R> p[12]) {
+#define DDWC_PIN6(a)                                                                                              \
+    asm volatile(""                                                                                               \
+                 : "+v"(p[a].re), "+v"(p[a].im), "+v"(p[a + 1].re), "+v"(p[a + 1].im), "+v"(p[a + 2].re),          \
+                   "+v"(p[a + 2].im), "+v"(p[a + 3].re), "+v"(p[a + 3].im), "+v"(p[a + 4].re), "+v"(p[a + 4].im),  \
+                   "+v"(p[a + 5].re), "+v"(p[a + 5].im))
+    DDWC_PIN6(0);
+    DDWC_PIN6(6);
+#undef DDWC_PIN6
+}
+// The loads addressed with the returned offset are issued after the last pin().
+__device__ __forceinline__ unsigned reissue(unsigned off) {
+    asm volatile("" : "+v"(off));
+    return off;
+}
+
+__device__ __forceinline__ void uload_spinor(const float4* f, unsigned n, unsigned off, cx<float> p[12]) {
+    Planes q(f, n);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const f4v w = q.load<f4v>(off);
+        p[2 * k] = mk(w.x, w.y);
+        p[2 * k + 1] = mk(w.z, w.w);
+    }
+}
+__device__ __forceinline__ void uload_spinor(const double2* f, unsigned n, unsigned off, cx<double> p[12]) {
+    Planes q(f, n);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        const d2v w = q.load<d2v>(off);
+        p[c] = mk(w.x, w.y);
+    }
+}
+__device__ __forceinline__ void ustore_spinor(float4* f, unsigned n, unsigned off, const cx<float> p[12]) {
+    Planes q(f, n);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        q.store<f4v>(off, (f4v){p[2 * k].re, p[2 * k].im, p[2 * k + 1].re, p[2 * k + 1].im});
+}
+__device__ __forceinline__ void ustore_spinor(double2* f, unsigned n, unsigned off, const cx<double> p[12]) {
+    Planes q(f, n);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) q.store<d2v>(off, (d2v){p[c].re, p[c].im});
+}
+
+// Packed FP32 links: per direction four planes of 16-byte words (entries 0 .. 7, two a word) and one
+// plane of 8-byte words (entry 8), n elements each: five loads per link instead of nine.
+struct PackedLinks {
+    Planes::gptr p;
+    unsigned long long n16;
+    __device__ __forceinline__ PackedLinks(const char* U, unsigned n) : p((Planes::gptr)(unsigned long long)U), n16(16ull * n) {}
+    // the link of the next direction of the site at byte offset off16 (its index times 16)
+    __device__ __forceinline__ void next(unsigned off16, cx<float> u[9]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            asm("" : "+s"(p));
+            const f4v w = *(const __attribute__((address_space(1))) f4v*)(p + off16);
+            u[2 * k] = mk(w.x, w.y);
+            u[2 * k + 1] = mk(w.z, w.w);
+            p += n16;
+        }
+        unsigned off8 = off16 >> 1;
+        asm("" : "+v"(off8));
+        asm("" : "+s"(p));
+        const f2v w = *(const __attribute__((address_space(1))) f2v*)(p + off8);
+        u[8] = mk(w.x, w.y);
+        p += n16 >> 1;
+    }
+};
+
+// The packed Hermitian 6x6 blocks K [NKW][n] of one site, loaded in two parts: the diagonals and the
+// first block's off-diagonal reals, then the second block's (which start inside the last word of the
+// first part in FP32).  y = (mass4 + C) p + hsc y as apply_diag.
+template <class R>
+struct UDiag {
+    typedef typename VecOf<R>::word V;
+    static constexpr int PW = sizeof(V) / sizeof(R);         // reals per word
+    static constexpr int W0 = (42 + PW - 1) / PW, W1 = 72 / PW;
+    Planes q;
+    unsigned off;
+    R w[72];
+    __device__ __forceinline__ UDiag(const typename Traits<R>::word* K, unsigned n, unsigned o) : q(K, n), off(o) {}
+    __device__ __forceinline__ void words(int k0, int k1) {
+#pragma unroll
+        for (int k = k0; k < k1; ++k) {
+            const V v = q.template load<V>(off);
+#pragma unroll
+            for (int i = 0; i < PW; ++i) w[PW * k + i] = v[i];
+        }
+    }
+    __device__ __forceinline__ void first() { words(0, W0); }
+    __device__ __forceinline__ void apply(R mass4, const cx<R> p[12], cx<R> y[12], R hsc) {
+        diag_block<R>(w, w + 12, mass4, p, y, hsc);
+        words(W0, W1);
+        diag_block<R>(w + 6, w + 42, mass4, p + 6, y + 6, hsc);
+    }
+};
+
+}  // namespace ddwc

@@ -57,7 +57,7 @@ typedef enum {
     DDWC_EUNDEF = -5      /* estimate undefined: non-finite step mean or variance */
 } ddwc_status;
 
-/* DDWC_MIXED16: as DDWC_MIXED32, except that the inner BiCGStab of the even-odd global solver
+/* DDWC_MIXED16: as DDWC_MIXED32, except that the inner solver of the even-odd global solver
  * and of the even-odd Schwarz block solver keeps its vectors in FP16 with one FP32 scale per
  * site and RHS, and its links in FP16 (clover, arithmetic and the solution correction in
  * FP32; FP64 defect correction restores the tolerance).  ddwc_dslash_apply, lattices with an
@@ -128,7 +128,7 @@ int ddwc_schur_apply(ddwc_ctx *ctx, double kappa, int inverse, const void *in, v
                      int prec, ddwc_stats *stats, void *stream);
 
 /*
- * x = D(m)^-1 b, BiCGStab on all nrhs at once (multi-RHS Dslash), until
+ * x = D(m)^-1 b, a Krylov solver on all nrhs at once (multi-RHS Dslash), until
  * ||b - D x|| <= tol ||b|| in FP64 for every RHS.  prec = DDWC_MIXED32: FP32 inner
  * solves with FP64 defect correction (the FP64 residual is recomputed after each).
  */
@@ -258,15 +258,17 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
 
 /*
  * Schedule options of a context.
- *   DDWC_OPT_GRAPHS        1: the global solver replays each chunk of BiCGStab iterations from
+ *   DDWC_OPT_GRAPHS        1: the global solver replays each chunk of Krylov iterations from
  *                          a captured HIP graph (cached per buffer set and mass; not while
  *                          profiling); 0: launches them one by one.  Default 1.
- *   DDWC_OPT_POLL          iterations between the host's convergence checks, [1, 64]; default 2.
+ *   DDWC_OPT_POLL          iterations per chunk, [1, 64]; default 2.  The host checks convergence
+ *                          after one or more chunks, as far ahead as the rate so far allows.
  *   DDWC_OPT_BLOCK_THREADS workgroup size of the Schwarz block kernels: 0 (enough waves for one
  *                          block parity, at most 768 for the FP32/FP16 inner solver and 256 for
  *                          the FP64 kernels) or a multiple of 64 in [64, 768] (capped alike).
- *   DDWC_OPT_SOLVER        global solver: 0 even-odd BiCGStab (default; lexicographic BiCGStab when
- *                          a block extent is odd), 1 GCR (8 directions per cycle, restarted with
+ *   DDWC_OPT_SOLVER        global solver: 0 even-odd (default): two-step minimal residual, changing
+ *                          over to BiCGStab where that converges faster (lexicographic BiCGStab
+ *                          when a block extent is odd), 1 GCR (8 directions per cycle, restarted with
  *                          the exact FP64 residual) preconditioned by the Schwarz alternating
  *                          procedure: 3 multiplicative cycles over the black then the white
  *                          blocks, each block solve by the persistent block solver to 1e-1.
@@ -277,7 +279,7 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *                          DDWC_MIXED16: 0 (default) the LDS-resident FP32 kernel wherever a block
  *                          parity has at most 768 sites and its two staged fields fit the LDS (both
  *                          precisions then run it, FP32 storage); 1 the global-memory kernel.
- *   DDWC_OPT_INNER_FLOOR   the FP32 inner BiCGStab of the even-odd global solver (DDWC_MIXED32) stops
+ *   DDWC_OPT_INNER_FLOOR   the FP32 inner solver of the even-odd global solver (DDWC_MIXED32) stops
  *                          at a relative residual of at least value x 1e-8 before the FP64 defect
  *                          correction restarts it, in [1, 100000]; default 200 (2e-6).
  *   DDWC_OPT_OP_THREADS    workgroup size of the RHS-innermost operator kernels (the even-odd

@@ -20,8 +20,14 @@ struct BiState {
 
 // Stages of the global BiCGStab's finalize (k_finalize): ST_OMEGA takes (t, s), (t, t), (rh, s) and
 // (rh, t) and sets omega, the next rho = (rh, s) - omega (rh, t) = (rh, r_new) and beta, so that one
-// kernel updates x, r and p; ST_RR takes ||r_new||^2 and decides convergence.
-enum Stage { ST_SUM = 0, ST_INIT = 1, ST_ALPHA = 2, ST_OMEGA = 3, ST_RR = 4 };
+// kernel updates x, r and p; ST_RR takes ||r_new||^2 and decides convergence.  ST_LS closes a cycle of the
+// two-step minimal-residual solver: from the dot products of t1 = M r and t2 = M t1 it takes the
+// coefficients a (alpha), b (omega) that minimise ||r - a t1 - b t2|| and decides convergence.
+enum Stage { ST_SUM = 0, ST_INIT = 1, ST_ALPHA = 2, ST_OMEGA = 3, ST_RR = 4, ST_LS = 5 };
+
+// Epilogues of the even-odd operator kernel (launch_eo_diaghop).
+enum EoEpi { EOE_NONE = 0, EOE_DOT = 1, EOE_DOT4 = 2, EOE_RESID = 3, EOE_LS1 = 4, EOE_LS2 = 5 };
+constexpr int LS1_NV = 4, LS_NV = 9;  // values of LS1, and of a whole cycle (LS1 then LS2)
 
 // Spinor masks for import / combination kernels.
 enum Mask { MASK_ALL = 0, MASK_P = 1, MASK_BLACK = 2, MASK_WHITE = 3 };
@@ -142,6 +148,16 @@ template <class S>
 void launch_bicg_init(Exec& e, unsigned n, bool ri, const double2* r64, const double* scale,
                       typename Traits<S>::word* r, typename Traits<S>::word* rh, typename Traits<S>::word* p,
                       typename Traits<typename Traits<S>::xs>::word* x, double* part, int nrhs);
+// r = scale r64, x = 0, partial ||r||^2 (start of the two-step minimal-residual solver)
+template <class S>
+void launch_ls_init(Exec& e, unsigned n, bool ri, const double2* r64, const double* scale,
+                    typename Traits<S>::word* r, typename Traits<typename Traits<S>::xs>::word* x, double* part,
+                    int nrhs);
+// x += a r + b t1; r -= a t1 + b t2 (its cycle's update; a, b of ST_LS)
+template <class S>
+void launch_ls_update(Exec& e, unsigned n, bool ri, const BiState* st, typename Traits<typename Traits<S>::xs>::word* x,
+                      typename Traits<S>::word* r, const typename Traits<S>::word* t1,
+                      const typename Traits<S>::word* t2, int nrhs);
 template <class S>
 void launch_bicg_s(Exec& e, unsigned n, bool ri, const BiState* st, const typename Traits<S>::word* r,
                    const typename Traits<S>::word* v, typename Traits<S>::word* s, int nrhs);
@@ -249,8 +265,7 @@ template <class S>
 void launch_eo_hopinv(Exec& e, const EoFields<S>& F, int p, bool ri, const typename Traits<S>::word* x,
                       const typename Traits<S>::word* c, double alpha, const typename Traits<S>::kword* Ainv,
                       typename Traits<S>::word* y, int nrhs, int kclass, double bytes);
-// y_p = [A_pp] c + beta H_{p,1-p} t with epilogue epi (0 none, 1 dot(aux, y), 2 dots (y, c), (y, y),
-// 3 residual y = aux - y with ||y||^2).
+// y_p = [A_pp] c + beta H_{p,1-p} t with epilogue epi (EoEpi).
 template <class S>
 void launch_eo_diaghop(Exec& e, const EoFields<S>& F, int p, bool ri, int epi, bool use_a,
                        const typename Traits<S>::word* c, const typename Traits<S>::word* tv, double beta,

@@ -288,7 +288,8 @@ __device__ __forceinline__ cx<R> cxs(const double* a) {
     (void)sizeof(R);                                    \
     (void)sizeof(XS)
 
-template <class S, bool RI>
+// r = scale r64, x = 0; BI (BiCGStab): rh = p = r too.
+template <class S, bool RI, bool BI>
 __global__ __launch_bounds__(WG) void k_bicg_init(unsigned n, const double2* __restrict__ r64,
                                                   const double* __restrict__ scale, typename Traits<S>::word* r,
                                                   typename Traits<S>::word* rh, typename Traits<S>::word* p,
@@ -311,8 +312,10 @@ __global__ __launch_bounds__(WG) void k_bicg_init(unsigned n, const double2* __r
             z[k] = mk(XS(0), XS(0));
         }
         store_spinor(r + w.base, w.stride, w.idx, q);
-        store_spinor(rh + w.base, w.stride, w.idx, q);
-        store_spinor(p + w.base, w.stride, w.idx, q);
+        if (BI) {
+            store_spinor(rh + w.base, w.stride, w.idx, q);
+            store_spinor(p + w.base, w.stride, w.idx, q);
+        }
         store_spinor(x + wx.base, wx.stride, wx.idx, z);
         if (std::is_same<S, H16>::value) load_spinor(r + w.base, w.stride, w.idx, q);  // r as stored
         v[0] = acc_nrm(q);
@@ -380,6 +383,37 @@ __global__ __launch_bounds__(WG) void k_bicg_xrp(unsigned n, const BiState* __re
     vpartials<1, RI>(q, part, ntiles, it, nrhs);
 }
 
+// Update of a two-step minimal-residual cycle: x += a r + b t1; r -= a t1 + b t2.  Six spinor passes for two
+// operator applications, where the BiCGStab updates take eleven.
+template <class S, bool RI>
+__global__ __launch_bounds__(WG) void k_ls_update(unsigned n, const BiState* __restrict__ st,
+                                                  typename Traits<typename Traits<S>::xs>::word* __restrict__ x,
+                                                  typename Traits<S>::word* __restrict__ r,
+                                                  const typename Traits<S>::word* __restrict__ t1,
+                                                  const typename Traits<S>::word* __restrict__ t2, int nrhs, int ntiles) {
+    VTYPES(S);
+    const VItem it = vitem<RI>(n, nrhs, ntiles);
+    if (!it.ok) return;
+    const VView<RI, S> w(n, nrhs, it.i, it.r);
+    const VView<RI, XS> wx(n, nrhs, it.i, it.r);
+    const cx<R> a = cxs<R>(st[it.r].alpha), b = cxs<R>(st[it.r].omega);
+    if (a.re == R(0) && a.im == R(0) && b.re == R(0) && b.im == R(0)) return;  // converged
+    cx<XS> xx[12];
+    cx<R> rr[12], ta[12], tb[12];
+    load_spinor(x + wx.base, wx.stride, wx.idx, xx);
+    load_spinor(r + w.base, w.stride, w.idx, rr);
+    load_spinor(t1 + w.base, w.stride, w.idx, ta);
+    load_spinor(t2 + w.base, w.stride, w.idx, tb);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const cx<R> d = a * rr[k] + b * ta[k];
+        xx[k] = xx[k] + mk((XS)d.re, (XS)d.im);
+        rr[k] = rr[k] - (a * ta[k] + b * tb[k]);
+    }
+    store_spinor(x + wx.base, wx.stride, wx.idx, xx);
+    store_spinor(r + w.base, w.stride, w.idx, rr);
+}
+
 template <class S, bool RI>
 __global__ __launch_bounds__(WG) void k_accumulate(unsigned n,
                                                    const typename Traits<typename Traits<S>::xs>::word* __restrict__ x,
@@ -420,7 +454,29 @@ void launch_bicg_init(Exec& e, unsigned n, bool ri, const double2* r64, const do
                       typename Traits<S>::word* r, typename Traits<S>::word* rh, typename Traits<S>::word* p,
                       typename Traits<typename Traits<S>::xs>::word* x, double* part, int nrhs) {
     Timed t(e, 3, 0);
-    VDISPATCH(k_bicg_init, S, r64, scale, r, rh, p, x, part);
+    const int nt = vector_tiles(n, nrhs, ri), ng = vector_grid(n, nrhs, ri);
+    if (ri)
+        k_bicg_init<S, true, true><<<ng, WG, 0, e.stream>>>(n, r64, scale, r, rh, p, x, part, nrhs, nt);
+    else
+        k_bicg_init<S, false, true><<<ng, WG, 0, e.stream>>>(n, r64, scale, r, rh, p, x, part, nrhs, nt);
+}
+template <class S>
+void launch_ls_init(Exec& e, unsigned n, bool ri, const double2* r64, const double* scale,
+                    typename Traits<S>::word* r, typename Traits<typename Traits<S>::xs>::word* x, double* part,
+                    int nrhs) {
+    Timed t(e, 3, 0);
+    const int nt = vector_tiles(n, nrhs, ri), ng = vector_grid(n, nrhs, ri);
+    if (ri)
+        k_bicg_init<S, true, false><<<ng, WG, 0, e.stream>>>(n, r64, scale, r, nullptr, nullptr, x, part, nrhs, nt);
+    else
+        k_bicg_init<S, false, false><<<ng, WG, 0, e.stream>>>(n, r64, scale, r, nullptr, nullptr, x, part, nrhs, nt);
+}
+template <class S>
+void launch_ls_update(Exec& e, unsigned n, bool ri, const BiState* st, typename Traits<typename Traits<S>::xs>::word* x,
+                      typename Traits<S>::word* r, const typename Traits<S>::word* t1,
+                      const typename Traits<S>::word* t2, int nrhs) {
+    Timed tm(e, 3, 0);
+    VDISPATCH(k_ls_update, S, st, x, r, t1, t2);
 }
 template <class S>
 void launch_bicg_s(Exec& e, unsigned n, bool ri, const BiState* st, const typename Traits<S>::word* r,
@@ -489,6 +545,35 @@ void launch_stream_copy(Exec& e, const float4* src, float4* dst, size_t n) {
 }
 
 // ------------------------------------------------------------------ finalize (one workgroup per RHS)
+// Coefficients a (alpha) and b (omega) minimising ||r - a t1 - b t2||^2 from the dot products v of one cycle, the
+// squared norm that they leave, and whether the RHS goes on.  t2 parallel to t1 (to rounding): b = 0.
+__device__ __forceinline__ void ls_step(const double* v, BiState& S) {
+    const cx<double> h1 = mk(v[0], v[1]), h2 = mk(v[7], v[8]);
+    const double c11 = v[2], rr = v[3], c22 = v[6];
+    const cx<double> g21 = mk(v[4], v[5]);  // (t2, t1); (t1, t2) is its conjugate
+    const double det = c11 * c22 - (g21.re * g21.re + g21.im * g21.im);
+    cx<double> a = mk(0.0, 0.0), b = a;
+    if (det > 1e-10 * c11 * c22) {
+        // [c11 conj(g21); g21 c22] [a; b] = [h1; h2]
+        const double i = 1.0 / det;
+        a = i * (c22 * h1 - conj_mul(g21, h2));
+        b = i * (c11 * h2 - g21 * h1);
+    } else if (c11 > 0) {
+        a = (1.0 / c11) * h1;
+    }
+    const double left = rr - (a.re * h1.re + a.im * h1.im) - (b.re * h2.re + b.im * h2.im);
+    S.rr = left > 0 ? left : 0;
+    const double size = a.re * a.re + a.im * a.im + b.re * b.re + b.im * b.im;
+    if (!isfinite(left) || !isfinite(size) || !(size > 0)) {
+        S.broken = 1;
+        S.active = 0;
+        return;
+    }
+    if (S.rr <= S.thr2) S.active = 0;
+    S.alpha[0] = a.re, S.alpha[1] = a.im;
+    S.omega[0] = b.re, S.omega[1] = b.im;
+}
+
 // Sums the first NV partial components of each RHS over the tiles (fixed order), then applies
 // the BiCGStab stage.  v has NPART entries so that every stage can name its components.
 template <int NV>
@@ -496,7 +581,7 @@ __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ pa
                                                   double* __restrict__ sums, BiState* __restrict__ st, int stage,
                                                   const double* __restrict__ thr_rel2) {
     const int rhs = blockIdx.x;
-    double v[NPART] = {};
+    double v[NV > NPART ? NV : NPART] = {};
     // four strides in flight per thread (independent sums, combined in a fixed order): a single
     // workgroup per RHS is otherwise bound by the latency of one load round per stride
     constexpr int U = 4;
@@ -567,6 +652,10 @@ __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ pa
             S.omega[0] = S.omega[1] = 0;
             if (S.active && !(v[2] >= 0)) S.broken = 1;
         }
+    } else if (stage == ST_LS) {
+        // v: (t1, r), (t1, t1), (r, r), then (t2, t1), (t2, t2), (t2, r)
+        S.alpha[0] = S.alpha[1] = S.omega[0] = S.omega[1] = 0;
+        if (S.active) ls_step(v, S);
     } else if (stage == ST_RR) {
         if (S.active) {
             S.rr = v[0];
@@ -592,13 +681,14 @@ __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ pa
 void launch_finalize(Exec& e, const double* part, int ntiles, int nrhs, double* sums, BiState* st, int stage,
                      const double* thr_rel2, int nv) {
     Timed t(e, 3, 0);
-    if (nv < 0) nv = stage == ST_ALPHA ? 2 : stage == ST_OMEGA ? 7 : stage == ST_SUM ? 3 : 1;
+    if (nv < 0) nv = stage == ST_ALPHA ? 2 : stage == ST_OMEGA ? 7 : stage == ST_LS ? LS_NV : stage == ST_SUM ? 3 : 1;
     // one workgroup of 16 waves per RHS: the partial sums of up to ~10^4 tiles in a few strides
 #define FIN(N) k_finalize<N><<<nrhs, 1024, 0, e.stream>>>(part, ntiles, nrhs, sums, st, stage, thr_rel2)
     switch (nv) {
         case 1: FIN(1); break;
         case 2: FIN(2); break;
         case 3: FIN(3); break;
+        case LS_NV: FIN(LS_NV); break;
         default: FIN(7); break;
     }
 #undef FIN
@@ -855,6 +945,10 @@ int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads) {
                                 int, const Ext4*, int, bool);                                                     \
     template void launch_bicg_init<R>(Exec&, unsigned, bool, const double2*, const double*, Traits<R>::word*,      \
                                       Traits<R>::word*, Traits<R>::word*, Traits<R>::word*, double*, int);        \
+    template void launch_ls_init<R>(Exec&, unsigned, bool, const double2*, const double*, Traits<R>::word*,       \
+                                    Traits<R>::word*, double*, int);                                              \
+    template void launch_ls_update<R>(Exec&, unsigned, bool, const BiState*, Traits<R>::word*, Traits<R>::word*,  \
+                                      const Traits<R>::word*, const Traits<R>::word*, int);                       \
     template void launch_bicg_s<R>(Exec&, unsigned, bool, const BiState*, const Traits<R>::word*,                 \
                                    const Traits<R>::word*, Traits<R>::word*, int);                                \
     template void launch_bicg_xrp<R>(Exec&, unsigned, bool, const BiState*, Traits<R>::word*, Traits<R>::word*,   \
@@ -867,6 +961,9 @@ INST(float)
 
 template void launch_bicg_init<H16>(Exec&, unsigned, bool, const double2*, const double*, hw16*, hw16*, hw16*, float4*,
                                     double*, int);
+template void launch_ls_init<H16>(Exec&, unsigned, bool, const double2*, const double*, hw16*, float4*, double*, int);
+template void launch_ls_update<H16>(Exec&, unsigned, bool, const BiState*, float4*, hw16*, const hw16*, const hw16*,
+                                    int);
 template void launch_bicg_s<H16>(Exec&, unsigned, bool, const BiState*, const hw16*, const hw16*, hw16*, int);
 template void launch_bicg_xrp<H16>(Exec&, unsigned, bool, const BiState*, float4*, hw16*, const hw16*, const hw16*,
                                    const hw16*, hw16*, double*, int);

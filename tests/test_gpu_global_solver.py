@@ -1,0 +1,57 @@
+"""The even-odd global solver on the smallest lattice on which it starts with the two-step
+minimal-residual method (8192 sites), one size below (BiCGStab from the start) and at a kappa where it changes
+over to BiCGStab on the way, for one, a few and many right-hand sides in every precision, against the C
+oracle's solves (1e-9 relative in the max norm at tol 1e-12, as for every solve)."""
+import sys
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_1211_1214_amd as dd  # noqa: E402
+from oracle import cref, dirac  # noqa: E402
+from paper_1211_1214_amd import binding, inputs  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+_cache = {}
+
+
+def setup(lat):
+    if lat not in _cache:
+        blk = (4, 4, 4, 4) if lat[3] % 8 == 0 else (4, 4, 4, 2)
+        U = inputs.make_links(lat, 0.3, 31)
+        ctx = dd.Context(torch.from_numpy(U).cuda(), lat, blk, -1, 1.0)
+        _cache[lat] = (ctx, cref.CRef(U, lat, blk, 1.0), {})
+    return _cache[lat]
+
+
+@pytest.mark.parametrize("prec", [dd.FP64, dd.MIXED32, dd.MIXED16])
+@pytest.mark.parametrize("lat,kappa,nrhs", [((8, 8, 8, 12), 0.121, 3), ((8, 8, 8, 16), 0.121, 1),
+                                            ((8, 8, 8, 16), 0.121, 3), ((8, 8, 8, 16), 0.121, 9),
+                                            ((8, 8, 8, 16), 0.131, 3)])
+def test_global_solver(lat, kappa, nrhs, prec):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("global solver", lat, kappa, nrhs, prec, flush=True)
+    sys.stdout.flush()
+    ctx, R, want = setup(lat)
+    b = inputs.make_spinor(lat, 32, nrhs=9)[:nrhs].copy()
+    if nrhs > 1:
+        b[1] = 0  # converged from the start, beside others that are not
+    x, st = ctx.solve(kappa, torch.from_numpy(b).cuda(), tol=1e-12, prec=prec)
+    x = x.cpu().numpy()
+    for j in (0, nrhs - 1):
+        if (kappa, j) not in want:
+            want[kappa, j] = R.solve(dirac.mass(kappa), b[j], 1e-13).reshape(b[j].shape)
+        w = want[kappa, j]
+        assert np.abs(x[j] - w).max() <= 1e-9 * np.abs(w).max()
+    assert nrhs == 1 or np.all(x[1] == 0)
+    assert st["rel_residual"] <= 1e-12
+    if kappa > 0.13:
+        assert st["outer_iters"] >= (2 if prec == dd.FP64 else 3)  # the change-over starts another outer step
+    # chunks replayed from graphs and launched one by one give the same bits
+    ctx.set_option(binding.OPT_GRAPHS, 0)
+    y, _ = ctx.solve(kappa, torch.from_numpy(b).cuda(), tol=1e-12, prec=prec)
+    ctx.set_option(binding.OPT_GRAPHS, 1)
+    assert np.array_equal(y.cpu().numpy(), x)

@@ -977,7 +977,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     const EoFields<double> F64 = eo_fields<double>(C);
     const unsigned n2 = F64.n2;
     // blocks whose parity fits the LDS-resident kernel run it in FP32 for both low precisions
-    const bool lds = !fp64 && C->opt_blk_kernel == 0 && blk_lds_fits(g, C->lds_max);
+    bool lds = !fp64 && C->opt_blk_kernel == 0 && blk_lds_fits(g, C->lds_max);
     const bool h16 = prec == DDWC_MIXED16 && !lds;
     const size_t hw64 = (size_t)nrhs * 12 * n2;
     // the correction vector (slot 5) is kept in FP32 when the others are FP16
@@ -989,12 +989,15 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     CK(ws_t(C, "be_xe", hw64, &xe));
     CK(ws_t(C, "be_to", hw64, &to));  // A_oo^-1 b_o (prep)
     CK(ws_t(C, "be_th", hw64, &th));  // A_oo^-1 H x_e of the last residual pass
-    void* w[7];
-    const char* names[7] = {"be_r", "be_rh", "be_p", "be_v", "be_t", "be_e", "be_tmp"};
-    for (int k = 0; k < 7; ++k)
-        CK(ws_get(C, std::string(names[k]) + (fp64 ? "64" : h16 ? "16" : "32"), (k == 5 ? slabX : slabS) * nrhs,
-                  &w[k]));
-    // (the LDS-resident kernel uses slots 1, 3, 5 only)
+    void* w[7];  // vectors of the global-memory kernel (the LDS-resident one has none)
+    auto slabs = [&]() -> int {
+        const char* names[7] = {"be_r", "be_rh", "be_p", "be_v", "be_t", "be_e", "be_tmp"};
+        for (int k = 0; k < 7; ++k)
+            CK(ws_get(C, std::string(names[k]) + (fp64 ? "64" : h16 ? "16" : "32"), (k == 5 ? slabX : slabS) * nrhs,
+                      &w[k]));
+        return DDWC_OK;
+    };
+    if (!lds) CK(slabs());
     const size_t nb = (size_t)nrhs * g.NBc;
     double *bb, *rr;
     int* iters;
@@ -1004,7 +1007,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     HC(hipMemsetAsync(iters, 0, nb * sizeof(int), ex.stream));
     // (k_blk_recon writes this colour's solution and clears the other colour)
     launch_blk_prep(ex, g, F64, A64, b64, bpe, re, xe, to, bb, rr, colour, nrhs);
-    std::vector<double> hbb(nb), hrr(nb);
+    std::vector<double> hbb(nb), hrr(nb), was;
     std::vector<int> hit(nb);
     HC(hipMemcpyAsync(hbb.data(), bb, nb * sizeof(double), hipMemcpyDeviceToHost, ex.stream));
     int nout = 0, imax = 0;
@@ -1030,12 +1033,27 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
         }
         if (imax >= maxit || nout >= 30) break;
         ++nout;
+        if (lds) {
+            // where a launch of the LDS-resident kernel (floor 2e-6) has left a block above 1e-2 of its last
+            // residual, with further than that to go, minimal residual converges too slowly there: BiCGStab
+            // for the rest
+            bool slow = false;
+            for (size_t k = 0; k < was.size(); ++k) {
+                const double goal = tol * tol * hbb[k];
+                slow = slow || (hbb[k] > 0 && hrr[k] > goal && hrr[k] > 1e-4 * was[k] && was[k] > 1e4 * goal);
+            }
+            if (slow) {
+                lds = false;
+                CK(slabs());
+            }
+            was = hrr;
+        }
         if (fp64) {
             const EoFields<double> F = F64;
             launch_blk_inner<double>(ex, g, F, A64, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
         } else if (lds) {
             const EoFields<float> F = eo_fields<float>(C);
-            launch_blk_lds(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
+            launch_blk_lds(ex, g, F, A32, re, xe, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
         } else if (h16) {
             const EoFields<H16> F = eo_fields<H16>(C);
             launch_blk_inner<H16>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);

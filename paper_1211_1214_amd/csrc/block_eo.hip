@@ -409,26 +409,31 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
 }
 
 // ------------------------------------------------------------------ LDS-resident inner solver
-// The same BiCGStab on M_k as k_blk_inner, one workgroup per (block, RHS), for block parities of
-// at most BL_MAX sites: one thread per local half index l < hvb owns the even site and the odd
-// site of that index.  The operand of M_k (p, then s; even sites) and the odd intermediate
-// A_oo^-1 H^k_oe (operand) are staged in LDS (2 x (hvb + 1) x 96 bytes, 124 KB for a 6^4 block), so
-// the in-block neighbour gathers of both passes, and each site's own operand, are LDS reads.  r
-// stays in registers until s is formed from it and v then takes its place until p is updated, so
-// that p, rh and the correction e are the only global slabs (slots 2, 1, 5), each touched once or
-// twice per iteration.  Links (packed, five loads each) and clover are read from global memory: the
-// RHS of one block run on one XCD and share them in its L2.  Arithmetic FP32, dot products accumulated
-// in FP64 as in k_blk_inner.
+// Minimal residual on M_k, one workgroup per (block, RHS), for block parities of at most BL_MAX sites:
+//     t = M_k r, omega = (t, r) / (t, t), e += omega r, r -= omega t.
+// The Dirichlet operators of the blocks are well conditioned, and it needs as many operator applications
+// as BiCGStab (to 2e-6: 19 against 20 at kappa = 0.1205, 22 / 22 at 0.125, 26 / 24 at 0.129; 6^4 blocks, eps = 0.3 links)
+// with one vector kept beside r.  A block whose residual falls by less than BL_GAIN in BL_WINDOW steps
+// is left to the caller, which goes on with the BiCGStab of k_blk_inner.
+//
+// One thread per local half index l < hvb owns the even site and the odd site of that index.  r (the
+// operand of M_k; even sites) and the odd intermediate A_oo^-1 H^k_oe r are staged in LDS
+// (2 x (hvb + 1) x 96 bytes, 124 KB for a 6^4 block), so the in-block neighbour gathers of both passes
+// are LDS reads; e stays in registers.  Links (packed, five loads each) and clover are read from
+// global memory: the RHS of one block run on one XCD and share them in its L2.  Arithmetic FP32, dot
+// products accumulated in FP64.
 //
 // What bounds it: one 11-wave workgroup per CU (6^4) issues vector loads and ALU work in barrier-
-// separated phases.  Times per launch at 48x24^3, 6^4, 12 RHS, one colour (9.5 iterations): 5677 us with
-// entry-major links (nine 8-byte loads each), r and v as slabs, conditional hops and shuffle
-// reductions; 4883 us with r and v in registers and branch-free hops; 4296 us with the packed links;
-// 4002 us with the exchanging reduction.  With no loads but the LDS reads it takes about 3000 us, which
-// is the ALU work (6500 instructions a site and iteration in 3 waves per SIMD): the load path, 64 bytes a
-// cycle and CU for 3.4 KB a site and iteration, is what remains.  Loading the next pass's first link
-// and the clover words earlier spilled and was slower (5033 to 5544 us).
-constexpr int BL_MAX = 768;  // 12 waves: 3 per SIMD at up to 168 VGPRs
+// separated phases, 1.7 KB of links and clover and 3300 vector
+// instructions a site and step.  Time per launch at 48x24^3,
+// 6^4, 12 RHS, one colour (to 2e-6, then to tol = 1e-10): BiCGStab with entry-major links (nine 8-byte
+// loads each), five global vectors, conditional hops and shuffle reductions 5677 us; 4883 us with r and v in
+// registers and branch-free hops; 4296 us with the packed links; 4002 us with the exchanging
+// reduction; 3500 us with minimal residual.  With no global loads but the same LDS reads and ALU work the BiCGStab
+// took 3000 us: the load path, 64 bytes a cycle and CU, is the rest.
+constexpr int BL_MAX = 768;     // 12 waves: 3 per SIMD at up to 168 VGPRs
+constexpr int BL_WINDOW = 8;    // steps
+constexpr double BL_GAIN = 0.4;  // 0.05 decades a step, where BiCGStab takes over in the global solver too
 
 // Exchanges halves between a and b and adds, on the two dwords of each double: with W = 32 the lower 32
 // lanes get a(lane) + a(lane + 32) and the upper ones b(lane - 32) + b(lane); with W = 16 the same
@@ -581,9 +586,7 @@ __device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own,
 }
 
 __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, const float4* __restrict__ Ainv,
-                                                    const double2* re, double2* xe, float4* rhg, float4* pg,
-                                                    float4* eg,
-                                                    const double* __restrict__ bb, const double* __restrict__ rr,
+                                                    const double2* re, double2* xe, const double* __restrict__ bb, const double* __restrict__ rr,
                                                     double mass4, double tol, double inner_floor, int maxit,
                                                     int* iters, int colour, int nrhs) {
     extern __shared__ float4 bl_lds[];
@@ -600,11 +603,8 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     const bool act = threadIdx.x < HV;
     const unsigned l = act ? threadIdx.x : HV, lg = act ? threadIdx.x : 0u;
     const unsigned lo = byte_offset(lg, 16), own = byte_offset(h0 + lg, 16);  // its byte offsets in the planes
-    const size_t oh = (size_t)k.rhs * 12 * n2 + h0, oR = (size_t)k.rhs * 6 * n2 + h0;
+    const size_t oh = (size_t)k.rhs * 12 * n2 + h0;
     // everything below is addressed from the block's first site
-    rhg += oR;
-    pg += oR;
-    eg += oR;
     re += oh;
     xe += oh;
     const char *Ue = (const char*)F.W[0], *Uo = (const char*)F.W[1];
@@ -625,135 +625,77 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
         K.apply(0.f, acc, w, 0.f);
         if (act) lds_store(tp, l, w);
     };
-    // y = (4 + m + C) q_e - 1/4 H^k_eo q_o on the even sites (q_e in op, q_o in tp); h = rh
-    auto even = [&](cx<float> y[12], cx<float> h[12]) {
+    // y = (4 + m + C) c - 1/4 H^k_eo q_o on the even sites (c: this site's operand; q_o in tp)
+    auto even = [&](cx<float> y[12], cx<float> c[12]) {
         UDiag<float> K(fresh(Ke), n2, lo);
         lds_hops(n2, h0, own, ne, HV, tp, Ue, Uo, y);
-        cx<float> c[12];
         lds_load(op, l, c);
         K.off = reissue(lo), K.first();
         K.apply(m4, c, y, -0.25f);
-        uload_spinor(fresh(rhg), n2, lo, h);
     };
     const double rn = sqrt(r2), sc = 1.0 / rn;
-    double eps = 0.5 * tol * sqrt(b2) / rn;
+    // (a step gains half as much as a BiCGStab iteration, so it stops closer to its aim: a quarter of tol
+    // leaves solutions as accurate as the BiCGStab kernel's half)
+    double eps = 0.25 * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     int phase = 0;  // reduction slot
-    double red[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    cx<float> r[12];  // r until s is formed, then v until p is updated
+    double red[4];
+    cx<float> e[12];  // the correction
     {
         cx<double> a[12];
         uload_spinor(re, n2, lo, a);
+        cx<float> r[12];
 #pragma unroll
-        for (int c = 0; c < 12; ++c) r[c] = act ? mk((float)(sc * a[c].re), (float)(sc * a[c].im)) : mk(0.f, 0.f);
+        for (int c = 0; c < 12; ++c) {
+            r[c] = act ? mk((float)(sc * a[c].re), (float)(sc * a[c].im)) : mk(0.f, 0.f);
+            e[c] = mk(0.f, 0.f);
+        }
+        if (act) lds_store(op, l, r);
+        red[0] = acc_nrm(r);
     }
-    if (act) {
-        const cx<float> z[12] = {};
-        ustore_spinor(fresh(rhg), n2, lo, r);
-        ustore_spinor(fresh(pg), n2, lo, r);
-        ustore_spinor(fresh(eg), n2, lo, z);
-        lds_store(op, l, r);
-    }
-    red[0] = acc_nrm(r);
     wg_sums<1>(red, red_lds[phase ^= 1]);  // (its barrier also publishes the operand)
-    cx<double> rho = mk(red[0], 0.0);
     const double thr2 = eps * eps * red[0];
+    double window = red[0];  // ||r||^2 when the current window began
     int it = 0;
     while (it < maxit) {
-        // v = M_k p, (rh, v)
+        // t = M_k r, (t, r), (t, t), (r, r)
         odd();
         __syncthreads();
+        cx<float> t[12], r[12];
+        even(t, r);
         red[0] = red[1] = 0;
-        cx<float> v[12];
-        {
-            cx<float> h[12];
-            even(v, h);
-            acc_dot(h, v, red[0], red[1]);
-        }
-        wg_sums<2>(red, red_lds[phase ^= 1]);
-        if (!(red[0] * red[0] + red[1] * red[1] > 0)) break;
-        const cx<float> alpha = cdiv_r<float>(rho, mk(red[0], red[1]));
-        // s = r - alpha v, staged as the operand
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            const cx<float> sv = r[c] - alpha * v[c];
-            r[c] = v[c];
-            v[c] = sv;
-        }
-        if (act) lds_store(op, l, v);
-        __syncthreads();
-        // t = M_k s, (t, s), (t, t), (rh, s), (rh, t), (s, s)
-        odd();
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 8; ++c) red[c] = 0;
-        cx<float> t[12], e[12], pp[12];
-        {
-            cx<float> sv[12], h[12];
-            even(t, h);
-            lds_load(op, l, sv);
-            acc_dot(t, sv, red[0], red[1]);
-            red[2] = acc_nrm(t);
-            acc_dot(h, sv, red[3], red[4]);
-            acc_dot(h, t, red[5], red[6]);
-            red[7] = acc_nrm(sv);
-            // (needed after the reduction)
-            uload_spinor(fresh(eg), n2, lo, e);
-            uload_spinor(fresh(pg), n2, lo, pp);
-        }
-        wg_sums<8>(red, red_lds[phase ^= 1]);
+        acc_dot(t, r, red[0], red[1]);
+        red[2] = acc_nrm(t);
+        red[3] = acc_nrm(r);
+        wg_sums<4>(red, red_lds[phase ^= 1]);
         ++it;
-        cx<float> omega = mk(0.f, 0.f);
-        if (red[2] > 0) omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
-        // r = s - omega t is orthogonal to t, so ||r||^2 = (s, s) - |(t, s)|^2 / (t, t); the next
-        // rho = (rh, r) = (rh, s) - omega (rh, t): one reduction serves omega, the stopping test and
-        // beta, and x, r and p are updated in one pass
-        const double r2n = red[2] > 0 ? red[7] - (red[0] * red[0] + red[1] * red[1]) / red[2] : red[7];
-        const cx<double> rn_ = mk(red[3] - ((double)omega.re * red[5] - (double)omega.im * red[6]),
-                                  red[4] - ((double)omega.re * red[6] + (double)omega.im * red[5]));
-        const double d1 = rho.re * rho.re + rho.im * rho.im;
-        const double d2 = (double)omega.re * omega.re + (double)omega.im * omega.im;
-        const bool stop = r2n <= thr2 || !isfinite(r2n) || !(d2 > 0) || !(d1 > 0);
-        cx<float> beta = mk(0.f, 0.f);
-        if (!stop) {
-            const cx<double> q = mk((rn_.re * rho.re + rn_.im * rho.im) / d1, (rn_.im * rho.re - rn_.re * rho.im) / d1);
-            const cx<double> ao = mk(((double)alpha.re * omega.re + (double)alpha.im * omega.im) / d2,
-                                     ((double)alpha.im * omega.re - (double)alpha.re * omega.im) / d2);
-            beta = mk((float)(q.re * ao.re - q.im * ao.im), (float)(q.re * ao.im + q.im * ao.re));
-        }
-        rho = rn_;
-        // e += alpha p + omega s ; r = s - omega t ; p = r + beta (p - omega v), staged as the next operand
-        lds_load(op, l, v);
+        if (!(red[2] > 0)) break;
+        // e += omega r, r -= omega t with the omega that minimises ||r||, staged as the next operand
+        const cx<float> omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            e[c] = e[c] + (alpha * pp[c] + omega * v[c]);
-            v[c] = v[c] - omega * t[c];
+            cmadd(e[c], omega, r[c]);
+            cmadd(r[c], mk(-omega.re, -omega.im), t[c]);
         }
-        if (act) ustore_spinor(fresh(eg), n2, lo, e);
-        if (stop) break;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            pp[c] = v[c] + beta * (pp[c] - omega * r[c]);
-            r[c] = v[c];
+        const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
+        if (!(r2n > thr2) || !isfinite(r2n)) break;
+        if (it % BL_WINDOW == 0) {
+            if (r2n > BL_GAIN * BL_GAIN * window) break;  // too slow: left to the caller
+            window = r2n;
         }
-        if (act) {
-            ustore_spinor(fresh(pg), n2, lo, pp);
-            // (only this thread reads its own operand slot after the last barrier)
-            lds_store(op, l, pp);
-        }
+        // (only this thread reads its own operand record after the last barrier)
+        if (act) lds_store(op, l, r);
         __syncthreads();
     }
     // x_e += ||r_e|| e in FP64
     if (act) {
-        cx<float> e[12];
         cx<double> x[12];
-        uload_spinor(fresh(eg), n2, lo, e);
         uload_spinor(xe, n2, lo, x);
 #pragma unroll
         for (int c = 0; c < 12; ++c) x[c] = x[c] + mk(rn * (double)e[c].re, rn * (double)e[c].im);
         ustore_spinor(xe, n2, lo, x);
     }
-    if (threadIdx.x == 0) iters[k.key] += it;
+    if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
 }
 
 bool blk_lds_fits(const Geom& g, int lds_max_bytes) {
@@ -761,15 +703,15 @@ bool blk_lds_fits(const Geom& g, int lds_max_bytes) {
 }
 
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
-                    double2* xe, void* const w[7], const double* bb, const double* rr, double mass4, double tol,
+                    double2* xe, const double* bb, const double* rr, double mass4, double tol,
                     int maxit, int* iters, int colour, int nrhs) {
     Timed t(e, 2, 0);
     const int threads = ((g.hvb + 63) / 64) * 64;
     const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
     // the inner solve stops at this relative residual at the least (FP32's reach)
-    k_blk_lds<<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (float4*)w[1], (float4*)w[2], (float4*)w[5],
-                                                        bb, rr, mass4, tol, 2e-6,
-                                                        maxit, iters, colour, nrhs);
+    // (a BiCGStab iteration, the unit of maxit, is two steps)
+    k_blk_lds<<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6,
+                                                        maxit < (1 << 30) ? 2 * maxit : maxit, iters, colour, nrhs);
 }
 
 void launch_blk_prep(Exec& e, const Geom& g, const EoFields<double>& F, const double2* Ainv, const double2* b,

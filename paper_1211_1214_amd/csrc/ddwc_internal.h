@@ -283,13 +283,13 @@ template <class S>
 void launch_blk_inner(Exec& e, const Geom& g, const EoFields<S>& F, const typename Traits<S>::kword* Ainv,
                       const double2* re, double2* xe, void* const w[7], const double* bb, const double* rr,
                       double mass4, double tol, int maxit, int* iters, int colour, int nrhs);
-// The LDS-resident FP32 inner solver (both staged block fields in LDS, per-site iterates in
-// registers): whether it takes this geometry with lds_max_bytes of LDS per workgroup, and its
-// launch (slabs w[1], w[3], w[5] hold rh, v and the correction in FP32).
+// The LDS-resident FP32 inner solver (r and the odd intermediate in LDS, the correction in registers):
+// whether it takes this geometry with lds_max_bytes of LDS per workgroup, and its launch.  It leaves
+// blocks on which minimal residual converges slowly where they stand.
 bool blk_lds_fits(const Geom& g, int lds_max_bytes);
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
-                    double2* xe, void* const w[7], const double* bb, const double* rr, double mass4, double tol,
-                    int maxit, int* iters, int colour, int nrhs);
+                    double2* xe, const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
+                    int colour, int nrhs);
 // bytes of one RHS of a block-solver vector in the storage of precision `prec` (n2 = V/2)
 size_t blk_slab_bytes(int prec, unsigned n2);
 

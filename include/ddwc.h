@@ -267,8 +267,7 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *                          block parity, at most 768 for the FP32/FP16 inner solver and 256 for
  *                          the FP64 kernels) or a multiple of 64 in [64, 768] (capped alike).
  *   DDWC_OPT_SOLVER        global solver: 0 even-odd (default): two-step minimal residual, changing
- *                          over to BiCGStab where that converges faster (lexicographic BiCGStab
- *                          when a block extent is odd), 1 GCR (8 directions per cycle, restarted with
+ *                          over to BiCGStab where that converges faster, 1 GCR (8 directions per cycle, restarted with
  *                          the exact FP64 residual) preconditioned by the Schwarz alternating
  *                          procedure: 3 multiplicative cycles over the black then the white
  *                          blocks, each block solve by the persistent block solver to 1e-1.

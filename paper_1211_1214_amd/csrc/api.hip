@@ -130,7 +130,7 @@ struct ddwc_ctx {
     double2* K64 = nullptr;
     float4* K32 = nullptr;
     int* nbr = nullptr;  // neighbour table [8][V]
-    // even-odd half fields (allocated when every block extent is even)
+    // even-odd half fields (the FP16 and packed links only when every block extent is even)
     cx<double>* Uh64 = nullptr;
     cx<float>* Uh32 = nullptr;
     double2* Kh64 = nullptr;
@@ -307,28 +307,23 @@ extern "C" int ddwc_create(ddwc_ctx** out, const int lat[4], const int blk[4], i
     launch_links_import(ex, g, links_dev, C->U64, C->U32);
     launch_links_own(ex, (unsigned)g.V, C->U32, C->U32, C->nbr, C->U32s);
     launch_clover_build(ex, g, C->U64, c_sw, C->K64, C->K32);
+    const size_t n2 = g.V / 2;
+    if (hipMalloc(&C->Uh64, (size_t)2 * 36 * n2 * sizeof(cx<double>)) != hipSuccess ||
+        hipMalloc(&C->Uh32, (size_t)2 * 36 * n2 * sizeof(cx<float>)) != hipSuccess ||
+        hipMalloc(&C->Kh64, (size_t)2 * 36 * n2 * sizeof(double2)) != hipSuccess ||
+        hipMalloc(&C->Kh32, (size_t)2 * 18 * n2 * sizeof(float4)) != hipSuccess ||
+        hipMalloc(&C->nbr_eo, (size_t)2 * 8 * n2 * sizeof(int)) != hipSuccess ||
+        hipMalloc(&C->Uh32s, (size_t)2 * 72 * n2 * sizeof(cx<float>)) != hipSuccess ||
+        (g.eo && (hipMalloc(&C->Uh16, (size_t)2 * 36 * n2 * sizeof(cx<f16>)) != hipSuccess ||
+                  hipMalloc(&C->Uh16s, (size_t)2 * 72 * n2 * sizeof(cx<f16>)) != hipSuccess)) ||
+        (blk_lds_fits(g, C->lds_max) && hipMalloc(&C->Uh32w, (size_t)8 * PACKED_LINK_BYTES * n2) != hipSuccess)) {
+        ddwc_destroy(C);
+        return fail(DDWC_EHIP, "device allocation of the even-odd fields failed");
+    }
+    launch_eo_setup(ex, g, C->U64, C->K64, C->nbr, C->Uh64, C->Uh32, C->Kh64, C->Kh32, C->nbr_eo);
+    launch_eo_links_own(ex, (unsigned)n2, C->Uh32, C->nbr_eo, C->Uh32s);
+    if (C->Uh32w) launch_eo_links_packed(ex, (unsigned)n2, C->Uh32, C->Uh32w);
     if (g.eo) {
-        const size_t n2 = g.V / 2;
-        if (hipMalloc(&C->Uh64, (size_t)2 * 36 * n2 * sizeof(cx<double>)) != hipSuccess ||
-            hipMalloc(&C->Uh32, (size_t)2 * 36 * n2 * sizeof(cx<float>)) != hipSuccess ||
-            hipMalloc(&C->Kh64, (size_t)2 * 36 * n2 * sizeof(double2)) != hipSuccess ||
-            hipMalloc(&C->Kh32, (size_t)2 * 18 * n2 * sizeof(float4)) != hipSuccess ||
-            hipMalloc(&C->nbr_eo, (size_t)2 * 8 * n2 * sizeof(int)) != hipSuccess ||
-            hipMalloc(&C->Uh16, (size_t)2 * 36 * n2 * sizeof(cx<f16>)) != hipSuccess ||
-            hipMalloc(&C->Uh32s, (size_t)2 * 72 * n2 * sizeof(cx<float>)) != hipSuccess ||
-            hipMalloc(&C->Uh16s, (size_t)2 * 72 * n2 * sizeof(cx<f16>)) != hipSuccess) {
-            ddwc_destroy(C);
-            return fail(DDWC_EHIP, "device allocation of the even-odd fields failed");
-        }
-        launch_eo_setup(ex, g, C->U64, C->K64, C->nbr, C->Uh64, C->Uh32, C->Kh64, C->Kh32, C->nbr_eo);
-        launch_eo_links_own(ex, (unsigned)n2, C->Uh32, C->nbr_eo, C->Uh32s);
-        if (blk_lds_fits(g, C->lds_max)) {
-            if (hipMalloc(&C->Uh32w, (size_t)8 * PACKED_LINK_BYTES * n2) != hipSuccess) {
-                ddwc_destroy(C);
-                return fail(DDWC_EHIP, "device allocation of the even-odd fields failed");
-            }
-            launch_eo_links_packed(ex, (unsigned)n2, C->Uh32, C->Uh32w);
-        }
         launch_links_to_half(ex, (size_t)2 * 36 * n2, C->Uh32, C->Uh16);
         launch_links_to_half(ex, (size_t)2 * 72 * n2, C->Uh32s, C->Uh16s);
     }
@@ -386,133 +381,12 @@ extern "C" int ddwc_destroy(ddwc_ctx* C) {
 }
 
 // ------------------------------------------------------------------ global solver
-// FP64 defect correction around BiCGStab in precision R on all RHS at once.
-// b64, x64: internal FP64 multi-vectors.  Scalars stay on the device; the host polls
-// the per-RHS state every `poll` iterations.
+// FP64 defect correction around a Krylov solver in the working precision on all RHS at once
+// (eo_solve).  Scalars stay on the device; the host polls the per-RHS state.
 struct SolveInfo {
     int outer = 0, inner = 0;
     double relres = 0;
 };
-
-template <class R>
-static int global_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, double2* x64, int nrhs, double tol,
-                        int maxit, SolveInfo* info) {
-    typedef typename Traits<R>::word W;
-    const Geom& g = C->g;
-    const bool fp64 = sizeof(R) == 8;
-    const size_t nw = vec_words(C, nrhs, fp64);
-    const int nt = tiles_of(g.V);
-    const cx<R>* U = fp64 ? (const cx<R>*)C->U64 : (const cx<R>*)C->U32;
-    const W* K = fp64 ? (const W*)C->K64 : (const W*)C->K32;
-    const int kcl = fp64 ? DDWC_K_DSLASH64 : DDWC_K_DSLASH32;
-    const double dbytes = ddwc_dslash_bytes(C, nrhs, fp64 ? DDWC_FP64 : DDWC_MIXED32);
-    const double rb = (double)nrhs * g.V * 24.0 * sizeof(R);  // one vector of nrhs spinors
-    const double mass4 = 4.0 + mass;
-    W *r, *rh, *p, *v, *s, *t, *xR;
-    double2* r64;
-    double *part, *sums, *scale, *thr;
-    BiState* st;
-    const std::string pre = fp64 ? "g64_" : "g32_";
-    CK(ws_t(C, pre + "r", nw, &r));
-    CK(ws_t(C, pre + "rh", nw, &rh));
-    CK(ws_t(C, pre + "p", nw, &p));
-    CK(ws_t(C, pre + "v", nw, &v));
-    CK(ws_t(C, pre + "s", nw, &s));
-    CK(ws_t(C, pre + "t", nw, &t));
-    CK(ws_t(C, pre + "x", nw, &xR));
-    CK(ws_t(C, "g_r64", vec_words(C, nrhs, true), &r64));
-    CK(ws_t(C, "g_part", (size_t)nt * nrhs * NPART, &part));
-    CK(ws_t(C, "g_sums", (size_t)nrhs * NPART, &sums));
-    CK(ws_t(C, "g_scale", (size_t)nrhs, &scale));
-    CK(ws_t(C, "g_thr", (size_t)nrhs, &thr));
-    CK(ws_t(C, "g_state", (size_t)nrhs, &st));
-    double* hb;
-    const size_t nst = (sizeof(BiState) + 7) / 8;
-    CK(host_buf(C, (size_t)nrhs * (NPART + 2 + nst) + 16, &hb));
-    double* h_sums = hb;
-    double* h_scale = hb + (size_t)nrhs * NPART;
-    double* h_thr = h_scale + nrhs;
-    BiState* h_st = (BiState*)(h_thr + nrhs);
-    hipStream_t sm = ex.stream;
-
-    // ||b||^2
-    launch_dots(ex, g, b64, b64, part, nrhs);
-    launch_finalize(ex, part, nt, nrhs, sums, nullptr, ST_SUM, nullptr);
-    HC(hipMemcpyAsync(h_sums, sums, sizeof(double) * nrhs * NPART, hipMemcpyDeviceToHost, sm));
-    HC(hipStreamSynchronize(sm));
-    std::vector<double> bb(nrhs), rr(nrhs);
-    for (int k = 0; k < nrhs; ++k) {
-        bb[k] = h_sums[k * NPART + 2];
-        rr[k] = bb[k];
-        if (!isfinite(bb[k])) return fail(DDWC_ENONFINITE, "non-finite right-hand side");
-    }
-    HC(hipMemsetAsync(x64, 0, sizeof(double2) * vec_words(C, nrhs, true), sm));
-    HC(hipMemcpyAsync(r64, b64, sizeof(double2) * vec_words(C, nrhs, true), hipMemcpyDeviceToDevice, sm));
-    const double floor_eps = fp64 ? 0.0 : 2e-6;
-    const int poll = 2;
-    int total = 0, nout = 0;
-    bool converged = false;
-    while (true) {
-        bool all = true;
-        for (int k = 0; k < nrhs; ++k)
-            if (bb[k] > 0 && rr[k] > tol * tol * bb[k]) all = false;
-        if (all) {
-            converged = true;
-            break;
-        }
-        if (total >= maxit || nout >= 100) break;
-        ++nout;
-        for (int k = 0; k < nrhs; ++k) {
-            bool done = !(bb[k] > 0 && rr[k] > tol * tol * bb[k]);
-            h_scale[k] = done ? 0.0 : 1.0 / sqrt(rr[k]);
-            double eps = done ? 0.0 : 0.5 * tol * sqrt(bb[k] / rr[k]);
-            if (eps < floor_eps) eps = floor_eps;
-            h_thr[k] = done ? 2.0 : eps * eps;
-        }
-        HC(hipMemcpyAsync(scale, h_scale, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
-        HC(hipMemcpyAsync(thr, h_thr, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
-        launch_bicg_init<R>(ex, g.V, false, r64, scale, r, rh, p, xR, part, nrhs);
-        launch_finalize(ex, part, nt, nrhs, nullptr, st, ST_INIT, thr);
-        int it = 0;
-        while (total < maxit) {
-            for (int k = 0; k < poll && total < maxit; ++k, ++it, ++total) {
-                launch_dslash_dot<R>(ex, g, U, K, mass4, p, v, rh, part, nrhs, kcl, dbytes + rb);
-                launch_finalize(ex, part, nt, nrhs, nullptr, st, ST_ALPHA, nullptr);
-                launch_bicg_s<R>(ex, g.V, false, st, r, v, s, nrhs);
-                launch_dslash_dot4<R>(ex, g, U, K, mass4, s, t, rh, part, nrhs, kcl, dbytes + rb);
-                launch_finalize(ex, part, nt, nrhs, nullptr, st, ST_OMEGA, nullptr);
-                launch_bicg_xrp<R>(ex, g.V, false, st, xR, p, s, t, v, r, part, nrhs);
-                launch_finalize(ex, part, nt, nrhs, nullptr, st, ST_RR, nullptr);
-            }
-            HC(hipGetLastError());
-            HC(hipMemcpyAsync(h_st, st, sizeof(BiState) * nrhs, hipMemcpyDeviceToHost, sm));
-            HC(hipStreamSynchronize(sm));
-            bool any = false;
-            for (int k = 0; k < nrhs; ++k) any = any || h_st[k].active;
-            if (!any) break;
-        }
-        launch_accumulate<R>(ex, g.V, false, xR, scale, x64, nrhs);
-        launch_residual<double>(ex, g, C->U64, C->K64, mass4, x64, b64, r64, part, nrhs, DDWC_K_DSLASH64,
-                                ddwc_dslash_bytes(C, nrhs, DDWC_FP64) + (double)nrhs * g.V * 192.0);
-        launch_finalize(ex, part, nt, nrhs, sums, nullptr, ST_SUM, nullptr, 1);
-        HC(hipMemcpyAsync(h_sums, sums, sizeof(double) * nrhs * NPART, hipMemcpyDeviceToHost, sm));
-        HC(hipStreamSynchronize(sm));
-        for (int k = 0; k < nrhs; ++k) {
-            rr[k] = h_sums[k * NPART];
-            if (!isfinite(rr[k])) return fail(DDWC_ENONFINITE, "non-finite residual in the global solve");
-        }
-    }
-    double worst = 0;
-    for (int k = 0; k < nrhs; ++k)
-        if (bb[k] > 0) worst = fmax(worst, sqrt(rr[k] / bb[k]));
-    if (info) {
-        info->outer += nout;
-        info->inner += total;
-        info->relres = fmax(info->relres, worst);
-    }
-    if (!converged) return fail(DDWC_ENOCONV, "global solve did not reach its tolerance within maxit");
-    return DDWC_OK;
-}
 
 // ------------------------------------------------------------------ even-odd global solver
 // Half-field operator data.  site_major selects the own-site link records (FP32, FP16) that the
@@ -933,13 +807,10 @@ static int sap_gcr(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doubl
 static int solve_internal(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, double2* x64, int nrhs,
                           double tol, int maxit, int prec, SolveInfo* info) {
     if (C->opt_solver == 1) return sap_gcr(C, ex, mass, b64, x64, nrhs, tol, maxit, prec, info);
-    if (C->g.eo) {
-        if (prec == DDWC_FP64) return eo_solve<double>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
-        if (prec == DDWC_MIXED16) return eo_solve<H16>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
-        return eo_solve<float>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
-    }
-    if (prec == DDWC_FP64) return global_solve<double>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
-    return global_solve<float>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
+    if (prec == DDWC_FP64) return eo_solve<double>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
+    // (lattices with an odd block extent have no FP16 fields)
+    if (prec == DDWC_MIXED16 && C->g.eo) return eo_solve<H16>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
+    return eo_solve<float>(C, ex, mass, b64, x64, nrhs, tol, maxit, info);
 }
 
 // ------------------------------------------------------------------ block solves

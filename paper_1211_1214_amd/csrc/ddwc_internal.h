@@ -109,16 +109,6 @@ template <class R>
 void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
                    const typename Traits<R>::word* in, typename Traits<R>::word* out, int nrhs, int kclass,
                    double bytes);
-// out = D(m) in, partial[rhs][tile] = (w, out) (complex).
-template <class R>
-void launch_dslash_dot(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                       const typename Traits<R>::word* in, typename Traits<R>::word* out,
-                       const typename Traits<R>::word* w, double* part, int nrhs, int kclass, double bytes);
-// out = D(m) in, partials (out, in) complex, (out, out), (rh, in) and (rh, out) complex.
-template <class R>
-void launch_dslash_dot4(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                        const typename Traits<R>::word* in, typename Traits<R>::word* out,
-                        const typename Traits<R>::word* rh, double* part, int nrhs, int kclass, double bytes);
 // r = b - D(m) x, partial ||r||^2.
 template <class R>
 void launch_residual(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,

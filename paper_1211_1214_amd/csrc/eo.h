@@ -10,17 +10,29 @@
 // and D x = b becomes Mee x_e = b_e + 1/2 H_eo A_oo^-1 b_o, x_o = A_oo^-1 (b_o + 1/2 H_oe x_e).
 // Restricting H to hops inside a block gives the same structure for the Dirichlet
 // block operators D_k.
+//
+// With an odd block extent the half fields of the global operator are in lexicographic order
+// instead: L3 is even (the number of blocks is), so sites 2 i and 2 i + 1 of the canonical order are of
+// opposite parity, and both have half index i.  (The block solvers then use full fields.)
 #pragma once
 #include "ddwc_device.h"
 
 namespace ddwc {
 
 DDWC_HD unsigned half_index(const Geom& g, unsigned s, int& p) {
+    if (!g.eo) {
+        const Site S = decode(g, (int)s);
+        int sum = 0;
+        for (int mu = 0; mu < 4; ++mu) sum += S.n[mu] * g.b[mu] + S.l[mu];
+        p = sum & 1;
+        return (unsigned)canonical_index(g, S) >> 1;
+    }
     const unsigned B = s / (unsigned)g.Vb, loc = s - B * (unsigned)g.Vb;
     p = loc >= (unsigned)g.hvb;
     return B * (unsigned)g.hvb + loc - (unsigned)p * g.hvb;
 }
 
+// (every block extent even)
 DDWC_HD unsigned full_index(const Geom& g, unsigned i, int p) {
     const unsigned B = i / (unsigned)g.hvb;
     return i + (B + (unsigned)p) * (unsigned)g.hvb;

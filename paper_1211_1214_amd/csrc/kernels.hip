@@ -153,9 +153,8 @@ void launch_export(Exec& e, const Geom& g, const typename Traits<R>::word* in, v
 }
 
 // ------------------------------------------------------------------ operator kernels
-// Epilogues: DOT partial (aux, y); DOT4 partials (y, in), (y, y), (aux, in), (aux, y) (the global
-// BiCGStab's t = M s with aux = rh); RESID: y = aux - y and partial ||y||^2.
-enum Epi { EPI_NONE = 0, EPI_DOT = 1, EPI_DOT4 = 2, EPI_RESID = 3 };
+// Epilogue RESID: y = aux - y and partial ||y||^2.
+enum Epi { EPI_NONE = 0, EPI_RESID = 1 };
 
 template <class R, int EPI>
 __global__ __launch_bounds__(WG) DDWC_OCC void k_dslash(Geom g, const cx<R>* __restrict__ U,
@@ -180,23 +179,7 @@ __global__ __launch_bounds__(WG) DDWC_OCC void k_dslash(Geom g, const cx<R>* __r
             v[0] = acc_nrm(y);
         }
         store_spinor(out + off, g.V, s, y);
-        if (EPI == EPI_DOT) {
-            cx<R> w[12];
-            load_spinor(aux + off, g.V, s, w);
-            acc_dot(w, y, v[0], v[1]);
-        }
-        if (EPI == EPI_DOT4) {
-            cx<R> c[12], w[12];
-            load_spinor(in + off, g.V, s, c);
-            acc_dot(y, c, v[0], v[1]);  // (t, s)
-            v[2] = acc_nrm(y);          // (t, t)
-            load_spinor(aux + off, g.V, s, w);
-            acc_dot(w, c, v[3], v[4]);  // (rh, s)
-            acc_dot(w, y, v[5], v[6]);  // (rh, t)
-        }
     }
-    if (EPI == EPI_DOT) write_partials<2>(v, part, ntiles, nrhs, tr);
-    if (EPI == EPI_DOT4) write_partials<7>(v, part, ntiles, nrhs, tr);
     if (EPI == EPI_RESID) write_partials<1>(v, part, ntiles, nrhs, tr);
 }
 
@@ -207,22 +190,6 @@ void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits
     Timed t(e, kclass, bytes);
     int nt = tiles_of(g.V);
     k_dslash<R, EPI_NONE><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr, 8);
-}
-template <class R>
-void launch_dslash_dot(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                       const typename Traits<R>::word* in, typename Traits<R>::word* out,
-                       const typename Traits<R>::word* w, double* part, int nrhs, int kclass, double bytes) {
-    Timed t(e, kclass, bytes);
-    int nt = tiles_of(g.V);
-    k_dslash<R, EPI_DOT><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, w, part, nrhs, nt, e.nbr, 8);
-}
-template <class R>
-void launch_dslash_dot4(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                        const typename Traits<R>::word* in, typename Traits<R>::word* out,
-                        const typename Traits<R>::word* rh, double* part, int nrhs, int kclass, double bytes) {
-    Timed t(e, kclass, bytes);
-    int nt = tiles_of(g.V);
-    k_dslash<R, EPI_DOT4><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, rh, part, nrhs, nt, e.nbr, 8);
 }
 template <class R>
 void launch_residual(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
@@ -932,12 +899,6 @@ int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads) {
     template void launch_export<R>(Exec&, const Geom&, const Traits<R>::word*, void*, int, int);                  \
     template void launch_dslash<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,              \
                                    const Traits<R>::word*, Traits<R>::word*, int, int, double);                   \
-    template void launch_dslash_dot<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,          \
-                                       const Traits<R>::word*, Traits<R>::word*, const Traits<R>::word*, double*, \
-                                       int, int, double);                                                         \
-    template void launch_dslash_dot4<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,         \
-                                        const Traits<R>::word*, Traits<R>::word*, const Traits<R>::word*,         \
-                                        double*, int, int, double);                                               \
     template void launch_residual<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,            \
                                      const Traits<R>::word*, const Traits<R>::word*, Traits<R>::word*, double*,   \
                                      int, int, double);                                                           \

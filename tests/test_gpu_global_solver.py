@@ -1,6 +1,6 @@
 """The even-odd global solver on the smallest lattice on which it starts with the two-step
 minimal-residual method (8192 sites), one size below (BiCGStab from the start) and at a kappa where it changes
-over to BiCGStab on the way, for one, a few and many right-hand sides in every precision, against the C
+over to BiCGStab on the way, with odd block extents (half fields in lexicographic order), for one, a few and many right-hand sides in every precision, against the C
 oracle's solves (1e-9 relative in the max norm at tol 1e-12, as for every solve)."""
 import sys
 
@@ -19,7 +19,7 @@ _cache = {}
 
 def setup(lat):
     if lat not in _cache:
-        blk = (4, 4, 4, 4) if lat[3] % 8 == 0 else (4, 4, 4, 2)
+        blk = {10: (3, 3, 3, 5), 6: (3, 3, 3, 1), 12: (4, 4, 4, 2)}.get(lat[3], (4, 4, 4, 4))
         U = inputs.make_links(lat, 0.3, 31)
         ctx = dd.Context(torch.from_numpy(U).cuda(), lat, blk, -1, 1.0)
         _cache[lat] = (ctx, cref.CRef(U, lat, blk, 1.0), {})
@@ -29,7 +29,8 @@ def setup(lat):
 @pytest.mark.parametrize("prec", [dd.FP64, dd.MIXED32, dd.MIXED16])
 @pytest.mark.parametrize("lat,kappa,nrhs", [((8, 8, 8, 12), 0.121, 3), ((8, 8, 8, 16), 0.121, 1),
                                             ((8, 8, 8, 16), 0.121, 3), ((8, 8, 8, 16), 0.121, 9),
-                                            ((8, 8, 8, 16), 0.131, 3)])
+                                            ((8, 8, 8, 16), 0.131, 3), ((12, 6, 6, 6), 0.121, 2),
+                                            ((12, 12, 6, 10), 0.121, 1), ((12, 12, 6, 10), 0.121, 9)])
 def test_global_solver(lat, kappa, nrhs, prec):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

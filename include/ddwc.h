@@ -285,9 +285,10 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *                          global solver's, and ddwc_dslash_apply's with several FP32 RHS): 128,
  *                          256 (default) or 512; a value below the RHS count runs 256.
  *   DDWC_OPT_TILE_ORDER    dispatch order of those kernels' workgroups: 0 site index order;
- *                          1 (default) interleaved by Schwarz-block rank, so that face-adjacent blocks
- *                          of the two colours run on the same XCD at about the same time (not in
- *                          ddwc_dslash_apply_noalloc, which builds no order table).  Neither option
+ *                          1 (default, with every block extent even) time slice by time slice
+ *                          through spatial columns of blocks, so that an XCD finds neighbours
+ *                          in its L2 (not in ddwc_dslash_apply_noalloc, which builds no order
+ *                          table).  Neither option
  *                          changes a result of ddwc_dslash_apply.
  * Results do not depend on the graph and LDS options; the others can change iteration counts and
  * rounding, never the tolerance reached.  EINVAL for unknown options or values.

@@ -433,27 +433,59 @@ EoFields<H16> eo_fields<H16>(const ddwc_ctx* C, bool site_major) {
     return F;
 }
 
-// Dispatch order of the tiles of the RHS-innermost operator kernels on fields of n2 sites with
-// per_block sites per block (half or full fields; nrhs RHS, nt pairs per tile): sorted by the
-// block rank of their first site, then by colour.
-// Blocks of the two colours with the same rank are neighbours along x3 (block_base), and after
-// the XCD remap each XCD takes a contiguous run of ranks (a time layer at 48x24^3), so a block's
-// face neighbours of the other colour are processed on the same XCD at nearly the same time,
-// while in index order they are on another XCD.
-static int tile_order(ddwc_ctx* C, unsigned n2, int nrhs, int nt, const int** out, int per_block = 0) {
+// Dispatch order of the tiles of the RHS-innermost operator kernels on half fields (parities = 1) or full fields
+// (parities = 2) with nrhs RHS, nt pairs per tile and `bytes` per stored spinor.
+// After the XCD remap each XCD takes a contiguous run of this order.  The tiles are sorted into
+// spatial columns of whole blocks that run through all of time, and inside a column by time slice, so that
+// an XCD sweeps a column slice by slice and finds the neighbours of a slice in its L2: those in
+// space except through the column's sides, and those in time until two slices later.  A
+// column's slice of spinors takes at most COLUMN_BYTES (three slices, the results and the links of the sites in
+// flight share 4 MiB), and its blocks divide an eighth of a slice's where that is whole; it grows by
+// blocks in its shortest direction.  48x24^3, 12 RHS (12^3 columns, one per XCD), with non-temporal stores and
+// staging: hop-and-inverse 324 -> 306 us, diagonal-and-hop 448 / 373 -> 415 / 350 us against blocks of both colours
+// in turn; columns of 6^3, 6x12x12, 12x12x24, 24^3: 322, 317, 318, 344 us.
+static int tile_order(ddwc_ctx* C, int parities, int nrhs, int nt, double bytes, const int** out) {
+    constexpr double COLUMN_BYTES = 1.4e6;
     const Geom& g = C->g;
-    if (per_block == 0) per_block = g.hvb;  // half fields; full fields pass Vb
-    const std::string key = std::to_string(n2) + "/" + std::to_string(nrhs) + "/" + std::to_string(nt) + "/" +
-                            std::to_string(per_block);
+    const int slice = g.Vb / g.b[0] / 2;  // sites of one parity in a time slice of a block
+    int c[4] = {g.nb[0], 1, 1, 1};        // column in blocks
+    const int blocks = g.nb[1] * g.nb[2] * g.nb[3];
+    const int share = blocks % 8 == 0 ? blocks / 8 : blocks;  // most blocks in a column
+    for (bool grown = true; grown;) {
+        grown = false;
+        int dir[3] = {1, 2, 3};
+        std::sort(dir, dir + 3, [&](int x, int y) { return c[x] * g.b[x] < c[y] * g.b[y]; });
+        for (int m : dir) {
+            int next = c[m] + 1;
+            while (next <= g.nb[m] && g.nb[m] % next != 0) ++next;
+            if (next > g.nb[m]) continue;
+            const int n = c[1] * c[2] * c[3] / c[m] * next;
+            if (share % n != 0 || (double)n * slice * parities * nrhs * bytes > COLUMN_BYTES) continue;
+            c[m] = next;
+            grown = true;
+            break;
+        }
+    }
+    const std::string key = std::to_string(parities) + "/" + std::to_string(nrhs) + "/" + std::to_string(nt) + "/" +
+                            std::to_string(c[1]) + "/" + std::to_string(c[2]) + "/" + std::to_string(c[3]);
     auto it = C->orders.find(key);
     if (it == C->orders.end()) {
-        const long long pairs = (long long)n2 * nrhs;
+        const long long per_block = (long long)parities * g.hvb;
+        const long long pairs = per_block * g.NB * nrhs;
         const int ntiles = (int)((pairs + nt - 1) / nt);
         std::vector<std::pair<long long, int>> keys(ntiles);
         for (int t = 0; t < ntiles; ++t) {
-            const long long b = ((long long)t * nt / nrhs) / per_block;  // colour-major block of the first pair
-            const long long c = b / g.NBc, rank = b % g.NBc;
-            keys[t] = {(rank * 2 + c) * (long long)ntiles + t, t};
+            const long long i = (long long)t * nt / nrhs;  // first site of the tile
+            const long long B = i / per_block;
+            const int h = (int)(i - B * per_block) % g.hvb;
+            const Site S = decode(g, (int)(B * g.Vb));
+            long long col = 0, in = 0;
+            for (int m = 1; m < 4; ++m) {
+                col = col * (g.nb[m] / c[m]) + S.n[m] / c[m];
+                in = in * c[m] + S.n[m] % c[m];
+            }
+            const long long time = (long long)S.n[0] * g.b[0] + h / slice;
+            keys[t] = {((col * g.L[0] + time) * ((long long)c[1] * c[2] * c[3]) + in) * (long long)ntiles + t, t};
         }
         std::sort(keys.begin(), keys.end());
         std::vector<int> ord(ntiles);
@@ -569,7 +601,8 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     CK(check_h16_global(C, nrhs, h16 ? DDWC_MIXED16 : DDWC_MIXED32));
     const bool ri = h16 || (nrhs > 1 && nrhs <= WG && ri_fits(n2, nrhs));
     EoFields<S> FR = eo_fields<S>(C, ri && !fp64);  // RI kernels read own-site link records
-    if (ri && g.eo && C->opt_tile_order == 1) CK(tile_order(C, n2, nrhs, eo_op_threads(FR, nrhs, ri), &FR.order));
+    const double rs = h16 ? 52.0 : 24.0 * sizeof(R);  // bytes of a stored spinor
+    if (ri && g.eo && C->opt_tile_order == 1) CK(tile_order(C, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs, &FR.order));
     const int ntR = vector_tiles(n2, nrhs, ri);
     const int ntM = eo_op_tiles(FR, nrhs, ri);  // tiles of the operator kernels' partial sums
     const double mass4 = 4.0 + mass;
@@ -584,7 +617,6 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     const int kcl = fp64 ? DDWC_K_DSLASH64 : DDWC_K_DSLASH32;
     // algorithmic bytes of one half operator (hop kernel): half input with neighbours, half
     // output, the links of all sites, the site matrix of one parity
-    const double rs = h16 ? 52.0 : 24.0 * sizeof(R);
     const double hbytes =
         (double)n2 * (nrhs * 2 * rs + 8 * 18.0 * sizeof(typename Traits<S>::link) + 72.0 * sizeof(R));
     double2 *be, *bo, *bpe, *xe, *xo, *re, *to;
@@ -1045,7 +1077,7 @@ static int dslash_apply_with(ddwc_ctx* C, Exec& ex, double kappa, const void* in
         const int* order = nullptr;
         const int nt = C->opt_op_threads;
         if (may_allocate && g.eo && C->opt_tile_order == 1)
-            CK(tile_order(C, (unsigned)g.V, nrhs, nrhs <= nt ? nt : WG, &order, g.Vb));
+            CK(tile_order(C, 2, nrhs, nrhs <= nt ? nt : WG, 96.0, &order));
         launch_import_ri32(ex, g, in, (float4*)a, nrhs);
         launch_dslash_ri32(ex, g, C->U32s, C->K32, mass4, (const float4*)a, (float4*)b, nrhs, DDWC_K_DSLASH32,
                            ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32), nt, order);

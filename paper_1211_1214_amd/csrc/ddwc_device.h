@@ -465,25 +465,27 @@ DDWC_HD void apply_diag(const typename Traits<R>::word* __restrict__ K, unsigned
 //   mu = k:  h = q_u +- i s_k q_l   lower spins = -+ i s_k k       (k = U h or U^+ h)
 // MU and DIR are compile-time, so each direction is straight-line code.
 template <class R, int MU, int DIR>
-DDWC_HD void hop_term(const cx<R> u[9], const cx<R> q[12], cx<R> acc[12]) {
-    cx<R> h0[3], h1[3];
+DDWC_HD void half_proj(const cx<R> q[12], cx<R> h[6]) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const cx<R> p0 = q[a], p1 = q[3 + a], p2 = q[6 + a], p3 = q[9 + a];
         if (MU == 0) {
-            h0[a] = DIR > 0 ? p0 + p2 : p0 - p2;
-            h1[a] = DIR > 0 ? p1 + p3 : p1 - p3;
+            h[a] = DIR > 0 ? p0 + p2 : p0 - p2;
+            h[3 + a] = DIR > 0 ? p1 + p3 : p1 - p3;
         } else if (MU == 1) {
-            h0[a] = DIR > 0 ? p0 + times_i(p3) : p0 - times_i(p3);
-            h1[a] = DIR > 0 ? p1 + times_i(p2) : p1 - times_i(p2);
+            h[a] = DIR > 0 ? p0 + times_i(p3) : p0 - times_i(p3);
+            h[3 + a] = DIR > 0 ? p1 + times_i(p2) : p1 - times_i(p2);
         } else if (MU == 2) {
-            h0[a] = DIR > 0 ? p0 + p3 : p0 - p3;
-            h1[a] = DIR > 0 ? p1 - p2 : p1 + p2;
+            h[a] = DIR > 0 ? p0 + p3 : p0 - p3;
+            h[3 + a] = DIR > 0 ? p1 - p2 : p1 + p2;
         } else {
-            h0[a] = DIR > 0 ? p0 + times_i(p2) : p0 - times_i(p2);
-            h1[a] = DIR > 0 ? p1 - times_i(p3) : p1 + times_i(p3);
+            h[a] = DIR > 0 ? p0 + times_i(p2) : p0 - times_i(p2);
+            h[3 + a] = DIR > 0 ? p1 - times_i(p3) : p1 + times_i(p3);
         }
     }
+}
+template <class R, int MU, int DIR>
+DDWC_HD void half_apply(const cx<R> u[9], const cx<R> h[6], cx<R> acc[12]) {
     cx<R> k0[3], k1[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -492,11 +494,11 @@ DDWC_HD void hop_term(const cx<R> u[9], const cx<R> q[12], cx<R> acc[12]) {
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             if (DIR > 0) {
-                cmadd(k0[a], u[3 * a + b], h0[b]);
-                cmadd(k1[a], u[3 * a + b], h1[b]);
+                cmadd(k0[a], u[3 * a + b], h[b]);
+                cmadd(k1[a], u[3 * a + b], h[3 + b]);
             } else {
-                cjmadd(k0[a], u[3 * b + a], h0[b]);
-                cjmadd(k1[a], u[3 * b + a], h1[b]);
+                cjmadd(k0[a], u[3 * b + a], h[b]);
+                cjmadd(k1[a], u[3 * b + a], h[3 + b]);
             }
         }
     }
@@ -522,6 +524,12 @@ DDWC_HD void hop_term(const cx<R> u[9], const cx<R> q[12], cx<R> acc[12]) {
         acc[9 + a] = acc[9 + a] + l1;
     }
 }
+template <class R, int MU, int DIR>
+DDWC_HD void hop_term(const cx<R> u[9], const cx<R> q[12], cx<R> acc[12]) {
+    cx<R> h[6];
+    half_proj<R, MU, DIR>(q, h);
+    half_apply<R, MU, DIR>(u, h, acc);
+}
 
 // Direction d = 2 mu + (backward ? 1 : 0), chosen at run time (uniform across the wave).
 template <class R>
@@ -535,6 +543,34 @@ DDWC_HD void hop_dispatch(int d, const cx<R> u[9], const cx<R> q[12], cx<R> acc[
         case 5: hop_term<R, 2, -1>(u, q, acc); break;
         case 6: hop_term<R, 3, +1>(u, q, acc); break;
         default: hop_term<R, 3, -1>(u, q, acc); break;
+    }
+}
+
+// The two halves of hop_dispatch: the projection to the half spinor, and its product with the link.
+template <class R>
+DDWC_HD void proj_dispatch(int d, const cx<R> q[12], cx<R> h[6]) {
+    switch (d) {
+        case 0: half_proj<R, 0, +1>(q, h); break;
+        case 1: half_proj<R, 0, -1>(q, h); break;
+        case 2: half_proj<R, 1, +1>(q, h); break;
+        case 3: half_proj<R, 1, -1>(q, h); break;
+        case 4: half_proj<R, 2, +1>(q, h); break;
+        case 5: half_proj<R, 2, -1>(q, h); break;
+        case 6: half_proj<R, 3, +1>(q, h); break;
+        default: half_proj<R, 3, -1>(q, h); break;
+    }
+}
+template <class R>
+DDWC_HD void apply_dispatch(int d, const cx<R> u[9], const cx<R> h[6], cx<R> acc[12]) {
+    switch (d) {
+        case 0: half_apply<R, 0, +1>(u, h, acc); break;
+        case 1: half_apply<R, 0, -1>(u, h, acc); break;
+        case 2: half_apply<R, 1, +1>(u, h, acc); break;
+        case 3: half_apply<R, 1, -1>(u, h, acc); break;
+        case 4: half_apply<R, 2, +1>(u, h, acc); break;
+        case 5: half_apply<R, 2, -1>(u, h, acc); break;
+        case 6: half_apply<R, 3, +1>(u, h, acc); break;
+        default: half_apply<R, 3, -1>(u, h, acc); break;
     }
 }
 

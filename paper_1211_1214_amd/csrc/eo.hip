@@ -145,19 +145,60 @@ void launch_eo_merge(Exec& e, const Geom& g, const double2* he, const double2* h
 // The RHS-innermost FP32/FP16 kernels (the global solver) read own-site link records (each half
 // site's eight hop links in one contiguous record); FP64 and the RHS-major kernels read
 // entry-major links (EoFields of eo_fields with site_major set alike).
-template <class S, bool RI>
-constexpr int site_major_links() {
-    return RI && !std::is_same<S, double>::value ? LK_OWN : LK_ENTRY;
-}
 
-// Pipelining of the hop loop (hop_sum): with the links, clover and table staged in LDS the
-// unpipelined loop's fewer registers (about 100 against 146) buy a fourth and fifth wave per
-// SIMD, which hides the neighbour-spinor latency better than loading one direction ahead.  (In
-// FP64 the pipelined loop needs 254 VGPRs, one wave per SIMD, and is still as fast as the
-// unpipelined one at two waves.)
-template <bool STG>
-constexpr int hop_pipe() {
-    return STG ? 0 : 1;
+// The hop loop (hops_pipelined) is unrolled, with scalar plane pointers: FP64 needs 210 registers (two waves
+// per SIMD) where the rolled loop that carried the next spinor and link beside the current ones took 254
+// and 24 accumulation registers (one), the unstaged FP32 and FP16 kernels 118 and 98 (four waves) instead of
+// 146 (three), and the staged kernels load the next spinor under the products at 98 registers where
+// their rolled loop did not load ahead.  us before / after: FP16 6 RHS at 64x32^3 hop-and-inverse 544 / 430,
+// diagonal-and-hop 615 / 551; FP32 12 RHS at 48x24^3 333 / 324, 452 / 448; FP64 12 RHS 1160 / 1105, 1353 / 1275.
+// acc = the eight hops into (site it.i, RHS it.r) of the field x (w: its view), links Up (own-site records, staged
+// in LDS from site l0 on with STG; else entry-major of the sites' parity) and Uq (entry-major of the other
+// parity), table nb (with STG staged too, stride nstr).
+template <class S, bool RI, bool STG>
+__device__ __forceinline__ void eo_hops(unsigned n2, const VItem& it, const VView<RI, S>& w, int nrhs,
+                                        const typename Traits<S>::word* x, const cx<typename Traits<S>::link>* Up,
+                                        const cx<typename Traits<S>::link>* Uq, const int* nb, unsigned l0,
+                                        unsigned nstr, cx<typename Traits<S>::real> acc[12]) {
+    typedef typename Traits<S>::real R;
+    constexpr bool OWN = RI && !std::is_same<S, double>::value;
+    int e[8];
+    if constexpr (STG) {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) e[d] = nb[d * nstr + it.i - l0];
+    } else {
+        Planes q(nb, n2);
+        const unsigned o = byte_offset(it.i, 4);
+#pragma unroll
+        for (int d = 0; d < 8; ++d) e[d] = q.load<int>(o);
+    }
+    const typename Traits<S>::word* xb = x + w.base;
+    auto target = [&](int d) { return d < 2 && e[d] < 0 ? (unsigned)~e[d] : (unsigned)e[d]; };  // (only hops in time cross)
+    auto lq = [&](int d, cx<R> q[12]) {
+        const unsigned t = target(d);
+        uload_spinor(xb, w.stride, reissue(byte_offset(RI ? t * (unsigned)nrhs + it.r : t, 16)), q);
+    };
+    auto flip = [&](int d) { return e[d] < 0; };
+    auto take = [](int) { return true; };
+    if constexpr (OWN) {
+        const cx<typename Traits<S>::link>* rec = Up + (size_t)(it.i - l0) * 72;
+        auto lu = [&](int d, cx<R> u[9]) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) u[k] = mk((R)rec[d * 9 + k].re, (R)rec[d * 9 + k].im);
+        };
+        hops_pipelined<R, !STG>(acc, lq, lu, flip, take);
+    } else {
+        constexpr unsigned LS = sizeof(cx<R>);
+        Planes pf(Up, n2), pb(Uq, n2);
+        const unsigned own = byte_offset(it.i, LS);
+        auto lu = [&](int d, cx<R> u[9]) {
+            if (d & 1)
+                uload_link(pb, reissue(byte_offset(target(d), LS)), u);
+            else
+                uload_link(pf, reissue(own), u);
+        };
+        hops_pipelined<R, true>(acc, lq, lu, flip, take);
+    }
 }
 
 // Work items as for the vector kernels (vec_items.h): RHS-major fields or, with RI, the
@@ -181,20 +222,19 @@ __global__ __launch_bounds__(NT) void k_eo_hopinv(unsigned n2, const typename Tr
     const typename Traits<S>::kword* Ak = Ainv;
     const int* nb = nbrp;
     unsigned kst = n2, l0 = 0, nstr = 0;
-    if (STG) {
+    if constexpr (STG) {
         const Staged<S> sd = stage_site_data<S, NT>(it, n2, nrhs, Up, Ainv, nbrp);
         Uf = sd.U;
         Ak = sd.K;
         nb = sd.nbr;
-        kst = nstr = stg_sites<NT>();
+        kst = nstr = sd.n;
         l0 = sd.l0;
     }
     if (!it.ok) return;
     const VView<RI, S> w(n2, nrhs, it.i, it.r);
     cx<R> acc[12], out[12];
     if (alpha != R(0))
-        hop_sum<R, HOPS_ALL, hop_pipe<STG>(), site_major_links<S, RI>()>(n2, it.i, x + w.base, Uf, Uq, nb, acc, 8,
-                                                              RI ? nrhs : 1, RI ? it.r : 0, w.stride, l0, nstr);
+        eo_hops<S, RI, STG>(n2, it, w, nrhs, x, Uf, Uq, nb, l0, nstr, acc);
     else
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = mk(R(0), R(0));
@@ -210,7 +250,10 @@ __global__ __launch_bounds__(NT) void k_eo_hopinv(unsigned n2, const typename Tr
 #pragma unroll
     for (int k = 0; k < 12; ++k) out[k] = mk(R(0), R(0));
     apply_diag<R>(Ak, kst, it.i - l0, R(0), acc, out, R(0));
-    store_spinor(y + w.base, w.stride, w.idx, out);
+    if constexpr (STG && std::is_same<S, float>::value)
+        ustore_spinor_nt(y, w.stride, byte_offset(w.idx, 16), out);
+    else
+        store_spinor(y + w.base, w.stride, w.idx, out);
 }
 
 
@@ -237,20 +280,19 @@ __global__ __launch_bounds__(NT) void k_eo_diaghop(unsigned n2, const typename T
     const typename Traits<S>::kword* Kk = Kp;
     const int* nb = nbrp;
     unsigned kst = n2, l0 = 0, nstr = 0;
-    if (STG) {
+    if constexpr (STG) {
         const Staged<S> sd = stage_site_data<S, NT>(it, n2, nrhs, Up, Kp, nbrp);
         Uf = sd.U;
         Kk = sd.K;
         nb = sd.nbr;
-        kst = nstr = stg_sites<NT>();
+        kst = nstr = sd.n;
         l0 = sd.l0;
     }
     double v[7] = {0, 0, 0, 0, 0, 0, 0};
     if (it.ok) {
         const VView<RI, S> w(n2, nrhs, it.i, it.r);
         cx<R> acc[12], cc[12];
-        hop_sum<R, HOPS_ALL, hop_pipe<STG>(), site_major_links<S, RI>()>(n2, it.i, t + w.base, Uf, Uq, nb, acc, 8,
-                                                              RI ? nrhs : 1, RI ? it.r : 0, w.stride, l0, nstr);
+        eo_hops<S, RI, STG>(n2, it, w, nrhs, t, Uf, Uq, nb, l0, nstr, acc);
         load_spinor(c + w.base, w.stride, w.idx, cc);
         if (USE_A) {
             apply_diag<R>(Kk, kst, it.i - l0, mass4, cc, acc, beta);
@@ -265,7 +307,10 @@ __global__ __launch_bounds__(NT) void k_eo_diaghop(unsigned n2, const typename T
             for (int k = 0; k < 12; ++k) acc[k] = b[k] - acc[k];
             v[0] = acc_nrm(acc);
         }
-        store_spinor(y + w.base, w.stride, w.idx, acc);
+        if constexpr (STG && std::is_same<S, float>::value)
+            ustore_spinor_nt(y, w.stride, byte_offset(w.idx, 16), acc);
+        else
+            store_spinor(y + w.base, w.stride, w.idx, acc);
         if (EPI == EOE_DOT) {
             cx<R> q[12];
             load_spinor(aux + w.base, w.stride, w.idx, q);
@@ -318,19 +363,20 @@ void launch_eo_hopinv(Exec& e, const EoFields<S>& F, int p, bool ri, const typen
     typedef typename Traits<S>::real R;
     Timed t(e, kclass, bytes);
     const int nt = eo_op_tiles(F, nrhs, ri);
-    if (!ri) {
+    if constexpr (!std::is_same<S, H16>::value) if (!ri) {  // (FP16 fields are always RHS-innermost)
         k_eo_hopinv<S, false, false, WG><<<nt * nrhs, WG, 0, e.stream>>>(F.n2, x, c, (R)alpha, F.U[p], F.U[1 - p],
                                                                          F.nbr[p], Ainv, y, nrhs, nt, nullptr);
         return;
     }
-    const bool stg = stage_ok<S>(nrhs);
+    const bool stg = stage_ok<S>(F.n2, nrhs);
     with_op_threads<S>(eo_op_threads(F, nrhs, ri), [&](auto ntc) {
         constexpr int NT = decltype(ntc)::value;
-        if (stg)
-            k_eo_hopinv<S, true, true, NT><<<nt, NT, stage_bytes<S, NT>(), e.stream>>>(
+        if constexpr (!std::is_same<S, double>::value) if (stg) {
+            k_eo_hopinv<S, true, true, NT><<<nt, NT, stage_bytes<S>(NT, nrhs), e.stream>>>(
                 F.n2, x, c, (R)alpha, F.U[p], F.U[1 - p], F.nbr[p], Ainv, y, nrhs, nt, F.order);
-        else
-            k_eo_hopinv<S, true, false, NT><<<nt, NT, 0, e.stream>>>(F.n2, x, c, (R)alpha, F.U[p], F.U[1 - p],
+            return;
+        }
+        k_eo_hopinv<S, true, false, NT><<<nt, NT, 0, e.stream>>>(F.n2, x, c, (R)alpha, F.U[p], F.U[1 - p],
                                                                      F.nbr[p], Ainv, y, nrhs, nt, F.order);
     });
 }
@@ -343,17 +389,18 @@ void launch_eo_diaghop(Exec& e, const EoFields<S>& F, int p, bool ri, int epi, b
     typedef typename Traits<S>::real R;
     Timed tm(e, kclass, bytes);
     const int nt = eo_op_tiles(F, nrhs, ri);
-    const bool stg = ri && stage_ok<S>(nrhs);
+    const bool stg = ri && stage_ok<S>(F.n2, nrhs);
     auto launch = [&](auto epc, auto uac, auto ric, auto ntc) {
         constexpr int EP = decltype(epc)::value, NT = decltype(ntc)::value;
         constexpr bool UA = decltype(uac)::value, RIV = decltype(ric)::value;
         const int ng = RIV ? nt : nt * nrhs;
-        if (RIV && stg)
-            k_eo_diaghop<S, EP, UA, RIV, RIV, NT><<<ng, NT, stage_bytes<S, NT>(), e.stream>>>(
+        if constexpr (RIV && !std::is_same<S, double>::value) if (stg) {
+            k_eo_diaghop<S, EP, UA, RIV, true, NT><<<ng, NT, stage_bytes<S>(NT, nrhs), e.stream>>>(
                 F.n2, c, tv, (R)beta, F.U[p], F.U[1 - p], F.nbr[p], F.K[p], (R)mass4, aux, y, part, nrhs, nt,
-                RIV ? F.order : nullptr);
-        else
-            k_eo_diaghop<S, EP, UA, RIV, false, NT><<<ng, NT, 0, e.stream>>>(
+                F.order);
+            return;
+        }
+        k_eo_diaghop<S, EP, UA, RIV, false, NT><<<ng, NT, 0, e.stream>>>(
                 F.n2, c, tv, (R)beta, F.U[p], F.U[1 - p], F.nbr[p], F.K[p], (R)mass4, aux, y, part, nrhs, nt,
                 RIV ? F.order : nullptr);
     };
@@ -375,7 +422,7 @@ void launch_eo_diaghop(Exec& e, const EoFields<S>& F, int p, bool ri, int epi, b
     };
     if (ri)
         with_op_threads<S>(eo_op_threads(F, nrhs, ri), [&](auto ntc) { epilogue(T_(), ntc); });
-    else
+    else if constexpr (!std::is_same<S, H16>::value)
         epilogue(F_(), std::integral_constant<int, WG>());
 }
 

@@ -841,12 +841,12 @@ __global__ __launch_bounds__(NT) void k_dslash_ri32(Geom g, const cx<float>* __r
     const float4* Kk = K;
     const int* nb = nbr;
     unsigned kst = (unsigned)g.V, l0 = 0, nstr = 0;
-    if (STG) {
+    if constexpr (STG) {
         const Staged<float> sd = stage_site_data<float, NT>(it, (unsigned)g.V, nrhs, Lown, K, nbr);
         Uf = sd.U;
         Kk = sd.K;
         nb = sd.nbr;
-        kst = nstr = stg_sites<NT>();
+        kst = nstr = sd.n;
         l0 = sd.l0;
     }
     if (!it.ok) return;
@@ -876,8 +876,8 @@ void launch_dslash_ri32(Exec& e, const Geom& g, const cx<float>* Us, const float
     const int nt = (int)(((long long)g.V * nrhs + NTr - 1) / NTr);
     auto launch = [&](auto ntc) {
         constexpr int NT = decltype(ntc)::value;
-        if (stage_ok<float>(nrhs))
-            k_dslash_ri32<true, NT><<<nt, NT, stage_bytes<float, NT>(), e.stream>>>(g, Us, K, (float)mass4, in, out,
+        if (stage_ok<float>((unsigned)g.V, nrhs))
+            k_dslash_ri32<true, NT><<<nt, NT, stage_bytes<float>(NT, nrhs), e.stream>>>(g, Us, K, (float)mass4, in, out,
                                                                                   e.nbr, nrhs, nt, order);
         else
             k_dslash_ri32<false, NT><<<nt, NT, 0, e.stream>>>(g, Us, K, (float)mass4, in, out, e.nbr, nrhs, nt, order);

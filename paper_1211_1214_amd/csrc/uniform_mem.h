@@ -57,6 +57,12 @@ struct Planes {
         return v;
     }
     template <class V>
+    __device__ __forceinline__ void store_nt(unsigned off, V v) {
+        asm("" : "+s"(p));
+        __builtin_nontemporal_store(v, (__attribute__((address_space(1))) V*)(p + off));
+        p += step;
+    }
+    template <class V>
     __device__ __forceinline__ void store(unsigned off, V v) {
         asm("" : "+s"(p));
         *(__attribute__((address_space(1))) V*)(p + off) = v;
@@ -77,15 +83,15 @@ __device__ __forceinline__ T* fresh(T* p) {
 // Orders the computation of a spinor before every later fresh(), pin() and reissue(): instruction
 // selection otherwise gathers the loads of a long straight-line body at its start and spills them.
 template <class R>
+__device__ __forceinline__ void pin6(cx<R> p[6]) {
+    asm volatile(""
+                 : "+v"(p[0].re), "+v"(p[0].im), "+v"(p[1].re), "+v"(p[1].im), "+v"(p[2].re), "+v"(p[2].im),
+                   "+v"(p[3].re), "+v"(p[3].im), "+v"(p[4].re), "+v"(p[4].im), "+v"(p[5].re), "+v"(p[5].im));
+}
+template <class R>
 __device__ __forceinline__ void pin(cx<R> p[12]) {
-#define DDWC_PIN6(a)                                                                                              \
-    asm volatile(""                                                                                               \
-                 : "+v"(p[a].re), "+v"(p[a].im), "+v"(p[a + 1].re), "+v"(p[a + 1].im), "+v"(p[a + 2].re),          \
-                   "+v"(p[a + 2].im), "+v"(p[a + 3].re), "+v"(p[a + 3].im), "+v"(p[a + 4].re), "+v"(p[a + 4].im),  \
-                   "+v"(p[a + 5].re), "+v"(p[a + 5].im))
-    DDWC_PIN6(0);
-    DDWC_PIN6(6);
-#undef DDWC_PIN6
+    pin6(p);
+    pin6(p + 6);
 }
 // The loads addressed with the returned offset are issued after the last pin().
 __device__ __forceinline__ unsigned reissue(unsigned off) {
@@ -110,6 +116,19 @@ __device__ __forceinline__ void uload_spinor(const double2* f, unsigned n, unsig
         p[c] = mk(w.x, w.y);
     }
 }
+// FP16 storage: three word planes and a plane of scales (ddwc_device.h)
+__device__ __forceinline__ void uload_spinor(const hw16* f, unsigned n, unsigned off, cx<float> p[12]) {
+    typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+    Planes q(f, n);
+    h8v w[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = q.load<h8v>(off);
+    unsigned o4 = off >> 2;
+    asm("" : "+v"(o4));
+    const float sc = q.load<float>(o4);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) p[k] = mk(sc * (float)w[k >> 2][2 * (k & 3)], sc * (float)w[k >> 2][2 * (k & 3) + 1]);
+}
 __device__ __forceinline__ void ustore_spinor(float4* f, unsigned n, unsigned off, const cx<float> p[12]) {
     Planes q(f, n);
 #pragma unroll
@@ -120,6 +139,16 @@ __device__ __forceinline__ void ustore_spinor(double2* f, unsigned n, unsigned o
     Planes q(f, n);
 #pragma unroll
     for (int c = 0; c < 12; ++c) q.store<d2v>(off, (d2v){p[c].re, p[c].im});
+}
+
+// The next link of a walk over entry-major links [4][9][n] (nine planes), of the site at byte offset off.
+template <class R>
+__device__ __forceinline__ void uload_link(Planes& q, unsigned off, cx<R> u[9]) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const typename VecOf<R>::link w = q.load<typename VecOf<R>::link>(off);
+        u[k] = mk(w.x, w.y);
+    }
 }
 
 // Packed FP32 links: per direction four planes of 16-byte words (entries 0 .. 7, two a word) and one
@@ -146,6 +175,13 @@ struct PackedLinks {
         p += n16 >> 1;
     }
 };
+
+__device__ __forceinline__ void ustore_spinor_nt(float4* f, unsigned n, unsigned off, const cx<float> p[12]) {
+    Planes q(f, n);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        q.store_nt<f4v>(off, (f4v){p[2 * k].re, p[2 * k].im, p[2 * k + 1].re, p[2 * k + 1].im});
+}
 
 // The packed Hermitian 6x6 blocks K [NKW][n] of one site, loaded in two parts: the diagonals and the
 // first block's off-diagonal reals, then the second block's (which start inside the last word of the
@@ -174,5 +210,41 @@ struct UDiag {
         diag_block<R>(w + 6, w + 42, mass4, p + 6, y + 6, hsc);
     }
 };
+
+// acc = sum over the eight hops of (1 -+ g_mu) W psi(neighbour), with the neighbour's spinor from lq(d, q) and
+// the link from lu(d, u), called at compile-time d in order; flip(d) (d = 0, 1: the hops in time) says
+// whether the hop crosses an antiperiodic boundary, and take(d) whether it belongs to the sum.
+// The spinor of hop d + 1 is loaded into the registers of the spinor of hop d as soon as that is projected, so that
+// it is in flight during the products of hop d at no cost in registers, and (NEXT_LINK) the next link
+// beside the current one.
+template <class R, bool NEXT_LINK, class LQ, class LU, class Flip, class Take>
+__device__ __forceinline__ void hops_pipelined(cx<R> acc[12], LQ&& lq, LU&& lu, Flip&& flip, Take&& take) {
+    cx<R> q[12], u[9], un[9], h[6];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] = mk(R(0), R(0));
+    lq(0, q);
+    lu(0, u);
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        if (NEXT_LINK && d + 1 < 8) lu(d + 1, un);
+        __builtin_amdgcn_sched_barrier(0);
+        proj_dispatch<R>(d, q, h);
+        if (d < 2 && flip(d)) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) h[c] = -h[c];
+        }
+        pin6(h);
+        if (d + 1 < 8) lq(d + 1, q);
+        __builtin_amdgcn_sched_barrier(0);
+        if (take(d)) apply_dispatch<R>(d, u, h, acc);
+        pin(acc);
+        if (NEXT_LINK) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) u[k] = un[k];
+        } else if (d + 1 < 8) {
+            lu(d + 1, u);
+        }
+    }
+}
 
 }  // namespace ddwc

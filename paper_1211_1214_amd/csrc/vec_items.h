@@ -106,38 +106,38 @@ __device__ __forceinline__ void vpartials(double v[NV], double* part, int ntiles
     }
 }
 
-// Staging of what the lanes of one site share (RHS-innermost kernels with at least STG_MIN_RHS
+// Staging of what the lanes of one site share (RHS-innermost FP32 and FP16 kernels with enough
 // RHS): the own-site link records, the clover words and the neighbour-table entries of the sites
 // a workgroup covers are copied into LDS with coalesced loads before the hop loop, which then
-// reads them there: one copy per site instead of one vector-memory load per (site, RHS) lane.
-constexpr int STG_MIN_RHS = 8;
-template <int NT = WG>
-constexpr int stg_sites() {  // sites that NT consecutive (site, RHS) pairs can touch
-    return NT / STG_MIN_RHS + 2;
+// reads them there: one copy per site instead of one vector-memory load per (site, RHS) lane.  They are
+// read once, so they bypass the caches (non-temporal) that keep the neighbours' spinors.
+// Fewer RHS cover more sites, and a workgroup's copy then leaves room for too few workgroups (solves of
+// 4 / 5 / 6 RHS at 48x24^3, unstaged and staged: FP32 34.5, 42.2, 47.7 and -, -, 44.5 ms; FP16 28.4, -, 39.2 and 29.5, -,
+// 36.6 ms; FP16 6 RHS at 32x16^3, whose fields stay in the last-level cache: 8.0 and 8.7 ms).
+template <class S>
+inline bool stage_ok(unsigned n, int nrhs) {
+    if (std::is_same<S, double>::value) return false;
+    return nrhs >= (std::is_same<S, H16>::value && n < (1u << 18) ? 8 : 6);
+}
+inline __host__ __device__ unsigned stg_sites(int nt, int nrhs) {  // sites that nt consecutive pairs can touch
+    return (unsigned)((nt - 1) / nrhs + 2);
 }
 
 template <class S>
 constexpr unsigned record_words() {  // 16-byte words of one own-site link record
     return 8 * 9 * sizeof(cx<typename Traits<S>::link>) / 16;
 }
-template <class S, int NT = WG>
-constexpr size_t stage_bytes() {
-    return (size_t)stg_sites<NT>() * ((record_words<S>() + Traits<S>::NKW) * 16 + 8 * sizeof(int));
-}
-
-// Staging applies to the RHS-innermost low-precision kernels (own-site link records) with enough
-// RHS per site.
 template <class S>
-inline bool stage_ok(int nrhs) {
-    return !std::is_same<S, double>::value && nrhs >= STG_MIN_RHS;
+inline size_t stage_bytes(int nt, int nrhs) {
+    return (size_t)stg_sites(nt, nrhs) * ((record_words<S>() + Traits<S>::NKW) * 16 + 8 * sizeof(int));
 }
 
 template <class S>
 struct Staged {
     const cx<typename Traits<S>::link>* U;  // link records of sites l0, l0 + 1, ...
-    const typename Traits<S>::kword* K;     // clover words [NKW][stg_sites] of the same sites
-    const int* nbr;                         // neighbour-table entries [8][stg_sites] of the same sites
-    unsigned l0;
+    const typename Traits<S>::kword* K;     // clover words [NKW][n] of the same sites
+    const int* nbr;                         // neighbour-table entries [8][n] of the same sites
+    unsigned l0, n;
 };
 
 // Copies the records, clover words and table entries of the sites of the workgroup's pairs;
@@ -147,21 +147,23 @@ __device__ __forceinline__ Staged<S> stage_site_data(const VItem& it, unsigned n
                                                      const cx<typename Traits<S>::link>* __restrict__ Up,
                                                      const typename Traits<S>::kword* __restrict__ K,
                                                      const int* __restrict__ nbr) {
-    typedef typename Traits<S>::kword KW;
-    extern __shared__ float4 stg[];
-    constexpr unsigned RW = record_words<S>(), NS = stg_sites<NT>();
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    static_assert(std::is_same<typename Traits<S>::kword, float4>::value, "clover words are float4");
+    extern __shared__ v4 stg[];
+    constexpr unsigned RW = record_words<S>(), NK = Traits<S>::NKW;
+    const unsigned NS = stg_sites(NT, nrhs);
     const unsigned l0 = it.g0 / (unsigned)nrhs;
     unsigned l1 = (it.g0 + NT - 1) / (unsigned)nrhs + 1;
     if (l1 > n2) l1 = n2;
-    const unsigned ns = l1 - l0;  // <= NS for nrhs >= STG_MIN_RHS
-    const float4* src = (const float4*)Up + (size_t)l0 * RW;
-    for (unsigned k = threadIdx.x; k < ns * RW; k += NT) stg[k] = src[k];
-    KW* ck = (KW*)(stg + NS * RW);
-    for (unsigned k = threadIdx.x; k < Traits<S>::NKW * ns; k += NT) {
+    const unsigned ns = l1 - l0;  // <= NS
+    const v4* src = (const v4*)Up + (size_t)l0 * RW;
+    for (unsigned k = threadIdx.x; k < ns * RW; k += NT) stg[k] = __builtin_nontemporal_load(src + k);
+    v4* ck = stg + NS * RW;
+    for (unsigned k = threadIdx.x; k < NK * ns; k += NT) {
         const unsigned w = k / ns, j = k - w * ns;
-        ck[w * NS + j] = K[(size_t)w * n2 + l0 + j];
+        ck[w * NS + j] = __builtin_nontemporal_load((const v4*)K + ((size_t)w * n2 + l0 + j));
     }
-    int* cn = (int*)(ck + Traits<S>::NKW * NS);
+    int* cn = (int*)(ck + NK * NS);
     for (unsigned k = threadIdx.x; k < 8 * ns; k += NT) {
         const unsigned d = k / ns, j = k - d * ns;
         cn[d * NS + j] = nbr[(size_t)d * n2 + l0 + j];
@@ -169,9 +171,10 @@ __device__ __forceinline__ Staged<S> stage_site_data(const VItem& it, unsigned n
     __syncthreads();
     Staged<S> st;
     st.U = (const cx<typename Traits<S>::link>*)stg;
-    st.K = ck;
+    st.K = (const typename Traits<S>::kword*)ck;
     st.nbr = cn;
     st.l0 = l0;
+    st.n = NS;
     return st;
 }
 

@@ -1056,20 +1056,20 @@ static void fill_stats(ddwc_stats* s, int outer, int inner, double rel, std::chr
     s->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
 }
 
-// out = D(m) in through internal-layout fields a and b (each dslash_field_bytes long): from the
-// context's workspace, or from the static scratch for the no-allocation entry point.
+// out = D(m) in through the internal-layout input field a (dslash_field_bytes long): from the
+// context's workspace, or from the static scratch for the no-allocation entry point.  The operator kernels
+// write the canonical layout themselves.
 static size_t dslash_field_bytes(const ddwc_ctx* C, int nrhs, int prec) {
     return vec_words(C, nrhs, prec == DDWC_FP64) * 16;
 }
 static int dslash_apply_with(ddwc_ctx* C, Exec& ex, double kappa, const void* in, void* out, int nrhs, int prec,
-                             void* a, void* b, bool may_allocate) {
+                             void* a, bool may_allocate) {
     const Geom& g = C->g;
     const double mass4 = 4.0 + mass_of(kappa);
     if (prec == DDWC_FP64) {
         launch_import<double>(ex, g, in, (double2*)a, nrhs, MASK_ALL);
-        launch_dslash<double>(ex, g, C->U64, C->K64, mass4, (const double2*)a, (double2*)b, nrhs, DDWC_K_DSLASH64,
+        launch_dslash<double>(ex, g, C->U64, C->K64, mass4, (const double2*)a, out, true, nrhs, DDWC_K_DSLASH64,
                               ddwc_dslash_bytes(C, nrhs, DDWC_FP64));
-        launch_export<double>(ex, g, (const double2*)b, out, nrhs, MASK_ALL);
     } else if (nrhs > 1 && nrhs <= WG && ri_fits((unsigned)g.V, nrhs)) {
         // several RHS: RHS-innermost fields, the RHS of a site share its links and clover
         // (the schedule's operator workgroup size; its dispatch order only where the order table
@@ -1079,14 +1079,12 @@ static int dslash_apply_with(ddwc_ctx* C, Exec& ex, double kappa, const void* in
         if (may_allocate && g.eo && C->opt_tile_order == 1)
             CK(tile_order(C, 2, nrhs, nrhs <= nt ? nt : WG, 96.0, &order));
         launch_import_ri32(ex, g, in, (float4*)a, nrhs);
-        launch_dslash_ri32(ex, g, C->U32s, C->K32, mass4, (const float4*)a, (float4*)b, nrhs, DDWC_K_DSLASH32,
+        launch_dslash_ri32(ex, g, C->U32s, C->K32, mass4, (const float4*)a, out, nrhs, DDWC_K_DSLASH32,
                            ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32), nt, order);
-        launch_export_ri32(ex, g, (const float4*)b, out, nrhs);
     } else {
         launch_import<float>(ex, g, in, (float4*)a, nrhs, MASK_ALL);
-        launch_dslash<float>(ex, g, C->U32, C->K32, mass4, (const float4*)a, (float4*)b, nrhs, DDWC_K_DSLASH32,
+        launch_dslash<float>(ex, g, C->U32, C->K32, mass4, (const float4*)a, out, true, nrhs, DDWC_K_DSLASH32,
                              ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32));
-        launch_export<float>(ex, g, (const float4*)b, out, nrhs, MASK_ALL);
     }
     HC(hipGetLastError());
     return DDWC_OK;
@@ -1097,11 +1095,9 @@ extern "C" int ddwc_dslash_apply(ddwc_ctx* C, double kappa, const void* in, void
     CK(check_common(C, kappa, nrhs, prec));
     if (!in || !out) return fail(DDWC_EINVAL, "null vector");
     Exec ex = make_exec(C, stream);
-    const bool fp64 = prec == DDWC_FP64;
-    void *a, *b;
-    CK(ws_get(C, fp64 ? "d_in64" : "d_in32", dslash_field_bytes(C, nrhs, prec), &a));
-    CK(ws_get(C, fp64 ? "d_out64" : "d_out32", dslash_field_bytes(C, nrhs, prec), &b));
-    return dslash_apply_with(C, ex, kappa, in, out, nrhs, prec, a, b, true);
+    void* a;
+    CK(ws_get(C, prec == DDWC_FP64 ? "d_in64" : "d_in32", dslash_field_bytes(C, nrhs, prec), &a));
+    return dslash_apply_with(C, ex, kappa, in, out, nrhs, prec, a, true);
 }
 
 extern "C" int ddwc_dslash_apply_noalloc(ddwc_ctx* C, double kappa, const void* in, void* out, int nrhs, int prec,
@@ -1116,8 +1112,7 @@ extern "C" int ddwc_dslash_apply_noalloc(ddwc_ctx* C, double kappa, const void* 
     if (!C->scratch) return fail(DDWC_EHIP, "no static scratch on this context's device");
     Exec ex = make_exec(C, stream);
     ex.prof = nullptr;  // no event pairs: nothing is created during the call
-    char* base = (char*)C->scratch;
-    return dslash_apply_with(C, ex, kappa, in, out, nrhs, prec, base, base + fb, false);
+    return dslash_apply_with(C, ex, kappa, in, out, nrhs, prec, C->scratch, false);
 }
 
 extern "C" int ddwc_block_solve(ddwc_ctx* C, int colour, double kappa, const void* rhs, void* sol, int nrhs,
@@ -1230,7 +1225,7 @@ static int sap_gcr(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doubl
                 const int st = block_internal(C, ex, colour, mass, rho, dl, nrhs, btol, 1000, prec, &bi);
                 if (st != DDWC_OK && st != DDWC_ENOCONV) return st;
                 launch_axpby(ex, g, 1.0, out, 1.0, dl, out, nrhs, MASK_ALL);
-                launch_residual<double>(ex, g, C->U64, C->K64, mass4, out, eta, rho, part, nrhs, DDWC_K_DSLASH64,
+                launch_residual(ex, g, C->U64, C->K64, mass4, out, eta, rho, part, nrhs, DDWC_K_DSLASH64,
                                         dbytes);
             }
         return DDWC_OK;
@@ -1263,7 +1258,7 @@ static int sap_gcr(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doubl
         int kused = 0;
         for (int k = 0; k < NKV && total < maxit; ++k) {
             CK(sap(r, Z[k]));
-            launch_dslash<double>(ex, g, C->U64, C->K64, mass4, Z[k], W[k], nrhs, DDWC_K_DSLASH64, dbytes);
+            launch_dslash<double>(ex, g, C->U64, C->K64, mass4, Z[k], W[k], false, nrhs, DDWC_K_DSLASH64, dbytes);
             for (int i = 0; i < k; ++i) {  // modified Gram-Schmidt
                 CK(cdots(C, ex, W[i], W[k], nrhs, xy, yy));
                 for (int j = 0; j < nrhs; ++j) {
@@ -1307,7 +1302,7 @@ static int sap_gcr(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doubl
             CK(caxpy(coef, Z[k], x64));
         }
         // exact residual
-        launch_residual<double>(ex, g, C->U64, C->K64, mass4, x64, b64, r, part, nrhs, DDWC_K_DSLASH64, dbytes);
+        launch_residual(ex, g, C->U64, C->K64, mass4, x64, b64, r, part, nrhs, DDWC_K_DSLASH64, dbytes);
         CK(cdots(C, ex, r, r, nrhs, xy, rr));
         for (int j = 0; j < nrhs; ++j)
             if (!isfinite(rr[j])) return fail(DDWC_ENONFINITE, "non-finite residual in the global solve");

@@ -87,13 +87,12 @@ void launch_links_import(Exec& e, const Geom& g, const void* canon, cx<double>* 
 // and Ub (the neighbours', [4][9][n]) and the table nbr [8][n].
 void launch_links_own(Exec& e, unsigned n, const cx<float>* Uf, const cx<float>* Ub, const int* nbr,
                       cx<float>* Lown);
-// Full-lattice FP32 Dslash on RHS-innermost fields [6][V][nrhs] (canonical FP64 in and out), with
+// Full-lattice FP32 Dslash on an RHS-innermost field [6][V][nrhs], result in the canonical FP64 layout, with
 // the own-site link records Us [V][8][9]; op_threads (128, 256 or 512; 256 below nrhs) threads per
 // workgroup, tiles dispatched in `order` (null: index order; dslash_ri32_tiles() entries).
 void launch_import_ri32(Exec& e, const Geom& g, const void* canon, float4* out, int nrhs);
-void launch_export_ri32(Exec& e, const Geom& g, const float4* in, void* canon, int nrhs);
 void launch_dslash_ri32(Exec& e, const Geom& g, const cx<float>* Us, const float4* K, double mass4, const float4* in,
-                        float4* out, int nrhs, int kclass, double bytes, int op_threads = WG,
+                        void* out, int nrhs, int kclass, double bytes, int op_threads = WG,
                         const int* order = nullptr);
 int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads);
 void launch_nbr_build(Exec& e, const Geom& g, int* nbr);
@@ -104,16 +103,13 @@ void launch_import(Exec& e, const Geom& g, const void* canon, typename Traits<R>
 template <class R>
 void launch_export(Exec& e, const Geom& g, const typename Traits<R>::word* in, void* canon, int nrhs, int mask);
 
-// out = D(m) in over all sites (no reductions).
+// out = D(m) in over all sites; canonical: out is the canonical FP64 layout, else an internal field.
 template <class R>
 void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                   const typename Traits<R>::word* in, typename Traits<R>::word* out, int nrhs, int kclass,
-                   double bytes);
+                   const typename Traits<R>::word* in, void* out, bool canonical, int nrhs, int kclass, double bytes);
 // r = b - D(m) x, partial ||r||^2.
-template <class R>
-void launch_residual(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                     const typename Traits<R>::word* x, const typename Traits<R>::word* b,
-                     typename Traits<R>::word* r, double* part, int nrhs, int kclass, double bytes);
+void launch_residual(Exec& e, const Geom& g, const cx<double>* U, const double2* K, double mass4, const double2* x,
+                     const double2* b, double2* r, double* part, int nrhs, int kclass, double bytes);
 // Extents of an outer block decomposition (nested domain decomposition).
 struct Ext4 {
     int v[4];

@@ -12,12 +12,10 @@
 
 #include "ddwc_internal.h"
 #include "clover_build.h"
+#include "uniform_mem.h"
 #include "vec_items.h"
 
 namespace ddwc {
-
-// Operator kernels are memory bound: ask for at least 4 waves per SIMD (<= 128 VGPRs).
-#define DDWC_OCC
 
 // ------------------------------------------------------------------ conversions
 __global__ void k_links_import(Geom g, const double2* __restrict__ can, cx<double>* __restrict__ U64,
@@ -153,55 +151,110 @@ void launch_export(Exec& e, const Geom& g, const typename Traits<R>::word* in, v
 }
 
 // ------------------------------------------------------------------ operator kernels
-// Epilogue RESID: y = aux - y and partial ||y||^2.
-enum Epi { EPI_NONE = 0, EPI_RESID = 1 };
+// Results in the canonical layout (FP64, [nrhs][V][12]) straight from an operator kernel of NT threads: every
+// thread puts its spinor into LDS, then the workgroup writes the records with consecutive lanes on
+// consecutive words (a record is 192 contiguous bytes; a store per lane and component would touch 64
+// lines).  at: the record's number r V + canonical site, ~0 for none.  All threads must call it, after the
+// last use of what lds (NT x (sizeof(cx<R>) * 12 + 4) bytes) held before.
+template <class R>
+constexpr size_t canon_bytes(int nt) {
+    return (size_t)nt * (12 * sizeof(cx<R>) + sizeof(unsigned));
+}
+template <class R, int NT>
+__device__ __forceinline__ void store_canonical(const cx<R> y[12], unsigned at, double2* __restrict__ can, void* lds) {
+    typedef typename VecOf<R>::link V2;
+    V2* rec = (V2*)lds;
+    unsigned* no = (unsigned*)(rec + NT * 12);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) rec[threadIdx.x * 12 + c] = (V2){y[c].re, y[c].im};
+    no[threadIdx.x] = at;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const unsigned e = k * NT + threadIdx.x, q = e / 12, n = no[q];
+        const V2 v = rec[e];
+        if (n != ~0u) can[(size_t)n * 12 + (e - 12 * q)] = make_double2((double)v.x, (double)v.y);
+    }
+}
+
+// Full-lattice operator on internal fields.  EPI_NONE: out = D in; EPI_RESID: out = aux - D in and partial
+// ||out||^2; EPI_CANON: D in to the canonical FP64 layout at out.
+enum Epi { EPI_NONE = 0, EPI_RESID = 1, EPI_CANON = 2 };
 
 template <class R, int EPI>
-__global__ __launch_bounds__(WG) DDWC_OCC void k_dslash(Geom g, const cx<R>* __restrict__ U,
+__global__ __launch_bounds__(WG) void k_dslash(Geom g, const cx<R>* __restrict__ U,
                                                const typename Traits<R>::word* __restrict__ K, R mass4,
-                                               const typename Traits<R>::word* __restrict__ in,
-                                               typename Traits<R>::word* __restrict__ out,
+                                               const typename Traits<R>::word* __restrict__ in, void* __restrict__ out,
                                                const typename Traits<R>::word* __restrict__ aux, double* part,
-                                               int nrhs, int ntiles, const int* __restrict__ nbr, int ndir) {
+                                               int nrhs, int ntiles, const int* __restrict__ nbr) {
     typedef typename Traits<R>::word W;
-    TileRhs tr = tile_rhs(ntiles, nrhs);
-    const int s = tr.tile * WG + threadIdx.x;
-    const size_t off = (size_t)tr.rhs * Traits<R>::NCW * g.V;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (s < g.V) {
-        cx<R> y[12];
-        site_operator<R, true, HOPS_ALL, 1>(g, s, in + off, U, K, nbr, mass4, y, ndir);
+    const TileRhs tr = tile_rhs(ntiles, nrhs);
+    const unsigned V = g.V, s = tr.tile * WG + threadIdx.x;
+    const bool ok = s < V;
+    const size_t off = (size_t)tr.rhs * Traits<R>::NCW * V;
+    double v[1] = {0};
+    cx<R> y[12];
+    if (ok) {
+        int e[8];
+        {
+            Planes q(nbr, V);
+            const unsigned o = byte_offset(s, 4);
+#pragma unroll
+            for (int d = 0; d < 8; ++d) e[d] = q.load<int>(o);
+        }
+        constexpr unsigned LS = sizeof(cx<R>);
+        const unsigned so = byte_offset(s, 16), lo = byte_offset(s, LS);
+        Planes pf(U, V), pb(U, V);
+        auto target = [&](int d) { return d < 2 && e[d] < 0 ? (unsigned)~e[d] : (unsigned)e[d]; };
+        auto lq = [&](int d, cx<R> q[12]) { uload_spinor(in + off, V, reissue(byte_offset(target(d), 16)), q); };
+        auto lu = [&](int d, cx<R> u[9]) {
+            if (d & 1)
+                uload_link(pb, reissue(byte_offset(target(d), LS)), u);
+            else
+                uload_link(pf, reissue(lo), u);
+        };
+        hops_pipelined<R, true>(y, lq, lu, [&](int d) { return e[d] < 0; }, [](int) { return true; });
+        cx<R> c[12];
+        UDiag<R> D(K, V, so);
+        D.first();
+        uload_spinor(in + off, V, so, c);
+        D.apply(mass4, c, y, R(-0.5));
         if (EPI == EPI_RESID) {
             cx<R> b[12];
-            load_spinor((const W*)aux + off, g.V, s, b);
+            uload_spinor(aux + off, V, so, b);
 #pragma unroll
             for (int k = 0; k < 12; ++k) y[k] = b[k] - y[k];
             v[0] = acc_nrm(y);
         }
-        store_spinor(out + off, g.V, s, y);
+        if (EPI != EPI_CANON) ustore_spinor((W*)out + off, V, so, y);
+    }
+    if constexpr (EPI == EPI_CANON) {
+        __shared__ __align__(16) char lds[canon_bytes<R>(WG)];
+        const unsigned at = ok ? (unsigned)canonical_index(g, decode(g, (int)s)) : ~0u;
+        store_canonical<R, WG>(y, at, (double2*)out + (size_t)tr.rhs * 12 * V, lds);
     }
     if (EPI == EPI_RESID) write_partials<1>(v, part, ntiles, nrhs, tr);
 }
 
 template <class R>
 void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                   const typename Traits<R>::word* in, typename Traits<R>::word* out, int nrhs, int kclass,
-                   double bytes) {
+                   const typename Traits<R>::word* in, void* out, bool canonical, int nrhs, int kclass, double bytes) {
     Timed t(e, kclass, bytes);
-    int nt = tiles_of(g.V);
-    k_dslash<R, EPI_NONE><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr, 8);
+    const int nt = tiles_of(g.V);
+    if (canonical)
+        k_dslash<R, EPI_CANON><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr);
+    else
+        k_dslash<R, EPI_NONE><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr);
 }
-template <class R>
-void launch_residual(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                     const typename Traits<R>::word* x, const typename Traits<R>::word* b,
-                     typename Traits<R>::word* r, double* part, int nrhs, int kclass, double bytes) {
+void launch_residual(Exec& e, const Geom& g, const cx<double>* U, const double2* K, double mass4, const double2* x,
+                     const double2* b, double2* r, double* part, int nrhs, int kclass, double bytes) {
     Timed t(e, kclass, bytes);
-    int nt = tiles_of(g.V);
-    k_dslash<R, EPI_RESID><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, x, r, b, part, nrhs, nt, e.nbr, 8);
+    const int nt = tiles_of(g.V);
+    k_dslash<double, EPI_RESID><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, mass4, x, r, b, part, nrhs, nt, e.nbr);
 }
 
 template <class R>
-__global__ __launch_bounds__(WG) DDWC_OCC void k_hop(Geom g, const cx<R>* __restrict__ U,
+__global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<R>* __restrict__ U,
                                             const typename Traits<R>::word* __restrict__ in,
                                             typename Traits<R>::word* __restrict__ out, int nrhs, int to_colour,
                                             const int* __restrict__ nbr, int ndir, Ext4 cut, int cut_colour, int s0,
@@ -817,46 +870,52 @@ __global__ __launch_bounds__(WG) void k_import_ri32(Geom g, const double2* __res
     store_spinor(out, w.stride, w.idx, q);
 }
 
-__global__ __launch_bounds__(WG) void k_export_ri32(Geom g, const float4* __restrict__ in, double2* __restrict__ can,
-                                                    int nrhs, int ntiles) {
-    const VItem it = vitem<true>((unsigned)g.V, nrhs, ntiles);
-    if (!it.ok) return;
-    const VView<true, float> w((unsigned)g.V, nrhs, it.i, it.r);
-    cx<float> q[12];
-    load_spinor(in, w.stride, w.idx, q);
-    double2* dst = can + ((size_t)it.r * g.V + canonical_index(g, decode(g, (int)it.i))) * 12;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) dst[c] = make_double2((double)q[c].re, (double)q[c].im);
-}
-
-// NT threads per workgroup; order (may be null): the tile of each dispatch slot.
+// NT threads per workgroup; order (may be null): the tile of each dispatch slot.  The result goes to the
+// canonical layout.
 template <bool STG, int NT>
 __global__ __launch_bounds__(NT) void k_dslash_ri32(Geom g, const cx<float>* __restrict__ Lown,
                                                     const float4* __restrict__ K, float mass4,
-                                                    const float4* __restrict__ in, float4* __restrict__ out,
+                                                    const float4* __restrict__ in, double2* __restrict__ out,
                                                     const int* __restrict__ nbr, int nrhs, int ntiles,
                                                     const int* __restrict__ order) {
-    const VItem it = vitem<true, NT>((unsigned)g.V, nrhs, ntiles, order);
+    extern __shared__ __align__(16) char dyn[];
+    const unsigned V = g.V;
+    const VItem it = vitem<true, NT>(V, nrhs, ntiles, order);
     const cx<float>* Uf = Lown;
     const float4* Kk = K;
     const int* nb = nbr;
-    unsigned kst = (unsigned)g.V, l0 = 0, nstr = 0;
+    unsigned kst = V, l0 = 0;
     if constexpr (STG) {
-        const Staged<float> sd = stage_site_data<float, NT>(it, (unsigned)g.V, nrhs, Lown, K, nbr);
+        const Staged<float> sd = stage_site_data<float, NT>(it, V, nrhs, Lown, K, nbr);
         Uf = sd.U;
         Kk = sd.K;
         nb = sd.nbr;
-        kst = nstr = sd.n;
+        kst = sd.n;
         l0 = sd.l0;
     }
-    if (!it.ok) return;
-    const VView<true, float> w((unsigned)g.V, nrhs, it.i, it.r);
-    cx<float> acc[12], c[12];
-    hop_sum<float, HOPS_ALL, STG ? 0 : 1, LK_OWN>((unsigned)g.V, it.i, in, Uf, Uf, nb, acc, 8, (unsigned)nrhs,
-                                                  (unsigned)it.r, w.stride, l0, nstr);
-    load_spinor(in, w.stride, w.idx, c);
-    apply_diag<float>(Kk, kst, it.i - l0, mass4, c, acc, -0.5f);
-    store_spinor(out, w.stride, w.idx, acc);
+    cx<float> acc[12];
+    if (it.ok) {
+        const VView<true, float> w(V, nrhs, it.i, it.r);
+        int e[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d) e[d] = nb[(size_t)d * kst + it.i - l0];
+        auto target = [&](int d) { return d < 2 && e[d] < 0 ? (unsigned)~e[d] : (unsigned)e[d]; };
+        auto lq = [&](int d, cx<float> q[12]) {
+            uload_spinor(in, w.stride, reissue(byte_offset(target(d) * (unsigned)nrhs + it.r, 16)), q);
+        };
+        const cx<float>* rec = Uf + (size_t)(it.i - l0) * 72;
+        auto lu = [&](int d, cx<float> u[9]) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) u[k] = rec[d * 9 + k];
+        };
+        hops_pipelined<float, !STG>(acc, lq, lu, [&](int d) { return e[d] < 0; }, [](int) { return true; });
+        cx<float> c[12];
+        uload_spinor(in, w.stride, byte_offset(w.idx, 16), c);
+        apply_diag<float>(Kk, kst, it.i - l0, mass4, c, acc, -0.5f);
+    }
+    const unsigned at = it.ok ? (unsigned)it.r * V + (unsigned)canonical_index(g, decode(g, (int)it.i)) : ~0u;
+    __syncthreads();  // the staged data gives way to the results
+    store_canonical<float, NT>(acc, at, out, dyn);
 }
 
 void launch_import_ri32(Exec& e, const Geom& g, const void* canon, float4* out, int nrhs) {
@@ -864,23 +923,19 @@ void launch_import_ri32(Exec& e, const Geom& g, const void* canon, float4* out, 
     const int nt = tiles_of(g.V * nrhs);
     k_import_ri32<<<nt, WG, 0, e.stream>>>(g, (const double2*)canon, out, nrhs, nt);
 }
-void launch_export_ri32(Exec& e, const Geom& g, const float4* in, void* canon, int nrhs) {
-    Timed t(e, 4, 0);
-    const int nt = tiles_of(g.V * nrhs);
-    k_export_ri32<<<nt, WG, 0, e.stream>>>(g, in, (double2*)canon, nrhs, nt);
-}
 void launch_dslash_ri32(Exec& e, const Geom& g, const cx<float>* Us, const float4* K, double mass4, const float4* in,
-                        float4* out, int nrhs, int kclass, double bytes, int op_threads, const int* order) {
+                        void* out, int nrhs, int kclass, double bytes, int op_threads, const int* order) {
     Timed t(e, kclass, bytes);
     const int NTr = nrhs <= op_threads ? op_threads : WG;
     const int nt = (int)(((long long)g.V * nrhs + NTr - 1) / NTr);
     auto launch = [&](auto ntc) {
         constexpr int NT = decltype(ntc)::value;
         if (stage_ok<float>((unsigned)g.V, nrhs))
-            k_dslash_ri32<true, NT><<<nt, NT, stage_bytes<float>(NT, nrhs), e.stream>>>(g, Us, K, (float)mass4, in, out,
-                                                                                  e.nbr, nrhs, nt, order);
+            k_dslash_ri32<true, NT><<<nt, NT, std::max(stage_bytes<float>(NT, nrhs), canon_bytes<float>(NT)), e.stream>>>(
+                g, Us, K, (float)mass4, in, (double2*)out, e.nbr, nrhs, nt, order);
         else
-            k_dslash_ri32<false, NT><<<nt, NT, 0, e.stream>>>(g, Us, K, (float)mass4, in, out, e.nbr, nrhs, nt, order);
+            k_dslash_ri32<false, NT><<<nt, NT, canon_bytes<float>(NT), e.stream>>>(g, Us, K, (float)mass4, in, (double2*)out,
+                                                                              e.nbr, nrhs, nt, order);
     };
     switch (NTr) {
         case 128: launch(std::integral_constant<int, 128>()); break;
@@ -898,10 +953,7 @@ int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads) {
     template void launch_import<R>(Exec&, const Geom&, const void*, Traits<R>::word*, int, int);                  \
     template void launch_export<R>(Exec&, const Geom&, const Traits<R>::word*, void*, int, int);                  \
     template void launch_dslash<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,              \
-                                   const Traits<R>::word*, Traits<R>::word*, int, int, double);                   \
-    template void launch_residual<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,            \
-                                     const Traits<R>::word*, const Traits<R>::word*, Traits<R>::word*, double*,   \
-                                     int, int, double);                                                           \
+                                   const Traits<R>::word*, void*, bool, int, int, double);                        \
     template void launch_hop<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, Traits<R>::word*, int,  \
                                 int, const Ext4*, int, bool);                                                     \
     template void launch_bicg_init<R>(Exec&, unsigned, bool, const double2*, const double*, Traits<R>::word*,      \

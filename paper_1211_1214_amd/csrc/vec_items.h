@@ -149,7 +149,8 @@ __device__ __forceinline__ Staged<S> stage_site_data(const VItem& it, unsigned n
                                                      const int* __restrict__ nbr) {
     typedef float v4 __attribute__((ext_vector_type(4)));
     static_assert(std::is_same<typename Traits<S>::kword, float4>::value, "clover words are float4");
-    extern __shared__ v4 stg[];
+    extern __shared__ __align__(16) char dyn[];
+    v4* stg = (v4*)dyn;
     constexpr unsigned RW = record_words<S>(), NK = Traits<S>::NKW;
     const unsigned NS = stg_sites(NT, nrhs);
     const unsigned l0 = it.g0 / (unsigned)nrhs;

@@ -434,12 +434,12 @@ EoFields<H16> eo_fields<H16>(const ddwc_ctx* C, bool site_major) {
 }
 
 // Dispatch order of the tiles of the RHS-innermost operator kernels on half fields (parities = 1) or full fields
-// (parities = 2) with nrhs RHS, nt pairs per tile and `bytes` per stored spinor.
+// (parities = 2) with nrhs RHS per site, nt (site, RHS) pairs per tile and `bytes` a site gathered from neighbours.
 // After the XCD remap each XCD takes a contiguous run of this order.  The tiles are sorted into
 // spatial columns of whole blocks that run through all of time, and inside a column by time slice, so that
 // an XCD sweeps a column slice by slice and finds the neighbours of a slice in its L2: those in
 // space except through the column's sides, and those in time until two slices later.  A
-// column's slice of spinors takes at most COLUMN_BYTES (three slices, the results and the links of the sites in
+// column's slice of what is gathered takes at most COLUMN_BYTES (three slices, the results and the links of the sites in
 // flight share 4 MiB), and its blocks divide an eighth of a slice's where that is whole; it grows by
 // blocks in its shortest direction.  48x24^3, 12 RHS (12^3 columns, one per XCD), with non-temporal stores and
 // staging: hop-and-inverse 324 -> 306 us, diagonal-and-hop 448 / 373 -> 415 / 350 us against blocks of both colours
@@ -460,7 +460,7 @@ static int tile_order(ddwc_ctx* C, int parities, int nrhs, int nt, double bytes,
             while (next <= g.nb[m] && g.nb[m] % next != 0) ++next;
             if (next > g.nb[m]) continue;
             const int n = c[1] * c[2] * c[3] / c[m] * next;
-            if (share % n != 0 || (double)n * slice * parities * nrhs * bytes > COLUMN_BYTES) continue;
+            if (share % n != 0 || (double)n * slice * parities * bytes > COLUMN_BYTES) continue;
             c[m] = next;
             grown = true;
             break;
@@ -602,7 +602,7 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     const bool ri = h16 || (nrhs > 1 && nrhs <= WG && ri_fits(n2, nrhs));
     EoFields<S> FR = eo_fields<S>(C, ri && !fp64);  // RI kernels read own-site link records
     const double rs = h16 ? 52.0 : 24.0 * sizeof(R);  // bytes of a stored spinor
-    if (ri && g.eo && C->opt_tile_order == 1) CK(tile_order(C, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs, &FR.order));
+    if (ri && g.eo && C->opt_tile_order == 1) CK(tile_order(C, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs * nrhs, &FR.order));
     const int ntR = vector_tiles(n2, nrhs, ri);
     const int ntM = eo_op_tiles(FR, nrhs, ri);  // tiles of the operator kernels' partial sums
     const double mass4 = 4.0 + mass;
@@ -1066,25 +1066,29 @@ static int dslash_apply_with(ddwc_ctx* C, Exec& ex, double kappa, const void* in
                              void* a, bool may_allocate) {
     const Geom& g = C->g;
     const double mass4 = 4.0 + mass_of(kappa);
+    // the dispatch order only where the order table may be built: the per-site arithmetic, and so the
+    // result, is the same in any order
+    const int* order = nullptr;
+    // (smaller lattices stay in the L2s, and finding their table takes as long as the launch)
+    const bool ordered = may_allocate && g.eo && C->opt_tile_order == 1 && g.V >= (1 << 15);
     if (prec == DDWC_FP64) {
+        // (spinors and backward links are gathered)
+        if (ordered) CK(tile_order(C, 2, 1, DW, 192.0 * nrhs + 576.0, &order));
         launch_import<double>(ex, g, in, (double2*)a, nrhs, MASK_ALL);
         launch_dslash<double>(ex, g, C->U64, C->K64, mass4, (const double2*)a, out, true, nrhs, DDWC_K_DSLASH64,
-                              ddwc_dslash_bytes(C, nrhs, DDWC_FP64));
+                              ddwc_dslash_bytes(C, nrhs, DDWC_FP64), order);
     } else if (nrhs > 1 && nrhs <= WG && ri_fits((unsigned)g.V, nrhs)) {
         // several RHS: RHS-innermost fields, the RHS of a site share its links and clover
-        // (the schedule's operator workgroup size; its dispatch order only where the order table
-        // may be built: the per-site arithmetic, and so the result, is the same in any order)
-        const int* order = nullptr;
         const int nt = C->opt_op_threads;
-        if (may_allocate && g.eo && C->opt_tile_order == 1)
-            CK(tile_order(C, 2, nrhs, nrhs <= nt ? nt : WG, 96.0, &order));
+        if (ordered) CK(tile_order(C, 2, nrhs, nrhs <= nt ? nt : WG, 96.0 * nrhs, &order));
         launch_import_ri32(ex, g, in, (float4*)a, nrhs);
         launch_dslash_ri32(ex, g, C->U32s, C->K32, mass4, (const float4*)a, out, nrhs, DDWC_K_DSLASH32,
                            ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32), nt, order);
     } else {
+        if (ordered) CK(tile_order(C, 2, 1, DW, 96.0 * nrhs + 288.0, &order));
         launch_import<float>(ex, g, in, (float4*)a, nrhs, MASK_ALL);
         launch_dslash<float>(ex, g, C->U32, C->K32, mass4, (const float4*)a, out, true, nrhs, DDWC_K_DSLASH32,
-                             ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32));
+                             ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32), order);
     }
     HC(hipGetLastError());
     return DDWC_OK;

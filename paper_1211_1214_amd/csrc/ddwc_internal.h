@@ -76,6 +76,7 @@ struct Timed {
 
 // ------------------------------------------------------------------ launchers (kernels.hip)
 constexpr int WG = 256;  // sites per workgroup of the site-parallel kernels
+constexpr int DW = 64;   // sites per workgroup of the full-lattice operator
 constexpr int NPART = 8; // doubles per partial-sum slot
 constexpr unsigned PACKED_LINK_BYTES = 72;  // one packed FP32 link (nine complex entries)
 
@@ -103,10 +104,12 @@ void launch_import(Exec& e, const Geom& g, const void* canon, typename Traits<R>
 template <class R>
 void launch_export(Exec& e, const Geom& g, const typename Traits<R>::word* in, void* canon, int nrhs, int mask);
 
-// out = D(m) in over all sites; canonical: out is the canonical FP64 layout, else an internal field.
+// out = D(m) in over all sites; canonical: out is the canonical FP64 layout, else an internal field.  order:
+// the tile (DW sites) that each dispatch slot processes (null: index order).
 template <class R>
 void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                   const typename Traits<R>::word* in, void* out, bool canonical, int nrhs, int kclass, double bytes);
+                   const typename Traits<R>::word* in, void* out, bool canonical, int nrhs, int kclass, double bytes,
+                   const int* order = nullptr);
 // r = b - D(m) x, partial ||r||^2.
 void launch_residual(Exec& e, const Geom& g, const cx<double>* U, const double2* K, double mass4, const double2* x,
                      const double2* b, double2* r, double* part, int nrhs, int kclass, double bytes);

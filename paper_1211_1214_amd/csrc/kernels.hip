@@ -173,7 +173,8 @@ __device__ __forceinline__ void store_canonical(const cx<R> y[12], unsigned at, 
     for (int k = 0; k < 12; ++k) {
         const unsigned e = k * NT + threadIdx.x, q = e / 12, n = no[q];
         const V2 v = rec[e];
-        if (n != ~0u) can[(size_t)n * 12 + (e - 12 * q)] = make_double2((double)v.x, (double)v.y);
+        if (n != ~0u)
+            __builtin_nontemporal_store((d2v){(double)v.x, (double)v.y}, (d2v*)can + ((size_t)n * 12 + (e - 12 * q)));
     }
 }
 
@@ -181,15 +182,21 @@ __device__ __forceinline__ void store_canonical(const cx<R> y[12], unsigned at, 
 // ||out||^2; EPI_CANON: D in to the canonical FP64 layout at out.
 enum Epi { EPI_NONE = 0, EPI_RESID = 1, EPI_CANON = 2 };
 
+// Bound by memory: at 48x24^3 one FP64 field takes 276 us for 1.02 GB (links and clover 0.76), 3.7 TB/s, and 294 us +
+// 65 us of export before (rolled loop, one wave per SIMD, index order); in index order 306 us, with
+// workgroups of 256 threads 288 us (2592 of them are five rounds of the chip and a sixth that is
+// nearly empty) and 10.1 instead of 6.8 us at 4^4.
 template <class R, int EPI>
-__global__ __launch_bounds__(WG) void k_dslash(Geom g, const cx<R>* __restrict__ U,
+__global__ __launch_bounds__(DW) __attribute__((amdgpu_waves_per_eu(2))) void k_dslash(Geom g, const cx<R>* __restrict__ U,
                                                const typename Traits<R>::word* __restrict__ K, R mass4,
                                                const typename Traits<R>::word* __restrict__ in, void* __restrict__ out,
                                                const typename Traits<R>::word* __restrict__ aux, double* part,
-                                               int nrhs, int ntiles, const int* __restrict__ nbr) {
+                                               int nrhs, int ntiles, const int* __restrict__ nbr,
+                                               const int* __restrict__ order) {
     typedef typename Traits<R>::word W;
-    const TileRhs tr = tile_rhs(ntiles, nrhs);
-    const unsigned V = g.V, s = tr.tile * WG + threadIdx.x;
+    TileRhs tr = tile_rhs(ntiles, nrhs);
+    if (order) tr.tile = order[tr.tile];
+    const unsigned V = g.V, s = tr.tile * DW + threadIdx.x;
     const bool ok = s < V;
     const size_t off = (size_t)tr.rhs * Traits<R>::NCW * V;
     double v[1] = {0};
@@ -229,28 +236,31 @@ __global__ __launch_bounds__(WG) void k_dslash(Geom g, const cx<R>* __restrict__
         if (EPI != EPI_CANON) ustore_spinor((W*)out + off, V, so, y);
     }
     if constexpr (EPI == EPI_CANON) {
-        __shared__ __align__(16) char lds[canon_bytes<R>(WG)];
+        __shared__ __align__(16) char lds[canon_bytes<R>(DW)];
         const unsigned at = ok ? (unsigned)canonical_index(g, decode(g, (int)s)) : ~0u;
-        store_canonical<R, WG>(y, at, (double2*)out + (size_t)tr.rhs * 12 * V, lds);
+        store_canonical<R, DW>(y, at, (double2*)out + (size_t)tr.rhs * 12 * V, lds);
     }
     if (EPI == EPI_RESID) write_partials<1>(v, part, ntiles, nrhs, tr);
 }
 
 template <class R>
 void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
-                   const typename Traits<R>::word* in, void* out, bool canonical, int nrhs, int kclass, double bytes) {
+                   const typename Traits<R>::word* in, void* out, bool canonical, int nrhs, int kclass, double bytes,
+                   const int* order) {
     Timed t(e, kclass, bytes);
-    const int nt = tiles_of(g.V);
+    const int nt = (g.V + DW - 1) / DW;
     if (canonical)
-        k_dslash<R, EPI_CANON><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr);
+        k_dslash<R, EPI_CANON><<<nt * nrhs, DW, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr,
+                                                                order);
     else
-        k_dslash<R, EPI_NONE><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr);
+        k_dslash<R, EPI_NONE><<<nt * nrhs, DW, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr,
+                                                                order);
 }
 void launch_residual(Exec& e, const Geom& g, const cx<double>* U, const double2* K, double mass4, const double2* x,
                      const double2* b, double2* r, double* part, int nrhs, int kclass, double bytes) {
     Timed t(e, kclass, bytes);
-    const int nt = tiles_of(g.V);
-    k_dslash<double, EPI_RESID><<<nt * nrhs, WG, 0, e.stream>>>(g, U, K, mass4, x, r, b, part, nrhs, nt, e.nbr);
+    const int nt = (g.V + DW - 1) / DW;
+    k_dslash<double, EPI_RESID><<<nt * nrhs, DW, 0, e.stream>>>(g, U, K, mass4, x, r, b, part, nrhs, nt, e.nbr, nullptr);
 }
 
 template <class R>
@@ -953,7 +963,7 @@ int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads) {
     template void launch_import<R>(Exec&, const Geom&, const void*, Traits<R>::word*, int, int);                  \
     template void launch_export<R>(Exec&, const Geom&, const Traits<R>::word*, void*, int, int);                  \
     template void launch_dslash<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,              \
-                                   const Traits<R>::word*, void*, bool, int, int, double);                        \
+                                   const Traits<R>::word*, void*, bool, int, int, double, const int*);            \
     template void launch_hop<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, Traits<R>::word*, int,  \
                                 int, const Ext4*, int, bool);                                                     \
     template void launch_bicg_init<R>(Exec&, unsigned, bool, const double2*, const double*, Traits<R>::word*,      \

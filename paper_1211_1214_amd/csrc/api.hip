@@ -135,7 +135,7 @@ struct ddwc_ctx {
     cx<float>* Uh32 = nullptr;
     double2* Kh64 = nullptr;
     cx<f16>* Uh16 = nullptr;  // FP16 half-order links (storage of the FP16 inner solver)
-    void* Uh32w = nullptr;       // packed FP32 half-order links (the LDS-resident block solver, where it applies)
+    void *Uh32w = nullptr, *Uh16w = nullptr;  // packed half-order links (block solvers)
     cx<float>* Uh32s = nullptr;  // own-site link records [2][V/2][8][9] (FP32, FP16) read by the
     cx<f16>* Uh16s = nullptr;    // RHS-innermost kernels of the global solver
     float4* Kh32 = nullptr;
@@ -315,16 +315,18 @@ extern "C" int ddwc_create(ddwc_ctx** out, const int lat[4], const int blk[4], i
         hipMalloc(&C->nbr_eo, (size_t)2 * 8 * n2 * sizeof(int)) != hipSuccess ||
         hipMalloc(&C->Uh32s, (size_t)2 * 72 * n2 * sizeof(cx<float>)) != hipSuccess ||
         (g.eo && (hipMalloc(&C->Uh16, (size_t)2 * 36 * n2 * sizeof(cx<f16>)) != hipSuccess ||
-                  hipMalloc(&C->Uh16s, (size_t)2 * 72 * n2 * sizeof(cx<f16>)) != hipSuccess)) ||
-        (blk_lds_fits(g, C->lds_max) && hipMalloc(&C->Uh32w, (size_t)8 * PACKED_LINK_BYTES * n2) != hipSuccess)) {
+                  hipMalloc(&C->Uh16s, (size_t)2 * 72 * n2 * sizeof(cx<f16>)) != hipSuccess ||
+                  hipMalloc(&C->Uh32w, (size_t)8 * packed_link_bytes<float>() * n2) != hipSuccess ||
+                  hipMalloc(&C->Uh16w, (size_t)8 * packed_link_bytes<f16>() * n2) != hipSuccess))) {
         ddwc_destroy(C);
         return fail(DDWC_EHIP, "device allocation of the even-odd fields failed");
     }
     launch_eo_setup(ex, g, C->U64, C->K64, C->nbr, C->Uh64, C->Uh32, C->Kh64, C->Kh32, C->nbr_eo);
     launch_eo_links_own(ex, (unsigned)n2, C->Uh32, C->nbr_eo, C->Uh32s);
-    if (C->Uh32w) launch_eo_links_packed(ex, (unsigned)n2, C->Uh32, C->Uh32w);
     if (g.eo) {
         launch_links_to_half(ex, (size_t)2 * 36 * n2, C->Uh32, C->Uh16);
+        launch_eo_links_packed<float>(ex, (unsigned)n2, C->Uh32, C->Uh32w);
+        launch_eo_links_packed<f16>(ex, (unsigned)n2, C->Uh16, C->Uh16w);
         launch_links_to_half(ex, (size_t)2 * 72 * n2, C->Uh32s, C->Uh16s);
     }
     double* fpp = nullptr;
@@ -366,7 +368,7 @@ extern "C" int ddwc_destroy(ddwc_ctx* C) {
     if (C->K32) (void)hipFree(C->K32);
     if (C->nbr) (void)hipFree(C->nbr);
     for (void* q : {(void*)C->Uh64, (void*)C->Uh32, (void*)C->Kh64, (void*)C->Kh32, (void*)C->nbr_eo, (void*)C->Uh16,
-                    (void*)C->Uh32s, (void*)C->Uh16s, C->Uh32w})
+                    (void*)C->Uh32s, (void*)C->Uh16s, C->Uh32w, C->Uh16w})
         if (q) (void)hipFree(q);
     for (auto& a : C->ainv) {
         (void)hipFree(a.a64);
@@ -415,7 +417,7 @@ EoFields<float> eo_fields<float>(const ddwc_ctx* C, bool site_major) {
         F.U[p] = site_major ? C->Uh32s + (size_t)p * 72 * F.n2 : C->Uh32 + (size_t)p * 36 * F.n2;
         F.K[p] = C->Kh32 + (size_t)p * 18 * F.n2;
         F.nbr[p] = C->nbr_eo + (size_t)p * 8 * F.n2;
-        if (C->Uh32w) F.W[p] = (const char*)C->Uh32w + (size_t)p * 4 * PACKED_LINK_BYTES * F.n2;
+        if (C->Uh32w) F.W[p] = (const char*)C->Uh32w + (size_t)p * 4 * packed_link_bytes<float>() * F.n2;
     }
     return F;
 }
@@ -429,6 +431,7 @@ EoFields<H16> eo_fields<H16>(const ddwc_ctx* C, bool site_major) {
         F.U[p] = site_major ? C->Uh16s + (size_t)p * 72 * F.n2 : C->Uh16 + (size_t)p * 36 * F.n2;
         F.K[p] = C->Kh32 + (size_t)p * 18 * F.n2;
         F.nbr[p] = C->nbr_eo + (size_t)p * 8 * F.n2;
+        F.W[p] = (const char*)C->Uh16w + (size_t)p * 4 * packed_link_bytes<f16>() * F.n2;
     }
     return F;
 }
@@ -880,7 +883,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     const EoFields<double> F64 = eo_fields<double>(C);
     const unsigned n2 = F64.n2;
     // blocks whose parity fits the LDS-resident kernel run it in FP32 for both low precisions
-    bool lds = !fp64 && C->opt_blk_kernel == 0 && blk_lds_fits(g, C->lds_max);
+    bool lds = !fp64 && C->opt_blk_kernel == 0 && blk_lds_fits(g, C->lds_max), mr = !fp64;
     const bool h16 = prec == DDWC_MIXED16 && !lds;
     const size_t hw64 = (size_t)nrhs * 12 * n2;
     // the correction vector (slot 5) is kept in FP32 when the others are FP16
@@ -936,17 +939,16 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
         }
         if (imax >= maxit || nout >= 30) break;
         ++nout;
-        if (lds) {
-            // where a launch of the LDS-resident kernel (floor 2e-6) has left a block above 1e-2 of its last
-            // residual, with further than that to go, minimal residual converges too slowly there: BiCGStab
-            // for the rest
+        if (mr) {
+            // where a launch of a minimal-residual kernel (floor 2e-6, FP16 1e-3) has left a block above 1e-2 of
+            // its last residual, with further than that to go, it converges too slowly there: BiCGStab for the rest
             bool slow = false;
             for (size_t k = 0; k < was.size(); ++k) {
                 const double goal = tol * tol * hbb[k];
                 slow = slow || (hbb[k] > 0 && hrr[k] > goal && hrr[k] > 1e-4 * was[k] && was[k] > 1e4 * goal);
             }
             if (slow) {
-                lds = false;
+                mr = lds = false;
                 CK(slabs());
             }
             was = hrr;
@@ -957,12 +959,19 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
         } else if (lds) {
             const EoFields<float> F = eo_fields<float>(C);
             launch_blk_lds(ex, g, F, A32, re, xe, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
-        } else if (h16) {
-            const EoFields<H16> F = eo_fields<H16>(C);
-            launch_blk_inner<H16>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
         } else {
-            const EoFields<float> F = eo_fields<float>(C);
-            launch_blk_inner<float>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
+            auto inner = [&](auto F) {
+                typedef typename decltype(F)::storage S;
+                if (mr)
+                    launch_blk_mr<S>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs,
+                                     C->lds_max);
+                else
+                    launch_blk_inner<S>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
+            };
+            if (h16)
+                inner(eo_fields<H16>(C));
+            else
+                inner(eo_fields<float>(C));
         }
         launch_blk_resid(ex, g, F64, A64, bpe, xe, re, th, rr, mass4, colour, nrhs);
     }

@@ -6,10 +6,12 @@
 // H^k the hops inside block k.  Every kernel here runs one workgroup per (block, RHS); the
 // block's even and odd sites occupy the same contiguous range of the two half fields.
 //   k_blk_prep    FP64: b'_e, r_e = b'_e, x_e = 0, ||b_k||^2, ||r_e||^2
-//   k_blk_inner   persistent BiCGStab in precision R on M_k for r_e / ||r_e||, adds the
-//                 correction to x_e in FP64 (blocks already converged return at once)
+//   k_blk_lds, k_blk_mr   persistent minimal residual in FP32 (FP16 storage) on M_k for r_e / ||r_e||, adds
+//                 the correction to x_e in FP64 (blocks already converged return at once)
+//   k_blk_inner   the same by BiCGStab: FP64, and where minimal residual converges slowly
 //   k_blk_resid   FP64: r_e = b'_e - M_k x_e and ||r_e||^2 (defect correction)
 //   k_blk_recon   FP64: x_o, and (x_e, x_o) written to the full solution
+#include <algorithm>
 #include <type_traits>
 
 #include "ddwc_internal.h"
@@ -560,7 +562,7 @@ __device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own,
                                          cx<float> acc[12]) {
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = mk(0.f, 0.f);
-    PackedLinks pf(fresh(Uf), n2), pb(fresh(Ub), n2);
+    PackedLinks<float> pf(fresh(Uf), n2), pb(fresh(Ub), n2);
     cx<float> u[9];
     pf.next(reissue(own), u);
     // (opaque here, so that the sixteen addresses formed from nb are not kept across the iteration loop)
@@ -607,7 +609,7 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     // everything below is addressed from the block's first site
     re += oh;
     xe += oh;
-    const char *Ue = (const char*)F.W[0], *Uo = (const char*)F.W[1];
+    const char *Ue = F.W[0], *Uo = F.W[1];
     const float4 *Ke = F.K[0] + h0, *Ko = Ainv + h0;
     const BlkNbr ne = blk_nbr(F.nbr[0], n2, h0 + lg, h0, HV, act), no = blk_nbr(F.nbr[1], n2, h0 + lg, h0, HV, act);
     for (unsigned k = threadIdx.x; k < 2 * 8 * 16; k += blockDim.x) red_lds[0][k] = 0;
@@ -713,6 +715,247 @@ void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const floa
     k_blk_lds<<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6,
                                                         maxit < (1 << 30) ? 2 * maxit : maxit, iters, colour, nrhs);
 }
+
+// ------------------------------------------------------------------ minimal residual in global memory
+// The same iteration for blocks that do not fit k_blk_lds (8^4: 2048 sites of a parity) and for FP16
+// storage: one workgroup per (block, RHS), a few sites per thread.  The odd intermediate, t = M_k r and the
+// correction e are slabs; r is in LDS where it fits (8^4 in FP16: 107 KB), else a slab too.
+//
+// An in-block neighbour is the site's own half index shifted by half the stride of its direction
+// (along x3: by 0 or 1, by the parity of l3), so the hops of a site are one 16-bit mask: bit d set where
+// hop d stays in the block, bit 8 the parity of l3.  The masks of all blocks are the same and lie in LDS.
+//
+// What bounds it: vector-memory instructions.  BiCGStab on entry-major links issued about 286 a site and operator
+// application in FP16 (nine 4-byte loads a link, eight table entries, eleven vector accesses), this 140.  Per launch:
+// 8^4 in FP16, 64x32^3, 6 RHS, one colour 8110 -> 5554 us; in FP32, 32x16^3, 8 RHS 2640 -> 2060 us.
+constexpr int BM_MAX = 1024;
+
+// LDS records of a stored spinor: FP32 as k_blk_lds, FP16 three words per site and after them the scales.
+__device__ __forceinline__ void rec_load(float4* L, unsigned, unsigned l, cx<float> q[12], float) { lds_load(L, l, q); }
+__device__ __forceinline__ void rec_store(float4* L, unsigned, unsigned l, const cx<float> q[12], float) { lds_store(L, l, q); }
+__device__ __forceinline__ void rec_load(float4* L, unsigned HV, unsigned l, cx<float> q[12], H16) {
+    const h8v* p = (const h8v*)L + l * 3;
+    const float sc = ((const float*)(L + HV * 3))[l];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const h8v w = p[k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[4 * k + i] = mk(sc * (float)w[2 * i], sc * (float)w[2 * i + 1]);
+    }
+}
+__device__ __forceinline__ void rec_store(float4* L, unsigned HV, unsigned l, const cx<float> q[12], H16) {
+    h8v w[3];
+    ((float*)(L + HV * 3))[l] = to_half(q, w);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ((h8v*)L)[l * 3 + k] = w[k];
+}
+
+template <class S, bool RLDS>
+__global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const float4* Ainv, const double2* re,
+                                                   double2* xe, typename Traits<S>::word* rg,
+                                                   typename Traits<S>::word* tg, typename Traits<S>::word* wg, float4* eg,
+                                                   const double* __restrict__ bb, const double* __restrict__ rr,
+                                                   double mass4, double tol, double inner_floor, int maxit, int* iters,
+                                                   int colour, int nrhs) {
+    extern __shared__ float4 bm_lds[];
+    __shared__ double red_lds[2][8 * 16];
+    typedef typename std::conditional<std::is_same<S, H16>::value, f16, float>::type L;
+    const S tag{};
+    const BlkIdx k = blk_idx(g, colour, nrhs);
+    const double b2 = bb[k.key], r2 = rr[k.key];
+    if (!(b2 > 0) || !(r2 > tol * tol * b2) || !isfinite(r2)) return;  // uniform over the workgroup
+    const unsigned n2 = F.n2, HV = (unsigned)g.hvb, h0 = k.h0;
+    unsigned short* mask = (unsigned short*)bm_lds;  // [2][HV]
+    float4* rl = bm_lds + (2 * HV * sizeof(unsigned short) + 15) / 16;
+    for (unsigned q = threadIdx.x; q < 2 * HV; q += blockDim.x) {
+        // coordinates inside the block of the q-th site (parity-major)
+        const Site st = decode(g, (int)q);
+        unsigned m = (unsigned)(st.l[3] & 1) << 8;
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu)
+            m |= (unsigned)(st.l[mu] < g.b[mu] - 1) << (2 * mu) | (unsigned)(st.l[mu] > 0) << (2 * mu + 1);
+        mask[q] = (unsigned short)m;
+    }
+    for (unsigned q = threadIdx.x; q < 2 * 8 * 16; q += blockDim.x) red_lds[0][q] = 0;
+    const size_t oh = (size_t)k.rhs * 12 * n2, oR = (size_t)k.rhs * slab_words<S>(n2), oX = (size_t)k.rhs * 6 * n2;
+    re += oh;
+    xe += oh;
+    rg += oR;
+    tg += oR;
+    wg += oR;
+    eg += oX;
+    const unsigned sh[3] = {(unsigned)g.lstr[0] / 2, (unsigned)g.lstr[1] / 2, (unsigned)g.lstr[2] / 2};
+    // local half index of the neighbour in direction d of the site (l, mask m); itself for a hop that leaves
+    auto target = [&](unsigned l, unsigned m, int d) {
+        const unsigned up = (m >> 8) & 1;
+        const unsigned t = d < 6 ? ((d & 1) ? l - sh[d >> 1] : l + sh[d >> 1]) : d == 6 ? l + up : l - 1 + up;
+        return (m >> d) & 1 ? t : l;
+    };
+    auto none = [](int) { return false; };
+    // acc = in-block hops of the site l of parity p from the field that lq reads by local half index
+    auto hops = [&](int p, unsigned l, auto&& lq, cx<float> acc[12]) {
+        const unsigned m = mask[p * HV + l];
+        PackedLinks<L> pf(fresh(F.W[p]), n2), pb(fresh(F.W[1 - p]), n2);
+        hops_pipelined<float, false>(
+            acc, [&](int d, cx<float> q[12]) { lq(reissue(target(l, m, d)), q); },
+            [&](int d, cx<float> u[9]) {
+                if (d & 1)
+                    pb.next(byte_offset(h0 + reissue(target(l, m, d)), 16), u);
+                else
+                    pf.next(byte_offset(h0 + reissue(l), 16), u);
+            },
+            none, [&](int d) { return ((m >> d) & 1) != 0; });
+    };
+    auto load_r = [&](unsigned l, cx<float> q[12]) {
+        if constexpr (RLDS)
+            rec_load(rl, HV, l, q, tag);
+        else
+            uload_spinor(fresh(rg), n2, byte_offset(h0 + l, 16), q);
+    };
+    auto store_r = [&](unsigned l, const cx<float> q[12]) {
+        if constexpr (RLDS)
+            rec_store(rl, HV, l, q, tag);
+        else
+            ustore_spinor(fresh(rg), n2, byte_offset(h0 + l, 16), q);
+    };
+    const float m4 = (float)mass4;
+    const double rn = sqrt(r2), sc = 1.0 / rn;
+    double eps = 0.25 * tol * sqrt(b2) / rn;  // (as k_blk_lds)
+    if (eps < inner_floor) eps = inner_floor;
+    const int nl = (int)((HV + blockDim.x - 1) / blockDim.x);  // sites per thread
+    int phase = 0;
+    double red[4] = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int j = 0; j < nl; ++j) {
+        const unsigned li = j * blockDim.x + threadIdx.x, l = li < HV ? li : 0u;
+        const unsigned lo = byte_offset(h0 + l, 16);
+        cx<double> a[12];
+        uload_spinor(fresh(re), n2, lo, a);
+        cx<float> r[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) r[c] = mk((float)(sc * a[c].re), (float)(sc * a[c].im));
+        if (li < HV) {
+            const cx<float> z[12] = {};
+            store_r(l, r);
+            ustore_spinor(fresh(eg), n2, lo, z);
+            red[0] += acc_nrm(r);
+        }
+    }
+    __syncthreads();
+    wg_sums<1>(red, red_lds[phase ^= 1]);
+    const double thr2 = eps * eps * red[0];
+    double window = red[0];
+    int it = 0;
+    while (it < maxit) {
+        // w = A_oo^-1 H^k_oe r
+#pragma unroll 1
+        for (int j = 0; j < nl; ++j) {
+            const unsigned li = j * blockDim.x + threadIdx.x, l = li < HV ? li : 0u;
+            cx<float> acc[12], y[12];
+            hops(1, l, load_r, acc);
+            const unsigned lo = byte_offset(h0 + l, 16);
+            UDiag<float> K(fresh(Ainv), n2, lo);
+            K.first();
+#pragma unroll
+            for (int c = 0; c < 12; ++c) y[c] = mk(0.f, 0.f);
+            K.apply(0.f, acc, y, 0.f);
+            if (li < HV) ustore_spinor(fresh(wg), n2, lo, y);
+        }
+        __syncthreads();
+        // t = (4 + m + C) r - 1/4 H^k_eo w, (t, r), (t, t), (r, r)
+        red[0] = red[1] = red[2] = red[3] = 0;
+#pragma unroll 1
+        for (int j = 0; j < nl; ++j) {
+            const unsigned li = j * blockDim.x + threadIdx.x, l = li < HV ? li : 0u;
+            cx<float> t[12], r[12];
+            hops(0, l, [&](unsigned q, cx<float> v[12]) { uload_spinor(fresh(wg), n2, byte_offset(h0 + q, 16), v); }, t);
+            const unsigned lo = byte_offset(h0 + l, 16);
+            UDiag<float> K(fresh(F.K[0]), n2, lo);
+            K.first();
+            load_r(l, r);
+            K.apply(m4, r, t, -0.25f);
+            if (li < HV) {
+                ustore_spinor(fresh(tg), n2, lo, t);
+                acc_dot(t, r, red[0], red[1]);
+                red[2] += acc_nrm(t);
+                red[3] += acc_nrm(r);
+            }
+        }
+        wg_sums<4>(red, red_lds[phase ^= 1]);
+        ++it;
+        if (!(red[2] > 0)) break;
+        const cx<float> omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
+        const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
+        // e += omega r, r -= omega t
+#pragma unroll 1
+        for (int j = 0; j < nl; ++j) {
+            const unsigned li = j * blockDim.x + threadIdx.x, l = li < HV ? li : 0u;
+            const unsigned lo = byte_offset(h0 + l, 16);
+            cx<float> e[12], r[12], t[12];
+            uload_spinor(fresh(eg), n2, lo, e);
+            uload_spinor(fresh(tg), n2, lo, t);
+            load_r(l, r);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                cmadd(e[c], omega, r[c]);
+                cmadd(r[c], mk(-omega.re, -omega.im), t[c]);
+            }
+            if (li < HV) {
+                ustore_spinor(fresh(eg), n2, lo, e);
+                store_r(l, r);
+            }
+        }
+        if (!(r2n > thr2) || !isfinite(r2n)) break;
+        if (it % BL_WINDOW == 0) {
+            if (r2n > BL_GAIN * BL_GAIN * window) break;  // too slow: left to the caller
+            window = r2n;
+        }
+        __syncthreads();
+    }
+    // x_e += ||r_e|| e in FP64
+#pragma unroll 1
+    for (int j = 0; j < nl; ++j) {
+        const unsigned li = j * blockDim.x + threadIdx.x, l = li < HV ? li : 0u;
+        const unsigned lo = byte_offset(h0 + l, 16);
+        cx<float> e[12];
+        cx<double> x[12];
+        uload_spinor(fresh(eg), n2, lo, e);
+        uload_spinor(fresh(xe), n2, lo, x);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) x[c] = x[c] + mk(rn * (double)e[c].re, rn * (double)e[c].im);
+        if (li < HV) ustore_spinor(fresh(xe), n2, lo, x);
+    }
+    if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
+}
+
+template <class S>
+void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* Ainv, const double2* re, double2* xe,
+                   void* const w[7], const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
+                   int colour, int nrhs, int lds_max) {
+    Timed t(e, 2, 0);
+    typedef typename Traits<S>::word W;
+    const int threads = block_threads_for(g, e.blk_threads, BM_MAX);
+    const size_t masks = ((size_t)2 * g.hvb * sizeof(unsigned short) + 15) / 16 * 16;
+    const size_t recs = (size_t)g.hvb * (std::is_same<S, H16>::value ? 52 : 96);
+    const bool rlds = masks + recs + 2 * 8 * 16 * 8 <= (size_t)lds_max;
+    const size_t lds = std::max(rlds ? masks + recs : masks, std::min((size_t)e.blk_lds << 10, (size_t)lds_max - 2 * 8 * 16 * 8));
+    const double floor_eps = std::is_same<S, H16>::value ? 1e-3 : 2e-6;
+    const int steps = maxit < (1 << 30) ? 2 * maxit : maxit;
+    if (rlds)
+        k_blk_mr<S, true><<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (W*)w[0], (W*)w[4], (W*)w[6],
+                                                                    (float4*)w[5], bb, rr, mass4, tol, floor_eps, steps,
+                                                                    iters, colour, nrhs);
+    else
+        k_blk_mr<S, false><<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (W*)w[0], (W*)w[4], (W*)w[6],
+                                                                     (float4*)w[5], bb, rr, mass4, tol, floor_eps, steps,
+                                                                     iters, colour, nrhs);
+}
+template void launch_blk_mr<float>(Exec&, const Geom&, const EoFields<float>&, const float4*, const double2*, double2*,
+                                   void* const[7], const double*, const double*, double, double, int, int*, int, int,
+                                   int);
+template void launch_blk_mr<H16>(Exec&, const Geom&, const EoFields<H16>&, const float4*, const double2*, double2*,
+                                 void* const[7], const double*, const double*, double, double, int, int*, int, int,
+                                 int);
 
 void launch_blk_prep(Exec& e, const Geom& g, const EoFields<double>& F, const double2* Ainv, const double2* b,
                      double2* bpe, double2* re, double2* xe, double2* to, double* bb, double* rr, int colour, int nrhs) {

@@ -78,7 +78,10 @@ struct Timed {
 constexpr int WG = 256;  // sites per workgroup of the site-parallel kernels
 constexpr int DW = 64;   // sites per workgroup of the full-lattice operator
 constexpr int NPART = 8; // doubles per partial-sum slot
-constexpr unsigned PACKED_LINK_BYTES = 72;  // one packed FP32 link (nine complex entries)
+template <class L>
+constexpr unsigned packed_link_bytes() {  // one packed link (nine complex entries of storage L)
+    return 9 * 2 * sizeof(L);
+}
 
 inline int tiles_of(int n) { return (n + WG - 1) / WG; }
 
@@ -211,11 +214,12 @@ void blas_handle_destroy(void* h);
 // Half-field data of one precision: links, clover and neighbour table of each parity.
 template <class R>
 struct EoFields {
+    typedef R storage;
     unsigned n2;                                        // V / 2
     const cx<typename Traits<R>::link>* U[2];           // [4][9][n2] links of the sites of parity p
     const typename Traits<R>::kword* K[2];              // clover of the sites of parity p
     const int* nbr[2];                                  // [8][n2] neighbour half indices (other parity)
-    const void* W[2] = {nullptr, nullptr};              // packed FP32 links (uniform_mem.h) of parity p (FP32 only)
+    const char* W[2] = {nullptr, nullptr};              // packed links (uniform_mem.h) of parity p (FP32, FP16)
     int op_threads = WG;                                // workgroup size of the RHS-innermost operator kernels
     const int* order = nullptr;                         // their tile dispatch order (null: index order)
 };
@@ -242,8 +246,9 @@ void launch_eo_setup(Exec& e, const Geom& g, const cx<double>* U64, const double
 // Own-site link records [2][V/2][8][9] (LK_OWN) read by the RHS-innermost kernels of the global
 // solver, from Uh32 and the half-field neighbour tables.
 void launch_eo_links_own(Exec& e, unsigned n2, const cx<float>* Uh32, const int* nbr_eo, cx<float>* Lown);
-// Packed FP32 links [2][4]{[4][V/2] float4, [V/2] float2} read by the LDS-resident block solver, from Uh32.
-void launch_eo_links_packed(Exec& e, unsigned n2, const cx<float>* Uh32, void* W);
+// Packed links (uniform_mem.h) [2][4][V/2] read by the block solvers, from the entry-major Uh.
+template <class L>
+void launch_eo_links_packed(Exec& e, unsigned n2, const cx<L>* Uh, void* W);
 void launch_eo_inverse(Exec& e, unsigned V2, const double2* Kp, double mass4, double2* A64, float4* A32);
 void launch_eo_split(Exec& e, const Geom& g, const double2* full, double2* he, double2* ho, int nrhs);
 void launch_eo_merge(Exec& e, const Geom& g, const double2* he, const double2* ho, double2* full, int nrhs,
@@ -268,6 +273,12 @@ void launch_blk_resid(Exec& e, const Geom& g, const EoFields<double>& F, const d
                       const double2* xe, double2* re, double2* to, double* rr, double mass4, int colour, int nrhs);
 void launch_blk_recon(Exec& e, const Geom& g, const double2* to, const double2* th, const double2* xe, double2* x,
                       int colour, int nrhs);
+// Minimal residual with its vectors in global memory (slots 0, 4, 5, 6; r in LDS where it fits), for FP32
+// and FP16 on blocks that the LDS-resident solver does not take.
+template <class S>
+void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* Ainv, const double2* re, double2* xe,
+                   void* const w[7], const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
+                   int colour, int nrhs, int lds_max);
 template <class S>
 void launch_blk_inner(Exec& e, const Geom& g, const EoFields<S>& F, const typename Traits<S>::kword* Ainv,
                       const double2* re, double2* xe, void* const w[7], const double* bb, const double* rr,

@@ -61,26 +61,27 @@ void launch_links_to_half(Exec& e, size_t n, const cx<float>* src, cx<f16>* dst)
     k_links_to_half<<<(unsigned)((n + 255) / 256), 256, 0, e.stream>>>(n, src, dst);
 }
 
-// Packed copy of the entry-major half links (setup): link (p, mu) of the n2 sites is four planes of
-// float4 (entries 2 k, 2 k + 1) and one of float2 (entry 8).
-__global__ void k_links_packed(unsigned n2, const cx<float>* __restrict__ Uh, char* __restrict__ W) {
+// Packed copy of the entry-major half links (setup): link (p, mu) of the n2 sites is planes of 16-byte words
+// (FP32 two, FP16 four entries each) and one plane of its last entry.
+template <class L>
+__global__ void k_links_packed(unsigned n2, const cx<L>* __restrict__ Uh, char* __restrict__ W) {
     const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n2) return;
-    const cx<float>* u = Uh + (size_t)blockIdx.y * 9 * n2 + i;  // blockIdx.y = 4 p + mu
-    char* w = W + (size_t)blockIdx.y * PACKED_LINK_BYTES * n2;
+    constexpr int PW = 16 / sizeof(cx<L>), NW = 8 / PW;
+    const cx<L>* u = Uh + (size_t)blockIdx.y * 9 * n2 + i;  // blockIdx.y = 4 p + mu
+    char* w = W + (size_t)blockIdx.y * packed_link_bytes<L>() * n2;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const cx<float> a = u[(size_t)(2 * k) * n2], b = u[(size_t)(2 * k + 1) * n2];
-        ((float4*)w)[(size_t)k * n2 + i] = make_float4(a.re, a.im, b.re, b.im);
-    }
-    const cx<float> a = u[(size_t)8 * n2];
-    ((float2*)(w + (size_t)64 * n2))[i] = make_float2(a.re, a.im);
+    for (int k = 0; k < 8; ++k) ((cx<L>*)w)[((size_t)(k / PW) * n2 + i) * PW + k % PW] = u[(size_t)k * n2];
+    ((cx<L>*)(w + (size_t)16 * NW * n2))[i] = u[(size_t)8 * n2];
 }
 
-void launch_eo_links_packed(Exec& e, unsigned n2, const cx<float>* Uh32, void* W) {
+template <class L>
+void launch_eo_links_packed(Exec& e, unsigned n2, const cx<L>* Uh, void* W) {
     Timed t(e, 4, 0);
-    k_links_packed<<<dim3((n2 + 255) / 256, 8), 256, 0, e.stream>>>(n2, Uh32, (char*)W);
+    k_links_packed<L><<<dim3((n2 + 255) / 256, 8), 256, 0, e.stream>>>(n2, Uh, (char*)W);
 }
+template void launch_eo_links_packed<float>(Exec&, unsigned, const cx<float>*, void*);
+template void launch_eo_links_packed<f16>(Exec&, unsigned, const cx<f16>*, void*);
 
 // A_pp^-1 for the sites of parity p of half clover Kp (once per mass).
 __global__ void k_eo_inverse(unsigned V2, const double2* __restrict__ Kp, double mass4, double2* __restrict__ A64,

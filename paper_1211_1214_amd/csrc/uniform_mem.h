@@ -116,9 +116,9 @@ __device__ __forceinline__ void uload_spinor(const double2* f, unsigned n, unsig
         p[c] = mk(w.x, w.y);
     }
 }
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 // FP16 storage: three word planes and a plane of scales (ddwc_device.h)
 __device__ __forceinline__ void uload_spinor(const hw16* f, unsigned n, unsigned off, cx<float> p[12]) {
-    typedef _Float16 h8v __attribute__((ext_vector_type(8)));
     Planes q(f, n);
     h8v w[3];
 #pragma unroll
@@ -128,6 +128,29 @@ __device__ __forceinline__ void uload_spinor(const hw16* f, unsigned n, unsigned
     const float sc = q.load<float>(o4);
 #pragma unroll
     for (int k = 0; k < 12; ++k) p[k] = mk(sc * (float)w[k >> 2][2 * (k & 3)], sc * (float)w[k >> 2][2 * (k & 3) + 1]);
+}
+// p as FP16 halves of multiples of its largest component modulus (returned)
+__device__ __forceinline__ float to_half(const cx<float> p[12], h8v w[3]) {
+    float m = 0.f;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) m = fmaxf(m, fmaxf(fabsf(p[c].re), fabsf(p[c].im)));
+    const float inv = m > 0.f ? 1.f / m : 0.f;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        w[c >> 2][2 * (c & 3)] = (_Float16)(inv * p[c].re);
+        w[c >> 2][2 * (c & 3) + 1] = (_Float16)(inv * p[c].im);
+    }
+    return m;
+}
+__device__ __forceinline__ void ustore_spinor(hw16* f, unsigned n, unsigned off, const cx<float> p[12]) {
+    h8v w[3];
+    const float m = to_half(p, w);
+    Planes q(f, n);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q.store<h8v>(off, w[k]);
+    unsigned o4 = off >> 2;
+    asm("" : "+v"(o4));
+    q.store<float>(o4, m);
 }
 __device__ __forceinline__ void ustore_spinor(float4* f, unsigned n, unsigned off, const cx<float> p[12]) {
     Planes q(f, n);
@@ -141,6 +164,13 @@ __device__ __forceinline__ void ustore_spinor(double2* f, unsigned n, unsigned o
     for (int c = 0; c < 12; ++c) q.store<d2v>(off, (d2v){p[c].re, p[c].im});
 }
 
+__device__ __forceinline__ void ustore_spinor_nt(float4* f, unsigned n, unsigned off, const cx<float> p[12]) {
+    Planes q(f, n);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        q.store_nt<f4v>(off, (f4v){p[2 * k].re, p[2 * k].im, p[2 * k + 1].re, p[2 * k + 1].im});
+}
+
 // The next link of a walk over entry-major links [4][9][n] (nine planes), of the site at byte offset off.
 template <class R>
 __device__ __forceinline__ void uload_link(Planes& q, unsigned off, cx<R> u[9]) {
@@ -151,37 +181,34 @@ __device__ __forceinline__ void uload_link(Planes& q, unsigned off, cx<R> u[9]) 
     }
 }
 
-// Packed FP32 links: per direction four planes of 16-byte words (entries 0 .. 7, two a word) and one
-// plane of 8-byte words (entry 8), n elements each: five loads per link instead of nine.
+// Packed links: per direction planes of 16-byte words (FP32: four planes of two entries, FP16: two of four)
+// and one plane of the last entry, n elements each: five (three) loads per link instead of nine.
+template <class L>
 struct PackedLinks {
     Planes::gptr p;
     unsigned long long n16;
     __device__ __forceinline__ PackedLinks(const char* U, unsigned n) : p((Planes::gptr)(unsigned long long)U), n16(16ull * n) {}
     // the link of the next direction of the site at byte offset off16 (its index times 16)
     __device__ __forceinline__ void next(unsigned off16, cx<float> u[9]) {
+        constexpr int PW = 16 / sizeof(cx<L>), NW = 8 / PW;
+        typedef L wv __attribute__((ext_vector_type(2 * PW)));
+        typedef L ev __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NW; ++k) {
             asm("" : "+s"(p));
-            const f4v w = *(const __attribute__((address_space(1))) f4v*)(p + off16);
-            u[2 * k] = mk(w.x, w.y);
-            u[2 * k + 1] = mk(w.z, w.w);
+            const wv w = *(const __attribute__((address_space(1))) wv*)(p + off16);
+#pragma unroll
+            for (int i = 0; i < PW; ++i) u[PW * k + i] = mk((float)w[2 * i], (float)w[2 * i + 1]);
             p += n16;
         }
-        unsigned off8 = off16 >> 1;
-        asm("" : "+v"(off8));
+        unsigned oe = off16 / PW;
+        asm("" : "+v"(oe));
         asm("" : "+s"(p));
-        const f2v w = *(const __attribute__((address_space(1))) f2v*)(p + off8);
-        u[8] = mk(w.x, w.y);
-        p += n16 >> 1;
+        const ev w = *(const __attribute__((address_space(1))) ev*)(p + oe);
+        u[8] = mk((float)w.x, (float)w.y);
+        p += n16 / PW;
     }
 };
-
-__device__ __forceinline__ void ustore_spinor_nt(float4* f, unsigned n, unsigned off, const cx<float> p[12]) {
-    Planes q(f, n);
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-        q.store_nt<f4v>(off, (f4v){p[2 * k].re, p[2 * k].im, p[2 * k + 1].re, p[2 * k + 1].im});
-}
 
 // The packed Hermitian 6x6 blocks K [NKW][n] of one site, loaded in two parts: the diagonals and the
 // first block's off-diagonal reals, then the second block's (which start inside the last word of the

@@ -1657,6 +1657,19 @@ static int redots(ddwc_ctx* C, Exec& ex, const double2* x, const double2* y, int
     return DDWC_OK;
 }
 
+// The force accumulators, cleared: G and, with a clover term, its outer products L (else null).
+static int force_buffers(ddwc_ctx* C, Exec& ex, cx<double>** G, cx<double>** L) {
+    const size_t V = C->g.V;
+    *L = nullptr;
+    CK(ws_t(C, "gr_force", 36 * V, G));
+    HC(hipMemsetAsync(*G, 0, 36 * V * sizeof(cx<double>), ex.stream));
+    if (C->csw != 0.0) {
+        CK(ws_t(C, "gr_outer", 54 * V, L));
+        HC(hipMemsetAsync(*L, 0, 54 * V * sizeof(cx<double>), ex.stream));
+    }
+    return DDWC_OK;
+}
+
 // Gradient of L = sum_ij gx_ij x_ij (x_ij the two-flavour exponents of ddwc_det_ratio_estimate)
 // with respect to kappa2 and the links.  With y = M eta and z = D_n^-+ y (full M; D^+ = g5 D g5)
 // or z = Dhat_n^-+ y (Schur):  dx = 2 Re <z, dD_p eta> - 2 Re <z, dD_n y>, and for the Schur
@@ -1687,17 +1700,14 @@ extern "C" int ddwc_det_ratio_grad(ddwc_ctx* C, double kappa1, double kappa2, in
                           "gr_W2n", "gr_Y5", "gr_Zh", "gr_Ap", "gr_Cp", "gr_An", "gr_Cn", "gr_B"};
     double2** vp[17] = {&E, &A, &W1, &W12, &A1, &Gs, &Z, &Y, &W1n, &W2n, &Y5, &Zh, &Ap, &Cp, &An, &Cn, &B};
     for (int k = 0; k < 17; ++k) CK(ws_t(C, nm[k], nw, vp[k]));
-    cx<double>* Gd = nullptr;
+    cx<double>*Gd = nullptr, *Ld = nullptr;
     double* wd;
     CK(ws_t(C, "gr_w", (size_t)nrhs, &wd));
-    if (dU) {
-        CK(ws_t(C, "gr_force", (size_t)36 * g.V, &Gd));
-        HC(hipMemsetAsync(Gd, 0, (size_t)36 * g.V * sizeof(cx<double>), ex.stream));
-    }
+    if (dU) CK(force_buffers(C, ex, &Gd, &Ld));
     auto force = [&](const double2* a, const double2* b, const std::vector<double>& w) -> int {
         HC(hipMemcpyAsync(wd, w.data(), sizeof(double) * nrhs, hipMemcpyHostToDevice, ex.stream));
         launch_force_hop(ex, g, C->nbr, a, b, wd, nrhs, Gd);
-        if (C->csw != 0.0) launch_force_clover(ex, g, C->U64, C->csw, a, b, wd, nrhs, Gd);
+        if (Ld) launch_force_outer(ex, g, a, b, wd, nrhs, Ld);
         HC(hipStreamSynchronize(ex.stream));
         return DDWC_OK;
     };
@@ -1792,6 +1802,7 @@ extern "C" int ddwc_det_ratio_grad(ddwc_ctx* C, double kappa1, double kappa2, in
         for (int j = 0; j < nrhs; ++j) dLdm2 += gi[j] * (dp[j] * fp + dn[j] * fn);
     }
     if (dkappa2) *dkappa2 = dLdm2 * (-0.5 / (kappa2 * kappa2));
+    if (Ld) launch_force_clover(ex, g, C->nbr, C->U64, C->csw, Ld, Gd);
     if (dU) launch_links_export(ex, g, Gd, dU);
     HC(hipStreamSynchronize(ex.stream));
     HC(hipGetLastError());
@@ -1811,17 +1822,19 @@ extern "C" int ddwc_link_force(ddwc_ctx* C, const void* a, const void* b, int nr
     const Geom& g = C->g;
     double2 *ai, *bi;
     double* wd;
-    cx<double>* Gd;
+    cx<double>*Gd, *Ld;
     CK(ws_t(C, "api_a", vec_words(C, nrhs, true), &ai));
     CK(ws_t(C, "api_b", vec_words(C, nrhs, true), &bi));
     CK(ws_t(C, "gr_w", (size_t)nrhs, &wd));
-    CK(ws_t(C, "gr_force", (size_t)36 * g.V, &Gd));
+    CK(force_buffers(C, ex, &Gd, &Ld));
     launch_import<double>(ex, g, a, ai, nrhs, MASK_ALL);
     launch_import<double>(ex, g, b, bi, nrhs, MASK_ALL);
     HC(hipMemcpyAsync(wd, w_host, sizeof(double) * nrhs, hipMemcpyHostToDevice, ex.stream));
-    HC(hipMemsetAsync(Gd, 0, (size_t)36 * g.V * sizeof(cx<double>), ex.stream));
     launch_force_hop(ex, g, C->nbr, ai, bi, wd, nrhs, Gd);
-    if (C->csw != 0.0) launch_force_clover(ex, g, C->U64, C->csw, ai, bi, wd, nrhs, Gd);
+    if (Ld) {
+        launch_force_outer(ex, g, ai, bi, wd, nrhs, Ld);
+        launch_force_clover(ex, g, C->nbr, C->U64, C->csw, Ld, Gd);
+    }
     launch_links_export(ex, g, Gd, dU);
     HC(hipStreamSynchronize(ex.stream));
     HC(hipGetLastError());

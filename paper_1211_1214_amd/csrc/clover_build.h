@@ -18,16 +18,21 @@ struct M3 {
     cx<double> a[9];
 };
 
+// (Unrolled: a run-time index into a matrix would put it in scratch memory.)
 DDWC_HD M3 ld(const cx<double>* U, const Geom& g, int mu, int s) {
     M3 m;
+#pragma unroll
     for (int k = 0; k < 9; ++k) m.a[k] = U[((size_t)mu * 9 + k) * g.V + s];
     return m;
 }
 DDWC_HD M3 mul(const M3& x, const M3& y) {
     M3 z;
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
         for (int j = 0; j < 3; ++j) {
             cx<double> t = mk(0.0, 0.0);
+#pragma unroll
             for (int k = 0; k < 3; ++k) t = t + x.a[3 * i + k] * y.a[3 * k + j];
             z.a[3 * i + j] = t;
         }
@@ -35,8 +40,16 @@ DDWC_HD M3 mul(const M3& x, const M3& y) {
 }
 DDWC_HD M3 dag(const M3& x) {
     M3 z;
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
         for (int j = 0; j < 3; ++j) z.a[3 * i + j] = mk(x.a[3 * j + i].re, -x.a[3 * j + i].im);
+    return z;
+}
+DDWC_HD M3 add(const M3& x, const M3& y) {
+    M3 z;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) z.a[k] = x.a[k] + y.a[k];
     return z;
 }
 
@@ -50,7 +63,9 @@ DDWC_HD M3 field_strength(const Geom& g, const cx<double>* U, int s, int mu, int
     M3 q3 = mul(mul(dag(ld(U, g, mu, xmm)), dag(ld(U, g, nu, xmm_mn))), mul(ld(U, g, mu, xmm_mn), ld(U, g, nu, xmn)));
     M3 q4 = mul(mul(dag(ld(U, g, nu, xmn)), ld(U, g, mu, xmn)), mul(ld(U, g, nu, xpm_mn), dag(ld(U, g, mu, s))));
     M3 F;
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
         for (int j = 0; j < 3; ++j) {
             cx<double> q = q1.a[3 * i + j] + q2.a[3 * i + j] + q3.a[3 * i + j] + q4.a[3 * i + j];
             cx<double> qt = q1.a[3 * j + i] + q2.a[3 * j + i] + q3.a[3 * j + i] + q4.a[3 * j + i];

@@ -190,12 +190,15 @@ void launch_dots(Exec& e, const Geom& g, const double2* x, const double2* y, dou
 // ------------------------------------------------------------------ derivatives (grad.hip)
 // v <- gamma_5 v (negates spins 2, 3), in place, FP64 internal fields.
 void launch_gamma5(Exec& e, const Geom& g, double2* v, int nrhs);
-// G += d/dU sum_r w_r Re <a_r, D b_r>: the hop part (force_hop) and the clover part
-// (force_clover, atomic adds).  G internal [4][9][V]; w device array [nrhs].
+// G += d/dU sum_r w_r Re <a_r, D b_r>: the hop part (G internal [4][9][V]; w device array [nrhs]), and the
+// clover part, which is linear in outer products: accumulate those of every pair of fields in Lacc
+// (internal [6][9][V], zero at first), then add the clover part of them all once (Lacc is overwritten).
 void launch_force_hop(Exec& e, const Geom& g, const int* nbr, const double2* a, const double2* b, const double* w,
                       int nrhs, cx<double>* G);
-void launch_force_clover(Exec& e, const Geom& g, const cx<double>* U, double csw, const double2* a, const double2* b,
-                         const double* w, int nrhs, cx<double>* G);
+void launch_force_outer(Exec& e, const Geom& g, const double2* a, const double2* b, const double* w, int nrhs,
+                        cx<double>* Lacc);
+void launch_force_clover(Exec& e, const Geom& g, const int* nbr, const cx<double>* U, double csw, cx<double>* Lacc,
+                         cx<double>* G);
 // internal link-shaped field -> canonical [4][V][3][3] complex128
 void launch_links_export(Exec& e, const Geom& g, const cx<double>* G, void* canon);
 

@@ -5,30 +5,6 @@
 
 namespace ddwc {
 
-// (1 + sgn g_mu) q on the 4 x 3 spinor q[spin * 3 + colour], MU fixed at compile time:
-//   g_0 q = (-q_l, -q_u),  g_k q = (-i s_k q_l, i s_k q_u)  (u = spins 0,1; l = spins 2,3).
-template <int MU>
-DDWC_HD void proj(double sgn, const cx<double> q[12], cx<double> o[12]) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const cx<double> u0 = q[a], u1 = q[3 + a], l0 = q[6 + a], l1 = q[9 + a];
-        cx<double> g0, g1, g2, g3;  // gamma_mu q, spins 0..3
-        if (MU == 0) {
-            g0 = -l0; g1 = -l1; g2 = -u0; g3 = -u1;
-        } else if (MU == 1) {  // s_1 = [[0,1],[1,0]]
-            g0 = times_mi(l1); g1 = times_mi(l0); g2 = times_i(u1); g3 = times_i(u0);
-        } else if (MU == 2) {  // s_2 = [[0,-i],[i,0]]:  -i s_2 (l0,l1) = (-l1, l0), i s_2 (u0,u1) = (u1, -u0)
-            g0 = -l1; g1 = l0; g2 = u1; g3 = -u0;
-        } else {  // s_3 = diag(1,-1)
-            g0 = times_mi(l0); g1 = times_i(l1); g2 = times_i(u0); g3 = times_mi(u1);
-        }
-        o[a] = u0 + sgn * g0;
-        o[3 + a] = u1 + sgn * g1;
-        o[6 + a] = l0 + sgn * g2;
-        o[9 + a] = l1 + sgn * g3;
-    }
-}
-
 DDWC_HD void ld12(const double2* f, unsigned V, unsigned s, cx<double> p[12]) {
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
@@ -37,7 +13,9 @@ DDWC_HD void ld12(const double2* f, unsigned V, unsigned s, cx<double> p[12]) {
     }
 }
 
-// Hop part of the gradient of sum_r w_r Re <a_r, D b_r> at link (x = s, MU), added to G.
+// Hop part of the gradient of sum_r w_r Re <a_r, D b_r> at link (x = s, MU), added to G.  The projectors satisfy
+// (1 -+ g)^2 = 2 (1 -+ g) and the lower components of a projected spinor repeat the upper ones up to a phase, so
+// the four-spin outer products are outer products of the two half spinors (half_proj).
 template <int MU>
 DDWC_HD void force_hop_site_t(const Geom& g, const int* nbr, const double2* a, const double2* b, const double* w,
                               int nrhs, cx<double>* G, unsigned s) {
@@ -47,33 +25,33 @@ DDWC_HD void force_hop_site_t(const Geom& g, const int* nbr, const double2* a, c
     cx<double> acc[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[k] = mk(0.0, 0.0);
+    // acc += f h_left h_right^+, summed over the two half spins
+    auto outer = [&](double f, const cx<double> hl[6], const cx<double> hr[6]) {
+#pragma unroll
+        for (int al = 0; al < 2; ++al)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const cx<double> x = f * hl[3 * al + i];
+#pragma unroll
+                for (int j = 0; j < 3; ++j) cjmadd(acc[3 * i + j], hr[3 * al + j], x);
+            }
+    };
     for (int r = 0; r < nrhs; ++r) {
         const double wr = w[r];
         if (wr == 0.0) continue;
         const double2* ar = a + (size_t)r * 12 * g.V;
         const double2* br = b + (size_t)r * 12 * g.V;
-        cx<double> as[12], bs[12], pb[12], pa[12];
-        {
-            cx<double> q[12];
-            ld12(br, g.V, t, q);
-            proj<MU>(-1.0, q, pb);  // (1 - g_mu) b(x + mu)
-            ld12(ar, g.V, t, q);
-            proj<MU>(+1.0, q, pa);  // (1 + g_mu) a(x + mu)
-        }
-        ld12(ar, g.V, s, as);
-        ld12(br, g.V, s, bs);
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                cx<double> z = mk(0.0, 0.0);
-#pragma unroll
-                for (int al = 0; al < 4; ++al) {
-                    z = z + as[3 * al + i] * mk(pb[3 * al + j].re, -pb[3 * al + j].im);
-                    z = z + bs[3 * al + i] * mk(pa[3 * al + j].re, -pa[3 * al + j].im);
-                }
-                acc[3 * i + j] = acc[3 * i + j] + (-0.5 * sg * wr) * z;
-            }
+        cx<double> q[12], hl[6], hr[6];
+        ld12(ar, g.V, s, q);
+        half_proj<double, MU, +1>(q, hl);
+        ld12(br, g.V, t, q);
+        half_proj<double, MU, +1>(q, hr);  // a(x) ((1 - g_mu) b(x + mu))^+
+        outer(-0.5 * sg * wr, hl, hr);
+        ld12(br, g.V, s, q);
+        half_proj<double, MU, -1>(q, hl);
+        ld12(ar, g.V, t, q);
+        half_proj<double, MU, -1>(q, hr);  // b(x) ((1 + g_mu) a(x + mu))^+
+        outer(-0.5 * sg * wr, hl, hr);
     }
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
@@ -92,84 +70,157 @@ DDWC_HD void force_hop_site(const Geom& g, const int* nbr, const double2* a, con
     }
 }
 
-// Clover part of the gradient of sum_r w_r Re <a_r, D b_r> from the clover term at site y:
-// add(dir, site, Z) receives the contribution Z to the gradient of link (site, dir).
-template <class ADD>
-DDWC_HD void force_clover_site(const Geom& g, const cx<double>* U, double csw, const double2* a, const double2* b,
-                               const double* w, int nrhs, int y, const ADD& add) {
-    // L[k][l]: chiral block k, Pauli matrix l + 1
-    M3 L[2][3];
-    for (int k = 0; k < 2; ++k)
-        for (int l = 0; l < 3; ++l)
-            for (int q = 0; q < 9; ++q) L[k][l].a[q] = mk(0.0, 0.0);
+// Clover part.  Its ingredients at one site: L[l], the colour matrices of Pauli index l + 1 and chiral block k,
+// (L_l)_{ba} = sum_{alpha beta} (s_l)_{alpha beta} b_{beta b} conj(a_{alpha a}), summed over the RHS with their weights.
+DDWC_HD void force_outer(const double2* a, const double2* b, const double* w, int nrhs, unsigned V, unsigned y, int k,
+                         M3 L[3]) {
+    cx<double> t01[9], t10[9], td[9];  // b_1 conj(a_0), b_0 conj(a_1), b_0 conj(a_0) - b_1 conj(a_1)
+#pragma unroll
+    for (int q = 0; q < 9; ++q) t01[q] = t10[q] = td[q] = mk(0.0, 0.0);
     for (int r = 0; r < nrhs; ++r) {
         const double wr = w[r];
         if (wr == 0.0) continue;
-        cx<double> av[12], bv[12];
-        ld12(a + (size_t)r * 12 * g.V, g.V, y, av);
-        ld12(b + (size_t)r * 12 * g.V, g.V, y, bv);
-        for (int k = 0; k < 2; ++k) {
-            const cx<double>* a0 = av + 6 * k;  // spin 2k, colours 0..2
-            const cx<double>* a1 = av + 6 * k + 3;
-            const cx<double>* b0 = bv + 6 * k;
-            const cx<double>* b1 = bv + 6 * k + 3;
-            for (int bb = 0; bb < 3; ++bb)
-                for (int aa = 0; aa < 3; ++aa) {
-                    // (L_l)_{bb aa} = sum_{al be} (s_l)_{al be} b_{be bb} conj(a_{al aa})
-                    const cx<double> ca0 = mk(a0[aa].re, -a0[aa].im), ca1 = mk(a1[aa].re, -a1[aa].im);
-                    const cx<double> t01 = b1[bb] * ca0;  // (al, be) = (0, 1)
-                    const cx<double> t10 = b0[bb] * ca1;  // (1, 0)
-                    const cx<double> t00 = b0[bb] * ca0;
-                    const cx<double> t11 = b1[bb] * ca1;
-                    const int q = 3 * bb + aa;
-                    L[k][0].a[q] = L[k][0].a[q] + wr * (t01 + t10);
-                    L[k][1].a[q] = L[k][1].a[q] + wr * (times_mi(t01) + times_i(t10));
-                    L[k][2].a[q] = L[k][2].a[q] + wr * (t00 - t11);
-                }
+        const double2* ar = a + ((size_t)r * 12 + 6 * k) * V + y;
+        const double2* br = b + ((size_t)r * 12 + 6 * k) * V + y;
+        cx<double> av[6], bv[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            const double2 p = ar[(size_t)c * V], q = br[(size_t)c * V];
+            av[c] = mk(p.x, p.y);
+            bv[c] = mk(wr * q.x, wr * q.y);
         }
+#pragma unroll
+        for (int bb = 0; bb < 3; ++bb)
+#pragma unroll
+            for (int aa = 0; aa < 3; ++aa) {
+                const int q = 3 * bb + aa;
+                cjmadd(t01[q], av[aa], bv[3 + bb]);
+                cjmadd(t10[q], av[3 + aa], bv[bb]);
+                cjmadd(td[q], av[aa], bv[bb]);
+                cjmadd(td[q], av[3 + aa], -bv[3 + bb]);
+            }
     }
-    // planes (0,1) (0,2) (0,3) (1,2) (1,3) (2,3): Pauli index and block coefficients of K
-    const int pm[6] = {0, 0, 0, 1, 1, 2}, pn[6] = {1, 2, 3, 2, 3, 3};
-    const int pl[6] = {0, 1, 2, 2, 1, 0};
-    const double s0[6] = {1, 1, 1, -1, 1, -1};
-    const double s1[6] = {-1, -1, -1, -1, 1, -1};
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        L[0].a[q] = t01[q] + t10[q];
+        L[1].a[q] = times_mi(t01[q]) + times_i(t10[q]);
+        L[2].a[q] = td[q];
+    }
+}
+
+// The planes (0, l + 1) and (j, k) with l + 1 their Pauli index, l = 0 (2,3), 1 (1,3), 2 (1,2), from L0, L1 of the two chiral
+// blocks: J = (K - K^+)/8, K = (i c_sw / 2) times the signed sum of clover_build.h.  Slot of a plane: l for (0, l + 1),
+// 3 + l for the other.
+DDWC_HD void force_planes(const M3& L0, const M3& L1, int l, double csw, M3& Ja, M3& Jb) {
     const cx<double> ic2 = mk(0.0, 0.5 * csw);
-    for (int pq = 0; pq < 6; ++pq) {
-        const int mu = pm[pq], nu = pn[pq];
-        M3 J;
-        {
-            M3 K;
-            for (int q = 0; q < 9; ++q) K.a[q] = ic2 * (s0[pq] * L[0][pl[pq]].a[q] + s1[pq] * L[1][pl[pq]].a[q]);
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j) {
-                    const cx<double> kij = K.a[3 * i + j], kji = K.a[3 * j + i];
-                    J.a[3 * i + j] = mk((kij.re - kji.re) / 8.0, (kij.im + kji.im) / 8.0);
-                }
+    const double sb = l == 1 ? 1.0 : -1.0;
+    M3 Ka, Kb;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        Ka.a[q] = ic2 * (L0.a[q] - L1.a[q]);
+        Kb.a[q] = ic2 * (sb * (L0.a[q] + L1.a[q]));
+    }
+    const M3 Da = dag(Ka), Db = dag(Kb);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        Ja.a[q] = 0.125 * (Ka.a[q] - Da.a[q]);
+        Jb.a[q] = 0.125 * (Kb.a[q] - Db.a[q]);
+    }
+}
+DDWC_HD int force_slot(int mu, int nu) { return mu == 0 ? nu - 1 : mu == 2 ? 3 : nu == 3 ? 4 : 5; }  // mu < nu
+
+// A plaquette X0 X1 X2 X3 (matrices as they stand in the product, daggers taken) appears in the leaves of its four
+// corners, which are cyclic shifts of it with the corner's J inserted: Re tr of X0 Ja X1 X2 X3 + X0 X1 Jb X2 X3 +
+// X0 X1 X2 Jc X3 + X0 X1 X2 X3 Jd, J's in the order of the corners.  This is Z of Re tr[X0 Z].
+template <class LX, class LJ>
+DDWC_HD M3 plaquette_force(const LX& X, const LJ& J) {
+    const M3 X1 = X(1);
+    M3 T = add(mul(J(0), X1), mul(X1, J(1)));
+    const M3 X2 = X(2), X3 = X(3);
+    const M3 S = mul(X2, X3);
+    T = mul(T, S);
+    const M3 W = add(mul(X2, mul(J(2), X3)), mul(S, J(3)));
+    return add(T, mul(X1, W));
+}
+
+// The link q (0 .. 3 in product order A B C^+ D^+, A = U_mu(z), B = U_nu(z + mu), C = U_mu(z + nu), D = U_nu(z)) of the
+// plaquette (z, mu < nu): its contribution to the link's gradient.  at(c): the corner sites z, z + mu, z + mu + nu,
+// z + nu; ldU(direction, site), ldJ(slot, site).
+template <class AT, class LU, class LJ>
+DDWC_HD M3 plaquette_link_force(int mu, int nu, int q, const AT& at, const LU& ldU, const LJ& ldJ) {
+    const int slot = force_slot(mu, nu);
+    auto link = [&](int k) {  // the k-th matrix of the product, cyclic
+        switch (k & 3) {
+            case 0: return ldU(mu, at(0));
+            case 1: return ldU(nu, at(1));
+            case 2: return dag(ldU(mu, at(3)));
+            default: return dag(ldU(nu, at(0)));
         }
-        const int xpm = step<+1>(g, y, mu), xpn = step<+1>(g, y, nu);
-        const int xmm = step<-1>(g, y, mu), xmn = step<-1>(g, y, nu);
-        const int xmm_pn = step<+1>(g, xmm, nu), xmm_mn = step<-1>(g, xmm, nu), xpm_mn = step<-1>(g, xpm, nu);
-        // leaves as (direction, site, dagger) x 4, in product order (clover_build.h)
-        const int lv[4][4][3] = {
-            {{mu, y, 0}, {nu, xpm, 0}, {mu, xpn, 1}, {nu, y, 1}},
-            {{nu, y, 0}, {mu, xmm_pn, 1}, {nu, xmm, 1}, {mu, xmm, 0}},
-            {{mu, xmm, 1}, {nu, xmm_mn, 1}, {mu, xmm_mn, 0}, {nu, xmn, 0}},
-            {{nu, xmn, 1}, {mu, xmn, 0}, {nu, xpm_mn, 0}, {mu, y, 1}}};
-        for (int lf = 0; lf < 4; ++lf) {
-            M3 f[4];
-            for (int p = 0; p < 4; ++p) {
-                f[p] = ld(U, g, lv[lf][p][0], lv[lf][p][1]);
-                if (lv[lf][p][2]) f[p] = dag(f[p]);
-            }
-            for (int p = 0; p < 4; ++p) {
-                // leaf = A X B with A = f[0..p-1], B = f[p+1..3]; Z = B J A
-                M3 Z = J;
-                for (int q = 0; q < p; ++q) Z = mul(Z, f[q]);
-                for (int q = 3; q > p; --q) Z = mul(f[q], Z);
-                add(lv[lf][p][0], lv[lf][p][1], lv[lf][p][2] ? Z : dag(Z));
-            }
+    };
+    // the corner after the k-th matrix: A ends at z + mu (1), B at z + mu + nu (2), C^+ at z + nu (3), D^+ at z (0)
+    const M3 Z = plaquette_force([&](int k) { return link(q + k); },
+                                 [&](int k) { return ldJ(slot, at((q + k + 1) & 3)); });
+    return q < 2 ? dag(Z) : Z;
+}
+
+// Clover part at link (x, mu): the plaquettes of its three planes on both sides.  nb(d, s): neighbour of s in
+// direction d = 2 mu + (backward ? 1 : 0).
+template <class NB, class LU, class LJ>
+DDWC_HD M3 force_clover_link(int mu, int x, const NB& nb, const LU& ldU, const LJ& ldJ) {
+    M3 G;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) G.a[k] = mk(0.0, 0.0);
+    const int xm = nb(2 * mu, x);
+#pragma unroll 1
+    for (int o = 0; o < 3; ++o) {
+        const int nu = o + (o >= mu);
+#pragma unroll 1
+        for (int side = 0; side < 2; ++side) {
+            // z: the plaquette's corner; the link is the near edge (side 0: z = x) or the far one (z = x - nu)
+            const int z = side ? nb(2 * nu + 1, x) : x;
+            const int zm = side ? nb(2 * mu, z) : xm, zn = side ? x : nb(2 * nu, x), zmn = side ? xm : nb(2 * nu, xm);
+            // in the plane (lo < hi) the corners in order are z, z + lo, z + lo + hi, z + hi
+            const bool first = mu < nu;
+            const int c1 = first ? zm : zn, c3 = first ? zn : zm;
+            const int q = first ? (side ? 2 : 0) : (side ? 1 : 3);
+            G = add(G, plaquette_link_force(first ? mu : nu, first ? nu : mu, q,
+                                            [&](int c) { return c == 0 ? z : c == 1 ? c1 : c == 2 ? zmn : c3; }, ldU, ldJ));
         }
     }
+    return G;
+}
+
+// The same from the clover term at one site y: add(dir, site, Z) receives the contribution to the gradient of
+// every link of the leaves at y (the kernels gather per link instead; checks on the host use this form).
+template <class ADD>
+DDWC_HD void force_clover_site(const Geom& g, const cx<double>* U, double csw, const double2* a, const double2* b,
+                               const double* w, int nrhs, int y, const ADD& adder) {
+    M3 L[2][3], J[6];
+    for (int k = 0; k < 2; ++k) force_outer(a, b, w, nrhs, (unsigned)g.V, (unsigned)y, k, L[k]);
+    for (int l = 0; l < 3; ++l) force_planes(L[0][l], L[1][l], l, csw, J[l], J[3 + l]);
+    M3 zero;
+    for (int k = 0; k < 9; ++k) zero.a[k] = mk(0.0, 0.0);
+    auto ldU = [&](int mu, int s) { return ld(U, g, mu, s); };
+    for (int mu = 0; mu < 4; ++mu)
+        for (int nu = mu + 1; nu < 4; ++nu)
+            for (int c = 0; c < 4; ++c) {  // y is corner c of the plaquette at z
+                int z = y;
+                if (c == 1 || c == 2) z = step<-1>(g, z, mu);
+                if (c == 2 || c == 3) z = step<-1>(g, z, nu);
+                const int zm = step<+1>(g, z, mu), zn = step<+1>(g, z, nu), zmn = step<+1>(g, zm, nu);
+                const int at[4] = {z, zm, zmn, zn};
+                // (on a lattice of extent 2 other corners can be the same site: only corner c counts here)
+                for (int q = 0; q < 4; ++q) {
+                    auto corner = [&](int k) { return at[k]; };
+                    int seen = 0;
+                    auto ldJ = [&](int slot, int) {  // called for corners q + 1, q + 2, q + 3, q + 4
+                        const int k = (q + 1 + seen++) & 3;
+                        return k == c ? J[slot] : zero;
+                    };
+                    const M3 Z = plaquette_link_force(mu, nu, q, corner, ldU, ldJ);
+                    adder((q & 1) ? nu : mu, q == 0 ? z : q == 1 ? zm : q == 2 ? zn : z, Z);
+                }
+            }
 }
 
 }  // namespace ddwc

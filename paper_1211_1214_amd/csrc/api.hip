@@ -700,6 +700,18 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     constexpr int LS_WINDOW = 4, LS_SITES = 8192;
     constexpr double LS_GAIN = 0.4;
     bool ls = g.V >= LS_SITES;
+    // Lattices whose parity fits the LDS-resident solver are one block of it, one workgroup per RHS: an inner solve is
+    // then one launch instead of seven per iteration, each shorter than its dispatch.  To 1e-10 with 8 RHS, launches /
+    // resident: 4^4 2.9 / 0.67 ms, 12x8x4x4 (768 sites of a parity, the most that fit) 3.3 / 1.4 ms at kappa 0.1205,
+    // 2.8 / 0.92 and 4.1 / 2.6 ms at 0.126; 300 RHS 3.0 / 0.86 and 8.0 / 3.3 ms.  (In FP32 for FP16 storage too, as for
+    // blocks.)
+    bool resident = !fp64 && eo_lds_fits(g, C->lds_max);
+    int* iters = nullptr;
+    if (resident) {
+        CK(ws_t(C, "eo_iters", (size_t)nrhs, &iters));
+        HC(hipMemsetAsync(iters, 0, sizeof(int) * nrhs, sm));
+    }
+    std::vector<double> before;  // ||r_e||^2 at the last launch of the resident solver
     // `iters` iterations on stream ee (the caller's, or the capture stream)
     auto chunk = [&](Exec& ee, int iters, bool two_step) {
         auto apply_M = [&](const W* in, W* out, int epi, const W* aux, double* pt) {
@@ -740,7 +752,7 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
                                       (uintptr_t)FR.order};
         return graph_for(C, key, [&](Exec& ee) { chunk(ee, poll, two_step); });
     };
-    hipGraphExec_t gx = chunk_graph(ls);
+    hipGraphExec_t gx = resident ? nullptr : chunk_graph(ls);
     while (true) {
         bool all = true;
         for (int k = 0; k < nrhs; ++k)
@@ -751,70 +763,92 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
         }
         if (total >= maxit || nout >= 100) break;
         ++nout;
-        for (int k = 0; k < nrhs; ++k) {
-            bool done = !(bb[k] > 0 && rr[k] > tol * tol * bb[k]);
-            h_scale[k] = done ? 0.0 : 1.0 / sqrt(rr[k]);
-            double eps = done ? 0.0 : 0.5 * tol * sqrt(bb[k] / rr[k]);
-            if (eps < floor_eps) eps = floor_eps;
-            h_thr[k] = done ? 2.0 : eps * eps;
-        }
-        HC(hipMemcpyAsync(scale, h_scale, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
-        HC(hipMemcpyAsync(thr, h_thr, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
-        if (ls)
-            launch_ls_init<S>(ex, n2, ri, re, scale, r, xR, part, nrhs);
-        else
-            launch_bicg_init<S>(ex, n2, ri, re, scale, r, rh, p, xR, part, nrhs);
-        launch_finalize(ex, part, ntR, nrhs, nullptr, st, ST_INIT, thr);
-        // ||r||^2 at the last poll and at the start of the window (1 after the scaling)
-        std::vector<double> last(nrhs, 1.0), was(nrhs, 1.0);
-        int in_window = 0, chunks = 1;
-        while (total < maxit) {
-            int since = 0;
-            for (int k = 0; k < chunks && total < maxit; ++k) {
-                const int it = std::min(poll, maxit - total);
-                if (gx && it == poll)
-                    HC(hipGraphLaunch(gx, sm));
-                else
-                    chunk(ex, it, ls);
-                total += it;
-                since += it;
-            }
-            HC(hipGetLastError());
-            HC(hipMemcpyAsync(h_st, st, sizeof(BiState) * nrhs, hipMemcpyDeviceToHost, sm));
-            HC(hipStreamSynchronize(sm));
-            bool any = false, slow = false;
-            for (int k = 0; k < nrhs; ++k) any = any || h_st[k].active;
-            in_window += since;
-            const bool window = ls && in_window >= LS_WINDOW;
-            const double gain = pow(LS_GAIN, 2.0 * in_window / LS_WINDOW);
-            // iterations that the slowest RHS still needs at the rate since the last poll; the next poll comes
-            // after half of them (a host round trip costs a small lattice as much as an iteration)
-            double need = 0;
+        if (!before.empty()) {
+            // a launch that left more than 1e-2 (or twice its floor) of a residual with further to go stopped for its
+            // slow convergence: BiCGStab for the rest
+            const double left = fmax(1e-4, 4e-16 * C->opt_inner_floor * C->opt_inner_floor);
             for (int k = 0; k < nrhs; ++k) {
-                if (ls && (h_st[k].broken || (window && h_st[k].active && h_st[k].rr > gain * was[k]))) slow = true;
-                if (window) was[k] = h_st[k].rr;
-                if (h_st[k].active) {
-                    const double rate = log(last[k] / h_st[k].rr) / since;
-                    if (rate > 0 && h_st[k].thr2 > 0) need = fmax(need, log(h_st[k].rr / h_st[k].thr2) / rate);
-                    last[k] = h_st[k].rr;
-                }
+                const double goal = tol * tol * bb[k];
+                if (bb[k] > 0 && rr[k] > goal && rr[k] > left * before[k] && before[k] > goal / left) resident = false;
             }
-            if (window) in_window = 0;
-            if (slow) {  // keep what was gained; the rest by BiCGStab
-                ls = false;
-                gx = chunk_graph(ls);
-                break;
-            }
-            if (!any) break;
-            chunks = need > 0 ? std::min(std::max(1, (int)(0.5 * need / poll)), 8) : 1;
+            before.clear();
+            if (!resident) gx = chunk_graph(ls);
         }
-        launch_accumulate<S>(ex, n2, ri, xR, scale, xe, nrhs);
+        if (resident) before = rr;
+        if (resident) {
+            for (int k = 0; k < nrhs; ++k) h_scale[k] = bb[k], h_thr[k] = rr[k];
+            HC(hipMemcpyAsync(scale, h_scale, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
+            HC(hipMemcpyAsync(thr, h_thr, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
+            launch_eo_lds(ex, g, eo_fields<float>(C), A32, re, xe, scale, thr, mass4, tol, 1e-8 * C->opt_inner_floor,
+                          maxit - total, iters, nrhs);
+            HC(hipMemcpyAsync(h_st, iters, sizeof(int) * nrhs, hipMemcpyDeviceToHost, sm));
+        } else {
+            for (int k = 0; k < nrhs; ++k) {
+                bool done = !(bb[k] > 0 && rr[k] > tol * tol * bb[k]);
+                h_scale[k] = done ? 0.0 : 1.0 / sqrt(rr[k]);
+                double eps = done ? 0.0 : 0.5 * tol * sqrt(bb[k] / rr[k]);
+                if (eps < floor_eps) eps = floor_eps;
+                h_thr[k] = done ? 2.0 : eps * eps;
+            }
+            HC(hipMemcpyAsync(scale, h_scale, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
+            HC(hipMemcpyAsync(thr, h_thr, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
+            if (ls)
+                launch_ls_init<S>(ex, n2, ri, re, scale, r, xR, part, nrhs);
+            else
+                launch_bicg_init<S>(ex, n2, ri, re, scale, r, rh, p, xR, part, nrhs);
+            launch_finalize(ex, part, ntR, nrhs, nullptr, st, ST_INIT, thr);
+            // ||r||^2 at the last poll and at the start of the window (1 after the scaling)
+            std::vector<double> last(nrhs, 1.0), was(nrhs, 1.0);
+            int in_window = 0, chunks = 1;
+            while (total < maxit) {
+                int since = 0;
+                for (int k = 0; k < chunks && total < maxit; ++k) {
+                    const int it = std::min(poll, maxit - total);
+                    if (gx && it == poll)
+                        HC(hipGraphLaunch(gx, sm));
+                    else
+                        chunk(ex, it, ls);
+                    total += it;
+                    since += it;
+                }
+                HC(hipGetLastError());
+                HC(hipMemcpyAsync(h_st, st, sizeof(BiState) * nrhs, hipMemcpyDeviceToHost, sm));
+                HC(hipStreamSynchronize(sm));
+                bool any = false, slow = false;
+                for (int k = 0; k < nrhs; ++k) any = any || h_st[k].active;
+                in_window += since;
+                const bool window = ls && in_window >= LS_WINDOW;
+                const double gain = pow(LS_GAIN, 2.0 * in_window / LS_WINDOW);
+                // iterations that the slowest RHS still needs at the rate since the last poll; the next poll comes
+                // after half of them (a host round trip costs a small lattice as much as an iteration)
+                double need = 0;
+                for (int k = 0; k < nrhs; ++k) {
+                    if (ls && (h_st[k].broken || (window && h_st[k].active && h_st[k].rr > gain * was[k]))) slow = true;
+                    if (window) was[k] = h_st[k].rr;
+                    if (h_st[k].active) {
+                        const double rate = log(last[k] / h_st[k].rr) / since;
+                        if (rate > 0 && h_st[k].thr2 > 0) need = fmax(need, log(h_st[k].rr / h_st[k].thr2) / rate);
+                        last[k] = h_st[k].rr;
+                    }
+                }
+                if (window) in_window = 0;
+                if (slow) {  // keep what was gained; the rest by BiCGStab
+                    ls = false;
+                    gx = chunk_graph(ls);
+                    break;
+                }
+                if (!any) break;
+                chunks = need > 0 ? std::min(std::max(1, (int)(0.5 * need / poll)), 8) : 1;
+            }
+            launch_accumulate<S>(ex, n2, ri, xR, scale, xe, nrhs);
+        }
         // r_e = b'_e - Mee x_e in FP64
         launch_eo_hopinv<double>(ex, F64, 1, false, xe, nullptr, 1.0, A64, to, nrhs, DDWC_K_DSLASH64, 0);
         launch_eo_diaghop<double>(ex, F64, 0, false, 3, true, xe, to, -0.25, mass4, bpe, re, part, nrhs, DDWC_K_DSLASH64, 0);
         launch_finalize(ex, part, nt, nrhs, sums, nullptr, ST_SUM, nullptr, 1);
         HC(hipMemcpyAsync(h_sums, sums, sizeof(double) * nrhs * NPART, hipMemcpyDeviceToHost, sm));
         HC(hipStreamSynchronize(sm));
+        if (resident) total = *std::max_element((const int*)h_st, (const int*)h_st + nrhs);
         for (int k = 0; k < nrhs; ++k) {
             rr[k] = h_sums[k * NPART];
             if (!isfinite(rr[k])) return fail(DDWC_ENONFINITE, "non-finite residual in the global solve");

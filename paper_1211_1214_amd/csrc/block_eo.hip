@@ -529,13 +529,20 @@ __device__ __forceinline__ void lds_store(float4* __restrict__ L, unsigned li, c
 
 // Local half indices of the in-block neighbours of one site, packed two per register; a hop that
 // leaves the block has index HV, the record of zeros after the block's sites in LDS.
+// WRAP (the whole lattice): no hop leaves, and bit 15 marks one across an antiperiodic time boundary (d < 2).
+template <bool WRAP>
 struct BlkNbr {
     unsigned w[4];
-    __device__ __forceinline__ unsigned operator[](int d) const { return (d & 1) ? w[d >> 1] >> 16 : w[d >> 1] & 0xffffu; }
+    __device__ __forceinline__ unsigned operator[](int d) const {
+        const unsigned e = (d & 1) ? w[d >> 1] >> 16 : w[d >> 1] & 0xffffu;
+        return WRAP && d < 2 ? e & 0x7fffu : e;
+    }
+    __device__ __forceinline__ bool flip(int d) const { return WRAP && d < 2 && (w[d >> 1] & (d ? 0x80000000u : 0x8000u)); }
 };
-__device__ __forceinline__ BlkNbr blk_nbr(const int* __restrict__ nbr, unsigned n2, unsigned s, unsigned h0, unsigned HV,
+template <bool WRAP>
+__device__ __forceinline__ BlkNbr<WRAP> blk_nbr(const int* __restrict__ nbr, unsigned n2, unsigned s, unsigned h0, unsigned HV,
                                           bool act) {
-    BlkNbr b;
+    BlkNbr<WRAP> b;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         unsigned li[2];
@@ -544,6 +551,7 @@ __device__ __forceinline__ BlkNbr blk_nbr(const int* __restrict__ nbr, unsigned 
             const int e = at(nbr + (size_t)(2 * k + q) * n2, s);
             const unsigned t = (e < 0 ? (unsigned)~e : (unsigned)e) - h0;
             li[q] = act && t < HV ? t : HV;
+            if (WRAP && e < 0) li[q] |= 0x8000u;
         }
         b.w[k] = li[0] | (li[1] << 16);
     }
@@ -557,7 +565,8 @@ __device__ __forceinline__ BlkNbr blk_nbr(const int* __restrict__ nbr, unsigned 
 // waves of a block take nearly every hop for some lane anyway, and as straight-line code the link of hop
 // d + 1 is loaded while d is computed.  (In-block hops never cross the time boundary,
 // whose sign the table carries: there are at least two blocks per direction.)
-__device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own, BlkNbr nb, unsigned HV,
+template <bool WRAP>
+__device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own, BlkNbr<WRAP> nb, unsigned HV,
                                          const float4* __restrict__ L, const char* Uf, const char* Ub,
                                          cx<float> acc[12]) {
 #pragma unroll
@@ -572,6 +581,11 @@ __device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own,
     for (int d = 0; d < 8; ++d) {
         cx<float> un[9], q[12];
         lds_load(L, nb[d], q);
+        if (WRAP && d < 2) {
+            const float sg = nb.flip(d) ? -1.f : 1.f;
+#pragma unroll
+            for (int c = 0; c < 12; ++c) q[c] = sg * q[c];
+        }
         if (d + 1 < 8) {
             const unsigned t = reissue(nb[d + 1]);
             if ((d + 1) & 1)
@@ -587,6 +601,8 @@ __device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own,
     }
 }
 
+// WRAP: the same for the whole lattice as one block with its boundary conditions, one workgroup per RHS (hvb = V / 2).
+template <bool WRAP>
 __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, const float4* __restrict__ Ainv,
                                                     const double2* re, double2* xe, const double* __restrict__ bb, const double* __restrict__ rr,
                                                     double mass4, double tol, double inner_floor, int maxit,
@@ -611,7 +627,7 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     xe += oh;
     const char *Ue = F.W[0], *Uo = F.W[1];
     const float4 *Ke = F.K[0] + h0, *Ko = Ainv + h0;
-    const BlkNbr ne = blk_nbr(F.nbr[0], n2, h0 + lg, h0, HV, act), no = blk_nbr(F.nbr[1], n2, h0 + lg, h0, HV, act);
+    const BlkNbr<WRAP> ne = blk_nbr<WRAP>(F.nbr[0], n2, h0 + lg, h0, HV, act), no = blk_nbr<WRAP>(F.nbr[1], n2, h0 + lg, h0, HV, act);
     for (unsigned k = threadIdx.x; k < 2 * 8 * 16; k += blockDim.x) red_lds[0][k] = 0;
     if (threadIdx.x < 12) (threadIdx.x < 6 ? op : tp)[HV * 6 + threadIdx.x % 6] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
@@ -620,7 +636,7 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     auto odd = [&]() {
         cx<float> acc[12], w[12];
         UDiag<float> K(fresh(Ko), n2, lo);
-        lds_hops(n2, h0, own, no, HV, op, Uo, Ue, acc);
+        lds_hops<WRAP>(n2, h0, own, no, HV, op, Uo, Ue, acc);
 #pragma unroll
         for (int c = 0; c < 12; ++c) w[c] = mk(0.f, 0.f);
         K.off = reissue(lo), K.first();
@@ -630,7 +646,7 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     // y = (4 + m + C) c - 1/4 H^k_eo q_o on the even sites (c: this site's operand; q_o in tp)
     auto even = [&](cx<float> y[12], cx<float> c[12]) {
         UDiag<float> K(fresh(Ke), n2, lo);
-        lds_hops(n2, h0, own, ne, HV, tp, Ue, Uo, y);
+        lds_hops<WRAP>(n2, h0, own, ne, HV, tp, Ue, Uo, y);
         lds_load(op, l, c);
         K.off = reissue(lo), K.first();
         K.apply(m4, c, y, -0.25f);
@@ -700,9 +716,11 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
 }
 
-bool blk_lds_fits(const Geom& g, int lds_max_bytes) {
-    return g.eo && g.hvb <= BL_MAX && (long long)2 * 6 * 16 * (g.hvb + 1) + 2 * 8 * 16 * 8 <= lds_max_bytes;
+static bool lds_fits(int hv, int lds_max_bytes) {
+    return hv <= BL_MAX && (long long)2 * 6 * 16 * (hv + 1) + 2 * 8 * 16 * 8 <= lds_max_bytes;
 }
+bool blk_lds_fits(const Geom& g, int lds_max_bytes) { return g.eo && lds_fits(g.hvb, lds_max_bytes); }
+bool eo_lds_fits(const Geom& g, int lds_max_bytes) { return g.eo && lds_fits(g.V / 2, lds_max_bytes); }
 
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                     double2* xe, const double* bb, const double* rr, double mass4, double tol,
@@ -712,8 +730,18 @@ void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const floa
     const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
     // the inner solve stops at this relative residual at the least (FP32's reach)
     // (a BiCGStab iteration, the unit of maxit, is two steps)
-    k_blk_lds<<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6,
-                                                        maxit < (1 << 30) ? 2 * maxit : maxit, iters, colour, nrhs);
+    k_blk_lds<false><<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6,
+                                                               maxit < (1 << 30) ? 2 * maxit : maxit, iters, colour, nrhs);
+}
+void launch_eo_lds(Exec& e, Geom g, const EoFields<float>& F, const float4* Ainv, const double2* re, double2* xe,
+                   const double* bb, const double* rr, double mass4, double tol, double floor_eps, int maxit, int* iters,
+                   int nrhs) {
+    Timed t(e, DDWC_K_DSLASH32, 0);
+    g.hvb = g.V / 2, g.NBc = 1;
+    const int threads = ((g.hvb + 63) / 64) * 64;
+    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);
+    k_blk_lds<true><<<nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps,
+                                                      maxit < (1 << 30) ? 2 * maxit : maxit, iters, 0, nrhs);
 }
 
 // ------------------------------------------------------------------ minimal residual in global memory

@@ -293,6 +293,12 @@ bool blk_lds_fits(const Geom& g, int lds_max_bytes);
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                     double2* xe, const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
                     int colour, int nrhs);
+// The same solver for the whole lattice as one block, one workgroup per RHS: whether it takes this lattice, and its
+// launch (bb, rr, iters per RHS).
+bool eo_lds_fits(const Geom& g, int lds_max_bytes);
+void launch_eo_lds(Exec& e, Geom g, const EoFields<float>& F, const float4* Ainv, const double2* re, double2* xe,
+                   const double* bb, const double* rr, double mass4, double tol, double floor_eps, int maxit, int* iters,
+                   int nrhs);
 // bytes of one RHS of a block-solver vector in the storage of precision `prec` (n2 = V/2)
 size_t blk_slab_bytes(int prec, unsigned n2);
 

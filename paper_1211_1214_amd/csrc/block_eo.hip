@@ -716,32 +716,283 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
 }
 
+// ------------------------------------------------------------------ two or four lanes per site
+// The iteration of k_blk_lds for launches that would leave SIMDs or lanes idle: there a step takes as long as one
+// wavefront needs to issue it (3300 vector instructions, of four cycles each), so the work of a site is shared by
+// two or four lanes.  Lane bit 0 is the spin s of the half spinors: h_s = psi_s + c psi_p with
+// p = 2 + s (mu = 0, 3) or 3 - s (mu = 1, 2) needs nothing of the other half, and c^* W h_s goes back to spin p.  Lane bit 1
+// (of four) is a pair of directions, (0, 1) or (3, 2) in this order, so that p is the same for both lanes of a slot
+// and only the constant c differs.  Exchanges between neighbouring lanes add the sums and turn them into chiral
+// halves (spins 0, 1 or 2, 3), on which a lane applies its clover block, the same in both lanes of bit 1.  The links
+// of a lane in either parity stay in registers for the whole solve.
+// One launch on 4^4 (128 sites a parity, two lanes), 8 RHS: 256 -> 187 us; on its 2^4 blocks (8 sites, four lanes), one
+// colour: 53 -> 30 us.
+constexpr int BQ_THREADS = 256;  // one wavefront per SIMD, so that the links fit its registers
+constexpr int CU_COUNT = 256;
+
+template <int N>  // v of the lane with bits N flipped (inside a quad)
+__device__ __forceinline__ float quad_xor(float v) {
+    constexpr int perm = (0 ^ N) | (1 ^ N) << 2 | (2 ^ N) << 4 | (3 ^ N) << 6;
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), perm, 0xf, 0xf, false));
+}
+template <int N>
+__device__ __forceinline__ cx<float> quad_xor(cx<float> v) {
+    return mk(quad_xor<N>(v.re), quad_xor<N>(v.im));
+}
+
+template <bool WRAP, int LANES>
+__global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Geom g, EoFields<float> F, const float4* Ainv, const double2* re,
+                                                        double2* xe, const double* bb, const double* rr, double mass4,
+                                                        double tol, double inner_floor, int maxit, int* iters, int colour,
+                                                        int nrhs) {
+    extern __shared__ float2 bq_lds[];  // the operand and the odd intermediate: records of four spins
+    __shared__ double red_lds[2][8 * 16];
+    constexpr int NS = 16 / LANES;  // directions of a lane
+    const BlkIdx k = blk_idx(g, colour, nrhs);
+    const double b2 = bb[k.key], r2 = rr[k.key];
+    if (!(b2 > 0) || !(r2 > tol * tol * b2) || !isfinite(r2)) return;  // uniform over the workgroup
+    const unsigned n2 = F.n2, HV = (unsigned)g.hvb, h0 = k.h0;
+    const unsigned s = threadIdx.x & 1, dg = LANES == 4 ? (threadIdx.x >> 1) & 1 : 0u;
+    const bool act = threadIdx.x / LANES < HV;
+    const unsigned l = act ? threadIdx.x / LANES : HV, own = h0 + (act ? l : 0u);
+    float2 *op = bq_lds, *tp = bq_lds + 12 * (HV + 1);
+    for (unsigned q = threadIdx.x; q < 2 * 8 * 16; q += blockDim.x) red_lds[0][q] = 0;
+    if (threadIdx.x < 24) (threadIdx.x < 12 ? op : tp)[12 * HV + threadIdx.x % 12] = make_float2(0.f, 0.f);
+    // the slots of a lane: hops along 0, (3,) 1 (and 2), or along 3 and 2 with bit 1 set; the links of both parities, with
+    // the sign of a time boundary
+    auto direction = [&](int q) -> unsigned { return LANES == 4 ? (dg ? q ^ 6 : q) : q < 2 ? q : q < 4 ? q + 4 : q - 2; };
+    cx<float> u[2][NS][9];
+    unsigned nb[2][NS / 2];  // LDS records of the neighbours, two per register
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const unsigned d = direction(q);
+            const int e = F.nbr[p][(size_t)d * n2 + own];
+            const unsigned t = (e < 0 ? (unsigned)~e : (unsigned)e) - h0;
+            const unsigned li = act && t < HV ? t : HV;
+            nb[p][q >> 1] = (q & 1) ? nb[p][q >> 1] | li << 16 : li;
+            const unsigned at = (q & 1) ? h0 + (li < HV ? li : 0u) : own;
+            const char* base = F.W[(q & 1) ? 1 - p : p] + (size_t)(d >> 1) * packed_link_bytes<float>() * n2;
+            const float sg = WRAP && e < 0 ? -1.f : 1.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 w = ((const float4*)base)[(size_t)j * n2 + at];
+                u[p][q][2 * j] = mk(sg * w.x, sg * w.y);
+                u[p][q][2 * j + 1] = mk(sg * w.z, sg * w.w);
+            }
+            const float2 w = ((const float2*)(base + (size_t)64 * n2))[at];
+            u[p][q][8] = mk(sg * w.x, sg * w.y);
+        }
+    // c of a forward hop: 1 (mu = 0), i (mu = 1), sg (mu = 2), i sg (mu = 3)
+    const float sg = s ? -1.f : 1.f;
+    const cx<float> c0 = dg ? mk(0.f, sg) : mk(1.f, 0.f), c2 = dg ? mk(sg, 0.f) : mk(0.f, 1.f);
+    // x += c z (four lanes), or its part for a c known to be real or imaginary, and x += c^* z
+    auto add_c = [&](cx<float>& x, int q, cx<float> z, bool conj) {
+        const float sign = (q & 1) ? -1.f : 1.f;
+        if (LANES == 4) {
+            const cx<float> cf = q < 2 ? c0 : c2, c = mk(sign * cf.re, sign * cf.im);
+            if (conj)
+                cjmadd(x, c, z);
+            else
+                cmadd(x, c, z);
+        } else {
+            const int mu = (int)direction(q) >> 1;
+            const float c = sign * (mu >= 2 ? sg : 1.f) * (conj && (mu & 1) ? -1.f : 1.f);
+            if (mu & 1)
+                x = mk(fmad(-c, z.im, x.re), fmad(c, z.re, x.im));
+            else
+                x = mk(fmad(c, z.re, x.re), fmad(c, z.im, x.im));
+        }
+    };
+    // y = the hops of parity p from L, this lane's chiral half
+    auto hops = [&](int p, const float2* L, cx<float> y[6]) {
+        cx<float> up[3], lo[2][3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) up[a] = lo[0][a] = lo[1][a] = mk(0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const unsigned li = (q & 1) ? nb[p][q >> 1] >> 16 : nb[p][q >> 1] & 0xffffu;
+            const float2 *r0 = L + 12 * li + 3 * s, *r1 = L + 12 * li + 3 * (q < NS / 2 ? 2 + s : 3 - s);
+            cx<float> h[3], w[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float2 x = r0[a], z = r1[a];
+                h[a] = mk(x.x, x.y);
+                add_c(h[a], q, mk(z.x, z.y), false);
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                w[a] = mk(0.f, 0.f);
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    if (q & 1)
+                        cjmadd(w[a], u[p][q][3 * b + a], h[b]);
+                    else
+                        cmadd(w[a], u[p][q][3 * a + b], h[b]);
+                }
+                up[a] = up[a] + w[a];
+                add_c(lo[q >= NS / 2][a], q, w[a], true);
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            // spin 2 + s from the first half of the slots here and the second half of the other spin; all directions
+            cx<float> v = lo[0][a] + quad_xor<1>(lo[1][a]);
+            if (LANES == 4) up[a] = up[a] + quad_xor<2>(up[a]), v = v + quad_xor<2>(v);
+            // spins (s, 2 + s) -> (0, 1) for s = 0, (2, 3) for s = 1
+            const cx<float> x = quad_xor<1>(s ? up[a] : v);
+            y[a] = s ? x : up[a];
+            y[3 + a] = s ? v : x;
+        }
+    };
+    // the words with a chiral half's diagonal and off-diagonal reals are planes s, s + 1 and 3 + 7 s to 10 + 7 s
+    const unsigned kd = byte_offset(own + s * n2, 16), ko = byte_offset(own + 7 * s * n2, 16);
+    // (two lanes, one wavefront per SIMD: loaded before the hops, whose time hides them: 216 -> 187 us on 4^4)
+    constexpr bool EARLY = LANES == 2;
+    auto load_diag = [&](const float4* K, float w[40]) {
+        Planes qd(fresh(K), n2), qo(fresh(K), n2, 3);
+        const unsigned od = reissue(kd), oo = reissue(ko);
+#pragma unroll
+        for (int j = 0; j < 10; ++j) {
+            const f4v x = j < 2 ? qd.load<f4v>(od) : qo.load<f4v>(oo);
+            w[4 * j] = x[0], w[4 * j + 1] = x[1], w[4 * j + 2] = x[2], w[4 * j + 3] = x[3];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // y = (m4 + C) v + hsc y on the chiral half
+    auto diag = [&](const float w[40], float m4, const cx<float> v[6], cx<float> y[6], float hsc) {
+        float d[6], o[30];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) d[j] = s ? w[j + 2] : w[j];
+#pragma unroll
+        for (int j = 0; j < 30; ++j) o[j] = s ? w[j + 10] : w[j + 8];
+        diag_block<float>(d, o, m4, v, y, hsc);
+    };
+    auto store = [&](float2* L, const cx<float> v[6]) {
+        if (act && !dg) {
+#pragma unroll
+            for (int a = 0; a < 6; ++a) L[12 * l + 6 * s + a] = make_float2(v[a].re, v[a].im);
+        }
+    };
+    const float m4 = (float)mass4;
+    const double rn = sqrt(r2), sc = 1.0 / rn;
+    double eps = 0.25 * tol * sqrt(b2) / rn;  // (as k_blk_lds)
+    if (eps < inner_floor) eps = inner_floor;
+    const size_t oh = (size_t)k.rhs * 12 * n2 + (size_t)(6 * s) * n2 + own;
+    cx<float> e[6], r[6];
+    int phase = 0;
+    // (with four lanes every value counts twice in the sums: only their ratios matter)
+    double red[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        const double2 x = re[oh + (size_t)a * n2];
+        r[a] = act ? mk((float)(sc * x.x), (float)(sc * x.y)) : mk(0.f, 0.f);
+        e[a] = mk(0.f, 0.f);
+        red[0] += (double)(r[a].re * r[a].re + r[a].im * r[a].im);
+    }
+    store(op, r);
+    __syncthreads();
+    wg_sums<1>(red, red_lds[phase ^= 1]);
+    const double thr2 = eps * eps * red[0];
+    double window = red[0];
+    int it = 0;
+    while (it < maxit) {
+        cx<float> t[6], w[6];
+        float kw[40];
+        if (EARLY) load_diag(Ainv, kw);
+        hops(1, op, t);
+        if (!EARLY) load_diag(Ainv, kw);
+#pragma unroll
+        for (int a = 0; a < 6; ++a) w[a] = mk(0.f, 0.f);
+        diag(kw, 0.f, t, w, 0.f);
+        store(tp, w);
+        if (EARLY) load_diag(F.K[0], kw);
+        __syncthreads();
+        hops(0, tp, t);
+        if (!EARLY) load_diag(F.K[0], kw);
+        diag(kw, m4, r, t, -0.25f);
+        float v[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            v[0] += t[a].re * r[a].re + t[a].im * r[a].im;
+            v[1] += t[a].re * r[a].im - t[a].im * r[a].re;
+            v[2] += t[a].re * t[a].re + t[a].im * t[a].im;
+            v[3] += r[a].re * r[a].re + r[a].im * r[a].im;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[q] = act ? (double)v[q] : 0.0;
+        wg_sums<4>(red, red_lds[phase ^= 1]);
+        ++it;
+        if (!(red[2] > 0)) break;
+        const cx<float> omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            cmadd(e[a], omega, r[a]);
+            cmadd(r[a], mk(-omega.re, -omega.im), t[a]);
+        }
+        const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
+        if (!(r2n > thr2) || !isfinite(r2n)) break;
+        if (it % BL_WINDOW == 0) {
+            if (r2n > BL_GAIN * BL_GAIN * window) break;  // too slow: left to the caller
+            window = r2n;
+        }
+        // (all reads of the operand were before the last barrier)
+        store(op, r);
+        __syncthreads();
+    }
+    if (act && !dg) {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            const double2 x = xe[oh + (size_t)a * n2];
+            xe[oh + (size_t)a * n2] = make_double2(x.x + rn * (double)e[a].re, x.y + rn * (double)e[a].im);
+        }
+    }
+    if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
+}
+
 static bool lds_fits(int hv, int lds_max_bytes) {
     return hv <= BL_MAX && (long long)2 * 6 * 16 * (hv + 1) + 2 * 8 * 16 * 8 <= lds_max_bytes;
 }
 bool blk_lds_fits(const Geom& g, int lds_max_bytes) { return g.eo && lds_fits(g.hvb, lds_max_bytes); }
 bool eo_lds_fits(const Geom& g, int lds_max_bytes) { return g.eo && lds_fits(g.V / 2, lds_max_bytes); }
 
+// Lanes per site.  More lanes issue more instructions for a site in all, and pay where they add no wavefronts (four
+// lanes on at most 16 sites) or where SIMDs are free for them (two).  One colour, 8 RHS, to 1e-10, one / two / four
+// lanes: 32x16^3, blocks of 8, 16, 32, 64 sites a parity 3.69 / 4.39 / 3.60, 2.24 / 2.59 / 2.16, 1.52 / 1.70 / 1.93,
+// 1.33 / 1.82 / 2.01 ms; 8^4, blocks of 16, 32, 64, 128 sites 0.326 / 0.287 / 0.280, 0.322 / 0.282 / 0.278, 0.338 / 0.303 /
+// 0.309, 0.389 / 0.345 / - ms.
+static int lanes_per_site(int hv, long long groups, unsigned n2) {
+    if (n2 >= 1u << 25) return 1;  // (the byte offsets over eight clover planes stay below 4 GiB)
+    if (4 * hv <= 64) return 4;
+    return 2 * hv <= BQ_THREADS && groups * ((hv + 63) / 64) <= 2 * CU_COUNT ? 2 : 1;
+}
+template <bool WRAP>
+static void launch_lds(hipStream_t st, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
+                       double2* xe, const double* bb, const double* rr, double mass4, double tol, double floor_eps,
+                       int maxit, int* iters, int colour, int nrhs) {
+    const int steps = maxit < (1 << 30) ? 2 * maxit : maxit;  // (a BiCGStab iteration, the unit of maxit, is two steps)
+    const int lanes = lanes_per_site(g.hvb, (long long)g.NBc * nrhs, F.n2);
+    auto k = lanes == 2 ? k_lds_lanes<WRAP, 2> : k_blk_lds<WRAP>;
+    if constexpr (!WRAP)  // (no lattice has that few sites)
+        if (lanes == 4) k = k_lds_lanes<false, 4>;
+    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
+    k<<<g.NBc * nrhs, (lanes * g.hvb + 63) / 64 * 64, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps, steps, iters,
+                                                               colour, nrhs);
+}
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                     double2* xe, const double* bb, const double* rr, double mass4, double tol,
                     int maxit, int* iters, int colour, int nrhs) {
     Timed t(e, 2, 0);
-    const int threads = ((g.hvb + 63) / 64) * 64;
-    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
     // the inner solve stops at this relative residual at the least (FP32's reach)
-    // (a BiCGStab iteration, the unit of maxit, is two steps)
-    k_blk_lds<false><<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6,
-                                                               maxit < (1 << 30) ? 2 * maxit : maxit, iters, colour, nrhs);
+    launch_lds<false>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6, maxit, iters, colour, nrhs);
 }
 void launch_eo_lds(Exec& e, Geom g, const EoFields<float>& F, const float4* Ainv, const double2* re, double2* xe,
                    const double* bb, const double* rr, double mass4, double tol, double floor_eps, int maxit, int* iters,
                    int nrhs) {
     Timed t(e, DDWC_K_DSLASH32, 0);
     g.hvb = g.V / 2, g.NBc = 1;
-    const int threads = ((g.hvb + 63) / 64) * 64;
-    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);
-    k_blk_lds<true><<<nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps,
-                                                      maxit < (1 << 30) ? 2 * maxit : maxit, iters, 0, nrhs);
+    launch_lds<true>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps, maxit, iters, 0, nrhs);
 }
 
 // ------------------------------------------------------------------ minimal residual in global memory

@@ -800,10 +800,13 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
             // ||r||^2 at the last poll and at the start of the window (1 after the scaling)
             std::vector<double> last(nrhs, 1.0), was(nrhs, 1.0);
             int in_window = 0, chunks = 1;
+            double need = 0;  // iterations that the slowest RHS still needs at the rate since the last poll
             while (total < maxit) {
                 int since = 0;
                 for (int k = 0; k < chunks && total < maxit; ++k) {
-                    const int it = std::min(poll, maxit - total);
+                    // (a cycle past the end costs as much as any: none where the rate says that fewer than poll remain)
+                    const int left = ls && need > 0 ? (int)fmin(fmax(1.0, ceil(need - 0.1)), poll) : poll;
+                    const int it = std::min(left, maxit - total);
                     if (gx && it == poll)
                         HC(hipGraphLaunch(gx, sm));
                     else
@@ -819,9 +822,9 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
                 in_window += since;
                 const bool window = ls && in_window >= LS_WINDOW;
                 const double gain = pow(LS_GAIN, 2.0 * in_window / LS_WINDOW);
-                // iterations that the slowest RHS still needs at the rate since the last poll; the next poll comes
-                // after half of them (a host round trip costs a small lattice as much as an iteration)
-                double need = 0;
+                // the next poll comes after half of the iterations needed (a host round trip costs a small lattice as much as
+                // an iteration)
+                need = 0;
                 for (int k = 0; k < nrhs; ++k) {
                     if (ls && (h_st[k].broken || (window && h_st[k].active && h_st[k].rr > gain * was[k]))) slow = true;
                     if (window) was[k] = h_st[k].rr;

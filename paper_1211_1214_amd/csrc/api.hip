@@ -949,7 +949,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     CK(ws_t(C, "be_iters", nb, &iters));
     HC(hipMemsetAsync(iters, 0, nb * sizeof(int), ex.stream));
     // (k_blk_recon writes this colour's solution and clears the other colour)
-    launch_blk_prep(ex, g, F64, A64, b64, bpe, re, xe, to, bb, rr, colour, nrhs);
+    launch_blk_prep(ex, g, F64, A64, b64, bpe, re, xe, to, bb, rr, colour, nrhs, C->lds_max);
     std::vector<double> hbb(nb), hrr(nb), was;
     std::vector<int> hit(nb);
     HC(hipMemcpyAsync(hbb.data(), bb, nb * sizeof(double), hipMemcpyDeviceToHost, ex.stream));
@@ -1010,7 +1010,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
             else
                 inner(eo_fields<float>(C));
         }
-        launch_blk_resid(ex, g, F64, A64, bpe, xe, re, th, rr, mass4, colour, nrhs);
+        launch_blk_resid(ex, g, F64, A64, bpe, xe, re, th, rr, mass4, colour, nrhs, C->lds_max);
     }
     // x_o = A_oo^-1 b_o + 1/2 A_oo^-1 H x_e from the prep and the last residual pass (x_e = 0 when
     // no inner solve ran)

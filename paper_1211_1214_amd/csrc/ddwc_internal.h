@@ -271,9 +271,11 @@ void launch_eo_diaghop(Exec& e, const EoFields<S>& F, int p, bool ri, int epi, b
 
 // ------------------------------------------------------------------ even-odd block solver (block_eo.hip)
 void launch_blk_prep(Exec& e, const Geom& g, const EoFields<double>& F, const double2* Ainv, const double2* b,
-                     double2* bpe, double2* re, double2* xe, double2* to, double* bb, double* rr, int colour, int nrhs);
+                     double2* bpe, double2* re, double2* xe, double2* to, double* bb, double* rr, int colour, int nrhs,
+                     int lds_max);
 void launch_blk_resid(Exec& e, const Geom& g, const EoFields<double>& F, const double2* Ainv, const double2* bpe,
-                      const double2* xe, double2* re, double2* to, double* rr, double mass4, int colour, int nrhs);
+                      const double2* xe, double2* re, double2* to, double* rr, double mass4, int colour, int nrhs,
+                      int lds_max);
 void launch_blk_recon(Exec& e, const Geom& g, const double2* to, const double2* th, const double2* xe, double2* x,
                       int colour, int nrhs);
 // Minimal residual with its vectors in global memory (slots 0, 4, 5, 6; r in LDS where it fits), for FP32

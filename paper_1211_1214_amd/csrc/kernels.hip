@@ -267,14 +267,19 @@ template <class R>
 __global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<R>* __restrict__ U,
                                             const typename Traits<R>::word* __restrict__ in,
                                             typename Traits<R>::word* __restrict__ out, int nrhs, int to_colour,
-                                            const int* __restrict__ nbr, int ndir, Ext4 cut, int cut_colour, int s0,
-                                            int s1) {
-    int s = s0 + blockIdx.x * blockDim.x + threadIdx.x;
-    int rhs = blockIdx.y;
-    if (s >= s1) return;
-    const size_t off = (size_t)rhs * Traits<R>::NCW * g.V;
+                                            const int* __restrict__ nbr, int ndir, Ext4 cut, int cut_colour,
+                                            bool both) {
+    // The RHS of a tile follow each other on one XCD, whose L2 then holds their links, and where both colours are
+    // written their tiles alternate, so that every XCD has as much of the hops as of the zeros.  48x24^3, 12 RHS: 901 ->
+    // 660 us; 64x32^3, 6 RHS: 1430 -> 1048 us; 32x16^3, 8 RHS: 146 -> 112 us (tiles of one RHS after another before).
+    const int nth = (g.V / 2 + WG - 1) / WG;
+    const TileRhs tr = tile_rhs(both ? 2 * nth : nth, nrhs);
+    const int colour = both ? tr.tile & 1 : to_colour, i = (both ? tr.tile >> 1 : tr.tile) * WG + (int)threadIdx.x;
+    if (i >= g.V / 2) return;
+    const int s = colour * (g.V / 2) + i;
+    const size_t off = (size_t)tr.rhs * Traits<R>::NCW * g.V;
     cx<R> y[12];
-    bool keep = (s / (g.V / 2)) == to_colour;
+    bool keep = colour == to_colour;
     if (keep && cut_colour >= 0) {  // output cut to the outer blocks (extents cut) of one colour
         const Site S = decode(g, s);
         int sum = 0;
@@ -299,9 +304,8 @@ void launch_hop(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>
     Timed t(e, 4, 0);
     const Ext4 c = cut ? *cut : Ext4{{1, 1, 1, 1}};
     // the sites of colour c are [c V/2, (c + 1) V/2) of the colour-major full index
-    const int s0 = clear_other ? 0 : to_colour * (g.V / 2), s1 = clear_other ? g.V : s0 + g.V / 2;
-    k_hop<R><<<dim3(tiles_of(s1 - s0), nrhs), WG, 0, e.stream>>>(g, U, in, out, nrhs, to_colour, e.nbr, 8, c,
-                                                                 cut ? cut_colour : -1, s0, s1);
+    k_hop<R><<<tiles_of(g.V / 2) * (clear_other ? 2 : 1) * nrhs, WG, 0, e.stream>>>(g, U, in, out, nrhs, to_colour, e.nbr, 8,
+                                                                                 c, cut ? cut_colour : -1, clear_other);
 }
 
 // ------------------------------------------------------------------ BiCGStab vector kernels

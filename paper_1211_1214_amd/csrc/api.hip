@@ -593,7 +593,7 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     typedef typename Traits<S>::kword KW;
     const Geom& g = C->g;
     const bool fp64 = std::is_same<S, double>::value, h16 = std::is_same<S, H16>::value;
-    const EoFields<double> F64 = eo_fields<double>(C);
+    EoFields<double> F64 = eo_fields<double>(C);
     const unsigned n2 = F64.n2;
     Geom gh = g;  // geometry of the half fields for the vector kernels (only V is used)
     gh.V = (int)n2;
@@ -605,7 +605,16 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     const bool ri = h16 || (nrhs > 1 && nrhs <= WG && ri_fits(n2, nrhs));
     EoFields<S> FR = eo_fields<S>(C, ri && !fp64);  // RI kernels read own-site link records
     const double rs = h16 ? 52.0 : 24.0 * sizeof(R);  // bytes of a stored spinor
-    if (ri && g.eo && C->opt_tile_order == 1) CK(tile_order(C, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs * nrhs, &FR.order));
+    if (g.eo && C->opt_tile_order == 1) {
+        if (ri) CK(tile_order(C, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs * nrhs, &FR.order));
+        // RHS-major kernels take the order for one RHS: 32x16^3 in FP64 (both parities in the last-level cache) hop-and-
+        // inverse 38.6 -> 24.9, diagonal-and-hop 39.2 -> 30.6 us.  With 12 RHS, whose tiles of sites are dispatched
+        // together, it costs 9% (48x24^3, diagonal-and-hop 1275 -> 1393 us); on 16^4 it gives nothing (FP32 solve 1.57 ->
+        // 1.60 ms).
+        const bool one = nrhs == 1 && g.V >= 1 << 17;
+        if (one) CK(tile_order(C, 1, 1, WG, 192.0, &F64.order));
+        if (one && !ri) CK(tile_order(C, 1, 1, WG, rs, &FR.order));
+    }
     const int ntR = vector_tiles(n2, nrhs, ri);
     const int ntM = eo_op_tiles(FR, nrhs, ri);  // tiles of the operator kernels' partial sums
     const double mass4 = 4.0 + mass;

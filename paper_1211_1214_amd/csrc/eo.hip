@@ -366,7 +366,7 @@ void launch_eo_hopinv(Exec& e, const EoFields<S>& F, int p, bool ri, const typen
     const int nt = eo_op_tiles(F, nrhs, ri);
     if constexpr (!std::is_same<S, H16>::value) if (!ri) {  // (FP16 fields are always RHS-innermost)
         k_eo_hopinv<S, false, false, WG><<<nt * nrhs, WG, 0, e.stream>>>(F.n2, x, c, (R)alpha, F.U[p], F.U[1 - p],
-                                                                         F.nbr[p], Ainv, y, nrhs, nt, nullptr);
+                                                                         F.nbr[p], Ainv, y, nrhs, nt, F.order);
         return;
     }
     const bool stg = stage_ok<S>(F.n2, nrhs);
@@ -403,7 +403,7 @@ void launch_eo_diaghop(Exec& e, const EoFields<S>& F, int p, bool ri, int epi, b
         }
         k_eo_diaghop<S, EP, UA, RIV, false, NT><<<ng, NT, 0, e.stream>>>(
                 F.n2, c, tv, (R)beta, F.U[p], F.U[1 - p], F.nbr[p], F.K[p], (R)mass4, aux, y, part, nrhs, nt,
-                RIV ? F.order : nullptr);
+                F.order);
     };
     typedef std::integral_constant<bool, true> T_;
     typedef std::integral_constant<bool, false> F_;

@@ -53,15 +53,15 @@ struct VItem {
 };
 
 // NT: threads per workgroup of an RHS-innermost kernel (the RHS-major path always uses WG).
-// order (RI, may be null): the tile each dispatch slot processes, after the XCD remap.
+// order (may be null): the tile each dispatch slot processes, after the XCD remap.
 template <bool RI, int NT = WG>
 __device__ __forceinline__ VItem vitem(unsigned n, int nrhs, int ntiles, const int* __restrict__ order = nullptr) {
     VItem it;
     if (!RI) {
         const TileRhs tr = tile_rhs(ntiles, nrhs);
-        it.tile = tr.tile;
+        it.tile = order ? order[tr.tile] : tr.tile;
         it.r = tr.rhs;
-        it.i = tr.tile * WG + threadIdx.x;
+        it.i = it.tile * WG + threadIdx.x;
         it.ok = it.i < n;
         it.g0 = 0;
     } else {

@@ -72,8 +72,8 @@ __host__ __device__ __forceinline__ size_t slab_words(unsigned n2) {
 // Direction loop of the in-block hops (hop_sum): unrolled for FP64 and FP32 storage, rolled for
 // FP16 (unrolled it spills).
 template <class S>
-constexpr int blk_hop_mode() {
-    return std::is_same<S, H16>::value ? 0 : 2;
+constexpr bool blk_hop_unroll() {
+    return !std::is_same<S, H16>::value;
 }
 
 template <class S>
@@ -83,7 +83,7 @@ __device__ __forceinline__ void odd_pass(unsigned n2, unsigned j, const typename
                                          cx<typename Traits<S>::real> w[12]) {
     typedef typename Traits<S>::real R;
     cx<R> acc[12];
-    hop_sum<R, HOPS_INSIDE, blk_hop_mode<S>()>(n2, j, x, F.U[1], F.U[0], F.nbr[1], acc, 8);
+    hop_sum<R, HOPS_INSIDE, blk_hop_unroll<S>()>(n2, j, x, F.U[1], F.U[0], F.nbr[1], acc, 8);
     if (c) {
         cx<R> cc[12];
         load_spinor(c, n2, j, cc);
@@ -106,7 +106,7 @@ __device__ __forceinline__ void even_pass(unsigned n2, unsigned i, const typenam
                                           cx<typename Traits<S>::real> y[12]) {
     typedef typename Traits<S>::real R;
     cx<R> cc[12];
-    hop_sum<R, HOPS_INSIDE, blk_hop_mode<S>()>(n2, i, t, F.U[0], F.U[1], F.nbr[0], y, 8);
+    hop_sum<R, HOPS_INSIDE, blk_hop_unroll<S>()>(n2, i, t, F.U[0], F.U[1], F.nbr[0], y, 8);
     load_spinor(c, n2, i, cc);
     if (USE_A) {
         apply_diag<R>(F.K[0], n2, i, mass4, cc, y, beta);
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(BE_MAX_THREADS) void k_blk_prep(Geom g, EoFields<do
         cx<double> be[12], y[12], z[12];
         load_spinor(b + of, g.V, s, be);
         red[0] += acc_nrm(be);
-        hop_sum<double, HOPS_INSIDE, 2>(n2, i, to + oh, F.U[0], F.U[1], F.nbr[0], y, 8);
+        hop_sum<double, HOPS_INSIDE, true>(n2, i, to + oh, F.U[0], F.U[1], F.nbr[0], y, 8);
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             y[c] = be[c] + 0.5 * y[c];

@@ -307,47 +307,6 @@ DDWC_HD void load_link(const cx<L>* __restrict__ U, unsigned V, int mu, unsigned
     }
 }
 
-// Site-major links [n][4][9]: the four forward links of a site are one contiguous record, so the
-// lanes of a site (RHS-innermost kernels) read whole cache lines at once.
-template <bool SITE_MAJOR, class R, class L>
-DDWC_HD void load_link_l(const cx<L>* __restrict__ U, unsigned V, int mu, unsigned s, cx<R> u[9]) {
-    if (!SITE_MAJOR) {
-        load_link(U, V, mu, s, u);
-        return;
-    }
-    const cx<L>* p = U + ((size_t)s * 4 + mu) * 9;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const cx<L> w = p[k];
-        u[k] = mk((R)w.re, (R)w.im);
-    }
-}
-
-// Link layouts of the hop kernels: LK_ENTRY entry-major [4][9][n] (forward links at s from Uf,
-// backward links at the neighbour t from Ub), LK_SITE site-major [n][4][9] (same roles),
-// LK_OWN own-site records [n][8][9] of Uf: for each site the eight links its hops use, d = 2 mu
-// holding U_mu(x) and d = 2 mu + 1 holding U_mu(x - mu), so that every hop reads its link from
-// the site's own contiguous record (no gather of backward links).
-enum LinkLayout { LK_ENTRY = 0, LK_SITE = 1, LK_OWN = 2 };
-
-template <int LK, class R, class L>
-DDWC_HD void hop_link(const cx<L>* __restrict__ Uf, const cx<L>* __restrict__ Ub, unsigned n, int d, unsigned s,
-                      unsigned t, cx<R> u[9]) {
-    if (LK == LK_OWN) {
-        const cx<L>* p = Uf + ((size_t)s * 8 + d) * 9;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const cx<L> w = p[k];
-            u[k] = mk((R)w.re, (R)w.im);
-        }
-        return;
-    }
-    if (d & 1)
-        load_link_l<LK == LK_SITE>(Ub, n, d >> 1, t, u);
-    else
-        load_link_l<LK == LK_SITE>(Uf, n, d >> 1, s, u);
-}
-
 // FP16 spinors: words k = 0..2 hold complex 4k .. 4k + 3; the scale plane follows the three
 // word planes of the field (f is the field base, `stride` its plane length).
 DDWC_HD float* scale_plane(hw16* f, unsigned stride) { return (float*)(f + 3 * (size_t)stride); }
@@ -586,111 +545,52 @@ DDWC_HD int table_entry(const Geom& g, int s, const Site& S, int mu) {
 }
 
 // Which hops a site operator includes.
-enum HopSet { HOPS_NONE = 0, HOPS_ALL = 1, HOPS_INSIDE = 2, HOPS_CROSSING = 3 };
+enum HopSet { HOPS_ALL = 1, HOPS_INSIDE = 2, HOPS_CROSSING = 3 };
 
 // acc = sum over the selected hops of site s of (1 -+ g_mu) W psi(neighbour), unscaled; a
 // hop across an antiperiodic time boundary is subtracted.  The index space has length n
 // (V for full fields, V/2 for even-odd half fields); nbr is its neighbour table [8][n];
-// forward links are read from Uf at s, backward links from Ub at the neighbour.  Both
+// forward links ([4][9][n]) are read from Uf at s, backward links from Ub at the neighbour.  Both
 // index spaces are colour-major, so a neighbour lies in the same Schwarz block exactly
 // when it lies in the same half.  `ndir` is 8; it is a run-time value so that the
 // direction loop stays a loop and only one neighbour spinor and link are live at a time.
-// PIPE 1: the next direction's spinor and link loads are issued before the current one is
-// computed.  PIPE 2: the direction loop is unrolled (no pipelining): the spin algebra of each
-// direction is then straight-line code instead of a switch whose merge copies the accumulator
-// (24 moves per hop); for hop sets with a per-hop condition (inside / crossing), whose branches
-// keep the scheduler from hoisting every direction's loads.  (With HOPS_ALL the unrolled loop
-// hoists them all: 256 VGPRs.)
-//
-// Spinors may be stored RHS-innermost: the spinor of site t is element t * smul + sadd of
-// component arrays sstride apart (RHS-major: smul = 1, sadd = 0, sstride = n).  Links are
-// in the layout LK (LinkLayout; Uf's own-site records with LK_OWN).
-// With LK_OWN the records may be a staged copy (in LDS) that starts at site `l0`: the record of
-// s is then record s - l0 of Uf.  With nstr > 0 the neighbour table is a staged copy too,
-// [8][nstr] entries starting at site l0.
-template <class R, int HOPS, int PIPE, int LK = LK_ENTRY, class W, class L>
+// UNROLL: the direction loop is unrolled: the spin algebra of each direction is then straight-line code
+// instead of a switch whose merge copies the accumulator (24 moves per hop); for hop sets with a per-hop
+// condition (inside / crossing), whose branches keep the scheduler from hoisting every direction's
+// loads.  (Kernels that take every hop pipeline them: hops_pipelined.)
+template <class R, int HOPS, bool UNROLL, class W, class L>
 DDWC_HD void hop_sum(unsigned n, unsigned s, const W* __restrict__ in, const cx<L>* __restrict__ Uf,
-                     const cx<L>* __restrict__ Ub, const int* __restrict__ nbr, cx<R> acc[12], int ndir,
-                     unsigned smul = 1, unsigned sadd = 0, unsigned sstride = 0, unsigned l0 = 0,
-                     unsigned nstr = 0) {
-    if (sstride == 0) sstride = n;
-    const unsigned sl = s - l0;  // record index of s (LK_OWN)
-    const unsigned ns = nstr ? nstr : n, sn = nstr ? sl : s;  // table stride and index of s
+                     const cx<L>* __restrict__ Ub, const int* __restrict__ nbr, cx<R> acc[12], int ndir) {
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = mk(R(0), R(0));
-    if (HOPS == HOPS_NONE) return;
     const bool s_black = s < n / 2;
-    if (PIPE == 0 || PIPE == 2) {
-#pragma unroll(PIPE == 2 ? 8 : 1)
-        for (int d = 0; d < (PIPE == 2 ? 8 : ndir); ++d) {
-            const int e = at(nbr + (size_t)d * ns, sn);
-            const unsigned t = e < 0 ? (unsigned)~e : (unsigned)e;
-            const bool inside = (t < n / 2) == s_black;
-            const bool take = HOPS == HOPS_ALL || (HOPS == HOPS_INSIDE && inside) || (HOPS == HOPS_CROSSING && !inside);
-            if (take) {
-                cx<R> q[12], u[9];
-                load_spinor(in, sstride, t * smul + sadd, q);
-                hop_link<LK>(Uf, Ub, n, d, LK == LK_OWN ? sl : s, t, u);
-                if (e < 0) {
+#pragma unroll(UNROLL ? 8 : 1)
+    for (int d = 0; d < (UNROLL ? 8 : ndir); ++d) {
+        const int e = at(nbr + (size_t)d * n, s);
+        const unsigned t = e < 0 ? (unsigned)~e : (unsigned)e;
+        const bool inside = (t < n / 2) == s_black;
+        const bool take = HOPS == HOPS_ALL || (HOPS == HOPS_INSIDE && inside) || (HOPS == HOPS_CROSSING && !inside);
+        if (take) {
+            cx<R> q[12], u[9];
+            load_spinor(in, n, t, q);
+            load_link((d & 1) ? Ub : Uf, n, d >> 1, (d & 1) ? t : s, u);
+            if (e < 0) {
 #pragma unroll
-                    for (int c = 0; c < 12; ++c) q[c] = -q[c];
-                }
-                hop_dispatch<R>(d, u, q, acc);
+                for (int c = 0; c < 12; ++c) q[c] = -q[c];
             }
-        }
-    } else {
-        // all eight table entries first, then a software-pipelined direction loop: the
-        // neighbour spinor and link of direction d + 1 are in flight while d is computed
-        int ent[8];
-#pragma unroll
-        for (int d = 0; d < 8; ++d) ent[d] = at(nbr + (size_t)d * ns, sn);
-        cx<R> q[12], u[9];
-        {
-            const int e = ent[0];
-            const unsigned t0 = e < 0 ? (unsigned)~e : (unsigned)e;
-            load_spinor(in, sstride, t0 * smul + sadd, q);
-            hop_link<LK>(Uf, Ub, n, 0, LK == LK_OWN ? sl : s, t0, u);
-        }
-#pragma unroll 1
-        for (int d = 0; d < ndir; ++d) {
-            int e = ent[0];
-#pragma unroll
-            for (int k = 1; k < 8; ++k) e = d == k ? ent[k] : e;
-            const unsigned t = e < 0 ? (unsigned)~e : (unsigned)e;
-            const bool inside = (t < n / 2) == s_black;
-            const bool take = HOPS == HOPS_ALL || (HOPS == HOPS_INSIDE && inside) || (HOPS == HOPS_CROSSING && !inside);
-            cx<R> qn[12], un[9];
-            if (d + 1 < ndir) {
-                int en = ent[1];
-#pragma unroll
-                for (int k = 2; k < 8; ++k) en = d + 1 == k ? ent[k] : en;
-                const unsigned tn = en < 0 ? (unsigned)~en : (unsigned)en;
-                load_spinor(in, sstride, tn * smul + sadd, qn);
-                hop_link<LK>(Uf, Ub, n, d + 1, LK == LK_OWN ? sl : s, tn, un);
-            }
-            if (take) {
-                if (e < 0) {
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) q[c] = -q[c];
-                }
-                hop_dispatch<R>(d, u, q, acc);
-            }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) q[c] = qn[c];
-#pragma unroll
-            for (int c = 0; c < 9; ++c) u[c] = un[c];
+            hop_dispatch<R>(d, u, q, acc);
         }
     }
 }
 
 // y = [diag] (4+m+C) psi(s) - 1/2 sum over the selected hops, on full fields.  `in`
 // points at one RHS, nbr is the neighbour table [8][V].
-template <class R, bool DIAG, int HOPS, int PIPE = 0>
+template <class R, bool DIAG, int HOPS, bool UNROLL = false>
 DDWC_HD void site_operator(const Geom& g, unsigned s, const typename Traits<R>::word* __restrict__ in,
                            const cx<R>* __restrict__ U, const typename Traits<R>::word* __restrict__ K,
                            const int* __restrict__ nbr, R mass4, cx<R> y[12], int ndir) {
     const unsigned V = g.V;
-    hop_sum<R, HOPS, PIPE>(V, s, in, U, U, nbr, y, ndir);
+    hop_sum<R, HOPS, UNROLL>(V, s, in, U, U, nbr, y, ndir);
     if (DIAG) {
         cx<R> c[12];
         load_spinor(in, V, s, c);

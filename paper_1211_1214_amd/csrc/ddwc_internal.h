@@ -87,7 +87,7 @@ inline int tiles_of(int n) { return (n + WG - 1) / WG; }
 
 // Links to the internal layouts: U64, U32 entry-major [4][9][V].
 void launch_links_import(Exec& e, const Geom& g, const void* canon, cx<double>* U64, cx<float>* U32);
-// Own-site link records [n][8][9] (LK_OWN) of n sites from entry-major forward links Uf ([4][9][n])
+// Own-site link records [n][8][9] of n sites from entry-major forward links Uf ([4][9][n])
 // and Ub (the neighbours', [4][9][n]) and the table nbr [8][n].
 void launch_links_own(Exec& e, unsigned n, const cx<float>* Uf, const cx<float>* Ub, const int* nbr,
                       cx<float>* Lown);
@@ -246,7 +246,7 @@ void launch_links_to_half(Exec& e, size_t n, const cx<float>* src, cx<f16>* dst)
 // Half-field links: entry-major Uh64, Uh32 [2][4][9][V/2].
 void launch_eo_setup(Exec& e, const Geom& g, const cx<double>* U64, const double2* K64, const int* nbr,
                      cx<double>* Uh64, cx<float>* Uh32, double2* Kh64, float4* Kh32, int* nbr_eo);
-// Own-site link records [2][V/2][8][9] (LK_OWN) read by the RHS-innermost kernels of the global
+// Own-site link records [2][V/2][8][9] read by the RHS-innermost kernels of the global
 // solver, from Uh32 and the half-field neighbour tables.
 void launch_eo_links_own(Exec& e, unsigned n2, const cx<float>* Uh32, const int* nbr_eo, cx<float>* Lown);
 // Packed links (uniform_mem.h) [2][4][V/2] read by the block solvers, from the entry-major Uh.

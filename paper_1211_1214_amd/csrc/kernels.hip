@@ -40,7 +40,7 @@ void launch_links_import(Exec& e, const Geom& g, const void* canon, cx<double>* 
     k_links_import<<<grid, WG, 0, e.stream>>>(g, (const double2*)canon, U64, U32);
 }
 
-// Own-site link records [n][8][9] (LK_OWN) of n sites: hop d = 2 mu takes U_mu(x), the site's own
+// Own-site link records [n][8][9] of n sites: hop d = 2 mu takes U_mu(x), the site's own
 // forward link from Uf ([4][9][n]); d = 2 mu + 1 takes U_mu(x - mu), the forward link of the
 // neighbour from Ub ([4][9][*], index from the table nbr [8][n]; the time-boundary sign stays with
 // the table entry).  Full lattice: Uf = Ub, one table; even-odd: the two parities' half fields.
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<R>* __restrict__ U,
     }
     if (keep) {
         // unrolled: 138 VGPRs in FP64 against 256 and AGPRs for the pipelined loop
-        site_operator<R, false, HOPS_CROSSING, 2>(g, s, in + off, U, nullptr, nbr, R(0), y, ndir);
+        site_operator<R, false, HOPS_CROSSING, true>(g, s, in + off, U, nullptr, nbr, R(0), y, ndir);
     } else {
 #pragma unroll
         for (int k = 0; k < 12; ++k) y[k] = mk(R(0), R(0));

@@ -4,7 +4,7 @@
 One step = one pass of the whole hot path over one batch: the Schur-complement
 estimator of Eq. (8) on the 48x24^3 lattice with 6^4 Schwarz blocks, all 12 noise
 vectors of the step as one multi-RHS batch: D_wb hop, four persistent block sweeps,
-D_bw hops, projector, one global mixed-precision solve (FP32 BiCGStab inside FP64
+D_bw hops, projector, one global mixed-precision solve (FP32 minimal residual inside FP64
 defect correction), the FP64 reductions for x_ij and the log-domain combination.
 Inputs (synthetic links, complex Gaussian noise) are resident in HBM before timing.
 
@@ -66,7 +66,7 @@ def main():
     ap.add_argument("--one-flavour", action="store_true",
                     help="time the one-flavour estimator (Eq. 11) instead (48x24^3)")
     ap.add_argument("--solver", choices=("bicgstab", "sap-gcr"), default="bicgstab",
-                    help="global solver: even-odd BiCGStab or GCR preconditioned by Schwarz sweeps")
+                    help="global solver: even-odd Krylov or GCR preconditioned by Schwarz sweeps")
     ap.add_argument("--block-kernel", choices=("auto", "global"), default="auto",
                     help="Schwarz block inner solver: LDS-resident where it fits (auto) or the global-memory kernel")
     ap.add_argument("--dslash-reps", type=int, default=20, help="launches per standalone Dslash measurement")

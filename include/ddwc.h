@@ -61,8 +61,8 @@ typedef enum {
  * and of the even-odd Schwarz block solver keeps its vectors in FP16 with one FP32 scale per
  * site and RHS, and its links in FP16 (clover, arithmetic and the solution correction in
  * FP32; FP64 defect correction restores the tolerance).  ddwc_dslash_apply, lattices with an
- * odd block extent, and block solves on blocks that the LDS-resident inner kernel takes
- * (DDWC_OPT_BLOCK_KERNEL) run as DDWC_MIXED32.  At most 256 RHS per call in the global solver. */
+ * odd block extent, and block solves on blocks, or global solves on lattices, whose parity the
+ * LDS-resident inner kernel takes (DDWC_OPT_BLOCK_KERNEL) run as DDWC_MIXED32.  At most 256 RHS per call in the global solver. */
 typedef enum { DDWC_FP64 = 0, DDWC_MIXED32 = 1, DDWC_MIXED16 = 2 } ddwc_precision;
 typedef enum { DDWC_BLACK = 0, DDWC_WHITE = 1 } ddwc_colour;
 typedef enum { DDWC_OP_FULL = 0, DDWC_OP_SCHUR = 1 } ddwc_operator;
@@ -113,7 +113,8 @@ int ddwc_dslash_apply_noalloc(ddwc_ctx *ctx, double kappa, const void *in, void 
  * Dirichlet block operators on the diagonal, Sec. 1).  Only sites of that colour
  * are read; the other colour of sol is set to zero.  One persistent launch: one
  * workgroup per (block, rhs) iterates to ||r_k|| <= tol ||b_k|| for its own block.
- * prec = DDWC_MIXED32 runs FP32 BiCGStab inside FP64 defect correction.
+ * prec = DDWC_MIXED32 runs FP32 minimal residual inside FP64 defect correction, and BiCGStab where
+ * that converges slowly.
  */
 int ddwc_block_solve(ddwc_ctx *ctx, int colour, double kappa, const void *rhs, void *sol, int nrhs, double tol,
                      int maxit, int prec, ddwc_stats *stats, void *stream);
@@ -262,10 +263,13 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *                          a captured HIP graph (cached per buffer set and mass; not while
  *                          profiling); 0: launches them one by one.  Default 1.
  *   DDWC_OPT_POLL          iterations per chunk, [1, 64]; default 2.  The host checks convergence
- *                          after one or more chunks, as far ahead as the rate so far allows.
- *   DDWC_OPT_BLOCK_THREADS workgroup size of the Schwarz block kernels: 0 (enough waves for one
- *                          block parity, at most 768 for the FP32/FP16 inner solver and 256 for
- *                          the FP64 kernels) or a multiple of 64 in [64, 768] (capped alike).
+ *                          after one or more chunks, as far ahead as the rate so far allows, and
+ *                          launches fewer where the rate says that fewer remain.
+ *   DDWC_OPT_BLOCK_THREADS workgroup size of the Schwarz block kernels that loop over a block parity:
+ *                          0 (enough waves for one parity, at most 1024 for the global-memory minimal
+ *                          residual, 768 for the FP32/FP16 BiCGStab and 256 for the FP64 kernels) or
+ *                          a multiple of 64 in [64, 768] (capped alike).  The LDS-resident solver, and
+ *                          the FP64 passes on parities of at most 768 sites, take a thread per site.
  *   DDWC_OPT_SOLVER        global solver: 0 even-odd (default): two-step minimal residual, changing
  *                          over to BiCGStab where that converges faster, 1 GCR (8 directions per cycle, restarted with
  *                          the exact FP64 residual) preconditioned by the Schwarz alternating
@@ -277,14 +281,16 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *   DDWC_OPT_BLOCK_KERNEL  inner solver of the even-odd Schwarz block solves in DDWC_MIXED32 and
  *                          DDWC_MIXED16: 0 (default) the LDS-resident FP32 kernel wherever a block
  *                          parity has at most 768 sites and its two staged fields fit the LDS (both
- *                          precisions then run it, FP32 storage); 1 the global-memory kernel.
+ *                          precisions then run it, FP32 storage); 1 the global-memory kernels
+ *                          (minimal residual, BiCGStab where that converges slowly).
  *   DDWC_OPT_INNER_FLOOR   the FP32 inner solver of the even-odd global solver (DDWC_MIXED32) stops
  *                          at a relative residual of at least value x 1e-8 before the FP64 defect
  *                          correction restarts it, in [1, 100000]; default 200 (2e-6).
  *   DDWC_OPT_OP_THREADS    workgroup size of the RHS-innermost operator kernels (the even-odd
  *                          global solver's, and ddwc_dslash_apply's with several FP32 RHS): 128,
  *                          256 (default) or 512; a value below the RHS count runs 256.
- *   DDWC_OPT_TILE_ORDER    dispatch order of those kernels' workgroups: 0 site index order;
+ *   DDWC_OPT_TILE_ORDER    dispatch order of those kernels' workgroups, and of the operator's with one
+ *                          RHS on lattices from 2^17 sites: 0 site index order;
  *                          1 (default, with every block extent even) time slice by time slice
  *                          through spatial columns of blocks, so that an XCD finds neighbours
  *                          in its L2 (not in ddwc_dslash_apply_noalloc, which builds no order

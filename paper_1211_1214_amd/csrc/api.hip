@@ -533,7 +533,7 @@ static int get_ainv(ddwc_ctx* C, Exec& ex, double mass4, const double2** a64, co
     return DDWC_OK;
 }
 
-// D(m) x = b with even-odd preconditioning: BiCGStab in precision R on
+// D(m) x = b with even-odd preconditioning: two-step minimal residual or BiCGStab in precision R on
 // Mee = A_ee - 1/4 H_eo A_oo^-1 H_oe inside FP64 defect correction, then
 // x_o = A_oo^-1 (b_o + 1/2 H_oe x_e).  The FP64 residual of the even system equals the
 // residual of the full system, so the stopping rule is ||b'_e - Mee x_e|| <= tol ||b||.
@@ -901,8 +901,8 @@ struct BlockInfo {
     long long block_iters = 0;  // summed over blocks and RHS
 };
 
-// Floating-point operations of one inner BiCGStab iteration of a block solve, per even site (eo)
-// or per block site: two applications of the block operator, each a pass over both parities
+// Floating-point operations of one inner iteration of a block solve (two minimal-residual steps or one of
+// BiCGStab), per even site (eo) or per block site: two applications of the block operator, each a pass over both parities
 // (eo) or one full pass, with 180 flops per hop term (spin projection, two 3x3 complex
 // products, reconstruction) over the hops that stay inside the block (2 sum_mu (b_mu - 1)/b_mu
 // per site on average) and 540 per site for the two packed Hermitian 6x6 blocks, plus about 400

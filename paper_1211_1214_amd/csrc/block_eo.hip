@@ -6,11 +6,13 @@
 // H^k the hops inside block k.  Every kernel here runs one workgroup per (block, RHS); the
 // block's even and odd sites occupy the same contiguous range of the two half fields.
 //   k_blk_prep    FP64: b'_e, r_e = b'_e, x_e = 0, ||b_k||^2, ||r_e||^2
-//   k_blk_lds, k_blk_mr   persistent minimal residual in FP32 (FP16 storage) on M_k for r_e / ||r_e||, adds
+//   k_blk_lds, k_lds_lanes, k_blk_mr   persistent minimal residual in FP32 (FP16 storage) on M_k for r_e / ||r_e||, adds
 //                 the correction to x_e in FP64 (blocks already converged return at once)
 //   k_blk_inner   the same by BiCGStab: FP64, and where minimal residual converges slowly
 //   k_blk_resid   FP64: r_e = b'_e - M_k x_e and ||r_e||^2 (defect correction)
 //   k_blk_recon   FP64: x_o, and (x_e, x_o) written to the full solution
+// k_blk_prep_lds and k_blk_resid_lds are the FP64 passes of blocks whose parity fits the LDS.  The LDS-resident solvers
+// also take whole small lattices as one block (WRAP) for the global solver.
 #include <algorithm>
 #include <type_traits>
 
@@ -61,7 +63,6 @@ __device__ __forceinline__ BlkIdx blk_idx(const Geom& g, int colour, int nrhs) {
     return b;
 }
 
-// Ainv (c + alpha H^k x) at odd half site j (x even), into y (odd).
 // Storage S (double, float or H16; arithmetic in Traits<S>::real).  A vector of one RHS is a
 // slab of slab_words<S>(n2) words: the word planes and, for H16, the plane of site scales.
 template <class S>
@@ -76,6 +77,7 @@ constexpr bool blk_hop_unroll() {
     return !std::is_same<S, H16>::value;
 }
 
+// Ainv (c + alpha H^k x) at odd half site j (x even).
 template <class S>
 __device__ __forceinline__ void odd_pass(unsigned n2, unsigned j, const typename Traits<S>::word* x,
                                          const typename Traits<S>::word* c, typename Traits<S>::real alpha,

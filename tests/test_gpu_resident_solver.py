@@ -28,7 +28,9 @@ def test_resident_solve(lat, blk, bc, prec):
     b = inputs.make_spinor(lat, 34, nrhs=5)
     b[1] = 0
     b[3] *= 1e-3
-    slow = ((0.133, 5),) if bc < 0 else ()  # (there the oracle does not converge on periodic lattices)
+    # (0.133 is so close to critical on 12x8x4x4, 1000 iterations and more, and beyond it on periodic lattices, that the
+    # oracle's own solve does not always converge there: 85 iterations at 0.126)
+    slow = () if bc > 0 else ((0.128 if lat == (12, 8, 4, 4) else 0.133, 5),)
     for kappa, nrhs in ((0.121, 5), (0.121, 1)) + slow:
         print("resident", lat, bc, prec, kappa, nrhs, flush=True)
         x, st = ctx.solve(kappa, torch.from_numpy(b[:nrhs].copy()).cuda(), tol=1e-12, prec=prec)

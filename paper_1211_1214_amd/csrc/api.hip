@@ -929,7 +929,8 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     const EoFields<double> F64 = eo_fields<double>(C);
     const unsigned n2 = F64.n2;
     // blocks whose parity fits the LDS-resident kernel run it in FP32 for both low precisions
-    bool lds = !fp64 && C->opt_blk_kernel == 0 && blk_lds_fits(g, C->lds_max), mr = !fp64;
+    bool lds = !fp64 && C->opt_blk_kernel == 0 && blk_lds_fits(g, C->lds_max);
+    bool mr = !fp64 && (lds || blk_mr_fits(g, C->lds_max));
     const bool h16 = prec == DDWC_MIXED16 && !lds;
     const size_t hw64 = (size_t)nrhs * 12 * n2;
     // the correction vector (slot 5) is kept in FP32 when the others are FP16
@@ -1019,6 +1020,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
             else
                 inner(eo_fields<float>(C));
         }
+        HC(hipGetLastError());
         launch_blk_resid(ex, g, F64, A64, bpe, xe, re, th, rr, mass4, colour, nrhs, C->lds_max);
     }
     // x_o = A_oo^-1 b_o + 1/2 A_oo^-1 H x_e from the prep and the last residual pass (x_e = 0 when

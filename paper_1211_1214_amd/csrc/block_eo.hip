@@ -1381,6 +1381,9 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
     if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
 }
 
+static size_t mr_mask_bytes(const Geom& g) { return ((size_t)2 * g.hvb * sizeof(unsigned short) + 15) / 16 * 16; }
+// (at most 40448 sites of a parity with 160 KB: larger blocks run k_blk_inner, which uses no LDS for a block's sites)
+bool blk_mr_fits(const Geom& g, int lds_max) { return g.eo && mr_mask_bytes(g) + 2 * 8 * 16 * 8 <= (size_t)lds_max; }
 template <class S>
 void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* Ainv, const double2* re, double2* xe,
                    void* const w[7], const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
@@ -1388,7 +1391,7 @@ void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* A
     Timed t(e, 2, 0);
     typedef typename Traits<S>::word W;
     const int threads = block_threads_for(g, e.blk_threads, BM_MAX);
-    const size_t masks = ((size_t)2 * g.hvb * sizeof(unsigned short) + 15) / 16 * 16;
+    const size_t masks = mr_mask_bytes(g);
     const size_t recs = (size_t)g.hvb * (std::is_same<S, H16>::value ? 52 : 96);
     const bool rlds = masks + recs + 2 * 8 * 16 * 8 <= (size_t)lds_max;
     const size_t lds = std::max(rlds ? masks + recs : masks, std::min((size_t)e.blk_lds << 10, (size_t)lds_max - 2 * 8 * 16 * 8));

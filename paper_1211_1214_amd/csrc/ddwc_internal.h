@@ -279,7 +279,9 @@ void launch_blk_resid(Exec& e, const Geom& g, const EoFields<double>& F, const d
 void launch_blk_recon(Exec& e, const Geom& g, const double2* to, const double2* th, const double2* xe, double2* x,
                       int colour, int nrhs);
 // Minimal residual with its vectors in global memory (slots 0, 4, 5, 6; r in LDS where it fits), for FP32
-// and FP16 on blocks that the LDS-resident solver does not take.
+// and FP16 on blocks that the LDS-resident solver does not take: whether it takes this geometry (the hop masks
+// of a block lie in LDS), and its launch.
+bool blk_mr_fits(const Geom& g, int lds_max_bytes);
 template <class S>
 void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* Ainv, const double2* re, double2* xe,
                    void* const w[7], const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,

@@ -716,9 +716,9 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     // blocks.)
     bool resident = !fp64 && eo_lds_fits(g, C->lds_max);
     int* iters = nullptr;
-    if (resident) {
-        CK(ws_t(C, "eo_iters", (size_t)nrhs, &iters));
-        HC(hipMemsetAsync(iters, 0, sizeof(int) * nrhs, sm));
+    if (resident) {  // (iterations, and the marks of slow convergence)
+        CK(ws_t(C, "eo_iters", (size_t)2 * nrhs, &iters));
+        HC(hipMemsetAsync(iters, 0, sizeof(int) * 2 * nrhs, sm));
     }
     std::vector<double> before;  // ||r_e||^2 at the last launch of the resident solver
     // `iters` iterations on stream ee (the caller's, or the capture stream)
@@ -773,12 +773,13 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
         if (total >= maxit || nout >= 100) break;
         ++nout;
         if (!before.empty()) {
-            // a launch that left more than 1e-2 (or twice its floor) of a residual with further to go stopped for its
-            // slow convergence: BiCGStab for the rest
-            const double left = fmax(1e-4, 4e-16 * C->opt_inner_floor * C->opt_inner_floor);
+            // launches for the rest where the resident solver stopped for slow convergence, or where it left more than
+            // 1e-2 of a residual with further than that to go
+            const int* slow = (const int*)h_st + nrhs;
             for (int k = 0; k < nrhs; ++k) {
                 const double goal = tol * tol * bb[k];
-                if (bb[k] > 0 && rr[k] > goal && rr[k] > left * before[k] && before[k] > goal / left) resident = false;
+                if (bb[k] > 0 && rr[k] > goal && (slow[k] || (rr[k] > 1e-4 * before[k] && before[k] > 1e4 * goal)))
+                    resident = false;
             }
             before.clear();
             if (!resident) gx = chunk_graph(ls);
@@ -790,7 +791,7 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
             HC(hipMemcpyAsync(thr, h_thr, sizeof(double) * nrhs, hipMemcpyHostToDevice, sm));
             launch_eo_lds(ex, g, eo_fields<float>(C), A32, re, xe, scale, thr, mass4, tol, 1e-8 * C->opt_inner_floor,
                           maxit - total, iters, nrhs);
-            HC(hipMemcpyAsync(h_st, iters, sizeof(int) * nrhs, hipMemcpyDeviceToHost, sm));
+            HC(hipMemcpyAsync(h_st, iters, sizeof(int) * 2 * nrhs, hipMemcpyDeviceToHost, sm));
         } else {
             for (int k = 0; k < nrhs; ++k) {
                 bool done = !(bb[k] > 0 && rr[k] > tol * tol * bb[k]);
@@ -956,19 +957,19 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     int* iters;
     CK(ws_t(C, "be_bb", nb, &bb));
     CK(ws_t(C, "be_rr", nb, &rr));
-    CK(ws_t(C, "be_iters", nb, &iters));
-    HC(hipMemsetAsync(iters, 0, nb * sizeof(int), ex.stream));
+    CK(ws_t(C, "be_iters", 2 * nb, &iters));
+    HC(hipMemsetAsync(iters, 0, 2 * nb * sizeof(int), ex.stream));
     // (k_blk_recon writes this colour's solution and clears the other colour)
     launch_blk_prep(ex, g, F64, A64, b64, bpe, re, xe, to, bb, rr, colour, nrhs, C->lds_max);
     std::vector<double> hbb(nb), hrr(nb), was;
-    std::vector<int> hit(nb);
+    std::vector<int> hit(2 * nb);  // iterations, and the marks of slow convergence
     HC(hipMemcpyAsync(hbb.data(), bb, nb * sizeof(double), hipMemcpyDeviceToHost, ex.stream));
     int nout = 0, imax = 0;
     long long isum = 0;
     bool converged = false, finite = true;
     while (true) {
         HC(hipMemcpyAsync(hrr.data(), rr, nb * sizeof(double), hipMemcpyDeviceToHost, ex.stream));
-        HC(hipMemcpyAsync(hit.data(), iters, nb * sizeof(int), hipMemcpyDeviceToHost, ex.stream));
+        HC(hipMemcpyAsync(hit.data(), iters, 2 * nb * sizeof(int), hipMemcpyDeviceToHost, ex.stream));
         HC(hipStreamSynchronize(ex.stream));
         bool all = true;
         imax = 0;
@@ -987,12 +988,13 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
         if (imax >= maxit || nout >= 30) break;
         ++nout;
         if (mr) {
-            // where a launch of a minimal-residual kernel (floor 2e-6, FP16 1e-3) has left a block above 1e-2 of
-            // its last residual, with further than that to go, it converges too slowly there: BiCGStab for the rest
+            // BiCGStab for the rest where a minimal-residual kernel stopped for slow convergence, or where its launch
+            // (floor 2e-6, FP16 1e-3) has left a block above 1e-2 of its last residual, with further than that to go
             bool slow = false;
             for (size_t k = 0; k < was.size(); ++k) {
                 const double goal = tol * tol * hbb[k];
-                slow = slow || (hbb[k] > 0 && hrr[k] > goal && hrr[k] > 1e-4 * was[k] && was[k] > 1e4 * goal);
+                slow = slow || (hbb[k] > 0 && hrr[k] > goal &&
+                                (hit[nb + k] || (hrr[k] > 1e-4 * was[k] && was[k] > 1e4 * goal)));
             }
             if (slow) {
                 mr = lds = false;

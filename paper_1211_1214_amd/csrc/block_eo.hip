@@ -418,7 +418,7 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
 // The Dirichlet operators of the blocks are well conditioned, and it needs as many operator applications
 // as BiCGStab (to 2e-6: 19 against 20 at kappa = 0.1205, 22 / 22 at 0.125, 26 / 24 at 0.129; 6^4 blocks, eps = 0.3 links)
 // with one vector kept beside r.  A block whose residual falls by less than BL_GAIN in BL_WINDOW steps
-// is left to the caller, which goes on with the BiCGStab of k_blk_inner.
+// is left where it stands and marked in the second half of iters, and the caller goes on with the BiCGStab of k_blk_inner.
 //
 // One thread per local half index l < hvb owns the even site and the odd site of that index.  r (the
 // operand of M_k; even sites) and the odd intermediate A_oo^-1 H^k_oe r are staged in LDS
@@ -606,7 +606,8 @@ __device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own,
 // WRAP: the same for the whole lattice as one block with its boundary conditions, one workgroup per RHS (hvb = V / 2).
 template <bool WRAP>
 __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, const float4* __restrict__ Ainv,
-                                                    const double2* re, double2* xe, const double* __restrict__ bb, const double* __restrict__ rr,
+                                                    const double2* re, double2* xe,
+                                                    const double* __restrict__ bb, const double* __restrict__ rr,
                                                     double mass4, double tol, double inner_floor, int maxit,
                                                     int* iters, int colour, int nrhs) {
     extern __shared__ float4 bl_lds[];
@@ -655,16 +656,15 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     };
     const double rn = sqrt(r2), sc = 1.0 / rn;
     // (a step gains half as much as a BiCGStab iteration, so it stops closer to its aim: a quarter of tol
-    // leaves solutions as accurate as the BiCGStab kernel's half)
+    // leaves solutions as accurate as BiCGStab's half)
     double eps = 0.25 * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     int phase = 0;  // reduction slot
     double red[4];
-    cx<float> e[12];  // the correction
+    cx<float> r[12], e[12];  // (e: the correction)
     {
         cx<double> a[12];
         uload_spinor(re, n2, lo, a);
-        cx<float> r[12];
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             r[c] = act ? mk((float)(sc * a[c].re), (float)(sc * a[c].im)) : mk(0.f, 0.f);
@@ -677,11 +677,12 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     const double thr2 = eps * eps * red[0];
     double window = red[0];  // ||r||^2 when the current window began
     int it = 0;
+    bool slow = false;
     while (it < maxit) {
         // t = M_k r, (t, r), (t, t), (r, r)
         odd();
         __syncthreads();
-        cx<float> t[12], r[12];
+        cx<float> t[12];
         even(t, r);
         red[0] = red[1] = 0;
         acc_dot(t, r, red[0], red[1]);
@@ -689,7 +690,8 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
         red[3] = acc_nrm(r);
         wg_sums<4>(red, red_lds[phase ^= 1]);
         ++it;
-        if (!(red[2] > 0)) break;
+        slow = !(red[2] > 0);
+        if (slow) break;
         // e += omega r, r -= omega t with the omega that minimises ||r||, staged as the next operand
         const cx<float> omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
 #pragma unroll
@@ -698,11 +700,9 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
             cmadd(r[c], mk(-omega.re, -omega.im), t[c]);
         }
         const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
-        if (!(r2n > thr2) || !isfinite(r2n)) break;
-        if (it % BL_WINDOW == 0) {
-            if (r2n > BL_GAIN * BL_GAIN * window) break;  // too slow: left to the caller
-            window = r2n;
-        }
+        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > BL_GAIN * BL_GAIN * window);
+        if (!(r2n > thr2) || slow) break;
+        if (it % BL_WINDOW == 0) window = r2n;
         // (only this thread reads its own operand record after the last barrier)
         if (act) lds_store(op, l, r);
         __syncthreads();
@@ -715,7 +715,10 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
         for (int c = 0; c < 12; ++c) x[c] = x[c] + mk(rn * (double)e[c].re, rn * (double)e[c].im);
         ustore_spinor(xe, n2, lo, x);
     }
-    if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
+    if (threadIdx.x == 0) {
+        iters[k.key] += (it + 1) / 2;
+        iters[gridDim.x + k.key] = slow;
+    }
 }
 
 // ------------------------------------------------------------------ two or four lanes per site
@@ -899,6 +902,7 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
     const double thr2 = eps * eps * red[0];
     double window = red[0];
     int it = 0;
+    bool slow = false;
     while (it < maxit) {
         cx<float> t[6], w[6];
         float kw[40];
@@ -926,7 +930,8 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
         for (int q = 0; q < 4; ++q) red[q] = act ? (double)v[q] : 0.0;
         wg_sums<4>(red, red_lds[phase ^= 1]);
         ++it;
-        if (!(red[2] > 0)) break;
+        slow = !(red[2] > 0);
+        if (slow) break;
         const cx<float> omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
 #pragma unroll
         for (int a = 0; a < 6; ++a) {
@@ -934,11 +939,9 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
             cmadd(r[a], mk(-omega.re, -omega.im), t[a]);
         }
         const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
-        if (!(r2n > thr2) || !isfinite(r2n)) break;
-        if (it % BL_WINDOW == 0) {
-            if (r2n > BL_GAIN * BL_GAIN * window) break;  // too slow: left to the caller
-            window = r2n;
-        }
+        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > BL_GAIN * BL_GAIN * window);
+        if (!(r2n > thr2) || slow) break;
+        if (it % BL_WINDOW == 0) window = r2n;
         // (all reads of the operand were before the last barrier)
         store(op, r);
         __syncthreads();
@@ -950,7 +953,10 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
             xe[oh + (size_t)a * n2] = make_double2(x.x + rn * (double)e[a].re, x.y + rn * (double)e[a].im);
         }
     }
-    if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
+    if (threadIdx.x == 0) {
+        iters[k.key] += (it + 1) / 2;
+        iters[gridDim.x + k.key] = slow;
+    }
 }
 
 static bool lds_fits(int hv, int lds_max_bytes) {
@@ -975,12 +981,17 @@ static void launch_lds(hipStream_t st, const Geom& g, const EoFields<float>& F, 
                        int maxit, int* iters, int colour, int nrhs) {
     const int steps = maxit < (1 << 30) ? 2 * maxit : maxit;  // (a BiCGStab iteration, the unit of maxit, is two steps)
     const int lanes = lanes_per_site(g.hvb, (long long)g.NBc * nrhs, F.n2);
-    auto k = lanes == 2 ? k_lds_lanes<WRAP, 2> : k_blk_lds<WRAP>;
+    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
+    const int groups = g.NBc * nrhs, threads = (lanes * g.hvb + 63) / 64 * 64;
+    if (lanes == 1) {
+        k_blk_lds<WRAP><<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol,
+                                                             floor_eps, steps, iters, colour, nrhs);
+        return;
+    }
+    auto k = k_lds_lanes<WRAP, 2>;
     if constexpr (!WRAP)  // (no lattice has that few sites)
         if (lanes == 4) k = k_lds_lanes<false, 4>;
-    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
-    k<<<g.NBc * nrhs, (lanes * g.hvb + 63) / 64 * 64, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps, steps, iters,
-                                                               colour, nrhs);
+    k<<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps, steps, iters, colour, nrhs);
 }
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                     double2* xe, const double* bb, const double* rr, double mass4, double tol,
@@ -1299,6 +1310,7 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
     const double thr2 = eps * eps * red[0];
     double window = red[0];
     int it = 0;
+    bool slow = false;
     while (it < maxit) {
         // w = A_oo^-1 H^k_oe r
 #pragma unroll 1
@@ -1336,7 +1348,8 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
         }
         wg_sums<4>(red, red_lds[phase ^= 1]);
         ++it;
-        if (!(red[2] > 0)) break;
+        slow = !(red[2] > 0);
+        if (slow) break;
         const cx<float> omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
         const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
         // e += omega r, r -= omega t
@@ -1358,11 +1371,9 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
                 store_r(l, r);
             }
         }
-        if (!(r2n > thr2) || !isfinite(r2n)) break;
-        if (it % BL_WINDOW == 0) {
-            if (r2n > BL_GAIN * BL_GAIN * window) break;  // too slow: left to the caller
-            window = r2n;
-        }
+        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > BL_GAIN * BL_GAIN * window);
+        if (!(r2n > thr2) || slow) break;
+        if (it % BL_WINDOW == 0) window = r2n;
         __syncthreads();
     }
     // x_e += ||r_e|| e in FP64
@@ -1378,7 +1389,10 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
         for (int c = 0; c < 12; ++c) x[c] = x[c] + mk(rn * (double)e[c].re, rn * (double)e[c].im);
         if (li < HV) ustore_spinor(fresh(xe), n2, lo, x);
     }
-    if (threadIdx.x == 0) iters[k.key] += (it + 1) / 2;
+    if (threadIdx.x == 0) {
+        iters[k.key] += (it + 1) / 2;
+        iters[gridDim.x + k.key] = slow;
+    }
 }
 
 static size_t mr_mask_bytes(const Geom& g) { return ((size_t)2 * g.hvb * sizeof(unsigned short) + 15) / 16 * 16; }

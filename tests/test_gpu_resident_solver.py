@@ -1,6 +1,6 @@
 """Global solves of lattices whose parity fits the LDS-resident solver (up to 768 sites): the smallest, one that does
 not fill its last wavefront's workgroup, the largest, and the first beyond it; both time boundary conditions; one,
-some and a zero right-hand side; and a kappa where minimal residual is left for BiCGStab.  Against the C oracle's
+some and a zero right-hand side; and a kappa where minimal residual is left for BiCGStab, at tight and at loose tolerances.  Against the C oracle's
 solves (1e-9 relative in the max norm at tol 1e-12, as for every solve)."""
 import numpy as np
 import pytest
@@ -37,11 +37,22 @@ def test_resident_solve(lat, blk, bc, prec):
         print(st, flush=True)
         x = x.cpu().numpy().reshape(nrhs, -1)
         assert st["rel_residual"] <= 1e-12 and st["inner_iters"] > 0
+        # (two launches of the resident solver reach 1e-12 from its floor of 2e-6: a third outer step is the change-over)
+        assert kappa == 0.121 or st["outer_iters"] >= 3
         for j in {0, nrhs - 1, nrhs // 2 + 1} - {1}:
             if j < nrhs:
                 w = R.solve(dirac.mass(kappa), b[j], 1e-13).reshape(-1)
                 assert np.abs(x[j] - w).max() <= 1e-9 * np.abs(w).max()
         assert nrhs == 1 or np.all(x[1] == 0)
+    # at loose tolerances a residual starts close to its goal
+    for tol in (1e-1, 1e-2):
+        for kappa, nrhs in slow:
+            x, st = ctx.solve(kappa, torch.from_numpy(b[:nrhs].copy()).cuda(), tol=tol, prec=prec)
+            x = x.cpu().numpy()
+            assert st["rel_residual"] <= tol
+            for j in (0, nrhs - 1):
+                r = b[j].reshape(-1) - R.dslash(dirac.mass(kappa), x[j]).reshape(-1)
+                assert np.linalg.norm(r) <= 1.01 * tol * np.linalg.norm(b[j])
     # an iteration limit is refused as before
     with pytest.raises(dd.binding.DDWCError):
         ctx.solve(0.121, torch.from_numpy(b).cuda(), tol=1e-12, maxit=2, prec=prec)

@@ -943,7 +943,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
     CK(ws_t(C, "be_xe", hw64, &xe));
     CK(ws_t(C, "be_to", hw64, &to));  // A_oo^-1 b_o (prep)
     CK(ws_t(C, "be_th", hw64, &th));  // A_oo^-1 H x_e of the last residual pass
-    void* w[7];  // vectors of the global-memory kernel (the LDS-resident one has none)
+    void* w[7];  // vectors of the global-memory kernels and of BiCGStab (LDS-resident minimal residual has none)
     auto slabs = [&]() -> int {
         const char* names[7] = {"be_r", "be_rh", "be_p", "be_v", "be_t", "be_e", "be_tmp"};
         for (int k = 0; k < 7; ++k)
@@ -997,8 +997,8 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
                                 (hit[nb + k] || (hrr[k] > 1e-4 * was[k] && was[k] > 1e4 * goal)));
             }
             if (slow) {
-                mr = lds = false;
-                CK(slabs());
+                mr = false;
+                if (lds) CK(slabs());
             }
             was = hrr;
         }
@@ -1007,7 +1007,10 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
             launch_blk_inner<double>(ex, g, F, A64, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
         } else if (lds) {
             const EoFields<float> F = eo_fields<float>(C);
-            launch_blk_lds(ex, g, F, A32, re, xe, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
+            if (mr)
+                launch_blk_lds(ex, g, F, A32, re, xe, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
+            else
+                launch_blk_lds_bi(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
         } else {
             auto inner = [&](auto F) {
                 typedef typename decltype(F)::storage S;

@@ -417,8 +417,10 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
 //     t = M_k r, omega = (t, r) / (t, t), e += omega r, r -= omega t.
 // The Dirichlet operators of the blocks are well conditioned, and it needs as many operator applications
 // as BiCGStab (to 2e-6: 19 against 20 at kappa = 0.1205, 22 / 22 at 0.125, 26 / 24 at 0.129; 6^4 blocks, eps = 0.3 links)
-// with one vector kept beside r.  A block whose residual falls by less than BL_GAIN in BL_WINDOW steps
-// is left where it stands and marked in the second half of iters, and the caller goes on with the BiCGStab of k_blk_inner.
+// with one vector kept beside r.  A block whose residual falls by less than the gain expected of BL_WINDOW steps
+// is left where it stands and marked in the second half of iters, and the caller goes on with BI: BiCGStab in the same
+// layout, with p (then s) as the operand and rh, p and e as slabs, r in registers until s is formed and v in its
+// place until p is updated.
 //
 // One thread per local half index l < hvb owns the even site and the odd site of that index.  r (the
 // operand of M_k; even sites) and the odd intermediate A_oo^-1 H^k_oe r are staged in LDS
@@ -437,7 +439,13 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
 // took 3000 us: the load path, 64 bytes a cycle and CU, is the rest.
 constexpr int BL_MAX = 768;     // 12 waves: 3 per SIMD at up to 168 VGPRs
 constexpr int BL_WINDOW = 8;    // steps
-constexpr double BL_GAIN = 0.4;  // 0.05 decades a step, where BiCGStab takes over in the global solver too
+// The fall of ||r|| in a window below which a block is left to BiCGStab: 0.1 decades a step, where the two meet.  One colour
+// to 1e-10, BiCGStab alone / minimal residual left at 0.05 decades a step for k_blk_inner / this: 6^4 blocks of
+// 24x12^3, 12 RHS, kappa 0.13 1.71 / 1.30 / 1.30, 0.14 2.17 / 2.39 / 1.61, 0.16 6.53 / 9.59 / 5.38 ms; 4^4 of 16^4, 8 RHS,
+// 0.15 1.39 / 1.33 / 1.42, 0.16 1.65 / 2.42 / 1.29 ms; 8^4 of 16^4 (k_blk_mr, k_blk_inner), 8 RHS, 0.13 6.72 / 6.82 / 6.89,
+// 0.14 9.73 / 9.78 / 9.87 ms.  A whole lattice (WRAP) goes on by launches of the global solver, at two to four times the
+// time an iteration, so it stays until 0.05 decades a step (4^4, 8 RHS, kappa 0.13: 3.03 / - / 1.10 ms).
+constexpr double BL_GAIN = 0.16, BL_GAIN_WRAP = 0.4;
 
 // Exchanges halves between a and b and adds, on the two dwords of each double: with W = 32 the lower 32
 // lanes get a(lane) + a(lane + 32) and the upper ones b(lane - 32) + b(lane); with W = 16 the same
@@ -604,14 +612,15 @@ __device__ __forceinline__ void lds_hops(unsigned n2, unsigned h0, unsigned own,
 }
 
 // WRAP: the same for the whole lattice as one block with its boundary conditions, one workgroup per RHS (hvb = V / 2).
-template <bool WRAP>
+template <bool WRAP, bool BI>
 __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, const float4* __restrict__ Ainv,
-                                                    const double2* re, double2* xe,
+                                                    const double2* re, double2* xe, float4* rhg, float4* pg, float4* eg,
                                                     const double* __restrict__ bb, const double* __restrict__ rr,
                                                     double mass4, double tol, double inner_floor, int maxit,
                                                     int* iters, int colour, int nrhs) {
     extern __shared__ float4 bl_lds[];
     __shared__ double red_lds[2][8 * 16];  // alternating slots of the workgroup reductions
+    constexpr double GAIN = WRAP ? BL_GAIN_WRAP : BL_GAIN;
     const BlkIdx k = blk_idx(g, colour, nrhs);
     const double b2 = bb[k.key], r2 = rr[k.key];
     if (!(b2 > 0) || !(r2 > tol * tol * b2) || !isfinite(r2)) return;  // uniform over the workgroup
@@ -635,6 +644,12 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     if (threadIdx.x < 12) (threadIdx.x < 6 ? op : tp)[HV * 6 + threadIdx.x % 6] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     const float m4 = (float)mass4;
+    if (BI) {
+        const size_t oR = (size_t)k.rhs * 6 * n2 + h0;
+        rhg += oR;
+        pg += oR;
+        eg += oR;
+    }
     // tp = A_oo^-1 H^k_oe q on the odd sites (q: operand in op)
     auto odd = [&]() {
         cx<float> acc[12], w[12];
@@ -657,11 +672,11 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     const double rn = sqrt(r2), sc = 1.0 / rn;
     // (a step gains half as much as a BiCGStab iteration, so it stops closer to its aim: a quarter of tol
     // leaves solutions as accurate as BiCGStab's half)
-    double eps = 0.25 * tol * sqrt(b2) / rn;
+    double eps = (BI ? 0.5 : 0.25) * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     int phase = 0;  // reduction slot
-    double red[4];
-    cx<float> r[12], e[12];  // (e: the correction)
+    double red[8];
+    cx<float> r[12], e[12];  // (BI: v in r from s on; e, the correction, otherwise)
     {
         cx<double> a[12];
         uload_spinor(re, n2, lo, a);
@@ -671,14 +686,107 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
             e[c] = mk(0.f, 0.f);
         }
         if (act) lds_store(op, l, r);
+        if (BI && act) {
+            ustore_spinor(fresh(rhg), n2, lo, r);
+            ustore_spinor(fresh(pg), n2, lo, r);
+            ustore_spinor(fresh(eg), n2, lo, e);
+        }
         red[0] = acc_nrm(r);
     }
     wg_sums<1>(red, red_lds[phase ^= 1]);  // (its barrier also publishes the operand)
     const double thr2 = eps * eps * red[0];
     double window = red[0];  // ||r||^2 when the current window began
+    cx<double> rho = mk(red[0], 0.0);
     int it = 0;
     bool slow = false;
-    while (it < maxit) {
+    while (BI && it < maxit) {
+        // v = M_k p, (rh, v)
+        odd();
+        __syncthreads();
+        red[0] = red[1] = 0;
+        cx<float> v[12];
+        {
+            cx<float> c[12], h[12];
+            even(v, c);
+            uload_spinor(fresh(rhg), n2, lo, h);
+            if (act) acc_dot(h, v, red[0], red[1]);
+        }
+        wg_sums<2>(red, red_lds[phase ^= 1]);
+        if (!(red[0] * red[0] + red[1] * red[1] > 0)) break;
+        const cx<float> alpha = cdiv_r<float>(rho, mk(red[0], red[1]));
+        // s = r - alpha v, staged as the operand
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const cx<float> sv = r[c] - alpha * v[c];
+            r[c] = v[c];
+            v[c] = sv;
+        }
+        if (act) lds_store(op, l, v);
+        __syncthreads();
+        // t = M_k s, (t, s), (t, t), (rh, s), (rh, t), (s, s)
+        odd();
+        __syncthreads();
+        cx<float> t[12], pp[12];
+        {
+            cx<float> sv[12], h[12];
+            even(t, sv);
+            uload_spinor(fresh(rhg), n2, lo, h);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) red[c] = 0;
+            if (act) {
+                acc_dot(t, sv, red[0], red[1]);
+                red[2] = acc_nrm(t);
+                acc_dot(h, sv, red[3], red[4]);
+                acc_dot(h, t, red[5], red[6]);
+                red[7] = acc_nrm(sv);
+            }
+            // (needed after the reduction)
+            uload_spinor(fresh(eg), n2, lo, e);
+            uload_spinor(fresh(pg), n2, lo, pp);
+        }
+        wg_sums<8>(red, red_lds[phase ^= 1]);
+        ++it;
+        cx<float> omega = mk(0.f, 0.f);
+        if (red[2] > 0) omega = mk((float)(red[0] / red[2]), (float)(red[1] / red[2]));
+        // r = s - omega t is orthogonal to t, so ||r||^2 = (s, s) - |(t, s)|^2 / (t, t); the next
+        // rho = (rh, r) = (rh, s) - omega (rh, t): one reduction serves omega, the stopping test and
+        // beta, and x, r and p are updated in one pass
+        const double r2n = red[2] > 0 ? red[7] - (red[0] * red[0] + red[1] * red[1]) / red[2] : red[7];
+        const cx<double> rn_ = mk(red[3] - ((double)omega.re * red[5] - (double)omega.im * red[6]),
+                                  red[4] - ((double)omega.re * red[6] + (double)omega.im * red[5]));
+        const double d1 = rho.re * rho.re + rho.im * rho.im;
+        const double d2 = (double)omega.re * omega.re + (double)omega.im * omega.im;
+        const bool stop = r2n <= thr2 || !isfinite(r2n) || !(d2 > 0) || !(d1 > 0);
+        cx<float> beta = mk(0.f, 0.f);
+        if (!stop) {
+            const cx<double> q = mk((rn_.re * rho.re + rn_.im * rho.im) / d1, (rn_.im * rho.re - rn_.re * rho.im) / d1);
+            const cx<double> ao = mk(((double)alpha.re * omega.re + (double)alpha.im * omega.im) / d2,
+                                     ((double)alpha.im * omega.re - (double)alpha.re * omega.im) / d2);
+            beta = mk((float)(q.re * ao.re - q.im * ao.im), (float)(q.re * ao.im + q.im * ao.re));
+        }
+        rho = rn_;
+        // e += alpha p + omega s ; r = s - omega t ; p = r + beta (p - omega v), staged as the next operand
+        lds_load(op, l, v);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            e[c] = e[c] + (alpha * pp[c] + omega * v[c]);
+            v[c] = v[c] - omega * t[c];
+        }
+        if (act) ustore_spinor(fresh(eg), n2, lo, e);
+        if (stop) break;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            pp[c] = v[c] + beta * (pp[c] - omega * r[c]);
+            r[c] = v[c];
+        }
+        if (act) {
+            ustore_spinor(fresh(pg), n2, lo, pp);
+            // (only this thread reads its own operand record after the last barrier)
+            lds_store(op, l, pp);
+        }
+        __syncthreads();
+    }
+    while (!BI && it < maxit) {
         // t = M_k r, (t, r), (t, t), (r, r)
         odd();
         __syncthreads();
@@ -700,7 +808,7 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
             cmadd(r[c], mk(-omega.re, -omega.im), t[c]);
         }
         const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
-        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > BL_GAIN * BL_GAIN * window);
+        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > GAIN * GAIN * window);
         if (!(r2n > thr2) || slow) break;
         if (it % BL_WINDOW == 0) window = r2n;
         // (only this thread reads its own operand record after the last barrier)
@@ -710,13 +818,14 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
     // x_e += ||r_e|| e in FP64
     if (act) {
         cx<double> x[12];
+        if (BI) uload_spinor(fresh(eg), n2, lo, e);
         uload_spinor(xe, n2, lo, x);
 #pragma unroll
         for (int c = 0; c < 12; ++c) x[c] = x[c] + mk(rn * (double)e[c].re, rn * (double)e[c].im);
         ustore_spinor(xe, n2, lo, x);
     }
     if (threadIdx.x == 0) {
-        iters[k.key] += (it + 1) / 2;
+        iters[k.key] += BI ? it : (it + 1) / 2;
         iters[gridDim.x + k.key] = slow;
     }
 }
@@ -753,6 +862,7 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
     extern __shared__ float2 bq_lds[];  // the operand and the odd intermediate: records of four spins
     __shared__ double red_lds[2][8 * 16];
     constexpr int NS = 16 / LANES;  // directions of a lane
+    constexpr double GAIN = WRAP ? BL_GAIN_WRAP : BL_GAIN;
     const BlkIdx k = blk_idx(g, colour, nrhs);
     const double b2 = bb[k.key], r2 = rr[k.key];
     if (!(b2 > 0) || !(r2 > tol * tol * b2) || !isfinite(r2)) return;  // uniform over the workgroup
@@ -939,7 +1049,7 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
             cmadd(r[a], mk(-omega.re, -omega.im), t[a]);
         }
         const double r2n = red[3] - (red[0] * red[0] + red[1] * red[1]) / red[2];
-        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > BL_GAIN * BL_GAIN * window);
+        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > GAIN * GAIN * window);
         if (!(r2n > thr2) || slow) break;
         if (it % BL_WINDOW == 0) window = r2n;
         // (all reads of the operand were before the last barrier)
@@ -984,7 +1094,7 @@ static void launch_lds(hipStream_t st, const Geom& g, const EoFields<float>& F, 
     const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);  // (a record of zeros after each field)
     const int groups = g.NBc * nrhs, threads = (lanes * g.hvb + 63) / 64 * 64;
     if (lanes == 1) {
-        k_blk_lds<WRAP><<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol,
+        k_blk_lds<WRAP, false><<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, nullptr, nullptr, nullptr, bb, rr, mass4, tol,
                                                              floor_eps, steps, iters, colour, nrhs);
         return;
     }
@@ -999,6 +1109,14 @@ void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const floa
     Timed t(e, 2, 0);
     // the inner solve stops at this relative residual at the least (FP32's reach)
     launch_lds<false>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6, maxit, iters, colour, nrhs);
+}
+void launch_blk_lds_bi(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
+                       double2* xe, void* const w[7], const double* bb, const double* rr, double mass4, double tol,
+                       int maxit, int* iters, int colour, int nrhs) {
+    Timed t(e, 2, 0);
+    const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);
+    k_blk_lds<false, true><<<g.NBc * nrhs, (g.hvb + 63) / 64 * 64, lds, e.stream>>>(
+        g, F, Ainv, re, xe, (float4*)w[1], (float4*)w[2], (float4*)w[5], bb, rr, mass4, tol, 2e-6, maxit, iters, colour, nrhs);
 }
 void launch_eo_lds(Exec& e, Geom g, const EoFields<float>& F, const float4* Ainv, const double2* re, double2* xe,
                    const double* bb, const double* rr, double mass4, double tol, double floor_eps, int maxit, int* iters,

@@ -293,11 +293,15 @@ void launch_blk_inner(Exec& e, const Geom& g, const EoFields<S>& F, const typena
 // The LDS-resident FP32 inner solver (r and the odd intermediate in LDS, the correction in registers):
 // whether it takes this geometry with lds_max_bytes of LDS per workgroup, and its launch.  Like launch_blk_mr it leaves
 // blocks on which minimal residual converges slowly where they stand: iters holds the iterations of every (RHS, block)
-// and after those of all a mark, set where the last launch stopped so.
+// and after those of all a mark, set where the last launch stopped so.  launch_blk_lds_bi is BiCGStab in the same
+// layout (slabs 1, 2, 5) for the blocks left.
 bool blk_lds_fits(const Geom& g, int lds_max_bytes);
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                     double2* xe, const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
                     int colour, int nrhs);
+void launch_blk_lds_bi(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
+                       double2* xe, void* const w[7], const double* bb, const double* rr, double mass4, double tol,
+                       int maxit, int* iters, int colour, int nrhs);
 // The minimal-residual solver for the whole lattice as one block, one workgroup per RHS: whether it takes this lattice, and its
 // launch (bb, rr, iters per RHS).
 bool eo_lds_fits(const Geom& g, int lds_max_bytes);

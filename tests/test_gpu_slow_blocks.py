@@ -14,7 +14,7 @@ from oracle import dirac, lattice as lt  # noqa: E402
 from oracle.schwarz import Schwarz  # noqa: E402
 from paper_1211_1214_amd import binding, inputs  # noqa: E402
 
-WINDOW, GAIN = 8, 0.4  # the kernels' rule: steps, and the least fall of ||r|| in them
+WINDOW, GAIN = 8, 0.16  # the kernels' rule: steps, and the least fall of ||r|| in them
 CASES = [((2, 2, 2, 4), (4, 4, 4, 8), 0.25), ((4, 4, 4, 4), (8, 8, 8, 8), 0.18), ((6, 4, 4, 4), (12, 8, 8, 8), 0.17)]
 
 

@@ -796,7 +796,7 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
             for (int k = 0; k < nrhs; ++k) {
                 bool done = !(bb[k] > 0 && rr[k] > tol * tol * bb[k]);
                 h_scale[k] = done ? 0.0 : 1.0 / sqrt(rr[k]);
-                double eps = done ? 0.0 : 0.5 * tol * sqrt(bb[k] / rr[k]);
+                double eps = done ? 0.0 : (ls ? LS_AIM : BI_AIM) * tol * sqrt(bb[k] / rr[k]);
                 if (eps < floor_eps) eps = floor_eps;
                 h_thr[k] = done ? 2.0 : eps * eps;
             }
@@ -989,7 +989,7 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
         ++nout;
         if (mr) {
             // BiCGStab for the rest where a minimal-residual kernel stopped for slow convergence, or where its launch
-            // (floor 2e-6, FP16 1e-3) has left a block above 1e-2 of its last residual, with further than that to go
+            // (floor MR_FLOOR32, FP16 1e-3) has left a block above 1e-2 of its last residual, with further than that to go
             bool slow = false;
             for (size_t k = 0; k < was.size(); ++k) {
                 const double goal = tol * tol * hbb[k];
@@ -1008,15 +1008,16 @@ static int block_internal_eo(ddwc_ctx* C, Exec& ex, int colour, double mass, con
         } else if (lds) {
             const EoFields<float> F = eo_fields<float>(C);
             if (mr)
-                launch_blk_lds(ex, g, F, A32, re, xe, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
+                launch_blk_lds(ex, g, F, A32, re, xe, bb, rr, mass4, tol, mr_aim(tol, MR_AIM_LDS), maxit - imax, iters, colour,
+                               nrhs);
             else
                 launch_blk_lds_bi(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
         } else {
             auto inner = [&](auto F) {
                 typedef typename decltype(F)::storage S;
                 if (mr)
-                    launch_blk_mr<S>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs,
-                                     C->lds_max);
+                    launch_blk_mr<S>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, mr_aim(tol, MR_AIM), maxit - imax, iters,
+                                     colour, nrhs, C->lds_max);
                 else
                     launch_blk_inner<S>(ex, g, F, A32, re, xe, w, bb, rr, mass4, tol, maxit - imax, iters, colour, nrhs);
             };

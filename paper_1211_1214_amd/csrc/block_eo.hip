@@ -301,7 +301,7 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
                  oX = (size_t)k.rhs * Traits<XS>::NCW * n2;
     const R m4 = (R)mass4;
     const double rn = sqrt(r2), sc = 1.0 / rn;
-    double eps = 0.5 * tol * sqrt(b2) / rn;
+    double eps = BI_AIM * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     double red[3] = {0, 0, 0};
 #pragma unroll 1
@@ -442,10 +442,10 @@ constexpr int BL_WINDOW = 8;    // steps
 // The fall of ||r|| in a window below which a block is left to BiCGStab: 0.1 decades a step, where the two meet.  One colour
 // to 1e-10, BiCGStab alone / minimal residual left at 0.05 decades a step for k_blk_inner / this: 6^4 blocks of
 // 24x12^3, 12 RHS, kappa 0.13 1.71 / 1.30 / 1.30, 0.14 2.17 / 2.39 / 1.61, 0.16 6.53 / 9.59 / 5.38 ms; 4^4 of 16^4, 8 RHS,
-// 0.15 1.39 / 1.33 / 1.42, 0.16 1.65 / 2.42 / 1.29 ms; 8^4 of 16^4 (k_blk_mr, k_blk_inner), 8 RHS, 0.13 6.72 / 6.82 / 6.89,
-// 0.14 9.73 / 9.78 / 9.87 ms.  A whole lattice (WRAP) goes on by launches of the global solver, at two to four times the
+// 0.15 1.39 / 1.33 / 1.42, 0.16 1.65 / 2.42 / 1.29 ms.  In k_blk_mr with FP32 storage (BiCGStab alone / this), 0.15 decades:
+// 8^4 of 16^4, 8 RHS, 0.125 5.5 / 5.5, 0.13 6.6 / 7.1, 0.14 9.8 / 9.9 ms.  A whole lattice (WRAP) goes on by launches of the global solver, at two to four times the
 // time an iteration, so it stays until 0.05 decades a step (4^4, 8 RHS, kappa 0.13: 3.03 / - / 1.10 ms).
-constexpr double BL_GAIN = 0.16, BL_GAIN_WRAP = 0.4;
+constexpr double BL_GAIN = 0.16, BL_GAIN_WRAP = 0.4, BM_GAIN32 = 0.06;
 
 // Exchanges halves between a and b and adds, on the two dwords of each double: with W = 32 the lower 32
 // lanes get a(lane) + a(lane + 32) and the upper ones b(lane - 32) + b(lane); with W = 16 the same
@@ -616,7 +616,7 @@ template <bool WRAP, bool BI>
 __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, const float4* __restrict__ Ainv,
                                                     const double2* re, double2* xe, float4* rhg, float4* pg, float4* eg,
                                                     const double* __restrict__ bb, const double* __restrict__ rr,
-                                                    double mass4, double tol, double inner_floor, int maxit,
+                                                    double mass4, double tol, double aim, double inner_floor, int maxit,
                                                     int* iters, int colour, int nrhs) {
     extern __shared__ float4 bl_lds[];
     __shared__ double red_lds[2][8 * 16];  // alternating slots of the workgroup reductions
@@ -670,9 +670,7 @@ __global__ __launch_bounds__(BL_MAX) void k_blk_lds(Geom g, EoFields<float> F, c
         K.apply(m4, c, y, -0.25f);
     };
     const double rn = sqrt(r2), sc = 1.0 / rn;
-    // (a step gains half as much as a BiCGStab iteration, so it stops closer to its aim: a quarter of tol
-    // leaves solutions as accurate as BiCGStab's half)
-    double eps = (BI ? 0.5 : 0.25) * tol * sqrt(b2) / rn;
+    double eps = aim * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     int phase = 0;  // reduction slot
     double red[8];
@@ -857,7 +855,7 @@ __device__ __forceinline__ cx<float> quad_xor(cx<float> v) {
 template <bool WRAP, int LANES>
 __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Geom g, EoFields<float> F, const float4* Ainv, const double2* re,
                                                         double2* xe, const double* bb, const double* rr, double mass4,
-                                                        double tol, double inner_floor, int maxit, int* iters, int colour,
+                                                        double tol, double aim, double inner_floor, int maxit, int* iters, int colour,
                                                         int nrhs) {
     extern __shared__ float2 bq_lds[];  // the operand and the odd intermediate: records of four spins
     __shared__ double red_lds[2][8 * 16];
@@ -992,7 +990,7 @@ __global__ __launch_bounds__(BQ_THREADS, LANES == 4 ? 2 : 1) void k_lds_lanes(Ge
     };
     const float m4 = (float)mass4;
     const double rn = sqrt(r2), sc = 1.0 / rn;
-    double eps = 0.25 * tol * sqrt(b2) / rn;  // (as k_blk_lds)
+    double eps = aim * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     const size_t oh = (size_t)k.rhs * 12 * n2 + (size_t)(6 * s) * n2 + own;
     cx<float> e[6], r[6];
@@ -1087,7 +1085,7 @@ static int lanes_per_site(int hv, long long groups, unsigned n2) {
 }
 template <bool WRAP>
 static void launch_lds(hipStream_t st, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
-                       double2* xe, const double* bb, const double* rr, double mass4, double tol, double floor_eps,
+                       double2* xe, const double* bb, const double* rr, double mass4, double tol, double aim, double floor_eps,
                        int maxit, int* iters, int colour, int nrhs) {
     const int steps = maxit < (1 << 30) ? 2 * maxit : maxit;  // (a BiCGStab iteration, the unit of maxit, is two steps)
     const int lanes = lanes_per_site(g.hvb, (long long)g.NBc * nrhs, F.n2);
@@ -1095,20 +1093,19 @@ static void launch_lds(hipStream_t st, const Geom& g, const EoFields<float>& F, 
     const int groups = g.NBc * nrhs, threads = (lanes * g.hvb + 63) / 64 * 64;
     if (lanes == 1) {
         k_blk_lds<WRAP, false><<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, nullptr, nullptr, nullptr, bb, rr, mass4, tol,
-                                                             floor_eps, steps, iters, colour, nrhs);
+                                                             aim, floor_eps, steps, iters, colour, nrhs);
         return;
     }
     auto k = k_lds_lanes<WRAP, 2>;
     if constexpr (!WRAP)  // (no lattice has that few sites)
         if (lanes == 4) k = k_lds_lanes<false, 4>;
-    k<<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps, steps, iters, colour, nrhs);
+    k<<<groups, threads, lds, st>>>(g, F, Ainv, re, xe, bb, rr, mass4, tol, aim, floor_eps, steps, iters, colour, nrhs);
 }
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
-                    double2* xe, const double* bb, const double* rr, double mass4, double tol,
+                    double2* xe, const double* bb, const double* rr, double mass4, double tol, double aim,
                     int maxit, int* iters, int colour, int nrhs) {
     Timed t(e, 2, 0);
-    // the inner solve stops at this relative residual at the least (FP32's reach)
-    launch_lds<false>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, 2e-6, maxit, iters, colour, nrhs);
+    launch_lds<false>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, aim, MR_FLOOR32, maxit, iters, colour, nrhs);
 }
 void launch_blk_lds_bi(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                        double2* xe, void* const w[7], const double* bb, const double* rr, double mass4, double tol,
@@ -1116,14 +1113,15 @@ void launch_blk_lds_bi(Exec& e, const Geom& g, const EoFields<float>& F, const f
     Timed t(e, 2, 0);
     const size_t lds = (size_t)2 * 6 * (g.hvb + 1) * sizeof(float4);
     k_blk_lds<false, true><<<g.NBc * nrhs, (g.hvb + 63) / 64 * 64, lds, e.stream>>>(
-        g, F, Ainv, re, xe, (float4*)w[1], (float4*)w[2], (float4*)w[5], bb, rr, mass4, tol, 2e-6, maxit, iters, colour, nrhs);
+        g, F, Ainv, re, xe, (float4*)w[1], (float4*)w[2], (float4*)w[5], bb, rr, mass4, tol, BI_AIM, 2e-6, maxit, iters,
+        colour, nrhs);
 }
 void launch_eo_lds(Exec& e, Geom g, const EoFields<float>& F, const float4* Ainv, const double2* re, double2* xe,
                    const double* bb, const double* rr, double mass4, double tol, double floor_eps, int maxit, int* iters,
                    int nrhs) {
     Timed t(e, DDWC_K_DSLASH32, 0);
     g.hvb = g.V / 2, g.NBc = 1;
-    launch_lds<true>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, floor_eps, maxit, iters, 0, nrhs);
+    launch_lds<true>(e.stream, g, F, Ainv, re, xe, bb, rr, mass4, tol, mr_aim(tol, MR_AIM), floor_eps, maxit, iters, 0, nrhs);
 }
 
 // ------------------------------------------------------------------ FP64 passes through LDS
@@ -1337,10 +1335,11 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
                                                    double2* xe, typename Traits<S>::word* rg,
                                                    typename Traits<S>::word* tg, typename Traits<S>::word* wg, float4* eg,
                                                    const double* __restrict__ bb, const double* __restrict__ rr,
-                                                   double mass4, double tol, double inner_floor, int maxit, int* iters,
+                                                   double mass4, double tol, double aim, double inner_floor, int maxit, int* iters,
                                                    int colour, int nrhs) {
     extern __shared__ float4 bm_lds[];
     __shared__ double red_lds[2][8 * 16];
+    constexpr double GAIN = std::is_same<S, H16>::value ? BL_GAIN : BM_GAIN32;
     typedef typename std::conditional<std::is_same<S, H16>::value, f16, float>::type L;
     const S tag{};
     const BlkIdx k = blk_idx(g, colour, nrhs);
@@ -1402,7 +1401,7 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
     };
     const float m4 = (float)mass4;
     const double rn = sqrt(r2), sc = 1.0 / rn;
-    double eps = 0.25 * tol * sqrt(b2) / rn;  // (as k_blk_lds)
+    double eps = aim * tol * sqrt(b2) / rn;
     if (eps < inner_floor) eps = inner_floor;
     const int nl = (int)((HV + blockDim.x - 1) / blockDim.x);  // sites per thread
     int phase = 0;
@@ -1489,7 +1488,7 @@ __global__ __launch_bounds__(BM_MAX) void k_blk_mr(Geom g, EoFields<S> F, const 
                 store_r(l, r);
             }
         }
-        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > BL_GAIN * BL_GAIN * window);
+        slow = !isfinite(r2n) || (r2n > thr2 && it % BL_WINDOW == 0 && r2n > GAIN * GAIN * window);
         if (!(r2n > thr2) || slow) break;
         if (it % BL_WINDOW == 0) window = r2n;
         __syncthreads();
@@ -1518,8 +1517,8 @@ static size_t mr_mask_bytes(const Geom& g) { return ((size_t)2 * g.hvb * sizeof(
 bool blk_mr_fits(const Geom& g, int lds_max) { return g.eo && mr_mask_bytes(g) + 2 * 8 * 16 * 8 <= (size_t)lds_max; }
 template <class S>
 void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* Ainv, const double2* re, double2* xe,
-                   void* const w[7], const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
-                   int colour, int nrhs, int lds_max) {
+                   void* const w[7], const double* bb, const double* rr, double mass4, double tol, double aim, int maxit,
+                   int* iters, int colour, int nrhs, int lds_max) {
     Timed t(e, 2, 0);
     typedef typename Traits<S>::word W;
     const int threads = block_threads_for(g, e.blk_threads, BM_MAX);
@@ -1527,23 +1526,23 @@ void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* A
     const size_t recs = (size_t)g.hvb * (std::is_same<S, H16>::value ? 52 : 96);
     const bool rlds = masks + recs + 2 * 8 * 16 * 8 <= (size_t)lds_max;
     const size_t lds = std::max(rlds ? masks + recs : masks, std::min((size_t)e.blk_lds << 10, (size_t)lds_max - 2 * 8 * 16 * 8));
-    const double floor_eps = std::is_same<S, H16>::value ? 1e-3 : 2e-6;
+    const double floor_eps = std::is_same<S, H16>::value ? 1e-3 : MR_FLOOR32;
     const int steps = maxit < (1 << 30) ? 2 * maxit : maxit;
     if (rlds)
         k_blk_mr<S, true><<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (W*)w[0], (W*)w[4], (W*)w[6],
-                                                                    (float4*)w[5], bb, rr, mass4, tol, floor_eps, steps,
+                                                                    (float4*)w[5], bb, rr, mass4, tol, aim, floor_eps, steps,
                                                                     iters, colour, nrhs);
     else
         k_blk_mr<S, false><<<g.NBc * nrhs, threads, lds, e.stream>>>(g, F, Ainv, re, xe, (W*)w[0], (W*)w[4], (W*)w[6],
-                                                                     (float4*)w[5], bb, rr, mass4, tol, floor_eps, steps,
+                                                                     (float4*)w[5], bb, rr, mass4, tol, aim, floor_eps, steps,
                                                                      iters, colour, nrhs);
 }
 template void launch_blk_mr<float>(Exec&, const Geom&, const EoFields<float>&, const float4*, const double2*, double2*,
-                                   void* const[7], const double*, const double*, double, double, int, int*, int, int,
-                                   int);
+                                   void* const[7], const double*, const double*, double, double, double, int, int*, int,
+                                   int, int);
 template void launch_blk_mr<H16>(Exec&, const Geom&, const EoFields<H16>&, const float4*, const double2*, double2*,
-                                 void* const[7], const double*, const double*, double, double, int, int*, int, int,
-                                 int);
+                                 void* const[7], const double*, const double*, double, double, double, int, int*, int,
+                                 int, int);
 
 // LDS bytes of the FP64 passes through LDS, 0 for blocks that do not fit
 static size_t pass_lds(const Geom& g, int lds_max) {

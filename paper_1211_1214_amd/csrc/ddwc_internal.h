@@ -25,6 +25,19 @@ struct BiState {
 // coefficients a (alpha), b (omega) that minimise ||r - a t1 - b t2|| and decides convergence.
 enum Stage { ST_SUM = 0, ST_INIT = 1, ST_ALPHA = 2, ST_OMEGA = 3, ST_RR = 4, ST_LS = 5 };
 
+// The residual that an inner solve aims at, in units of the tolerance.  Minimal residual stops close to its aim, and what
+// it leaves are the smooth modes, which add up in an exponent, where BiCGStab ends below its aim with a residual like
+// noise.  So it aims lower, the one-step one of the blocks most (by what a step costs, in the LDS or in memory), and its FP32
+// launches end lower than BiCGStab's 2e-6, so that two of them reach the aim.  Relative errors of exponents at tol 1e-10
+// (six configurations each), BiCGStab alone / minimal residual at 0.5 (global) and 0.25 (blocks) / as here: 48x24^3, 6^4
+// blocks 0.50 / 6.7 / 0.29e-12, 24x12^3 2.1 / 2.5 / 0.8e-12, 32x16^3, 4^4 2.5 / 2.3 / 0.9e-12, 8^4 in FP16 2.6 / 5.0 /
+// 1.3e-12, 4^4 lattice 8.2 / 8.3 / 0.8e-12, nested 32x16^3 1.6 / 2.9 / 0.1e-12; of solutions, 24x12^3 1.9 / 2.2 / 0.7e-10.
+// An estimate at 48x24^3 takes 6% longer for it.
+constexpr double BI_AIM = 0.5, LS_AIM = 0.25, MR_AIM = 0.05, MR_AIM_LDS = 0.01;
+constexpr double MR_FLOOR32 = 5e-7;
+// (loose solves precondition or smooth: nobody adds up what they leave)
+inline double mr_aim(double tol, double aim) { return tol >= 1e-4 ? 0.25 : aim; }
+
 // Epilogues of the even-odd operator kernel (launch_eo_diaghop).
 enum EoEpi { EOE_NONE = 0, EOE_DOT = 1, EOE_DOT4 = 2, EOE_RESID = 3, EOE_LS1 = 4, EOE_LS2 = 5 };
 constexpr int LS1_NV = 4, LS_NV = 9;  // values of LS1, and of a whole cycle (LS1 then LS2)
@@ -284,8 +297,8 @@ void launch_blk_recon(Exec& e, const Geom& g, const double2* to, const double2* 
 bool blk_mr_fits(const Geom& g, int lds_max_bytes);
 template <class S>
 void launch_blk_mr(Exec& e, const Geom& g, const EoFields<S>& F, const float4* Ainv, const double2* re, double2* xe,
-                   void* const w[7], const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
-                   int colour, int nrhs, int lds_max);
+                   void* const w[7], const double* bb, const double* rr, double mass4, double tol, double aim, int maxit,
+                   int* iters, int colour, int nrhs, int lds_max);
 template <class S>
 void launch_blk_inner(Exec& e, const Geom& g, const EoFields<S>& F, const typename Traits<S>::kword* Ainv,
                       const double2* re, double2* xe, void* const w[7], const double* bb, const double* rr,
@@ -297,8 +310,8 @@ void launch_blk_inner(Exec& e, const Geom& g, const EoFields<S>& F, const typena
 // layout (slabs 1, 2, 5) for the blocks left.
 bool blk_lds_fits(const Geom& g, int lds_max_bytes);
 void launch_blk_lds(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
-                    double2* xe, const double* bb, const double* rr, double mass4, double tol, int maxit, int* iters,
-                    int colour, int nrhs);
+                    double2* xe, const double* bb, const double* rr, double mass4, double tol, double aim, int maxit,
+                    int* iters, int colour, int nrhs);
 void launch_blk_lds_bi(Exec& e, const Geom& g, const EoFields<float>& F, const float4* Ainv, const double2* re,
                        double2* xe, void* const w[7], const double* bb, const double* rr, double mass4, double tol,
                        int maxit, int* iters, int colour, int nrhs);

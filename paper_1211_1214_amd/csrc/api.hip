@@ -13,6 +13,7 @@
 
 #include "../../include/ddwc.h"
 #include "ddwc_internal.h"
+#include "tile_order.h"
 
 using namespace ddwc;
 
@@ -167,7 +168,12 @@ struct ddwc_ctx {
     int opt_blk_kernel = 0;   // block inner solver: 0 LDS-resident where it fits (FP32/FP16), 1 global-memory
     int opt_op_threads = WG;  // workgroup size of the global solver's RHS-innermost operator kernels
     int opt_tile_order = 1;   // their dispatch order: 0 half-site index order, 1 interleaved by block rank
-    std::map<std::string, std::pair<int*, std::vector<int>>> orders;  // cached tile orders (device, host)
+    struct Order {
+        int* tile = nullptr;           // the table
+        hipStream_t on = nullptr;      // the stream that it was written on, and the end of that (null: known to be over)
+        hipEvent_t written = nullptr;
+    };
+    std::map<std::vector<int>, Order> orders;  // dispatch orders by shape
     int lds_max = 0;          // LDS bytes per workgroup of the device
     void* scratch = nullptr;  // this device's copy of the static scratch (ddwc_dslash_apply_noalloc)
     hipStream_t cap = nullptr;  // private stream the graphs are captured on
@@ -376,7 +382,10 @@ extern "C" int ddwc_destroy(ddwc_ctx* C) {
     }
     for (auto& kv : C->ws)
         if (kv.second.p) (void)hipFree(kv.second.p);
-    for (auto& kv : C->orders) (void)hipFree(kv.second.first);
+    for (auto& kv : C->orders) {
+        if (kv.second.written) (void)hipEventDestroy(kv.second.written);
+        (void)hipFree(kv.second.tile);
+    }
     if (C->host) (void)hipHostFree(C->host);
     delete C;
     return DDWC_OK;
@@ -447,7 +456,11 @@ EoFields<H16> eo_fields<H16>(const ddwc_ctx* C, bool site_major) {
 // blocks in its shortest direction.  48x24^3, 12 RHS (12^3 columns, one per XCD), with non-temporal stores and
 // staging: hop-and-inverse 324 -> 306 us, diagonal-and-hop 448 / 373 -> 415 / 350 us against blocks of both colours
 // in turn; columns of 6^3, 6x12x12, 12x12x24, 24^3: 322, 317, 318, 344 us.
-static int tile_order(ddwc_ctx* C, int parities, int nrhs, int nt, double bytes, const int** out) {
+//
+// The table of a shape is written by a kernel on the stream of the first call that uses it, and later calls on other streams wait
+// for that.  Nothing is allocated or waited for on a stream that is being captured: a call there runs in index order (null)
+// unless its table is complete.
+static int tile_order(ddwc_ctx* C, Exec& ex, int parities, int nrhs, int nt, double bytes, const int** out) {
     constexpr double COLUMN_BYTES = 1.4e6;
     const Geom& g = C->g;
     const int slice = g.Vb / g.b[0] / 2;  // sites of one parity in a time slice of a block
@@ -469,36 +482,47 @@ static int tile_order(ddwc_ctx* C, int parities, int nrhs, int nt, double bytes,
             break;
         }
     }
-    const std::string key = std::to_string(parities) + "/" + std::to_string(nrhs) + "/" + std::to_string(nt) + "/" +
-                            std::to_string(c[1]) + "/" + std::to_string(c[2]) + "/" + std::to_string(c[3]);
+    TileOrder o{{c[1], c[2], c[3]}, parities, nrhs, 0};
+    while (1 << o.shift < nt) ++o.shift;
+    *out = nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ex.stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return DDWC_OK;
+    }
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    const std::vector<int> key = {parities, nrhs, nt, c[1], c[2], c[3]};
     auto it = C->orders.find(key);
     if (it == C->orders.end()) {
-        const long long per_block = (long long)parities * g.hvb;
-        const long long pairs = per_block * g.NB * nrhs;
-        const int ntiles = (int)((pairs + nt - 1) / nt);
-        std::vector<std::pair<long long, int>> keys(ntiles);
-        for (int t = 0; t < ntiles; ++t) {
-            const long long i = (long long)t * nt / nrhs;  // first site of the tile
-            const long long B = i / per_block;
-            const int h = (int)(i - B * per_block) % g.hvb;
-            const Site S = decode(g, (int)(B * g.Vb));
-            long long col = 0, in = 0;
-            for (int m = 1; m < 4; ++m) {
-                col = col * (g.nb[m] / c[m]) + S.n[m] / c[m];
-                in = in * c[m] + S.n[m] % c[m];
-            }
-            const long long time = (long long)S.n[0] * g.b[0] + h / slice;
-            keys[t] = {((col * g.L[0] + time) * ((long long)c[1] * c[2] * c[3]) + in) * (long long)ntiles + t, t};
+        if (capturing) return DDWC_OK;
+        ddwc_ctx::Order q;
+        HC(hipMalloc(&q.tile, sizeof(int) * o.first((long long)parities * g.hvb * g.NB)));
+        launch_tile_order(ex, g, o, q.tile);
+        q.on = ex.stream;
+        if (hipEventCreateWithFlags(&q.written, hipEventDisableTiming) != hipSuccess ||
+            hipEventRecord(q.written, ex.stream) != hipSuccess) {
+            (void)hipGetLastError();
+            if (q.written) (void)hipEventDestroy(q.written);
+            q.written = nullptr;
+            HC(hipStreamSynchronize(ex.stream));
         }
-        std::sort(keys.begin(), keys.end());
-        std::vector<int> ord(ntiles);
-        for (int t = 0; t < ntiles; ++t) ord[t] = keys[t].second;
-        int* d = nullptr;
-        HC(hipMalloc(&d, sizeof(int) * ntiles));
-        HC(hipMemcpy(d, ord.data(), sizeof(int) * ntiles, hipMemcpyHostToDevice));
-        it = C->orders.emplace(key, std::make_pair(d, std::move(ord))).first;
+        it = C->orders.emplace(key, q).first;
+    } else if (it->second.written) {
+        ddwc_ctx::Order& q = it->second;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (a query is no work of the captured stream)
+        HC(hipThreadExchangeStreamCaptureMode(&mode));
+        const hipError_t e = hipEventQuery(q.written);
+        HC(hipThreadExchangeStreamCaptureMode(&mode));
+        if (e == hipSuccess) {
+            (void)hipEventDestroy(q.written);
+            q.written = nullptr;
+        } else {
+            (void)hipGetLastError();
+            if (capturing) return DDWC_OK;
+            if (q.on != ex.stream) HC(hipStreamWaitEvent(ex.stream, q.written, 0));
+        }
     }
-    *out = it->second.first;
+    *out = it->second.tile;
     return DDWC_OK;
 }
 
@@ -606,14 +630,14 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     EoFields<S> FR = eo_fields<S>(C, ri && !fp64);  // RI kernels read own-site link records
     const double rs = h16 ? 52.0 : 24.0 * sizeof(R);  // bytes of a stored spinor
     if (g.eo && C->opt_tile_order == 1) {
-        if (ri) CK(tile_order(C, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs * nrhs, &FR.order));
+        if (ri) CK(tile_order(C, ex, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs * nrhs, &FR.order));
         // RHS-major kernels take the order for one RHS: 32x16^3 in FP64 (both parities in the last-level cache) hop-and-
         // inverse 38.6 -> 24.9, diagonal-and-hop 39.2 -> 30.6 us.  With 12 RHS, whose tiles of sites are dispatched
         // together, it costs 9% (48x24^3, diagonal-and-hop 1275 -> 1393 us); on 16^4 it gives nothing (FP32 solve 1.57 ->
         // 1.60 ms).
         const bool one = nrhs == 1 && g.V >= 1 << 17;
-        if (one) CK(tile_order(C, 1, 1, WG, 192.0, &F64.order));
-        if (one && !ri) CK(tile_order(C, 1, 1, WG, rs, &FR.order));
+        if (one) CK(tile_order(C, ex, 1, 1, WG, 192.0, &F64.order));
+        if (one && !ri) CK(tile_order(C, ex, 1, 1, WG, rs, &FR.order));
     }
     const int ntR = vector_tiles(n2, nrhs, ri);
     const int ntM = eo_op_tiles(FR, nrhs, ri);  // tiles of the operator kernels' partial sums
@@ -1136,19 +1160,19 @@ static int dslash_apply_with(ddwc_ctx* C, Exec& ex, double kappa, const void* in
     const bool ordered = may_allocate && g.eo && C->opt_tile_order == 1 && g.V >= (1 << 15);
     if (prec == DDWC_FP64) {
         // (spinors and backward links are gathered)
-        if (ordered) CK(tile_order(C, 2, 1, DW, 192.0 * nrhs + 576.0, &order));
+        if (ordered) CK(tile_order(C, ex, 2, 1, DW, 192.0 * nrhs + 576.0, &order));
         launch_import<double>(ex, g, in, (double2*)a, nrhs, MASK_ALL);
         launch_dslash<double>(ex, g, C->U64, C->K64, mass4, (const double2*)a, out, true, nrhs, DDWC_K_DSLASH64,
                               ddwc_dslash_bytes(C, nrhs, DDWC_FP64), order);
     } else if (nrhs > 1 && nrhs <= WG && ri_fits((unsigned)g.V, nrhs)) {
         // several RHS: RHS-innermost fields, the RHS of a site share its links and clover
         const int nt = C->opt_op_threads;
-        if (ordered) CK(tile_order(C, 2, nrhs, nrhs <= nt ? nt : WG, 96.0 * nrhs, &order));
+        if (ordered) CK(tile_order(C, ex, 2, nrhs, nrhs <= nt ? nt : WG, 96.0 * nrhs, &order));
         launch_import_ri32(ex, g, in, (float4*)a, nrhs);
         launch_dslash_ri32(ex, g, C->U32s, C->K32, mass4, (const float4*)a, out, nrhs, DDWC_K_DSLASH32,
                            ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32), nt, order);
     } else {
-        if (ordered) CK(tile_order(C, 2, 1, DW, 96.0 * nrhs + 288.0, &order));
+        if (ordered) CK(tile_order(C, ex, 2, 1, DW, 96.0 * nrhs + 288.0, &order));
         launch_import<float>(ex, g, in, (float4*)a, nrhs, MASK_ALL);
         launch_dslash<float>(ex, g, C->U32, C->K32, mass4, (const float4*)a, out, true, nrhs, DDWC_K_DSLASH32,
                              ddwc_dslash_bytes(C, nrhs, DDWC_MIXED32), order);

@@ -112,6 +112,9 @@ void launch_dslash_ri32(Exec& e, const Geom& g, const cx<float>* Us, const float
                         void* out, int nrhs, int kclass, double bytes, int op_threads = WG,
                         const int* order = nullptr);
 int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads);
+// order[slot] = the tile dispatched there, for all tiles of the fields (tile_order.h; every block extent even)
+struct TileOrder;
+void launch_tile_order(Exec& e, const Geom& g, const TileOrder& o, int* order);
 void launch_nbr_build(Exec& e, const Geom& g, int* nbr);
 void launch_clover_build(Exec& e, const Geom& g, const cx<double>* U64, double csw, double2* K64, float4* K32);
 

@@ -12,6 +12,7 @@
 
 #include "ddwc_internal.h"
 #include "clover_build.h"
+#include "tile_order.h"
 #include "uniform_mem.h"
 #include "vec_items.h"
 
@@ -957,6 +958,53 @@ void launch_dslash_ri32(Exec& e, const Geom& g, const cx<float>* Us, const float
         default: launch(std::integral_constant<int, WG>()); break;
     }
 }
+// The table of a dispatch order (tile_order.h), one workgroup per column: the tiles of the columns before give its place,
+// then every thread counts the tiles of a run of cells and, after a scan, writes them.  On the call's stream, where a table
+// made by the host (a sort of 10368 tiles, an allocation and a blocking copy) made the first call on a context at
+// 48x24^3 take 0.90 ms in FP64 with one RHS and 2.55 in FP32 with 12 instead of 0.50 and 1.51.
+constexpr int TO_THREADS = 1024;
+__global__ __launch_bounds__(TO_THREADS) void k_tile_order(Geom g, TileOrder o, int* __restrict__ order) {
+    __shared__ int scan[TO_THREADS];
+    __shared__ int start;
+    const int t = threadIdx.x, col = blockIdx.x, nin = o.blocks(), cells = g.L[0] * nin;
+    if (t == 0) start = 0;
+    __syncthreads();
+    const int per_column = g.nb[0] * nin, per_block = o.parities * g.hvb;
+    int before = 0;
+    for (int j = t; j < col * per_column; j += TO_THREADS) {
+        const int q = j / per_column, w = j - q * per_column;
+        const long long B = o.block(g, q, w / nin, w % nin);
+        before += o.first((B + 1) * per_block) - o.first(B * per_block);
+    }
+    atomicAdd(&start, before);
+    const int run = (cells + TO_THREADS - 1) / TO_THREADS;
+    const int k0 = min(cells, t * run), k1 = min(cells, k0 + run);
+    int mine = 0, from, to;
+    for (int k = k0; k < k1; ++k)
+        for (int p = 0; p < o.parities; ++p) {
+            o.tiles(g, col, k, p, from, to);
+            mine += to - from;
+        }
+    scan[t] = mine;
+    __syncthreads();
+    for (int d = 1; d < TO_THREADS; d *= 2) {
+        const int v = t >= d ? scan[t - d] : 0;
+        __syncthreads();
+        scan[t] += v;
+        __syncthreads();
+    }
+    int at = start + scan[t] - mine;
+    for (int k = k0; k < k1; ++k)
+        for (int p = 0; p < o.parities; ++p) {
+            o.tiles(g, col, k, p, from, to);
+            for (int tile = from; tile < to; ++tile) order[at++] = tile;
+        }
+}
+void launch_tile_order(Exec& e, const Geom& g, const TileOrder& o, int* order) {
+    Timed t(e, 4, 0);
+    k_tile_order<<<o.columns(g), TO_THREADS, 0, e.stream>>>(g, o, order);
+}
+
 int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads) {
     const int NTr = nrhs <= op_threads ? op_threads : WG;
     return (int)(((long long)g.V * nrhs + NTr - 1) / NTr);

@@ -206,3 +206,44 @@ extern "C" int host_h16_roundtrip(const double* in, double* out, float* scale_ou
     *scale_out = buf.scale[0];
     return 0;
 }
+
+// Dispatch order of the tiles: the kernel's walk over columns and cells, and the same by sorting all tiles on the position
+// of their first site.  Returns the number of tiles; -1 if a column does not start where the counts of those before say.
+#include <algorithm>
+#include <array>
+#include "../../paper_1211_1214_amd/csrc/tile_order.h"
+extern "C" int host_tile_order(const int* lat, const int* blk, int parities, int nrhs, int nt, const int* c, int* walked,
+                               int* sorted) {
+    const Geom g = make_geom(lat, blk, -1);
+    TileOrder o{{c[0], c[1], c[2]}, parities, nrhs, 0};
+    while (1 << o.shift < nt) ++o.shift;
+    const int per_block = parities * g.hvb, nin = o.blocks();
+    int at = 0, before = 0;
+    for (int col = 0; col < o.columns(g); ++col) {
+        if (at != before) return -1;
+        for (int k = 0; k < g.L[0] * nin; ++k)
+            for (int p = 0; p < parities; ++p) {
+                int from, to;
+                o.tiles(g, col, k, p, from, to);
+                for (int t = from; t < to; ++t) walked[at++] = t;
+            }
+        for (int w = 0; w < g.nb[0] * nin; ++w) {
+            const long long B = o.block(g, col, w / nin, w % nin);
+            before += o.first((B + 1) * per_block) - o.first(B * per_block);
+        }
+    }
+    const long long pairs = (long long)per_block * g.NB * nrhs;
+    const int n = (int)((pairs + nt - 1) / nt);
+    std::vector<std::array<int, 9>> keys(n);
+    for (int t = 0; t < n; ++t) {
+        const long long i = (long long)t * nt / nrhs;
+        const int B = (int)(i / per_block), loc = (int)(i % per_block);
+        // (half fields: site h of block B is taken as the even site there, which has its coordinates up to x3)
+        const Site S = decode(g, B * g.Vb + loc);
+        const int time = S.n[0] * g.b[0] + S.l[0];
+        keys[t] = {S.n[1] / c[0], S.n[2] / c[1], S.n[3] / c[2], time, S.n[1] % c[0], S.n[2] % c[1], S.n[3] % c[2], t, 0};
+    }
+    std::sort(keys.begin(), keys.end());
+    for (int t = 0; t < n; ++t) sorted[t] = keys[t][7];
+    return at == n && at == before ? n : -1;
+}

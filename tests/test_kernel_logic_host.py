@@ -24,7 +24,7 @@ def L():
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     deps = [SRC] + [os.path.join(HERE, "..", "paper_1211_1214_amd", "csrc", f)
-                    for f in ("ddwc_device.h", "clover_build.h", "eo.h", "force.h")]
+                    for f in ("ddwc_device.h", "clover_build.h", "eo.h", "force.h", "tile_order.h")]
     if not os.path.exists(LIB) or os.path.getmtime(LIB) < max(os.path.getmtime(d) for d in deps):
         subprocess.check_call([hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-shared", SRC,
                                "-o", LIB + ".tmp"], stderr=subprocess.DEVNULL)
@@ -152,3 +152,18 @@ def test_host_fp16_spinor_storage(L):
     sc = np.ones(1, dtype=np.float32)
     L.host_h16_roundtrip(z.ctypes.data, out.ctypes.data, sc.ctypes.data)
     assert sc[0] == 0 and np.all(out == 0)
+
+
+@pytest.mark.parametrize("nrhs,nt", [(1, 64), (1, 256), (3, 128), (12, 256), (7, 512), (200, 256)])
+@pytest.mark.parametrize("parities", [1, 2])
+@pytest.mark.parametrize("lat,blk,col", [((4, 4, 4, 4), (2, 2, 2, 2), (1, 1, 1)), ((12, 8, 8, 16), (6, 4, 2, 4), (1, 2, 2)),
+                                         ((8, 12, 8, 4), (2, 2, 4, 2), (3, 1, 2)), ((16, 4, 12, 12), (4, 2, 6, 2), (2, 2, 3))])
+def test_host_tile_order(L, lat, blk, col, parities, nrhs, nt):
+    """The table of the dispatch order is the tiles sorted by column, time slice, block and number."""
+    most = int(np.prod(lat)) * nrhs // nt + 2
+    walked, want = np.full(most, -1, np.int32), np.full(most, -1, np.int32)
+    I4 = ctypes.c_int * 4
+    n = L.host_tile_order(I4(*lat), I4(*blk), parities, nrhs, nt, (ctypes.c_int * 3)(*col),
+                          walked.ctypes.data_as(ctypes.c_void_p), want.ctypes.data_as(ctypes.c_void_p))
+    assert n == -(-int(np.prod(lat)) // 2 * parities * nrhs // nt)
+    assert np.array_equal(walked, want)

@@ -289,8 +289,9 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *   DDWC_OPT_OP_THREADS    workgroup size of the RHS-innermost operator kernels (the even-odd
  *                          global solver's, and ddwc_dslash_apply's with several FP32 RHS): 128,
  *                          256 (default) or 512; a value below the RHS count runs 256.
- *   DDWC_OPT_TILE_ORDER    dispatch order of those kernels' workgroups, and of the operator's with one
- *                          RHS on lattices from 2^17 sites: 0 site index order;
+ *   DDWC_OPT_TILE_ORDER    dispatch order of those kernels' workgroups, of ddwc_dslash_apply's on lattices
+ *                          from 2^15 sites, and of the global solver's with one RHS on lattices from
+ *                          114688 sites: 0 site index order;
  *                          1 (default, with every block extent even) time slice by time slice
  *                          through spatial columns of blocks, so that an XCD finds neighbours
  *                          in its L2 (not in ddwc_dslash_apply_noalloc, which builds no order

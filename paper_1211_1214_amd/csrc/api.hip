@@ -631,11 +631,14 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     const double rs = h16 ? 52.0 : 24.0 * sizeof(R);  // bytes of a stored spinor
     if (g.eo && C->opt_tile_order == 1) {
         if (ri) CK(tile_order(C, ex, 1, nrhs, eo_op_threads(FR, nrhs, ri), rs * nrhs, &FR.order));
-        // RHS-major kernels take the order for one RHS: 32x16^3 in FP64 (both parities in the last-level cache) hop-and-
-        // inverse 38.6 -> 24.9, diagonal-and-hop 39.2 -> 30.6 us.  With 12 RHS, whose tiles of sites are dispatched
-        // together, it costs 9% (48x24^3, diagonal-and-hop 1275 -> 1393 us); on 16^4 it gives nothing (FP32 solve 1.57 ->
-        // 1.60 ms).
-        const bool one = nrhs == 1 && g.V >= 1 << 17;
+        // RHS-major kernels take the order for one RHS, from 114688 sites on, where the links are twice the L2s.  Solves to
+        // 1e-10, index order / this, in FP64 and in FP32: 16^4 with 4^4 and 8^4 blocks 3.47 / 3.48, 3.36 / 3.43 and 2.59 / 2.63,
+        // 2.52 / 2.58 ms; 24x16^3 with 4^4 and 6x8^3 blocks 4.41 / 4.16, 4.19 / 4.36 and 3.00 / 3.00, 2.88 / 3.01 ms; 28x16^3
+        // 5.39 / 4.58 and 3.24 / 3.17 ms; 32x16^3 with 4^4 and 8^4 blocks 6.93 / 5.14, 6.55 / 5.83 and 3.61 / 3.44, 3.44 / 3.54 ms;
+        // 48x24^3 31.7 / 29.6 and 16.1 / 15.7 ms.  With several RHS only the FP64 residuals of a mixed solve are RHS-major:
+        // 2, 4, 8 RHS at 32x16^3 gain 1.3%, 0.6%, 0, and 12 RHS, whose tiles of sites are dispatched together, lose 9% of them
+        // (48x24^3, diagonal-and-hop 1275 / 1393 us).
+        const bool one = nrhs == 1 && g.V >= 7 << 14;
         if (one) CK(tile_order(C, ex, 1, 1, WG, 192.0, &F64.order));
         if (one && !ri) CK(tile_order(C, ex, 1, 1, WG, rs, &FR.order));
     }

@@ -1,6 +1,6 @@
 """Dispatch orders of the operator: the first call of a shape (its table is written on the call's stream), later ones, one on
 another stream, and one that is captured into a graph before its table exists give what index order gives
-(ddwc_dslash_apply_noalloc), bit for bit."""
+(ddwc_dslash_apply_noalloc), bit for bit; and so does a solve."""
 import numpy as np
 import pytest
 
@@ -85,4 +85,17 @@ def test_captured_call(warm):
         assert torch.equal(out, index_order(ctx, w, dd.FP64))
         assert torch.equal(out, ctx.dslash_apply(KAPPA, w))
     del g
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", [dd.FP64, dd.MIXED32])
+@pytest.mark.parametrize("lat,blk", [((24, 16, 16, 16), (4, 4, 4, 4)), ((28, 16, 16, 16), (2, 4, 4, 4))])
+def test_solve(lat, blk, prec):
+    """One right-hand side below and from the size on from which the global solver's tiles are ordered: the same bits."""
+    ctx = context(lat, blk)
+    v = spinors(lat, 1)
+    x, _ = ctx.solve(KAPPA, v, tol=1e-10, prec=prec)
+    ctx.set_option(binding.OPT_TILE_ORDER, 0)
+    y, _ = ctx.solve(KAPPA, v, tol=1e-10, prec=prec)
+    assert torch.equal(x, y)
     ctx.close()

@@ -545,7 +545,7 @@ DDWC_HD int table_entry(const Geom& g, int s, const Site& S, int mu) {
 }
 
 // Which hops a site operator includes.
-enum HopSet { HOPS_ALL = 1, HOPS_INSIDE = 2, HOPS_CROSSING = 3 };
+enum HopSet { HOPS_INSIDE = 2, HOPS_CROSSING = 3 };
 
 // acc = sum over the selected hops of site s of (1 -+ g_mu) W psi(neighbour), unscaled; a
 // hop across an antiperiodic time boundary is subtracted.  The index space has length n
@@ -569,7 +569,7 @@ DDWC_HD void hop_sum(unsigned n, unsigned s, const W* __restrict__ in, const cx<
         const int e = at(nbr + (size_t)d * n, s);
         const unsigned t = e < 0 ? (unsigned)~e : (unsigned)e;
         const bool inside = (t < n / 2) == s_black;
-        const bool take = HOPS == HOPS_ALL || (HOPS == HOPS_INSIDE && inside) || (HOPS == HOPS_CROSSING && !inside);
+        const bool take = HOPS == HOPS_INSIDE ? inside : !inside;
         if (take) {
             cx<R> q[12], u[9];
             load_spinor(in, n, t, q);

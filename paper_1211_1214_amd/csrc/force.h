@@ -190,37 +190,4 @@ DDWC_HD M3 force_clover_link(int mu, int x, const NB& nb, const LU& ldU, const L
     return G;
 }
 
-// The same from the clover term at one site y: add(dir, site, Z) receives the contribution to the gradient of
-// every link of the leaves at y (the kernels gather per link instead; checks on the host use this form).
-template <class ADD>
-DDWC_HD void force_clover_site(const Geom& g, const cx<double>* U, double csw, const double2* a, const double2* b,
-                               const double* w, int nrhs, int y, const ADD& adder) {
-    M3 L[2][3], J[6];
-    for (int k = 0; k < 2; ++k) force_outer(a, b, w, nrhs, (unsigned)g.V, (unsigned)y, k, L[k]);
-    for (int l = 0; l < 3; ++l) force_planes(L[0][l], L[1][l], l, csw, J[l], J[3 + l]);
-    M3 zero;
-    for (int k = 0; k < 9; ++k) zero.a[k] = mk(0.0, 0.0);
-    auto ldU = [&](int mu, int s) { return ld(U, g, mu, s); };
-    for (int mu = 0; mu < 4; ++mu)
-        for (int nu = mu + 1; nu < 4; ++nu)
-            for (int c = 0; c < 4; ++c) {  // y is corner c of the plaquette at z
-                int z = y;
-                if (c == 1 || c == 2) z = step<-1>(g, z, mu);
-                if (c == 2 || c == 3) z = step<-1>(g, z, nu);
-                const int zm = step<+1>(g, z, mu), zn = step<+1>(g, z, nu), zmn = step<+1>(g, zm, nu);
-                const int at[4] = {z, zm, zmn, zn};
-                // (on a lattice of extent 2 other corners can be the same site: only corner c counts here)
-                for (int q = 0; q < 4; ++q) {
-                    auto corner = [&](int k) { return at[k]; };
-                    int seen = 0;
-                    auto ldJ = [&](int slot, int) {  // called for corners q + 1, q + 2, q + 3, q + 4
-                        const int k = (q + 1 + seen++) & 3;
-                        return k == c ? J[slot] : zero;
-                    };
-                    const M3 Z = plaquette_link_force(mu, nu, q, corner, ldU, ldJ);
-                    adder((q & 1) ? nu : mu, q == 0 ? z : q == 1 ? zm : q == 2 ? zn : z, Z);
-                }
-            }
-}
-
 }  // namespace ddwc

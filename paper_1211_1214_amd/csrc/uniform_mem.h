@@ -81,17 +81,25 @@ __device__ __forceinline__ T* fresh(T* p) {
 }
 
 // Orders the computation of a spinor before every later fresh(), pin() and reissue(): instruction
-// selection otherwise gathers the loads of a long straight-line body at its start and spills them.
+// selection otherwise gathers the loads of a long straight-line body at its start and spills them.  (On the host, where
+// hops_pipelined is checked too, there is nothing to order.)
 template <class R>
-__device__ __forceinline__ void pin6(cx<R> p[6]) {
+DDWC_HD void pin6(cx<R> p[6]) {
+#if defined(__HIP_DEVICE_COMPILE__)
     asm volatile(""
                  : "+v"(p[0].re), "+v"(p[0].im), "+v"(p[1].re), "+v"(p[1].im), "+v"(p[2].re), "+v"(p[2].im),
                    "+v"(p[3].re), "+v"(p[3].im), "+v"(p[4].re), "+v"(p[4].im), "+v"(p[5].re), "+v"(p[5].im));
+#endif
 }
 template <class R>
-__device__ __forceinline__ void pin(cx<R> p[12]) {
+DDWC_HD void pin(cx<R> p[12]) {
     pin6(p);
     pin6(p + 6);
+}
+DDWC_HD void sched_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
 }
 // The loads addressed with the returned offset are issued after the last pin().
 __device__ __forceinline__ unsigned reissue(unsigned off) {
@@ -245,7 +253,7 @@ struct UDiag {
 // it is in flight during the products of hop d at no cost in registers, and (NEXT_LINK) the next link
 // beside the current one.
 template <class R, bool NEXT_LINK, class LQ, class LU, class Flip, class Take>
-__device__ __forceinline__ void hops_pipelined(cx<R> acc[12], LQ&& lq, LU&& lu, Flip&& flip, Take&& take) {
+DDWC_HD void hops_pipelined(cx<R> acc[12], LQ&& lq, LU&& lu, Flip&& flip, Take&& take) {
     cx<R> q[12], u[9], un[9], h[6];
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = mk(R(0), R(0));
@@ -254,7 +262,7 @@ __device__ __forceinline__ void hops_pipelined(cx<R> acc[12], LQ&& lq, LU&& lu, 
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
         if (NEXT_LINK && d + 1 < 8) lu(d + 1, un);
-        __builtin_amdgcn_sched_barrier(0);
+        sched_barrier();
         proj_dispatch<R>(d, q, h);
         if (d < 2 && flip(d)) {
 #pragma unroll
@@ -262,7 +270,7 @@ __device__ __forceinline__ void hops_pipelined(cx<R> acc[12], LQ&& lq, LU&& lu, 
         }
         pin6(h);
         if (d + 1 < 8) lq(d + 1, q);
-        __builtin_amdgcn_sched_barrier(0);
+        sched_barrier();
         if (take(d)) apply_dispatch<R>(d, u, h, acc);
         pin(acc);
         if (NEXT_LINK) {

@@ -5,8 +5,21 @@
 #include <vector>
 
 #include "../../paper_1211_1214_amd/csrc/clover_build.h"
+#include "../../paper_1211_1214_amd/csrc/uniform_mem.h"
 
 using namespace ddwc;
+
+// All hops of site s, as the operator kernels take them: field in, forward links Uf at s, backward links Ub at the
+// neighbour, table nbr (index spaces of n sites).
+static void all_hops(unsigned n, unsigned s, const double2* in, const cx<double>* Uf, const cx<double>* Ub, const int* nbr,
+                     cx<double> acc[12]) {
+    auto entry = [&](int d) { return nbr[(size_t)d * n + s]; };
+    auto target = [&](int d) { return d < 2 && entry(d) < 0 ? (unsigned)~entry(d) : (unsigned)entry(d); };
+    hops_pipelined<double, true>(
+        acc, [&](int d, cx<double> q[12]) { load_spinor(in, n, target(d), q); },
+        [&](int d, cx<double> u[9]) { load_link((d & 1) ? Ub : Uf, n, d >> 1, (d & 1) ? target(d) : s, u); },
+        [&](int d) { return entry(d) < 0; }, [](int) { return true; });
+}
 
 // mode: 0 full operator, 1 Dirichlet blocks of colour `colour` (other colour zero),
 //       2 hops crossing block faces into colour `colour` (other colour zero).
@@ -50,9 +63,12 @@ extern "C" int host_apply(const int* lat, const int* blk, int tbc, double csw, c
     for (int s = 0; s < V; ++s) {
         cx<double> y[12];
         const int c_s = s / (V / 2);
-        if (mode == 0)
-            site_operator<double, true, HOPS_ALL>(g, s, in.data(), U.data(), K.data(), nbr.data(), mass4, y, 8);
-        else if (mode == 1 && c_s == colour)
+        if (mode == 0) {
+            cx<double> c[12];
+            all_hops(V, s, in.data(), U.data(), U.data(), nbr.data(), y);
+            load_spinor(in.data(), V, s, c);
+            apply_diag<double>(K.data(), V, s, mass4, c, y, -0.5);
+        } else if (mode == 1 && c_s == colour)
             site_operator<double, true, HOPS_INSIDE>(g, s, in.data(), U.data(), K.data(), nbr.data(), mass4, y, 8);
         else if (mode == 2 && c_s == colour)
             site_operator<double, false, HOPS_CROSSING>(g, s, in.data(), U.data(), nullptr, nbr.data(), 0.0, y, 8);
@@ -118,7 +134,7 @@ extern "C" int host_eo_apply(const int* lat, const int* blk, int tbc, double csw
     // t_o = A_oo^-1 H_oe x_e
     for (int i = 0; i < n2; ++i) {
         cx<double> acc[12], w[12];
-        hop_sum<double, HOPS_ALL, false>(n2, i, xe.data(), U1, U0, nh.data() + (size_t)8 * n2, acc, 8);
+        all_hops(n2, i, xe.data(), U1, U0, nh.data() + (size_t)8 * n2, acc);
         for (int c = 0; c < 12; ++c) w[c] = mk(0.0, 0.0);
         apply_diag<double>(Ah.data(), n2, i, 0.0, acc, w, 0.0);
         store_spinor(xo.data(), n2, i, w);
@@ -127,7 +143,7 @@ extern "C" int host_eo_apply(const int* lat, const int* blk, int tbc, double csw
     // y_e = A_ee x_e - 1/4 H_eo t_o
     for (int i = 0; i < n2; ++i) {
         cx<double> acc[12], c[12];
-        hop_sum<double, HOPS_ALL, false>(n2, i, xo.data(), U0, U1, nh.data(), acc, 8);
+        all_hops(n2, i, xo.data(), U0, U1, nh.data(), acc);
         load_spinor(xe.data(), n2, i, c);
         apply_diag<double>(Kh.data(), n2, i, mass4, c, acc, -0.25);
         const int s = can[full_index(g, i, 0)];
@@ -142,13 +158,6 @@ extern "C" int host_eo_apply(const int* lat, const int* blk, int tbc, double csw
 // Link gradient of Re <a, D(U) b> (one RHS, weight 1) with the library's force code: hop part
 // and clover part, in canonical layout [4][V][3][3] (re, im).
 #include "../../paper_1211_1214_amd/csrc/force.h"
-struct HostAdder {
-    std::vector<cx<double>>* G;
-    int V;
-    void operator()(int mu, int s, const M3& m) const {
-        for (int k = 0; k < 9; ++k) (*G)[((size_t)mu * 9 + k) * V + s] = (*G)[((size_t)mu * 9 + k) * V + s] + m.a[k];
-    }
-};
 extern "C" int host_force(const int* lat, const int* blk, int tbc, double csw, const double* links_canon,
                           const double* a_canon, const double* b_canon, double* grad_canon) {
     Geom g = make_geom(lat, blk, tbc);
@@ -175,9 +184,29 @@ extern "C" int host_force(const int* lat, const int* blk, int tbc, double csw, c
     const double w = 1.0;
     for (int s = 0; s < V; ++s)
         for (int mu = 0; mu < 4; ++mu) force_hop_site(g, nbr.data(), a.data(), b.data(), &w, 1, G.data(), s, mu);
-    if (csw != 0.0) {
-        HostAdder add{&G, V};
-        for (int y = 0; y < V; ++y) force_clover_site(g, U.data(), csw, a.data(), b.data(), &w, 1, y, add);
+    if (csw != 0.0) {  // (the three passes of the kernels: outer products, planes, links)
+        std::vector<cx<double>> J((size_t)54 * V);
+        for (int y = 0; y < V; ++y) {
+            M3 L[2][3], P[6];
+            for (int k = 0; k < 2; ++k) force_outer(a.data(), b.data(), &w, 1, (unsigned)V, (unsigned)y, k, L[k]);
+            for (int l = 0; l < 3; ++l) force_planes(L[0][l], L[1][l], l, csw, P[l], P[3 + l]);
+            for (int slot = 0; slot < 6; ++slot)
+                for (int k = 0; k < 9; ++k) J[((size_t)slot * 9 + k) * V + y] = P[slot].a[k];
+        }
+        auto nb = [&](int d, int s) {
+            const int e = nbr[(size_t)d * V + s];
+            return e < 0 ? ~e : e;
+        };
+        for (int s = 0; s < V; ++s)
+            for (int mu = 0; mu < 4; ++mu) {
+                const M3 Z = force_clover_link(
+                    mu, s, nb, [&](int m, int t) { return ld(U.data(), g, m, t); },
+                    [&](int slot, int t) { return ld(J.data(), g, slot, t); });
+                for (int k = 0; k < 9; ++k) {
+                    cx<double>& o = G[((size_t)mu * 9 + k) * V + s];
+                    o = o + Z.a[k];
+                }
+            }
     }
     for (int s = 0; s < V; ++s)
         for (int mu = 0; mu < 4; ++mu)

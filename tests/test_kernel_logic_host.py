@@ -24,7 +24,7 @@ def L():
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     deps = [SRC] + [os.path.join(HERE, "..", "paper_1211_1214_amd", "csrc", f)
-                    for f in ("ddwc_device.h", "clover_build.h", "eo.h", "force.h", "tile_order.h")]
+                    for f in ("ddwc_device.h", "clover_build.h", "eo.h", "force.h", "tile_order.h", "uniform_mem.h")]
     if not os.path.exists(LIB) or os.path.getmtime(LIB) < max(os.path.getmtime(d) for d in deps):
         subprocess.check_call([hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-shared", SRC,
                                "-o", LIB + ".tmp"], stderr=subprocess.DEVNULL)

@@ -97,10 +97,10 @@ int ddwc_dslash_apply(ddwc_ctx *ctx, double kappa, const void *in, void *out, in
 /*
  * ddwc_dslash_apply for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): the same operator and result, bit for
- * bit, with the internal-layout fields in a static device array of the library (256 MiB per GPU,
+ * bit, with the internal-layout field in a static device array of the library (128 MiB per GPU,
  * held until the process ends) instead of the context's workspace.  The call allocates nothing
- * and creates no events.  EINVAL (nothing launched) when the two fields need more than 256 MiB:
- * 2 x nrhs x V x 192 bytes for DDWC_FP64, 2 x nrhs x V x 96 bytes otherwise (at 48x24^3: one FP64
+ * and creates no events.  EINVAL (nothing launched) when the field needs more than 128 MiB:
+ * nrhs x V x 192 bytes for DDWC_FP64, nrhs x V x 96 bytes otherwise (at 48x24^3: one FP64
  * RHS, two FP32 RHS).  Every call on one GPU shares that GPU's array, which keeps the last call's
  * contents: calls that overlap in time on one GPU (other streams, other threads, other contexts)
  * race and must be serialised by the caller.  Asynchronous on `stream`.

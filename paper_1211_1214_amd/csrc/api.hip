@@ -91,10 +91,10 @@ Profiler::~Profiler() {
 
 // ------------------------------------------------------------------ static device scratch
 // Scratch of ddwc_dslash_apply_noalloc, for callers that cannot allocate device memory: the
-// internal-layout input and output fields of one call.  Each GPU the library runs on holds its
+// internal-layout input field of one call.  Each GPU the library runs on holds its
 // own copy for the life of the process; host code never uses the array's name as a device
 // address, only the per-device address that hipGetSymbolAddress returns (scratch_address).
-static constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)256 << 20;
+static constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)128 << 20;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 static std::mutex g_scratch_mu;
 static std::map<int, void*> g_scratch_addr;  // device -> its copy of `scratch`
@@ -1199,8 +1199,8 @@ extern "C" int ddwc_dslash_apply_noalloc(ddwc_ctx* C, double kappa, const void* 
     CK(check_common(C, kappa, nrhs, prec));
     if (!in || !out) return fail(DDWC_EINVAL, "null vector");
     const size_t fb = (dslash_field_bytes(C, nrhs, prec) + 255) / 256 * 256;
-    if (2 * fb > NOALLOC_SCRATCH_BYTES)
-        return fail(DDWC_EINVAL, "ddwc_dslash_apply_noalloc: the two internal fields need " + std::to_string(2 * fb) +
+    if (fb > NOALLOC_SCRATCH_BYTES)
+        return fail(DDWC_EINVAL, "ddwc_dslash_apply_noalloc: the internal field needs " + std::to_string(fb) +
                                      " bytes, more than the static scratch of " +
                                      std::to_string(NOALLOC_SCRATCH_BYTES) + " bytes");
     if (!C->scratch) return fail(DDWC_EHIP, "no static scratch on this context's device");

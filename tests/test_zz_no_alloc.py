@@ -1,8 +1,8 @@
-"""ddwc_dslash_apply_noalloc: the Dslash with its internal fields in the library's static device
+"""ddwc_dslash_apply_noalloc: the Dslash with its internal field in the library's static device
 scratch instead of the context's workspace, for callers that cannot allocate.  Through the C ABI it
 must give exactly (bit for bit) what ddwc_dslash_apply gives, on two calls in a row with the second
 smaller than the first (the scratch keeps the first call's contents), in FP64 and FP32 on an
-RHS-innermost and an RHS-major batch, and it refuses a call whose fields exceed the scratch before
+RHS-innermost and an RHS-major batch, and it takes the largest batch that fits and refuses a call whose field exceeds the scratch before
 launching anything.  The FP64 result is also checked against the oracle (<= 1e-12 relative).
 """
 import ctypes
@@ -69,10 +69,24 @@ def test_noalloc_matches_dslash_apply(env, prec):
 def test_noalloc_rejects_oversized_batch(env):
     dev, U, ctx = env
     V = int(np.prod(LAT))
-    nrhs = (256 << 20) // (2 * V * 192) + 1  # FP64 fields just beyond the 256 MiB scratch
+    nrhs = (256 << 20) // (2 * V * 192) + 1  # an FP64 field just beyond the 128 MiB scratch
     dummy = torch.zeros(16, dtype=torch.complex128, device=dev)
     rc = binding.lib().ddwc_dslash_apply_noalloc(ctx._h, ctypes.c_double(KAPPA), ctypes.c_void_p(dummy.data_ptr()),
                                                  ctypes.c_void_p(dummy.data_ptr()), int(nrhs), dd.FP64,
                                                  binding._stream())
     assert rc == binding.EINVAL
     assert b"static scratch" in binding.lib().ddwc_last_error()
+
+
+def test_noalloc_takes_the_largest_batch(env):
+    dev, U, ctx = env
+    V = int(np.prod(LAT))
+    nrhs = (128 << 20) // (V * 192)  # (1365 RHS: the field ends 0.1 MB before the scratch does)
+    say("noalloc", nrhs)
+    psi = torch.from_numpy(inputs.make_spinor(LAT, 79, nrhs=3).reshape(3, V, 4, 3)).to(dev)
+    inp = psi[torch.arange(nrhs, device=dev) % 3].contiguous()
+    got = torch.full_like(inp, float("nan"))
+    assert noalloc(ctx, inp, got, nrhs, dd.FP64) == binding.OK
+    torch.cuda.synchronize()
+    want = ctx.dslash_apply(KAPPA, psi)
+    assert torch.equal(got, want[torch.arange(nrhs, device=dev) % 3])

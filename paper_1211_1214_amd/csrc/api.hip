@@ -159,15 +159,15 @@ struct ddwc_ctx {
     void* blas = nullptr;    // dense linear-algebra handle (block determinants), created on first use
     // schedule options (ddwc_set_option, ddwc_autotune)
     int opt_graphs = 1;       // replay the global solver's iteration chunks from captured graphs
-    int opt_poll = 2;         // BiCGStab iterations between host convergence checks
+    int opt_poll = 2;         // Krylov iterations per chunk of launches
     int opt_inner_floor = 200;  // FP32 inner solves of the even-odd global solver stop at a relative
                                 // residual of at least opt_inner_floor x 1e-8
     int opt_blk_threads = 0;  // block-solver workgroup size (0: default rule)
-    int opt_solver = 0;       // global solver: 0 even-odd BiCGStab, 1 SAP-preconditioned GCR
+    int opt_solver = 0;       // global solver: 0 even-odd minimal residual and BiCGStab, 1 SAP-preconditioned GCR
     int opt_blk_lds = 0;      // KiB of LDS reserved per persistent block-solver workgroup
     int opt_blk_kernel = 0;   // block inner solver: 0 LDS-resident where it fits (FP32/FP16), 1 global-memory
     int opt_op_threads = WG;  // workgroup size of the global solver's RHS-innermost operator kernels
-    int opt_tile_order = 1;   // their dispatch order: 0 half-site index order, 1 interleaved by block rank
+    int opt_tile_order = 1;   // dispatch order of the operator kernels: 0 site index order, 1 columns of blocks
     struct Order {
         int* tile = nullptr;           // the table
         hipStream_t on = nullptr;      // the stream that it was written on, and the end of that (null: known to be over)
@@ -730,7 +730,8 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     // BiCGStab: 56/58, 66/74, 86/82, 112/104, 164/138, 328/206 at kappa 0.118, 0.1205, 0.123, 0.125, 0.127, 0.129.
     // So a solve starts with minimal residual and changes over when LS_WINDOW cycles gain less than LS_GAIN in
     // the norm (0.05 decades an application, where the two cost the same): 48x24^3 x 12 RHS 102.2 ->
-    // 76.1 ms; 32x16^3 x 8 at kappa 0.121 / 0.128: 15.9 -> 12.0, 34.7 -> 35.9 ms.  Below LS_SITES the spectrum is so
+    // 76.1 ms; 32x16^3 x 8 at kappa 0.121 / 0.127 / 0.128: 15.9 -> 12.0, 31.7 -> 24.4, 35.9 -> 36.5 ms.  Where it changes over late, it
+    // loses up to 12% (32x24^3 x 4, 0.128: 71.2 -> 79.8 ms); 0.33 or 0.37 instead of 0.4 only moves where.  Below LS_SITES the spectrum is so
     // coarse that BiCGStab converges superlinearly (8^4, 8 RHS: 2.54 against 2.77 ms; 8x8x8x16: 3.59 against
     // 3.03 ms).
     constexpr int LS_WINDOW = 4, LS_SITES = 8192;
@@ -1224,7 +1225,7 @@ extern "C" int ddwc_block_solve(ddwc_ctx* C, int colour, double kappa, const voi
     BlockInfo bi;
     int st = block_internal(C, ex, colour, mass_of(kappa), b, x, nrhs, tol, maxit, prec, &bi);
     if (st == DDWC_OK || st == DDWC_ENOCONV) {
-        launch_export<double>(ex, C->g, x, sol, nrhs, colour == 0 ? MASK_BLACK : MASK_WHITE);
+        launch_export(ex, C->g, x, sol, nrhs, colour == 0 ? MASK_BLACK : MASK_WHITE);
         HC(hipStreamSynchronize(ex.stream));
     }
     fill_stats(stats, bi.outer, bi.inner, bi.relres, t0);
@@ -1246,7 +1247,7 @@ extern "C" int ddwc_solve(ddwc_ctx* C, double kappa, const void* b, void* x, int
     SolveInfo si;
     int st = solve_internal(C, ex, mass_of(kappa), bi, xi, nrhs, tol, maxit, prec, &si);
     if (st == DDWC_OK || st == DDWC_ENOCONV) {
-        launch_export<double>(ex, C->g, xi, x, nrhs, MASK_ALL);
+        launch_export(ex, C->g, xi, x, nrhs, MASK_ALL);
         HC(hipStreamSynchronize(ex.stream));
     }
     fill_stats(stats, si.outer, si.inner, si.relres, t0);
@@ -1421,9 +1422,9 @@ static int schur_hat(ddwc_ctx* C, Exec& ex, double mass, const double2* e, doubl
     CK(ws_t(C, "s_a", nw, &a));
     CK(ws_t(C, "s_w", nw, &w));
     // (each hop output feeds only the block solves of its colour)
-    launch_hop<double>(ex, C->g, C->U64, e, a, nrhs, 1, nullptr, -1, false);
+    launch_hop(ex, C->g, C->U64, e, a, nrhs, 1, nullptr, -1, false);
     CK(block_internal(C, ex, 1, mass, a, w, nrhs, tol, 5000, prec, bi));
-    launch_hop<double>(ex, C->g, C->U64, w, a, nrhs, 0, nullptr, -1, false);
+    launch_hop(ex, C->g, C->U64, w, a, nrhs, 0, nullptr, -1, false);
     CK(block_internal(C, ex, 0, mass, a, w, nrhs, tol, 5000, prec, bi));
     launch_axpby(ex, C->g, 1.0, e, -1.0, w, out, nrhs, MASK_P);
     return DDWC_OK;
@@ -1436,7 +1437,7 @@ static int schur_hat_inverse(ddwc_ctx* C, Exec& ex, double mass, const double2* 
     double2 *a, *chi;
     CK(ws_t(C, "s_src", nw, &a));
     CK(ws_t(C, "s_chi", nw, &chi));
-    launch_hop<double>(ex, C->g, C->U64, f, a, nrhs, 1);
+    launch_hop(ex, C->g, C->U64, f, a, nrhs, 1);
     CK(solve_internal(C, ex, mass, a, chi, nrhs, tol, 5000, prec, si));
     launch_axpby(ex, C->g, 1.0, f, -1.0, chi, out, nrhs, MASK_P);
     return DDWC_OK;
@@ -1468,7 +1469,7 @@ extern "C" int ddwc_schur_apply(ddwc_ctx* C, double kappa, int inverse, const vo
         outer = si.outer, inner = si.inner, rel = si.relres;
     }
     if (st == DDWC_OK) {
-        launch_export<double>(ex, C->g, o, out, nrhs, MASK_ALL);
+        launch_export(ex, C->g, o, out, nrhs, MASK_ALL);
         HC(hipStreamSynchronize(ex.stream));
     }
     fill_stats(stats, outer, inner, rel, t0);
@@ -1495,7 +1496,7 @@ static int schur_diff_source(ddwc_ctx* C, Exec& ex, double mp, double mn, const 
     CK(ws_t(C, "e_A1", nw, &A1));
     // each hop output feeds only the block solves of its colour (and the black-masked sum)
     auto hop = [&](const double2* in, double2* out, int dir) {
-        launch_hop<double>(ex, g, C->U64, in, out, nrhs, dir, rg ? &rg->Bo : nullptr, rg ? rg->colour : -1, false);
+        launch_hop(ex, g, C->U64, in, out, nrhs, dir, rg ? &rg->Bo : nullptr, rg ? rg->colour : -1, false);
     };
     hop(E, A, 1);
     CK(block_internal(C, ex, 1, mp, A, W1, nrhs, tol, 5000, prec, bi));
@@ -1706,7 +1707,7 @@ extern "C" int ddwc_det_ratio_nested(ddwc_ctx* O, ddwc_ctx* I, int colour, doubl
         launch_region(ex, g, rg.Bo, colour, E, nrhs);
         CK(schur_diff_source(I, ex, mp, mn, E, G, nrhs, tol, prec, &bi, &rg));
         // Ahat(mn)^-1 G
-        launch_hop<double>(ex, g, I->U64, G, S, nrhs, 1, &rg.Bo, colour);
+        launch_hop(ex, g, I->U64, G, S, nrhs, 1, &rg.Bo, colour);
         launch_relayout(ex, g, O->g, S, So, nrhs);
         CK(block_internal(O, exo, colour, mn, So, Xo, nrhs, tol, 5000, prec, &bo));
         launch_relayout(ex, O->g, g, Xo, S, nrhs);
@@ -1829,21 +1830,21 @@ extern "C" int ddwc_det_ratio_grad(ddwc_ctx* C, double kappa1, double kappa2, in
         } else {
             // forward quantities of the difference form (as in ddwc_det_ratio_estimate)
             launch_import<double>(ex, g, eta_i, E, nrhs, MASK_P);
-            launch_hop<double>(ex, g, C->U64, E, A, nrhs, 1);
+            launch_hop(ex, g, C->U64, E, A, nrhs, 1);
             CK(block_internal(C, ex, 1, mp, A, W1, nrhs, tol, MAXIT, prec, &bi));
             CK(block_internal(C, ex, 1, mn, W1, W12, nrhs, tol, MAXIT, prec, &bi));
-            launch_hop<double>(ex, g, C->U64, W1, A, nrhs, 0);
+            launch_hop(ex, g, C->U64, W1, A, nrhs, 0);
             CK(block_internal(C, ex, 0, mp, A, A1, nrhs, tol, MAXIT, prec, &bi));
-            launch_hop<double>(ex, g, C->U64, W12, A, nrhs, 0);
+            launch_hop(ex, g, C->U64, W12, A, nrhs, 0);
             launch_axpby(ex, g, 1.0, A1, 1.0, A, A, nrhs, MASK_BLACK);
             CK(block_internal(C, ex, 0, mn, A, Gs, nrhs, tol, MAXIT, prec, &bi));
             launch_axpby(ex, g, dm, Gs, 0.0, nullptr, Gs, nrhs, MASK_P);
             CK(schur_hat_inverse(C, ex, mn, Gs, Z, nrhs, tol, prec, &si));
             launch_axpby(ex, g, 1.0, E, 1.0, Z, Y, nrhs, MASK_P);  // y = Mhat e
             // w1, w2 for v = y at m_n (for v = e at m_p they are W1 and A1)
-            launch_hop<double>(ex, g, C->U64, Y, A, nrhs, 1);
+            launch_hop(ex, g, C->U64, Y, A, nrhs, 1);
             CK(block_internal(C, ex, 1, mn, A, W1n, nrhs, tol, MAXIT, prec, &bi));
-            launch_hop<double>(ex, g, C->U64, W1n, A, nrhs, 0);
+            launch_hop(ex, g, C->U64, W1n, A, nrhs, 0);
             CK(block_internal(C, ex, 0, mn, A, W2n, nrhs, tol, MAXIT, prec, &bi));
             // adjoint: Dhat_P is not gamma_5-hermitian (D_bb^-1 acts from the left), but
             // Dhat_P^-+ v = v - g5 P D_bw [D^-1 (g5 v)]_w, so zh = g5 z = u - P D_bw [D_n^-1 u]_w
@@ -1851,13 +1852,13 @@ extern "C" int ddwc_det_ratio_grad(ddwc_ctx* C, double kappa1, double kappa2, in
             launch_axpby(ex, g, 1.0, Y, 0.0, nullptr, Y5, nrhs, MASK_P);
             launch_gamma5(ex, g, Y5, nrhs);
             CK(solve_internal(C, ex, mn, Y5, W12, nrhs, tol, MAXIT, prec, &si));
-            launch_hop<double>(ex, g, C->U64, W12, A, nrhs, 0);
+            launch_hop(ex, g, C->U64, W12, A, nrhs, 0);
             launch_axpby(ex, g, 1.0, Y5, -1.0, A, Zh, nrhs, MASK_P);
             CK(block_internal(C, ex, 0, mp, Zh, Ap, nrhs, tol, MAXIT, prec, &bi));
-            launch_hop<double>(ex, g, C->U64, Ap, A, nrhs, 1);
+            launch_hop(ex, g, C->U64, Ap, A, nrhs, 1);
             CK(block_internal(C, ex, 1, mp, A, Cp, nrhs, tol, MAXIT, prec, &bi));
             CK(block_internal(C, ex, 0, mn, Zh, An, nrhs, tol, MAXIT, prec, &bi));
-            launch_hop<double>(ex, g, C->U64, An, A, nrhs, 1);
+            launch_hop(ex, g, C->U64, An, A, nrhs, 1);
             CK(block_internal(C, ex, 1, mn, A, Cn, nrhs, tol, MAXIT, prec, &bi));
             launch_gamma5(ex, g, Ap, nrhs);
             launch_gamma5(ex, g, Cp, nrhs);

@@ -435,7 +435,7 @@ __global__ __launch_bounds__(be_inner_max<S>()) void k_blk_inner(Geom g, EoField
 // 6^4, 12 RHS, one colour (to 2e-6, then to tol = 1e-10): BiCGStab with entry-major links (nine 8-byte
 // loads each), five global vectors, conditional hops and shuffle reductions 5677 us; 4883 us with r and v in
 // registers and branch-free hops; 4296 us with the packed links; 4002 us with the exchanging
-// reduction; 3500 us with minimal residual.  With no global loads but the same LDS reads and ALU work the BiCGStab
+// reduction; 3500 us with minimal residual to a quarter of tol, 3990 us to MR_AIM_LDS of it.  With no global loads but the same LDS reads and ALU work the BiCGStab
 // took 3000 us: the load path, 64 bytes a cycle and CU, is the rest.
 constexpr int BL_MAX = 768;     // 12 waves: 3 per SIMD at up to 168 VGPRs
 constexpr int BL_WINDOW = 8;    // steps

@@ -9,7 +9,7 @@
 
 namespace ddwc {
 
-// Per-RHS BiCGStab scalars, kept on the device so that iterations need no host round trip.
+// Per-RHS scalars of the Krylov solvers, kept on the device so that iterations need no host round trip.
 struct BiState {
     double rho[2], alpha[2], omega[2], beta[2];
     double rr;    // ||r||^2 after the last iteration
@@ -106,12 +106,11 @@ void launch_links_own(Exec& e, unsigned n, const cx<float>* Uf, const cx<float>*
                       cx<float>* Lown);
 // Full-lattice FP32 Dslash on an RHS-innermost field [6][V][nrhs], result in the canonical FP64 layout, with
 // the own-site link records Us [V][8][9]; op_threads (128, 256 or 512; 256 below nrhs) threads per
-// workgroup, tiles dispatched in `order` (null: index order; dslash_ri32_tiles() entries).
+// workgroup, tiles dispatched in `order` (null: index order).
 void launch_import_ri32(Exec& e, const Geom& g, const void* canon, float4* out, int nrhs);
 void launch_dslash_ri32(Exec& e, const Geom& g, const cx<float>* Us, const float4* K, double mass4, const float4* in,
                         void* out, int nrhs, int kclass, double bytes, int op_threads = WG,
                         const int* order = nullptr);
-int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads);
 // order[slot] = the tile dispatched there, for all tiles of the fields (tile_order.h; every block extent even)
 struct TileOrder;
 void launch_tile_order(Exec& e, const Geom& g, const TileOrder& o, int* order);
@@ -120,10 +119,9 @@ void launch_clover_build(Exec& e, const Geom& g, const cx<double>* U64, double c
 
 template <class R>
 void launch_import(Exec& e, const Geom& g, const void* canon, typename Traits<R>::word* out, int nrhs, int mask);
-template <class R>
-void launch_export(Exec& e, const Geom& g, const typename Traits<R>::word* in, void* canon, int nrhs, int mask);
+void launch_export(Exec& e, const Geom& g, const double2* in, void* canon, int nrhs, int mask);
 
-// out = D(m) in over all sites; canonical: out is the canonical FP64 layout, else an internal field.  order:
+// out = D(m) in over all sites; canonical: out is the canonical FP64 layout, else an internal field (FP64).  order:
 // the tile (DW sites) that each dispatch slot processes (null: index order).
 template <class R>
 void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* K, double mass4,
@@ -142,10 +140,8 @@ struct Ext4 {
 // consumers that read only colour to_colour: the block solves of that colour).  With cut, out is
 // also zero outside the outer blocks (extents *cut) of colour cut_colour: the hops of the
 // Dirichlet operator of those blocks.
-template <class R>
-void launch_hop(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* in,
-                typename Traits<R>::word* out, int nrhs, int to_colour, const Ext4* cut = nullptr,
-                int cut_colour = -1, bool clear_other = true);
+void launch_hop(Exec& e, const Geom& g, const cx<double>* U, const double2* in, double2* out, int nrhs, int to_colour,
+                const Ext4* cut = nullptr, int cut_colour = -1, bool clear_other = true);
 
 // BiCGStab vector kernels on fields of n sites, nrhs RHS, per-RHS scalars in st, storage S
 // (double, float or H16; H16 fields must be RHS-innermost).  ri selects the RHS-innermost
@@ -179,7 +175,7 @@ template <class S>
 void launch_accumulate(Exec& e, unsigned n, bool ri, const typename Traits<typename Traits<S>::xs>::word* x,
                        const double* scale, double2* x64, int nrhs);
 
-// Sums partials per RHS in a fixed order and applies the BiCGStab stage update.
+// Sums partials per RHS in a fixed order and applies the update of the stage.
 void launch_finalize(Exec& e, const double* part, int ntiles, int nrhs, double* sums, BiState* st, int stage,
                      const double* thr_rel2, int nv = -1);
 

@@ -1,5 +1,5 @@
 // Site-parallel kernels: layout conversion, clover build, Wilson-clover operator
-// variants with fused reductions, BiCGStab vector updates, FP64 reductions.
+// variants with fused reductions, vector updates of the Krylov solvers, FP64 reductions.
 //
 // Mapping: one thread per (site, RHS); a workgroup holds WG consecutive internal
 // sites of one RHS.  Workgroups are numbered tile-major / RHS-minor and remapped so
@@ -126,18 +126,17 @@ __global__ void k_import(Geom g, const double2* __restrict__ can, typename Trait
     store_spinor(out + (size_t)rhs * Traits<R>::NCW * g.V, g.V, s, p);
 }
 
-template <class R>
-__global__ void k_export(Geom g, const typename Traits<R>::word* __restrict__ in, double2* __restrict__ can, int nrhs,
+__global__ void k_export(Geom g, const double2* __restrict__ in, double2* __restrict__ can, int nrhs,
                          int mask) {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
     int rhs = blockIdx.y;
     if (s >= g.V) return;
     Site S = decode(g, s);
     bool keep = mask_keep(g, S, mask);
-    cx<R> p[12];
-    load_spinor(in + (size_t)rhs * Traits<R>::NCW * g.V, g.V, s, p);
+    cx<double> p[12];
+    load_spinor(in + (size_t)rhs * Traits<double>::NCW * g.V, g.V, s, p);
     double2* dst = can + ((size_t)rhs * g.V + canonical_index(g, S)) * 12;
-    for (int c = 0; c < 12; ++c) dst[c] = keep ? make_double2((double)p[c].re, (double)p[c].im) : make_double2(0, 0);
+    for (int c = 0; c < 12; ++c) dst[c] = keep ? make_double2(p[c].re, p[c].im) : make_double2(0, 0);
 }
 
 template <class R>
@@ -145,10 +144,9 @@ void launch_import(Exec& e, const Geom& g, const void* canon, typename Traits<R>
     Timed t(e, 4, 0);
     k_import<R><<<dim3(tiles_of(g.V), nrhs), WG, 0, e.stream>>>(g, (const double2*)canon, out, nrhs, mask);
 }
-template <class R>
-void launch_export(Exec& e, const Geom& g, const typename Traits<R>::word* in, void* canon, int nrhs, int mask) {
+void launch_export(Exec& e, const Geom& g, const double2* in, void* canon, int nrhs, int mask) {
     Timed t(e, 4, 0);
-    k_export<R><<<dim3(tiles_of(g.V), nrhs), WG, 0, e.stream>>>(g, in, (double2*)canon, nrhs, mask);
+    k_export<<<dim3(tiles_of(g.V), nrhs), WG, 0, e.stream>>>(g, in, (double2*)canon, nrhs, mask);
 }
 
 // ------------------------------------------------------------------ operator kernels
@@ -253,7 +251,7 @@ void launch_dslash(Exec& e, const Geom& g, const cx<R>* U, const typename Traits
     if (canonical)
         k_dslash<R, EPI_CANON><<<nt * nrhs, DW, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr,
                                                                 order);
-    else
+    else if constexpr (std::is_same<R, double>::value)
         k_dslash<R, EPI_NONE><<<nt * nrhs, DW, 0, e.stream>>>(g, U, K, (R)mass4, in, out, nullptr, nullptr, nrhs, nt, e.nbr,
                                                                 order);
 }
@@ -264,10 +262,9 @@ void launch_residual(Exec& e, const Geom& g, const cx<double>* U, const double2*
     k_dslash<double, EPI_RESID><<<nt * nrhs, DW, 0, e.stream>>>(g, U, K, mass4, x, r, b, part, nrhs, nt, e.nbr, nullptr);
 }
 
-template <class R>
-__global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<R>* __restrict__ U,
-                                            const typename Traits<R>::word* __restrict__ in,
-                                            typename Traits<R>::word* __restrict__ out, int nrhs, int to_colour,
+__global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<double>* __restrict__ U,
+                                            const double2* __restrict__ in,
+                                            double2* __restrict__ out, int nrhs, int to_colour,
                                             const int* __restrict__ nbr, int ndir, Ext4 cut, int cut_colour,
                                             bool both) {
     // The RHS of a tile follow each other on one XCD, whose L2 then holds their links, and where both colours are
@@ -278,8 +275,8 @@ __global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<R>* __restrict__ U,
     const int colour = both ? tr.tile & 1 : to_colour, i = (both ? tr.tile >> 1 : tr.tile) * WG + (int)threadIdx.x;
     if (i >= g.V / 2) return;
     const int s = colour * (g.V / 2) + i;
-    const size_t off = (size_t)tr.rhs * Traits<R>::NCW * g.V;
-    cx<R> y[12];
+    const size_t off = (size_t)tr.rhs * Traits<double>::NCW * g.V;
+    cx<double> y[12];
     bool keep = colour == to_colour;
     if (keep && cut_colour >= 0) {  // output cut to the outer blocks (extents cut) of one colour
         const Site S = decode(g, s);
@@ -290,22 +287,21 @@ __global__ __launch_bounds__(WG) void k_hop(Geom g, const cx<R>* __restrict__ U,
     }
     if (keep) {
         // unrolled: 138 VGPRs in FP64 against 256 and AGPRs for the pipelined loop
-        site_operator<R, false, HOPS_CROSSING, true>(g, s, in + off, U, nullptr, nbr, R(0), y, ndir);
+        site_operator<double, false, HOPS_CROSSING, true>(g, s, in + off, U, nullptr, nbr, 0.0, y, ndir);
     } else {
 #pragma unroll
-        for (int k = 0; k < 12; ++k) y[k] = mk(R(0), R(0));
+        for (int k = 0; k < 12; ++k) y[k] = mk(0.0, 0.0);
     }
     store_spinor(out + off, g.V, s, y);
 }
 
-template <class R>
-void launch_hop(Exec& e, const Geom& g, const cx<R>* U, const typename Traits<R>::word* in,
-                typename Traits<R>::word* out, int nrhs, int to_colour, const Ext4* cut, int cut_colour,
+void launch_hop(Exec& e, const Geom& g, const cx<double>* U, const double2* in,
+                double2* out, int nrhs, int to_colour, const Ext4* cut, int cut_colour,
                 bool clear_other) {
     Timed t(e, 4, 0);
     const Ext4 c = cut ? *cut : Ext4{{1, 1, 1, 1}};
     // the sites of colour c are [c V/2, (c + 1) V/2) of the colour-major full index
-    k_hop<R><<<tiles_of(g.V / 2) * (clear_other ? 2 : 1) * nrhs, WG, 0, e.stream>>>(g, U, in, out, nrhs, to_colour, e.nbr, 8,
+    k_hop<<<tiles_of(g.V / 2) * (clear_other ? 2 : 1) * nrhs, WG, 0, e.stream>>>(g, U, in, out, nrhs, to_colour, e.nbr, 8,
                                                                                  c, cut ? cut_colour : -1, clear_other);
 }
 
@@ -610,7 +606,7 @@ __device__ __forceinline__ void ls_step(const double* v, BiState& S) {
 }
 
 // Sums the first NV partial components of each RHS over the tiles (fixed order), then applies
-// the BiCGStab stage.  v has NPART entries so that every stage can name its components.
+// the stage of the solver.  v has NPART entries so that every stage can name its components.
 template <int NV>
 __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ part, int ntiles, int nrhs,
                                                   double* __restrict__ sums, BiState* __restrict__ st, int stage,
@@ -1005,19 +1001,11 @@ void launch_tile_order(Exec& e, const Geom& g, const TileOrder& o, int* order) {
     k_tile_order<<<o.columns(g), TO_THREADS, 0, e.stream>>>(g, o, order);
 }
 
-int dslash_ri32_tiles(const Geom& g, int nrhs, int op_threads) {
-    const int NTr = nrhs <= op_threads ? op_threads : WG;
-    return (int)(((long long)g.V * nrhs + NTr - 1) / NTr);
-}
-
 // ------------------------------------------------------------------ instantiations
 #define INST(R)                                                                                                    \
     template void launch_import<R>(Exec&, const Geom&, const void*, Traits<R>::word*, int, int);                  \
-    template void launch_export<R>(Exec&, const Geom&, const Traits<R>::word*, void*, int, int);                  \
     template void launch_dslash<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, double,              \
                                    const Traits<R>::word*, void*, bool, int, int, double, const int*);            \
-    template void launch_hop<R>(Exec&, const Geom&, const cx<R>*, const Traits<R>::word*, Traits<R>::word*, int,  \
-                                int, const Ext4*, int, bool);                                                     \
     template void launch_bicg_init<R>(Exec&, unsigned, bool, const double2*, const double*, Traits<R>::word*,      \
                                       Traits<R>::word*, Traits<R>::word*, Traits<R>::word*, double*, int);        \
     template void launch_ls_init<R>(Exec&, unsigned, bool, const double2*, const double*, Traits<R>::word*,       \

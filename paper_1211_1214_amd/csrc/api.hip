@@ -170,8 +170,7 @@ struct ddwc_ctx {
     int opt_tile_order = 1;   // dispatch order of the operator kernels: 0 site index order, 1 columns of blocks
     struct Order {
         int* tile = nullptr;           // the table
-        hipStream_t on = nullptr;      // the stream that it was written on, and the end of that (null: known to be over)
-        hipEvent_t written = nullptr;
+        hipEvent_t written = nullptr;  // the end of its writing (null: known to be over)
     };
     std::map<std::vector<int>, Order> orders;  // dispatch orders by shape
     int lds_max = 0;          // LDS bytes per workgroup of the device
@@ -457,7 +456,7 @@ EoFields<H16> eo_fields<H16>(const ddwc_ctx* C, bool site_major) {
 // staging: hop-and-inverse 324 -> 306 us, diagonal-and-hop 448 / 373 -> 415 / 350 us against blocks of both colours
 // in turn; columns of 6^3, 6x12x12, 12x12x24, 24^3: 322, 317, 318, 344 us.
 //
-// The table of a shape is written by a kernel on the stream of the first call that uses it, and later calls on other streams wait
+// The table of a shape is written by a kernel on the stream of the first call that uses it, and the streams of later calls wait
 // for that.  Nothing is allocated or waited for on a stream that is being captured: a call there runs in index order (null)
 // unless its table is complete.
 static int tile_order(ddwc_ctx* C, Exec& ex, int parities, int nrhs, int nt, double bytes, const int** out) {
@@ -498,7 +497,6 @@ static int tile_order(ddwc_ctx* C, Exec& ex, int parities, int nrhs, int nt, dou
         ddwc_ctx::Order q;
         HC(hipMalloc(&q.tile, sizeof(int) * o.first((long long)parities * g.hvb * g.NB)));
         launch_tile_order(ex, g, o, q.tile);
-        q.on = ex.stream;
         if (hipEventCreateWithFlags(&q.written, hipEventDisableTiming) != hipSuccess ||
             hipEventRecord(q.written, ex.stream) != hipSuccess) {
             (void)hipGetLastError();
@@ -519,7 +517,7 @@ static int tile_order(ddwc_ctx* C, Exec& ex, int parities, int nrhs, int nt, dou
         } else {
             (void)hipGetLastError();
             if (capturing) return DDWC_OK;
-            if (q.on != ex.stream) HC(hipStreamWaitEvent(ex.stream, q.written, 0));
+            HC(hipStreamWaitEvent(ex.stream, q.written, 0));
         }
     }
     *out = it->second.tile;

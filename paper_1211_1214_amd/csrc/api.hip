@@ -822,7 +822,7 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
             for (int k = 0; k < nrhs; ++k) {
                 bool done = !(bb[k] > 0 && rr[k] > tol * tol * bb[k]);
                 h_scale[k] = done ? 0.0 : 1.0 / sqrt(rr[k]);
-                double eps = done ? 0.0 : (ls ? LS_AIM : BI_AIM) * tol * sqrt(bb[k] / rr[k]);
+                double eps = done ? 0.0 : (ls ? (fp64 ? LS_AIM64 : LS_AIM) : BI_AIM) * tol * sqrt(bb[k] / rr[k]);
                 if (eps < floor_eps) eps = floor_eps;
                 h_thr[k] = done ? 2.0 : eps * eps;
             }

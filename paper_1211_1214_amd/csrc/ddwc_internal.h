@@ -32,8 +32,10 @@ enum Stage { ST_SUM = 0, ST_INIT = 1, ST_ALPHA = 2, ST_OMEGA = 3, ST_RR = 4, ST_
 // (six configurations each), BiCGStab alone / minimal residual at 0.5 (global) and 0.25 (blocks) / as here: 48x24^3, 6^4
 // blocks 0.50 / 6.7 / 0.29e-12, 24x12^3 2.1 / 2.5 / 0.8e-12, 32x16^3, 4^4 2.5 / 2.3 / 0.9e-12, 8^4 in FP16 2.6 / 5.0 /
 // 1.3e-12, 4^4 lattice 8.2 / 8.3 / 0.8e-12, nested 32x16^3 1.6 / 2.9 / 0.1e-12; of solutions, 24x12^3 1.9 / 2.2 / 0.7e-10.
-// An estimate at 48x24^3 takes 6% longer for it.
-constexpr double BI_AIM = 0.5, LS_AIM = 0.25, MR_AIM = 0.05, MR_AIM_LDS = 0.01;
+// An estimate at 48x24^3 takes 6% longer for it.  In FP64, where the blocks are BiCGStab's, 0.25 would leave
+// the exponents further off than BiCGStab alone (BiCGStab / 0.25 / 0.07): 16^4, 8^4 blocks 2.1 / 2.4 / 2.1e-12, 32x16^3, 4^4
+// 2.8 / 3.0 / 2.0e-12, 32x16^3, 8^4 1.3 / 1.7 / 1.4e-12; it costs 3% more.
+constexpr double BI_AIM = 0.5, LS_AIM = 0.25, LS_AIM64 = 0.07, MR_AIM = 0.05, MR_AIM_LDS = 0.01;
 constexpr double MR_FLOOR32 = 5e-7;
 // (loose solves precondition or smooth: nobody adds up what they leave)
 inline double mr_aim(double tol, double aim) { return tol >= 1e-4 ? 0.25 : aim; }

@@ -300,7 +300,7 @@ def kernel_sources_digest():
 
 # kernel whose counters stand for each profiler class
 # kernel of a profiling class in the counter records; {nt}: the operator workgroup size in use
-CLASS_KERNEL = {"eohop": "void ddwc::k_eo_hopinv<float, true, true, {nt}>", "block": "ddwc::k_blk_lds"}
+CLASS_KERNEL = {"eohop": "void ddwc::k_eo_hopinv<float, true, true, {nt}>", "block": "void ddwc::k_blk_lds<false, false>"}
 
 
 def nested_bench(args, dd, inputs, np, torch):

@@ -282,7 +282,8 @@ int ddwc_log_w_nested_total(ddwc_ctx *outer, ddwc_ctx *inner, double kappa1, dou
  *                          DDWC_MIXED16: 0 (default) the LDS-resident FP32 kernel wherever a block
  *                          parity has at most 768 sites and its two staged fields fit the LDS (both
  *                          precisions then run it, FP32 storage); 1 the global-memory kernels
- *                          (minimal residual, BiCGStab where that converges slowly).
+ *                          (minimal residual, BiCGStab where that converges slowly and, alone, on blocks
+ *                          above 40448 sites of a parity).
  *   DDWC_OPT_INNER_FLOOR   the FP32 inner solver of the even-odd global solver (DDWC_MIXED32) stops
  *                          at a relative residual of at least value x 1e-8 before the FP64 defect
  *                          correction restarts it, in [1, 100000]; default 200 (2e-6).

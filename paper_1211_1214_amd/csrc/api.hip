@@ -728,9 +728,9 @@ static int eo_solve(ddwc_ctx* C, Exec& ex, double mass, const double2* b64, doub
     // BiCGStab: 56/58, 66/74, 86/82, 112/104, 164/138, 328/206 at kappa 0.118, 0.1205, 0.123, 0.125, 0.127, 0.129.
     // So a solve starts with minimal residual and changes over when LS_WINDOW cycles gain less than LS_GAIN in
     // the norm (0.05 decades an application, where the two cost the same): 48x24^3 x 12 RHS 102.2 ->
-    // 76.1 ms; 32x16^3 x 8 at kappa 0.121 / 0.127 / 0.128: 15.9 -> 12.0, 31.7 -> 24.4, 35.9 -> 36.5 ms.  Where it changes over late, it
-    // loses up to 12% (32x24^3 x 4, 0.128: 71.2 -> 79.8 ms); 0.33 or 0.37 instead of 0.4 only moves where.  Below LS_SITES the spectrum is so
-    // coarse that BiCGStab converges superlinearly (8^4, 8 RHS: 2.54 against 2.77 ms; 8x8x8x16: 3.59 against
+    // 76.1 ms; 32x16^3 x 8 at kappa 0.121 / 0.127 / 0.128: 15.9 -> 12.0, 31.7 -> 24.4, 35.9 -> 36.5 ms.  Where it
+    // changes over late, it loses up to 12% (32x24^3 x 4, 0.128: 71.2 -> 79.8 ms); 0.33 or 0.37 instead of 0.4 only
+    // moves where.  Below LS_SITES the spectrum is so coarse that BiCGStab converges superlinearly (8^4, 8 RHS: 2.54 against 2.77 ms; 8x8x8x16: 3.59 against
     // 3.03 ms).
     constexpr int LS_WINDOW = 4, LS_SITES = 8192;
     constexpr double LS_GAIN = 0.4;

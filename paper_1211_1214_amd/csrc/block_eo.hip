@@ -8,7 +8,8 @@
 //   k_blk_prep    FP64: b'_e, r_e = b'_e, x_e = 0, ||b_k||^2, ||r_e||^2
 //   k_blk_lds, k_lds_lanes, k_blk_mr   persistent minimal residual in FP32 (FP16 storage) on M_k for r_e / ||r_e||, adds
 //                 the correction to x_e in FP64 (blocks already converged return at once)
-//   k_blk_inner   the same by BiCGStab: FP64, and where minimal residual converges slowly
+//   k_blk_lds (BI), k_blk_inner   the same by BiCGStab, in the LDS and in memory: where minimal residual converges slowly, in
+//                 FP64, and on blocks whose hop masks k_blk_mr cannot hold
 //   k_blk_resid   FP64: r_e = b'_e - M_k x_e and ||r_e||^2 (defect correction)
 //   k_blk_recon   FP64: x_o, and (x_e, x_o) written to the full solution
 // k_blk_prep_lds and k_blk_resid_lds are the FP64 passes of blocks whose parity fits the LDS.  The LDS-resident solvers
@@ -441,10 +442,11 @@ constexpr int BL_MAX = 768;     // 12 waves: 3 per SIMD at up to 168 VGPRs
 constexpr int BL_WINDOW = 8;    // steps
 // The fall of ||r|| in a window below which a block is left to BiCGStab: 0.1 decades a step, where the two meet.  One colour
 // to 1e-10, BiCGStab alone / minimal residual left at 0.05 decades a step for k_blk_inner / this: 6^4 blocks of
-// 24x12^3, 12 RHS, kappa 0.13 1.71 / 1.30 / 1.30, 0.14 2.17 / 2.39 / 1.61, 0.16 6.53 / 9.59 / 5.38 ms; 4^4 of 16^4, 8 RHS,
-// 0.15 1.39 / 1.33 / 1.42, 0.16 1.65 / 2.42 / 1.29 ms.  In k_blk_mr with FP32 storage (BiCGStab alone / this), 0.15 decades:
-// 8^4 of 16^4, 8 RHS, 0.125 5.5 / 5.5, 0.13 6.6 / 7.1, 0.14 9.8 / 9.9 ms.  A whole lattice (WRAP) goes on by launches of the global solver, at two to four times the
-// time an iteration, so it stays until 0.05 decades a step (4^4, 8 RHS, kappa 0.13: 3.03 / - / 1.10 ms).
+// 24x12^3, 12 RHS, kappa 0.13 1.71 / 1.30 / 1.40, 0.14 2.17 / 2.39 / 1.60, 0.16 6.53 / 9.59 / 5.37 ms; 4^4 of 16^4, 8 RHS,
+// 0.14 1.22 / 0.96 / 1.01, 0.15 1.39 / 1.33 / 1.49, 0.16 1.65 / 2.42 / 1.27 ms.  In k_blk_mr with FP32 storage 0.15 decades
+// (BiCGStab alone / this): 8^4 of 16^4, 8 RHS, 0.1205 4.9 / 4.4, 0.13 6.7 / 7.0, 0.14 9.7 / 9.8 ms.  A whole lattice (WRAP) goes on
+// by launches of the global solver, at two to four times the time an iteration, so it stays until 0.05 decades a step
+// (4^4, 8 RHS, kappa 0.13: 3.03 / - / 1.18 ms).
 constexpr double BL_GAIN = 0.16, BL_GAIN_WRAP = 0.4, BM_GAIN32 = 0.06;
 
 // Exchanges halves between a and b and adds, on the two dwords of each double: with W = 32 the lower 32
